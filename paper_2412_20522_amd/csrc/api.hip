@@ -276,6 +276,7 @@ struct mgs_frame {
     DevSettings st{};
     CompositeConfig cfg_fwd{}, cfg_bwd{};
     int persistent = 0;
+    bool fine = false;  // composited by the kernels for small splats (use_fine)
     int n_views = 0;
     int64_t n = 0, R = 0, P = 0, K = 0, W = 0, total_tiles = 0, capacity = 0;
     int sort_passes = 0, tile_bits = 0;
@@ -309,7 +310,8 @@ struct mgs_frame {
     bool fwd_order_measured = false;
     // misc: flags (u32) at 0, list entry count (u64) at 8, wide record count
     // (u64) at 16, checkpoint count (u64) at 24, region entry count (u64) at
-    // 32, staged-entry counter (u32) at 192; the tile orders' histogram and
+    // 32, footprint tiles of all and of large splats (u64) at 40 and 48,
+    // staged-entry counter (u32) at 192; the tile orders' histogram and
     // cursors (2 x 256 u32) from 256
     uint64_t* h_pinned = nullptr;  // read-back of misc
     uint32_t* keys_sorted() { return (uint32_t*)(sorted_in_alt ? keys_alt.p : keys.p); }
@@ -329,7 +331,7 @@ struct mgs_frame {
         const uint64_t n2 = clear_drec ? ((uint64_t)R * DREC + 1) / 2 : 0;
         return HybridBuffers{vals_sorted(), (const uint32_t*)ranges.p, (uint32_t*)cur.p, (const uint32_t*)cur_off.p, (uint32_t*)nbatch.p, cur_need(), cap,
                              flags(), (uint32_t*)cur_stg.p, (uint32_t*)stg.p, stg_count(), scap,
-                             clear_drec ? (double*)d_rec.p : nullptr, n2, (const uint32_t*)order.p};
+                             clear_drec ? (double*)d_rec.p : nullptr, n2, (const uint32_t*)order.p, fine};
     }
 };
 
@@ -545,6 +547,10 @@ mgs_status forward_impl(mgs_frame* f, mgs_stream stream_, const mgs_gaussians* g
     f->cfg_bwd = CompositeConfig{st->tile_w, st->tile_h, st->bwd_ppt};
     f->persistent = st->persistent;
     f->total_tiles = f->views.total_tiles;
+    // the plain path picks the compositing kernels from this forward's splat
+    // sizes, read with the list counts; a fixed workspace keeps the choice of
+    // the forward it was sized from
+    const bool sizes = !f->reserved && fine_needs_sizes(f->P);
     const int64_t R = f->R, P = f->P, T = f->total_tiles, NR = f->views.total_regions;
     f->tile_bits = bits_for((uint64_t)(T + NR));
     if (f->reserved && (R > f->res_R || P > f->res_P || T > f->res_T))
@@ -592,13 +598,13 @@ mgs_status forward_impl(mgs_frame* f, mgs_stream stream_, const mgs_gaussians* g
                                 (const float*)f->rec.p, R, f->n, f->views, f->st,
                                 (uint32_t*)f->cnt_sorted.p,
                                 (uint64_t*)f->tmask.p, (float*)f->srec.p,
-                                (uint32_t*)f->cls_part.p);
+                                (uint32_t*)f->cls_part.p, sizes);
     }
     {
         // list offsets: one scan over the classification's per-workgroup
         // counts; the duplication adds the counts within its workgroup
         StageTimer t(ctx, stream, MGS_STAGE_SCAN);
-        launch_list_offsets(stream, (uint32_t*)f->cls_part.p, R, f->total(), f->wide_counts());
+        launch_list_offsets(stream, (uint32_t*)f->cls_part.p, R, f->total(), f->wide_counts(), sizes);
     }
     MGS_CHECK_LAUNCH(ctx);
     const int64_t B = st->batch_depth;
@@ -622,6 +628,7 @@ mgs_status forward_impl(mgs_frame* f, mgs_stream stream_, const mgs_gaussians* g
                                                     (unsigned long long)K);
         f->K = (int64_t)K;
         f->W = (int64_t)W;
+        f->fine = use_fine(P, f->h_pinned[5], f->h_pinned[6]);
         // checkpoints: per tile 2 (ceil(narrow / B) + ceil(region / B)) + 2,
         // and a region list is read by at most REGION^2 tiles
         const int64_t cur_bound =
@@ -675,7 +682,7 @@ mgs_status forward_impl(mgs_frame* f, mgs_stream stream_, const mgs_gaussians* g
         launch_tile_setup(stream, (const uint32_t*)f->ranges.p, f->views, (int)B,
                           measured ? (const uint32_t*)f->nbatch.p : nullptr, (uint32_t*)f->tcost.p,
                           (uint32_t*)f->cur_off.p, f->cur_need(), (uint32_t*)f->caps.p, f->order_hist(),
-                          (uint32_t*)f->order.p);
+                          (uint32_t*)f->order.p, (uint32_t*)f->nbatch.p);
     }
     const bool imp = imp_sum != nullptr;
     if (imp) {

@@ -101,6 +101,10 @@ __device__ __forceinline__ Rect record_rect(const float4* __restrict__ rec, cons
 
 __device__ __forceinline__ int lane_id() { return __lane_id(); }
 
+// Lanes of the wave where p holds (HIP's __ballot first turns the condition
+// into an integer per lane).
+__device__ __forceinline__ uint64_t ballot(bool p) { return __builtin_amdgcn_ballot_w64(p); }
+
 __device__ __forceinline__ uint64_t lanemask_lt() {
     const int l = lane_id();
     return l == 0 ? 0ull : (~0ull >> (64 - l));

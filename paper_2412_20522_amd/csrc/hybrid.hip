@@ -242,6 +242,37 @@ __device__ __forceinline__ bool row_cells(const RowCull& p, int cy, int cw, int 
     return true;
 }
 
+// The four 4x4 pixel blocks (bit 2 (y / 4) + x / 4) of the 8x8 pixels at
+// (x0, y0) that an entry can reach: row_cells' band test with the bands and
+// columns of the blocks.  The margin grows with the centre's distance, whose
+// rounding the per-pixel evaluation shares, and a comparison with a NaN
+// counts as reached, so a block left out holds no pixel that passes the
+// filters.
+__device__ __forceinline__ uint32_t block_mask(const float4& A, const float4& B, int x0, int y0, int height,
+                                               const DevSettings& st) {
+    const RowCull p = row_prep(A, B, st);
+    if (p.mode == 1) return 15u;
+    if (p.mode == 2) return 0u;
+    uint32_t mask = 0;
+#pragma unroll
+    for (int r = 0; r < 2; ++r) {
+        const float Y0 = (float)(y0 + 4 * r) + 0.5f, Y1 = (float)min(y0 + 4 * r + 4, height) - 0.5f;
+        const float e0 = fmaxf(Y0 - p.v, -p.H), e1 = fminf(Y1 - p.v, p.H);
+        if (e0 > e1) continue;
+        const float eR = fminf(fmaxf(p.eyR, e0), e1), eL = fminf(fmaxf(-p.eyR, e0), e1);
+        const float sR = __builtin_amdgcn_sqrtf(fmaxf(0.f, (p.cut - p.gamma * eR * eR) * p.inva));
+        const float sL = __builtin_amdgcn_sqrtf(fmaxf(0.f, (p.cut - p.gamma * eL * eL) * p.inva));
+        const float mg = 1e-3f + 1e-6f * (fabsf(p.u) + fabsf(p.beta) * fmaxf(fabsf(eR), fabsf(eL)));
+        const float xhi = p.u + (sR - p.beta * eR) + mg, xlo = p.u - (sL + p.beta * eL) - mg;
+#pragma unroll
+        for (int c = 0; c < 2; ++c) {
+            const float X0 = (float)(x0 + 4 * c) + 0.5f;
+            if (!(xhi < X0 || xlo > X0 + 3.f)) mask |= 1u << (2 * r + c);
+        }
+    }
+    return mask;
+}
+
 // With culling, the kept cells of a rectangle of at most CULL_MAX cells
 // travel from the classification to the duplication as a bit mask (bit j:
 // cell j, row-major); larger rectangles have their rows recomputed.
@@ -252,6 +283,8 @@ constexpr uint32_t KEY_NONE = 0xffffffffu;
 // Bit of a position's entry count that marks a wide record (listed per
 // region); the count itself is below 2^24.
 constexpr uint32_t CNT_WIDE = 0x80000000u;
+// Splats of a larger radius (pixels) cover most of the tiles they reach.
+constexpr float LARGE_RADIUS = 24.f;
 
 __device__ __forceinline__ float4 shfl4(const float4& v, int src) {
     return make_float4(__shfl(v.x, src), __shfl(v.y, src), __shfl(v.z, src), __shfl(v.w, src));
@@ -264,14 +297,17 @@ __device__ __forceinline__ float4 shfl4(const float4& v, int src) {
 // number of wide records and of their region entries (part[b], part[nb +
 // b]), and per wave the number of all list entries (part[2 nb + wave]; a
 // position has fewer than 2^24 entries, so a wave's 64 stay below 2^32).
+// With sizes, also per workgroup the tiles of all footprints and those of
+// splats larger than LARGE_RADIUS (part[6 nb + b], part[7 nb + b]; at most
+// 2^22 tiles each): the compositing's choice of kernel.
 // A record without tiles (key all ones, sorted last in its view) is listed
 // nowhere: it gets no copy, which nothing uses.
 __global__ void __launch_bounds__(256) permute_classify_kernel(
     const uint32_t* __restrict__ order, const uint32_t* __restrict__ skeys, const float4* __restrict__ rec,
     int64_t R, int64_t n, ViewSet views, DevSettings st, uint32_t* __restrict__ cnt_out,
     uint64_t* __restrict__ tmask, float4* __restrict__ srec,
-    uint32_t* __restrict__ part) {
-    __shared__ uint32_t s_part[2][4];
+    uint32_t* __restrict__ part, int sizes) {
+    __shared__ uint32_t s_part[4][4];
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     const int lane = lane_id();
     const bool live = i < R;
@@ -328,20 +364,23 @@ __global__ void __launch_bounds__(256) permute_classify_kernel(
     const uint32_t e = wave_add_scan(live && wide ? cnt : 0u);
     const uint32_t ea = wave_add_scan(live ? cnt : 0u);
     const int wid = threadIdx.x >> 6;
+    if (sizes) {
+        const uint32_t all = wave_add_scan(c), large = wave_add_scan(B.w > LARGE_RADIUS ? c : 0u);
+        if (lane == 63) {
+            s_part[2][wid] = all;
+            s_part[3][wid] = large;
+        }
+    }
     if (lane == 63) {
         s_part[0][wid] = (uint32_t)__popcll(wb);
         s_part[1][wid] = e;
         part[2 * gridDim.x + (blockIdx.x * blockDim.x + threadIdx.x) / 64] = ea;
     }
     __syncthreads();
-    if (threadIdx.x == 0) {
-        uint32_t a = 0, b = 0;
-        for (int w = 0; w < (int)(blockDim.x >> 6); ++w) {
-            a += s_part[0][w];
-            b += s_part[1][w];
-        }
-        part[blockIdx.x] = a;
-        part[gridDim.x + blockIdx.x] = b;
+    if (threadIdx.x < 4u) {
+        const uint32_t k = threadIdx.x;
+        const uint32_t a = s_part[k][0] + s_part[k][1] + s_part[k][2] + s_part[k][3];
+        if (k < 2 || sizes) part[(k < 2 ? k : k + 4) * gridDim.x + blockIdx.x] = a;
     }
 }
 
@@ -349,30 +388,32 @@ __global__ void __launch_bounds__(256) permute_classify_kernel(
 // LO_GROUP waves (LO_GROUP / 4 classification workgroups).  Step 1, one
 // workgroup per group: each wave's first entry relative to its group (an
 // exclusive scan of the per-wave entry counts), the group's entry total and
-// its totals of wide records and their region entries.  Step 2, one
-// workgroup: the groups' first entries, the entry total (*total) and the
-// wide totals (wide[0], wide[2]).  A wave's first entry is then
+// its totals of wide records, their region entries and the footprint tiles.
+// Step 2, one workgroup: the groups' first entries, the entry total (*total),
+// the wide totals (wide[0], wide[2]) and the footprint tiles, all and of large
+// splats (wide[3], wide[4]).  A wave's first entry is then
 // wave_rel[wave] + group_off[wave / LO_GROUP].  Integer sums: no result
 // depends on an order.
 constexpr int LO_GROUP = 1024;
 struct ListOffsets {
     uint64_t* wave_rel;   // [waves]
-    uint64_t* group_tot;  // [groups, 3]: entries, wide records, region entries
+    uint64_t* group_tot;  // [groups, 5]: entries, wide records, region entries, footprint tiles (all, large)
     uint64_t* group_off;  // [groups]
 };
 
 __global__ void __launch_bounds__(LO_GROUP) list_offsets_group_kernel(const uint32_t* __restrict__ part, int64_t nb,
-                                                                     int64_t nw, ListOffsets lo) {
-    __shared__ uint64_t s_w[LO_GROUP / 64][3];
+                                                                     int64_t nw, ListOffsets lo, int sizes) {
+    __shared__ uint64_t s_w[LO_GROUP / 64][5];
     const int t = threadIdx.x, lane = lane_id(), wid = t >> 6;
     const int64_t w = (int64_t)blockIdx.x * LO_GROUP + t;  // this thread's wave
     const uint64_t c = w < nw ? part[2 * nb + w] : 0u;
     // the group's classification workgroups: LO_GROUP / 4 of them
     const int64_t b = (int64_t)blockIdx.x * (LO_GROUP / 4) + t;
-    uint64_t a = 0, r = 0;
+    uint64_t sum[4] = {0, 0, 0, 0};
     if (t < LO_GROUP / 4 && b < nb) {
-        a = part[b];
-        r = part[nb + b];
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+            if (k < 2 || sizes) sum[k] = part[(k < 2 ? k : k + 4) * nb + b];
     }
     uint64_t x = c;
 #pragma unroll
@@ -380,38 +421,35 @@ __global__ void __launch_bounds__(LO_GROUP) list_offsets_group_kernel(const uint
         const uint64_t y = __shfl_up(x, d);
         if (lane >= d) x += y;
     }
-    for (int off = 32; off > 0; off >>= 1) {
-        a += __shfl_xor(a, off);
-        r += __shfl_xor(r, off);
-    }
     if (lane == 63) s_w[wid][0] = x;
-    if (lane == 0) {
-        s_w[wid][1] = a;
-        s_w[wid][2] = r;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        for (int off = 32; off > 0; off >>= 1) sum[k] += __shfl_xor(sum[k], off);
+        if (lane == 0) s_w[wid][1 + k] = sum[k];
     }
     __syncthreads();
     uint64_t wo = 0;
     for (int v = 0; v < wid; ++v) wo += s_w[v][0];
     if (w < nw) lo.wave_rel[w] = wo + x - c;
-    if (t < 3) {
+    if (t < 5) {
         uint64_t tot = 0;
         for (int v = 0; v < LO_GROUP / 64; ++v) tot += s_w[v][t];
-        lo.group_tot[3 * blockIdx.x + t] = tot;
+        lo.group_tot[5 * blockIdx.x + t] = tot;
     }
 }
 
 __global__ void __launch_bounds__(LO_GROUP) list_offsets_total_kernel(int64_t ng, ListOffsets lo,
                                                                      uint64_t* __restrict__ total,
                                                                      uint64_t* __restrict__ wide) {
-    __shared__ uint64_t s_w[LO_GROUP / 64][3];
+    __shared__ uint64_t s_w[LO_GROUP / 64][5];
     const int t = threadIdx.x, lane = lane_id(), wid = t >> 6;
-    uint64_t carry = 0, a = 0, r = 0;
+    uint64_t carry = 0, sum[4] = {0, 0, 0, 0};
     for (int64_t base = 0; base < ng; base += LO_GROUP) {
         const int64_t g = base + t;
-        const uint64_t c = g < ng ? lo.group_tot[3 * g] : 0u;
+        const uint64_t c = g < ng ? lo.group_tot[5 * g] : 0u;
         if (g < ng) {
-            a += lo.group_tot[3 * g + 1];
-            r += lo.group_tot[3 * g + 2];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) sum[k] += lo.group_tot[5 * g + 1 + k];
         }
         uint64_t x = c;
 #pragma unroll
@@ -430,24 +468,17 @@ __global__ void __launch_bounds__(LO_GROUP) list_offsets_total_kernel(int64_t ng
         carry += tot;
         __syncthreads();  // s_w is written again by the next round
     }
-    for (int off = 32; off > 0; off >>= 1) {
-        a += __shfl_xor(a, off);
-        r += __shfl_xor(r, off);
-    }
-    if (lane == 0) {
-        s_w[wid][1] = a;
-        s_w[wid][2] = r;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        for (int off = 32; off > 0; off >>= 1) sum[k] += __shfl_xor(sum[k], off);
+        if (lane == 0) s_w[wid][1 + k] = sum[k];
     }
     __syncthreads();
-    if (t == 0) {
-        uint64_t ta = 0, tr = 0;
-        for (int v = 0; v < LO_GROUP / 64; ++v) {
-            ta += s_w[v][1];
-            tr += s_w[v][2];
-        }
-        *total = carry;
-        wide[0] = ta;
-        wide[2] = tr;
+    if (t == 0) *total = carry;
+    if (t < 4) {
+        uint64_t tot = 0;
+        for (int v = 0; v < LO_GROUP / 64; ++v) tot += s_w[v][1 + t];
+        wide[t == 0 ? 0 : t + 1] = tot;
     }
 }
 
@@ -760,15 +791,17 @@ __global__ void __launch_bounds__(256) order_place_kernel(const uint32_t* __rest
 // order_place_kernel for the forward's set-up (the keys: key[t], or cost[t]
 // when key is null), which also completes the checkpoint offsets: cur_off[t]
 // (a prefix within its workgroup of 256 tiles) plus the totals of the
-// earlier workgroups (blk), and *cur_need = the grand total.
-__global__ void __launch_bounds__(256) order_offsets_kernel(const uint32_t* __restrict__ key,
+// earlier workgroups (blk), and *cur_need = the grand total.  The batch
+// counts of the tiles (nbatch, which key may be) are cleared for the forward.
+__global__ void __launch_bounds__(256) order_offsets_kernel(const uint32_t* key,
                                                              const uint32_t* __restrict__ cost, uint32_t n,
                                                              const uint32_t* __restrict__ hist,
                                                              uint32_t* __restrict__ cursor,
                                                              uint32_t* __restrict__ order,
                                                              uint32_t* __restrict__ cur_off,
                                                              const uint32_t* __restrict__ blk,
-                                                             uint64_t* __restrict__ cur_need) {
+                                                             uint64_t* __restrict__ cur_need,
+                                                             uint32_t* nbatch) {
     __shared__ uint32_t s_base[256];
     __shared__ uint32_t s_cnt[256];
     __shared__ uint32_t s_wsum[4];
@@ -803,7 +836,10 @@ __global__ void __launch_bounds__(256) order_offsets_kernel(const uint32_t* __re
     __syncthreads();
     if (s_cnt[t]) s_base[t] = start + atomicAdd(&cursor[t], s_cnt[t]);
     __syncthreads();
-    if (i < n) order[s_base[b] + rank] = i;
+    if (i < n) {
+        order[s_base[b] + rank] = i;
+        nbatch[i] = 0u;  // (key may be the same array: read above by this thread only)
+    }
 }
 
 // ---------------------------------------------------------------------------
@@ -822,10 +858,11 @@ struct Lds {
     // LDS address per entry, the three reads at fixed offsets
     float4* E;
     uint32_t* m;      // merged positions of the batch
+    uint8_t* bm;      // the 4x4 blocks each staged entry can reach (kernels for small splats)
     uint32_t* wsum;   // per-wave partial counts
 };
 
-__host__ __device__ constexpr size_t lds_bytes(int batch) { return (size_t)batch * (48 + 4) + 64; }
+__host__ __device__ constexpr size_t lds_bytes(int batch) { return (size_t)batch * (48 + 4 + 1) + 64; }
 
 __device__ __forceinline__ Lds carve(char* smem, int batch) {
     Lds L;
@@ -835,7 +872,8 @@ __device__ __forceinline__ Lds carve(char* smem, int batch) {
     L.yk = L.yraw + batch;
     L.ypass = reinterpret_cast<uint8_t*>(L.yk + batch);
     L.m = reinterpret_cast<uint32_t*>(smem + 48 * (size_t)batch);
-    L.wsum = L.m + batch;
+    L.bm = reinterpret_cast<uint8_t*>(L.m + batch);
+    L.wsum = reinterpret_cast<uint32_t*>(L.bm + batch);
     return L;
 }
 
@@ -886,6 +924,28 @@ struct Batch {
     int nYraw;  // region entries consumed (including those not belonging to the tile)
 };
 
+// Stages a record as entry j of the batch: a and gamma scaled for eval_entry,
+// the entry's index k in the tile's full list in B.w (which held the radius,
+// unused here), and, for the kernels for small splats, the blocks of the part
+// at (qx0, qy0) it can reach.
+template <bool FINE>
+__device__ __forceinline__ void put_entry(const Lds& L, int j, const float4& A, const float4& B, const float4& C,
+                                          int k, int qx0, int qy0, int height, const DevSettings& st) {
+    float4 Bs = stage_b(B);
+    Bs.w = __int_as_float(k);
+    L.E[3 * j] = stage_a(A);
+    L.E[3 * j + 1] = Bs;
+    L.E[3 * j + 2] = C;
+    if constexpr (FINE) L.bm[j] = (uint8_t)block_mask(A, B, qx0, qy0, height, st);
+}
+
+// ... the record at sorted position p
+template <bool FINE>
+__device__ __forceinline__ void stage_entry(const Lds& L, int j, const float4* __restrict__ srec, size_t p, int k,
+                                            int qx0, int qy0, int height, const DevSettings& st) {
+    put_entry<FINE>(L, j, srec[3 * p], srec[3 * p + 1], srec[3 * p + 2], k, qx0, qy0, height, st);
+}
+
 // Stages the next (at most `batch`) entries of the tile's merged list in LDS.
 // Every thread of the block calls it; the result is uniform.  The first
 // stream is the tile's narrow list, the second its region list, of which
@@ -894,10 +954,22 @@ struct Batch {
 // culled the same way, so every merged entry is staged); without, those
 // whose tile rectangle contains the tile (the list of Sec. 3.1), and the
 // touch test then only decides which merged entries are staged.
+template <bool FINE>
 __device__ Batch merge_batch(const Lds& L, const uint32_t* __restrict__ vals, const float4* __restrict__ srec,
                              int i1, int e1, int i2, int e2, int batch, int tcx, int tcy, const TileBox& tb,
-                             const DevView& cam, const DevSettings& st, int kbase) {
+                             const DevView& cam, const DevSettings& st, int kbase, int qx0 = 0, int qy0 = 0) {
     const int t = threadIdx.x, NT = blockDim.x;
+    if (st.tile_cull && i2 >= e2) {
+        // no region entries left: the next narrow entries are the batch
+        const int M = min(batch, e1 - i1);
+        for (int j = t; j < M; j += NT) {
+            const uint32_t p = vals[i1 + j];
+            L.m[j] = p;
+            stage_entry<FINE>(L, j, srec, p, kbase + j, qx0, qy0, cam.height, st);
+        }
+        __syncthreads();
+        return Batch{M, M, M, 0};
+    }
     const int cX = min(batch, e1 - i1), cY = min(batch, e2 - i2);
     for (int l = t; l < cX; l += NT) L.xk[l] = vals[i1 + l];
     for (int l = t; l < cY; l += NT) {
@@ -957,20 +1029,12 @@ __device__ Batch merge_batch(const Lds& L, const uint32_t* __restrict__ vals, co
     for (int b = t; b < nY; b += NT) L.m[b + count_lt(L.xk, nX, L.yk[b])] = L.yk[b];
     __syncthreads();
     // the windows are dead: stage over them, in merged order, the records
-    // that can reach a pixel of the tile (a and gamma scaled for
-    // eval_entry); B.w (the radius, unused here) carries the entry's index
-    // in the tile's full list: kbase (the merged entries of the earlier
-    // batches) plus its index within the merged batch
+    // that can reach a pixel of the tile; an entry's index in the tile's full
+    // list is kbase (the merged entries of the earlier batches) plus its
+    // index within the merged batch
     const int M = nX + nY;
     if (st.tile_cull) {
-        for (int j = t; j < M; j += NT) {
-            const size_t i = L.m[j];
-            float4 B = stage_b(srec[3 * i + 1]);
-            B.w = __int_as_float(kbase + j);
-            L.E[3 * j] = stage_a(srec[3 * i]);
-            L.E[3 * j + 1] = B;
-            L.E[3 * j + 2] = srec[3 * i + 2];
-        }
+        for (int j = t; j < M; j += NT) stage_entry<FINE>(L, j, srec, L.m[j], kbase + j, qx0, qy0, cam.height, st);
         __syncthreads();
         return Batch{M, M, nX, nYr};
     }
@@ -991,12 +1055,7 @@ __device__ Batch merge_batch(const Lds& L, const uint32_t* __restrict__ vals, co
     for (int q = 0; q < run; ++q) {
         if (!((keep >> q) & 1u)) continue;
         const int j = t * run + q;
-        const size_t i = L.m[j];
-        float4 B = stage_b(srec[3 * i + 1]);
-        B.w = __int_as_float(kbase + j);
-        L.E[3 * p] = stage_a(srec[3 * i]);
-        L.E[3 * p + 1] = B;
-        L.E[3 * p + 2] = srec[3 * i + 2];
+        stage_entry<FINE>(L, (int)p, srec, L.m[j], kbase + j, qx0, qy0, cam.height, st);
         ++p;
     }
     __syncthreads();
@@ -1167,7 +1226,8 @@ __global__ void __launch_bounds__(TW * TH / PPT, PPT >= 4 ? 5 : 7) hybrid_fwd_ke
             for (int i = 0; i < PPT; ++i) active |= stopk[i] < 0;
             if (!__syncthreads_or(active)) break;
             if (t == 0) cur[b] = make_uint4((uint32_t)i1, (uint32_t)i2, (uint32_t)m, 0u);
-            const Batch bt = merge_batch(L, hl.vals, srec, i1, e1, i2, e2, batch, tcx, tcy, tb, cam, st, m);
+            const Batch bt =
+                merge_batch<false>(L, hl.vals, srec, i1, e1, i2, e2, batch, tcx, tcy, tb, cam, st, m);
             // room for the staged entries in the list kept for the backward:
             // thread 0 sub-allocates from a chunk the workgroup took from the
             // global counter (one atomic per chunk, not per batch)
@@ -1396,8 +1456,8 @@ __global__ void __launch_bounds__(TW * TH / PPT, 5) hybrid_bwd_kernel(
                 }
                 __syncthreads();
             } else {
-                Mb = merge_batch(L, hl.vals, srec, (int)c.x, (int)r1.y, (int)c.y, (int)r2.y, batch, tcx, tcy, tb,
-                                 cam, st, m).M;
+                Mb = merge_batch<false>(L, hl.vals, srec, (int)c.x, (int)r1.y, (int)c.y, (int)r2.y, batch, tcx,
+                                            tcy, tb, cam, st, m).M;
             }
             for (int j = Mb - 1; j >= 0; --j) {
                 const float4 A = L.E[3 * j], B = L.E[3 * j + 1], Cc = L.E[3 * j + 2];
@@ -1464,11 +1524,536 @@ __global__ void __launch_bounds__(TW * TH / PPT, 5) hybrid_bwd_kernel(
     }
 }
 
+// ---------------------------------------------------------------------------
+// compositing of small splats: four list entries of a 4x4 pixel block at a time
+// ---------------------------------------------------------------------------
+
+// A wave of the kernels above takes a tile's entries one after the other; a
+// wave that has its SIMD to itself needs about 650 (forward) and 1100
+// (backward) cycles per entry, and where splats are small, most pixels of the
+// tile evaluate an entry in vain and a few long lists decide the launch's
+// time.  Here a workgroup of four waves owns an 8x8 pixel part of a tile and
+// each wave a 4x4 block of it.  The block's list is the staged batch without
+// the entries that cannot reach the block, and the wave's four 16-lane rows
+// take four consecutive entries of it at a time; the transmittance passes
+// along the rows through the gfx950 lane swaps.  Per pixel and entry this
+// issues about three times the instructions of the kernels above, so it pays
+// where splats reach a fraction of the tile or the tiles leave the device idle
+// (rule: use_fine).  Measured against the kernels above at two pixels per
+// thread: 200 k small splats at 800x800, forward 304 -> 80 us, backward 449 ->
+// 112 us; 4096 splats at 128x128, 216 -> 33 and 336 -> 44 us.  Bound by VALU
+// issue where a few parts hold long lists.  Launches are plain (one workgroup
+// per part, the tiles in queue order): a loop over a device queue keeps the
+// kernel arguments live and spills (forward 97 -> 80 us without it).
+constexpr int FINE_NT = 256;
+constexpr int FINE_BATCH = 256;  // entries per batch: one per thread
+
+// Row exchanges of a value x with rows (x0, x1, x2, x3): the even and the odd
+// row of each row pair (x0, x0, x2, x2), (x1, x1, x3, x3); the lower and the
+// upper half (xa, xa), (xb, xb).
+struct Rows2 {
+    float lo, hi;
+};
+__device__ __forceinline__ Rows2 row_pairs(float x) {
+    const auto s = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    return Rows2{__uint_as_float(s[0]), __uint_as_float(s[1])};
+}
+__device__ __forceinline__ Rows2 row_halves(float x) {
+    const auto s = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    return Rows2{__uint_as_float(s[0]), __uint_as_float(s[1])};
+}
+// maximum and sum over the four rows, per column
+__device__ __forceinline__ int rows_max(int x) {
+    const auto a = __builtin_amdgcn_permlane16_swap((uint32_t)x, (uint32_t)x, false, false);
+    const int y = max((int)a[0], (int)a[1]);
+    const auto b = __builtin_amdgcn_permlane32_swap((uint32_t)y, (uint32_t)y, false, false);
+    return max((int)b[0], (int)b[1]);
+}
+__device__ __forceinline__ int rows_add(int x) {
+    const auto a = __builtin_amdgcn_permlane16_swap((uint32_t)x, (uint32_t)x, false, false);
+    const int y = (int)(a[0] + a[1]);
+    const auto b = __builtin_amdgcn_permlane32_swap((uint32_t)y, (uint32_t)y, false, false);
+    return (int)(b[0] + b[1]);
+}
+// maximum over the 16 lanes of each row, in every lane of the row
+__device__ __forceinline__ float row_max(float x) {
+    x = fmaxf(x, dpp_ror8(x));
+    x = fmaxf(x, dpp_ror4(x));
+    x = fmaxf(x, dpp_xor2(x));
+    return fmaxf(x, dpp_xor1(x));
+}
+
+// LDS of one workgroup after the staging area of lds_bytes: per wave the
+// block's list (byte offsets of its entries in L.E, two rounds of padding)
+// and, in the backward, ten partial sums per staged entry.
+constexpr int FINE_LIST = FINE_BATCH + 8;
+constexpr size_t fine_lds_bytes(bool bwd) {
+    return lds_bytes(FINE_BATCH) + (FINE_NT / 64) * FINE_LIST * 2 + (bwd ? FINE_BATCH * 40 : 0);
+}
+
+// Part q of a launch over the 8x8 parts of every tile, tiles in queue order.
+struct FinePart {
+    uint32_t tile;
+    TileGeom tg;
+    int qx0, qy0;  // first pixel of the part
+};
+__device__ __forceinline__ FinePart fine_part(const ViewSet& views, const HybridLists& hl, const DevSettings& st,
+                                              uint32_t q, uint32_t parts) {
+    FinePart f;
+    const uint32_t s = q / parts, part = q - s * parts;
+    f.tile = hl.order ? hl.order[s] : s;
+    f.tg = tile_geom(views, f.tile, st.tile_w, st.tile_h);
+    const uint32_t pw = (uint32_t)st.tile_w / 8u;
+    f.qx0 = f.tg.tx0 + (int)(part % pw) * 8;
+    f.qy0 = f.tg.ty0 + (int)(part / pw) * 8;
+    return f;
+}
+
+// The staged entries that can reach this wave's block (and have index at most
+// kmax in the tile's list) as a list of their offsets in order, followed by
+// zeros; returns their number (uniform).  LDS operations of one wave complete
+// in program order.
+__device__ __forceinline__ int block_list(const Lds& L, int M, int wave, int lane, int kmax, uint16_t* list) {
+    uint32_t bm[FINE_BATCH / 64];
+    int k[FINE_BATCH / 64];
+#pragma unroll
+    for (int i = 0; i < FINE_BATCH / 64; ++i) {
+        const int j = 64 * i + lane;
+        bm[i] = L.bm[j];
+        k[i] = __float_as_int(L.E[3 * j + 1].w);
+    }
+    int n = 0;
+#pragma unroll
+    for (int i = 0; i < FINE_BATCH / 64; ++i) {
+        const int j = 64 * i + lane;
+        const bool in = (j < M) & (((bm[i] >> wave) & 1u) != 0) & (k[i] <= kmax);
+        const uint64_t m = ballot(in);
+        if (in) list[n + (int)__popcll(m & lanemask_lt())] = (uint16_t)(48 * j);
+        n += (int)__popcll(m);
+    }
+    if (lane < 8) list[n + lane] = 0;
+    __builtin_amdgcn_wave_barrier();
+    return n;
+}
+
+// A part's batches.  While a batch whose tile has no region entries left is
+// composited, the thread's record of the next batch and its position of the
+// one after are on their way.
+struct FineStream {
+    float4 A, B, C;
+    uint32_t p, pn;
+    bool have;  // A, B, C, p hold the next batch's record (uniform)
+};
+
+__device__ __forceinline__ Batch fine_batch(const Lds& L, FineStream& fs, const HybridLists& hl,
+                                            const float4* __restrict__ srec, int i1, int e1, int i2, int e2, int tcx,
+                                            int tcy, const TileBox& tb, const DevView& cam, const DevSettings& st,
+                                            int kbase, int qx0, int qy0) {
+    if (!(st.tile_cull && i2 >= e2)) {
+        fs.have = false;
+        return merge_batch<true>(L, hl.vals, srec, i1, e1, i2, e2, FINE_BATCH, tcx, tcy, tb, cam, st, kbase, qx0, qy0);
+    }
+    const int t = threadIdx.x;
+    const int M = min(FINE_BATCH, e1 - i1);
+    if (!fs.have) {
+        fs.p = t < M ? hl.vals[i1 + t] : 0u;
+        if (t < M) {
+            fs.A = srec[3 * (size_t)fs.p];
+            fs.B = srec[3 * (size_t)fs.p + 1];
+            fs.C = srec[3 * (size_t)fs.p + 2];
+        }
+        fs.pn = i1 + FINE_BATCH + t < e1 ? hl.vals[i1 + FINE_BATCH + t] : 0u;
+    }
+    if (t < M) put_entry<true>(L, t, fs.A, fs.B, fs.C, kbase + t, qx0, qy0, cam.height, st);
+    __syncthreads();
+    fs.have = i1 + FINE_BATCH < e1;
+    if (fs.have) {
+        fs.p = fs.pn;
+        if (i1 + FINE_BATCH + t < e1) {
+            fs.A = srec[3 * (size_t)fs.p];
+            fs.B = srec[3 * (size_t)fs.p + 1];
+            fs.C = srec[3 * (size_t)fs.p + 2];
+        }
+        fs.pn = i1 + 2 * FINE_BATCH + t < e1 ? hl.vals[i1 + 2 * FINE_BATCH + t] : 0u;
+    }
+    return Batch{M, M, M, 0};
+}
+
+template <bool STATS, bool IMP>
+__global__ void __launch_bounds__(FINE_NT, 6) hybrid_fwd_fine_kernel(
+    const float4* __restrict__ srec, HybridLists hl, ViewSet views, DevSettings st, float* __restrict__ images,
+    float* __restrict__ t_final, int32_t* __restrict__ last_out, int4* __restrict__ stats_out,
+    int4* __restrict__ eval_out, int64_t n, double* __restrict__ imp_sum, uint32_t* __restrict__ imp_max,
+    uint32_t parts) {
+    extern __shared__ __align__(16) char smem[];
+    const int t = threadIdx.x;
+    const int lane = lane_id();
+    const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
+    const int row = lane >> 4, col = lane & 15;
+    const bool odd = (row & 1) != 0, upper = row >= 2;
+    const Lds L = carve(smem, FINE_BATCH);
+    uint16_t* list = reinterpret_cast<uint16_t*>(smem + lds_bytes(FINE_BATCH)) + wave * FINE_LIST;
+    const uint2* list4 = reinterpret_cast<const uint2*>(list);
+    const int chan = 32 + 4 * min(row, 2);  // offset of this row's channel in a staged entry
+    const float bgr = row == 0 ? st.bg[0] : (row == 1 ? st.bg[1] : st.bg[2]);
+    const EvalConsts ek = eval_consts(st);
+    if (*hl.cur_need > hl.cur_cap) {  // a fixed workspace too small: report, write nothing
+        if (blockIdx.x == 0 && t == 0) atomicOr(hl.flags, FLAG_CAPACITY);
+        return;
+    }
+    const uint32_t q = blockIdx.x;
+    const FinePart fp = fine_part(views, hl, st, q, parts);
+    const uint32_t tile = fp.tile;
+    const TileGeom tg = fp.tg;
+    const DevView& cam = views.v[tg.vi];
+    const int x = fp.qx0 + (wave & 1) * 4 + (col & 3), y = fp.qy0 + (wave >> 1) * 4 + (col >> 2);
+    const bool inside = x < cam.width && y < cam.height;
+    const float px = (float)x + 0.5f, py = (float)y + 0.5f;
+    // T: the pixel's transmittance (the same in its four lanes); C: the
+    // channel of this row; the last blended index and the counters are
+    // those of the entries this row took
+    float T = 1.f, C = 0.f;
+    int last = -1, stopk = 0x7fffffff, nblend = 0, nmasked = 0, nev = 0x7fffffff, nev_last = 0, staged = 0;
+    bool run = inside;
+    const int tcx = tg.tx0 / st.tile_w, tcy = tg.ty0 / st.tile_h;
+    const uint2 r1 = hl.ranges[tile];
+    const uint2 r2 = hl.ranges[region_of_tile(tcx, tcy, cam, views)];
+    const int e1 = (int)r1.y, e2 = (int)r2.y;
+    int i1 = (int)r1.x, i2 = (int)r2.x, m = 0, b = 0;
+    const TileBox tb{(float)tg.tx0 + 0.5f, (float)min(tg.tx0 + st.tile_w, cam.width) - 0.5f,
+                     (float)tg.ty0 + 0.5f, (float)min(tg.ty0 + st.tile_h, cam.height) - 0.5f};
+    uint4* cur = hl.cur + hl.cur_off[tile];
+    FineStream fs;
+    fs.have = false;
+    while (i1 < e1 || i2 < e2) {
+        if (!__syncthreads_or(run)) break;
+        // (every part of the tile that gets here writes the same values)
+        if (t == 0) cur[b] = make_uint4((uint32_t)i1, (uint32_t)i2, (uint32_t)m, 0u);
+        const Batch bt = fine_batch(L, fs, hl, srec, i1, e1, i2, e2, tcx, tcy, tb, cam, st, m, fp.qx0, fp.qy0);
+        const int ne = ballot(run) ? block_list(L, bt.M, wave, lane, 0x7fffffff, list) : 0;
+        // one entry per row and round; the offsets of the four are read
+        // two rounds ahead, the geometry one round ahead
+        uint2 o0 = make_uint2(0u, 0u), o1 = o0;
+        if (ne > 0) {  // (without a list its words hold anything)
+            o0 = list4[0];
+            o1 = list4[1];
+        }
+        uint32_t own = ((upper ? o0.y : o0.x) >> (odd ? 16 : 0)) & 0xffffu;
+        float4 A = *reinterpret_cast<const float4*>(smem + own);
+        float4 B = *reinterpret_cast<const float4*>(smem + own + 16);
+        for (int e0 = 0; e0 < ne; e0 += 4) {
+            const uint2 o2 = list4[e0 / 4 + 2 < FINE_LIST / 4 ? e0 / 4 + 2 : 0];
+            const uint32_t ownn = ((upper ? o1.y : o1.x) >> (odd ? 16 : 0)) & 0xffffu;
+            const float4 An = *reinterpret_cast<const float4*>(smem + ownn);
+            const float4 Bn = *reinterpret_cast<const float4*>(smem + ownn + 16);
+            const float c0 = *reinterpret_cast<const float*>(smem + (o0.x & 0xffffu) + chan);
+            const float c1 = *reinterpret_cast<const float*>(smem + (o0.x >> 16) + chan);
+            const float c2 = *reinterpret_cast<const float*>(smem + (o0.y & 0xffffu) + chan);
+            const float c3 = *reinterpret_cast<const float*>(smem + (o0.y >> 16) + chan);
+            const int k = __float_as_int(B.w);  // index in the tile's full list
+            Eval e;
+            bool hit = eval_entry(A, B, px, py, ek, e) & (e0 + row < ne) & run;
+            const float f = hit ? fmaf(-B.z, e.alpha, 1.f) : 1.f;
+            // the transmittance after each entry, by one product after
+            // the other as in hybrid_fwd_kernel: images do not depend on
+            // the kernel
+            const Rows2 fr = row_pairs(f);
+            const Rows2 fa = row_halves(fr.lo), fb = row_halves(fr.hi);
+            const float t1 = T * fa.lo, t2 = t1 * fb.lo, t3 = t2 * fa.hi, t4 = t3 * fb.hi;
+            const float Tb = upper ? (odd ? t3 : t2) : (odd ? t1 : T);
+            float Tn = t4;
+            const bool over = run & (t4 < st.t_min);
+            const uint64_t om = ballot(over);
+            if (om) {
+                // the first entry that would leave less than t_min stops
+                // the pixel and is excluded, as are those behind it
+                const int s = !over ? 4 : (t1 < st.t_min ? 0 : (t2 < st.t_min ? 1 : (t3 < st.t_min ? 2 : 3)));
+                if (over) Tn = s == 0 ? T : (s == 1 ? t1 : (s == 2 ? t2 : t3));
+                if (STATS && row == s) {
+                    stopk = k;
+                    nev = staged + (int)(own / 48u) + 1;
+                }
+                hit = hit & (row < s);
+                run = run & !over;
+            }
+            T = Tn;
+            const float wgt = hit ? B.z * e.alpha * Tb : 0.f;
+            const Rows2 wr = row_pairs(wgt);
+            const Rows2 wa = row_halves(wr.lo), wb = row_halves(wr.hi);
+            // (an entry that does not reach the pixel must not touch its
+            // colour: it may be infinite)
+            if (wa.lo != 0.f) C = fmaf(wa.lo, c0, C);
+            if (wb.lo != 0.f) C = fmaf(wb.lo, c1, C);
+            if (wa.hi != 0.f) C = fmaf(wa.hi, c2, C);
+            if (wb.hi != 0.f) C = fmaf(wb.hi, c3, C);
+            if (hit) {
+                last = k;
+                if (STATS) {
+                    ++nblend;
+                    nmasked += B.z == 0.f;
+                    nev_last = staged + (int)(own / 48u) + 1;
+                }
+            }
+            if (IMP && ballot(wgt > 0.f)) {
+                const float ws = row_total(wgt), wm = row_max(wgt);
+                if (col == 0 && !(ws <= 0.f)) {
+                    const uint32_t r = *reinterpret_cast<const uint32_t*>(smem + own + 44);
+                    const int64_t g = (int64_t)r - (int64_t)tg.vi * n;
+                    atomicAdd(imp_sum + g, (double)ws);
+                    atomicMax(imp_max + g, __float_as_uint(wm));
+                }
+            }
+            if (om && !ballot(run)) break;
+            own = ownn;
+            A = An;
+            B = Bn;
+            o0 = o1;
+            o1 = o2;
+        }
+        i1 += bt.nX;
+        i2 += bt.nYraw;
+        m += bt.Mfull;
+        staged += bt.M;
+        ++b;
+        __syncthreads();  // the next batch overwrites the LDS
+    }
+    if (t == 0) atomicMax(hl.nbatch + tile, (uint32_t)b);
+    if (hl.drec_clear) {
+        // the backward's accumulator, one slice per part (as in
+        // hybrid_fwd_kernel)
+        const uint64_t np = (uint64_t)views.total_tiles * parts;
+        const uint64_t per = (hl.drec_clear_n2 + np - 1) / np;
+        const uint64_t q0 = (uint64_t)q * per;
+        const uint64_t q1 = min(q0 + per, hl.drec_clear_n2);
+        double2* z = reinterpret_cast<double2*>(hl.drec_clear);
+        for (uint64_t zq = q0 + (uint64_t)t; zq < q1; zq += FINE_NT) z[zq] = make_double2(0.0, 0.0);
+    }
+    last = rows_max(last);
+    const int64_t pv = (int64_t)cam.width * cam.height;
+    const int64_t loc = (int64_t)y * cam.width + x;
+    const int64_t p = (int64_t)cam.px_off + loc;
+    if (inside) {
+        // row r writes channel r, the last row the per-pixel state
+        if (row < 3) {
+            images[3 * (int64_t)cam.px_off + row * pv + loc] = fmaf(T, bgr, C);
+        } else {
+            t_final[p] = T;
+            last_out[p] = last;
+        }
+    }
+    if (STATS) {
+        stopk = -rows_max(-stopk);
+        nev = -rows_max(-nev);
+        nev_last = rows_max(nev_last);
+        nblend = rows_add(nblend);
+        nmasked = rows_add(nmasked);
+        if (inside && row == 0) {
+            stats_out[p] = make_int4(stopk != 0x7fffffff ? stopk + 1 : m, nblend, nmasked, last + 1);
+            eval_out[p] = make_int4(nev != 0x7fffffff ? nev : staged, nev_last, 0, 0);
+        }
+    }
+}
+
+// Row sums of ten per-lane quantities, folded pairwise while the lanes are
+// halved: after the step over 8 lanes a lane holds one of two quantities, and
+// so on; the quantity whose row total lane col ends with is
+// fold10_quantity(col) (-1: none).  The step that chooses on bit 2 pairs lanes
+// l and l ^ 7 (the mirror within 8 lanes): the four lanes of a quad then still
+// cover the eight.
+__device__ __forceinline__ float dpp_xor7(float x) {
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x141, 0xf, 0xf, false));
+}
+__device__ __forceinline__ int fold10_quantity(int col) {
+    const int q = ((col >> 3) & 1) + ((col >> 2) & 1) * 2 + ((col >> 1) & 1) * 4;
+    if ((col & 1) == 0) return q;
+    return (col & 6) == 0 ? 8 + ((col >> 3) & 1) : -1;
+}
+__device__ __forceinline__ float row_fold10(const float (&v)[10], int col) {
+    const bool b3 = (col & 8) != 0, b2 = (col & 4) != 0, b1 = (col & 2) != 0, b0 = (col & 1) != 0;
+    float a[5];
+#pragma unroll
+    for (int i = 0; i < 5; ++i) a[i] = (b3 ? v[2 * i + 1] : v[2 * i]) + dpp_ror8(b3 ? v[2 * i] : v[2 * i + 1]);
+    // a[i]: quantity 2 i + b3
+    const float c0 = (b2 ? a[1] : a[0]) + dpp_xor7(b2 ? a[0] : a[1]);
+    const float c1 = (b2 ? a[3] : a[2]) + dpp_xor7(b2 ? a[2] : a[3]);
+    const float c2 = a[4] + dpp_xor7(a[4]);
+    const float d0 = (b1 ? c1 : c0) + dpp_xor2(b1 ? c0 : c1);
+    const float d1 = c2 + dpp_xor2(c2);
+    return (b0 ? d1 : d0) + dpp_xor1(b0 ? d0 : d1);
+}
+
+__global__ void __launch_bounds__(FINE_NT, 5) hybrid_bwd_fine_kernel(
+    const float4* __restrict__ srec, HybridLists hl, ViewSet views, DevSettings st, const float* __restrict__ t_final,
+    const int32_t* __restrict__ last_in, const float* __restrict__ dl_dimages, int64_t n, double* __restrict__ d_rec,
+    double* __restrict__ d_masks, uint32_t parts) {
+    extern __shared__ __align__(16) char smem[];
+    __shared__ int s_top;
+    const int t = threadIdx.x;
+    const int lane = lane_id();
+    const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
+    const int row = lane >> 4, col = lane & 15;
+    const bool odd = (row & 1) != 0, upper = row >= 2;
+    const Lds L = carve(smem, FINE_BATCH);
+    uint16_t* list = reinterpret_cast<uint16_t*>(smem + lds_bytes(FINE_BATCH)) + wave * FINE_LIST;
+    // ten partial sums per staged entry, added up over the part's blocks
+    float* acc = reinterpret_cast<float*>(smem + lds_bytes(FINE_BATCH) + (FINE_NT / 64) * FINE_LIST * 2);
+    const int qi = fold10_quantity(col);
+    const EvalConsts ek = eval_consts(st);
+    if (*hl.cur_need > hl.cur_cap) return;  // the forward reported it
+    for (int i = t; i < FINE_BATCH * 10; i += FINE_NT) acc[i] = 0.f;
+    const uint32_t q = blockIdx.x;
+    const FinePart fp = fine_part(views, hl, st, q, parts);
+    const uint32_t tile = fp.tile;
+    const TileGeom tg = fp.tg;
+    const DevView& cam = views.v[tg.vi];
+    const int64_t rec_base = (int64_t)tg.vi * n;
+    const int64_t pv = (int64_t)cam.width * cam.height;
+    const int x = fp.qx0 + (wave & 1) * 4 + (col & 3), y = fp.qy0 + (wave >> 1) * 4 + (col >> 2);
+    const float px = (float)x + 0.5f, py = (float)y + 0.5f;
+    float Tf = 1.f, w0 = 0.f, w1 = 0.f, w2 = 0.f;
+    int lastk = -1;
+    if (x < cam.width && y < cam.height) {
+        const int64_t loc = (int64_t)y * cam.width + x;
+        const int64_t p = (int64_t)cam.px_off + loc;
+        const float* dl = dl_dimages + 3 * (int64_t)cam.px_off;
+        lastk = last_in[p];
+        Tf = t_final[p];
+        w0 = dl[loc];
+        w1 = dl[pv + loc];
+        w2 = dl[2 * pv + loc];
+    }
+    // T and sb (the loss weights dotted with the colour behind) of the
+    // pixel are the same in its four lanes
+    float T = Tf, sb = 0.f;
+    const float wbg = w0 * st.bg[0] + w1 * st.bg[1] + w2 * st.bg[2];
+    const int wlast = __builtin_amdgcn_readlane(wave_max_scan(lastk), 63);  // the block's last blended index
+    if (t == 0) s_top = -1;
+    __syncthreads();
+    if (lane == 0) atomicMax(&s_top, wlast);
+    __syncthreads();
+    const int top = s_top;
+    const uint4* cur = hl.cur + hl.cur_off[tile];
+    const int tcx = tg.tx0 / st.tile_w, tcy = tg.ty0 / st.tile_h;
+    const uint2 r1 = hl.ranges[tile];
+    const uint2 r2 = hl.ranges[region_of_tile(tcx, tcy, cam, views)];
+    const TileBox tb{(float)tg.tx0 + 0.5f, (float)min(tg.tx0 + st.tile_w, cam.width) - 0.5f,
+                     (float)tg.ty0 + 0.5f, (float)min(tg.ty0 + st.tile_h, cam.height) - 0.5f};
+    // the batch holding the largest last-blended entry (the batches'
+    // first indices ascend), then backwards.  A tile without region entries
+    // has its narrow list as its batches, one after the other: there the
+    // thread's record of the next batch and its position of the one after
+    // are on their way while a batch is worked on.
+    const bool plain = st.tile_cull != 0 && r2.x >= r2.y;
+    int bstar = -1;
+    if (top >= 0 && plain) {
+        bstar = top / FINE_BATCH;
+    } else if (top >= 0) {
+        const int nb = (int)hl.nbatch[tile];
+        for (int b0 = 0; b0 < nb; b0 += 64)
+            bstar += (int)__popcll(ballot(b0 + lane < nb && (int)cur[min(b0 + lane, nb - 1)].z <= top));
+    }
+    float4 nA, nB, nC;
+    uint32_t np = 0;
+    if (plain && bstar >= 0) {
+        if (bstar * FINE_BATCH + t <= top) {
+            const size_t p = hl.vals[r1.x + (uint32_t)(bstar * FINE_BATCH + t)];
+            nA = srec[3 * p];
+            nB = srec[3 * p + 1];
+            nC = srec[3 * p + 2];
+        }
+        if (bstar > 0) np = hl.vals[r1.x + (uint32_t)((bstar - 1) * FINE_BATCH + t)];
+    }
+    for (int b = bstar; b >= 0; --b) {
+        int m, Mb;
+        if (plain) {
+            m = b * FINE_BATCH;
+            Mb = min(FINE_BATCH, top + 1 - m);
+            if (t < Mb) put_entry<true>(L, t, nA, nB, nC, m + t, fp.qx0, fp.qy0, cam.height, st);
+            __syncthreads();
+            if (b > 0) {
+                nA = srec[3 * (size_t)np];
+                nB = srec[3 * (size_t)np + 1];
+                nC = srec[3 * (size_t)np + 2];
+                if (b > 1) np = hl.vals[r1.x + (uint32_t)((b - 2) * FINE_BATCH + t)];
+            }
+        } else {
+            const uint4 c = cur[b];
+            m = (int)c.z;
+            Mb = merge_batch<true>(L, hl.vals, srec, (int)c.x, (int)r1.y, (int)c.y, (int)r2.y, FINE_BATCH, tcx, tcy,
+                                   tb, cam, st, m, fp.qx0, fp.qy0).M;
+        }
+        const int ne = wlast >= m ? block_list(L, Mb, wave, lane, wlast, list) : 0;
+        for (int e0 = (ne - 1) & ~3; e0 >= 0; e0 -= 4) {
+            const uint32_t own = list[e0 + row];
+            const float4 A = *reinterpret_cast<const float4*>(smem + own);
+            const float4 B = *reinterpret_cast<const float4*>(smem + own + 16);
+            const float4 Cc = *reinterpret_cast<const float4*>(smem + own + 32);
+            Eval e;
+            const bool hit =
+                eval_entry(A, B, px, py, ek, e) & (e0 + row < ne) & (__float_as_int(B.w) <= lastk);
+            if (!ballot(hit)) continue;
+            const float M = B.z;
+            const float ma = hit ? M * e.alpha : 0.f;
+            const float f = 1.f - ma;
+            // the entries behind this one among the four: their factors,
+            // and their colours against the loss weights
+            const float wc = fmaf(w0, Cc.x, fmaf(w1, Cc.y, w2 * Cc.z));
+            const float S = hit ? ma * wc : 0.f;
+            const Rows2 f1 = row_pairs(f), s1 = row_pairs(S);
+            const Rows2 f2 = row_halves(f1.lo * f1.hi), s2 = row_halves(fmaf(f1.lo, s1.hi, s1.lo));
+            const float mid = fmaf(f2.hi, sb, s2.hi);  // behind the first two
+            const float base = upper ? sb : mid;       // behind this one's pair
+            const float behind = odd ? base : fmaf(f1.hi, base, s1.hi);
+            const float Ti = T * __builtin_amdgcn_rcpf((odd ? f : f1.lo * f1.hi) * (upper ? 1.f : f2.hi));
+            sb = fmaf(f2.lo, mid, s2.lo);
+            T *= __builtin_amdgcn_rcpf(f2.lo * f2.hi);
+            float v[10] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+            if (hit) {
+                const float X = Ti * (wc - behind) - Tf * __builtin_amdgcn_rcpf(f) * wbg;
+                const float wt = ma * Ti;
+                v[6] = wt * w0;
+                v[7] = wt * w1;
+                v[8] = wt * w2;
+                v[9] = e.alpha * X;
+                if (e.oG <= ek.amax) {
+                    // as in hybrid_bwd_kernel
+                    const float GdA = e.G * (M * X);
+                    const float kq = GdA * (B.y * QSCALE_NINV);
+                    const float kapt = kq * e.apt;
+                    v[0] = kapt;
+                    v[1] = kq * fmaf(A.w, e.apt, e.gdy);
+                    v[2] = (kq * e.t) * e.t;
+                    v[3] = kapt * e.dy;
+                    v[4] = (kq * e.dy) * e.dy;
+                    v[5] = GdA;
+                }
+            }
+            const float x10 = row_fold10(v, col);
+            // (own / 48) 10 + qi
+            if (qi >= 0 && x10 != 0.f) atomicAdd(acc + (own / 48u) * 10u + (uint32_t)qi, x10);
+        }
+        __syncthreads();
+        for (int i = t; i < Mb * 10; i += FINE_NT) {
+            const float xs = acc[i];
+            if (xs == 0.f) continue;
+            acc[i] = 0.f;
+            const int j = i / 10, k = i - j * 10;
+            const uint32_t r = __float_as_uint(L.E[3 * j + 2].w);
+            // (the totals of t^2 and dy^2 rescaled, as in hybrid_bwd_kernel)
+            if (k < DREC)
+                atomicAdd(d_rec + (size_t)r * DREC + k, (double)(xs * (k == 2 || k == 4 ? 0.5f * QSCALE : 1.f)));
+            else
+                atomicAdd(d_masks + ((int64_t)r - rec_base), (double)xs);
+        }
+        __syncthreads();  // the next batch overwrites the LDS
+    }
+}
+
 // Persistent grid per batch depth (index log2(batch / 32)).
 template <typename Kernel>
-int cached_grid(int (&cache)[4], Kernel k, int block, int num_cus, int batch) {
+int cached_grid(int (&cache)[4], Kernel k, int block, int num_cus, int batch, size_t lds) {
     const int idx = batch <= 32 ? 0 : batch <= 64 ? 1 : batch <= 128 ? 2 : 3;
-    if (!cache[idx]) cache[idx] = persistent_grid(k, block, num_cus, lds_bytes(batch));
+    if (!cache[idx]) cache[idx] = persistent_grid(k, block, num_cus, lds);
     return cache[idx];
 }
 
@@ -1480,7 +2065,7 @@ void hybrid_fwd_s(hipStream_t s, int num_cus, const float* srec, const HybridLis
     if (queue) {
         static int cache[4] = {0, 0, 0, 0};
         grid = min(cached_grid(cache, hybrid_fwd_kernel<TW, TH, PPT, STATS, IMP>, TW * TH / PPT, num_cus,
-                               st.batch),
+                               st.batch, lds_bytes(st.batch)),
                    grid);
     }
     hipLaunchKernelGGL((hybrid_fwd_kernel<TW, TH, PPT, STATS, IMP>), dim3(grid), dim3(TW * TH / PPT),
@@ -1504,6 +2089,26 @@ void hybrid_fwd_t(hipStream_t s, int num_cus, const float* srec, const HybridLis
                                                 nullptr, queue, n, nullptr, nullptr);
 }
 
+template <bool STATS, bool IMP>
+void hybrid_fwd_fine(hipStream_t s, const float* srec, const HybridLists& hl, const ViewSet& views,
+                     const DevSettings& st, float* images, float* t_final, int32_t* last, int32_t* stats,
+                     int32_t* evals, int64_t n, double* imp_sum, uint32_t* imp_max) {
+    const uint32_t parts = (uint32_t)(st.tile_w * st.tile_h / 64);
+    hipLaunchKernelGGL((hybrid_fwd_fine_kernel<STATS, IMP>), dim3(views.total_tiles * parts), dim3(FINE_NT),
+                       fine_lds_bytes(false), s, reinterpret_cast<const float4*>(srec), hl, views, st, images, t_final,
+                       last, reinterpret_cast<int4*>(stats), reinterpret_cast<int4*>(evals), n, imp_sum, imp_max,
+                       parts);
+}
+
+void hybrid_bwd_fine(hipStream_t s, const float* srec, const HybridLists& hl, const ViewSet& views,
+                     const DevSettings& st, const float* t_final, const int32_t* last, const float* dl, int64_t n,
+                     double* d_rec, double* d_masks) {
+    const uint32_t parts = (uint32_t)(st.tile_w * st.tile_h / 64);
+    hipLaunchKernelGGL(hybrid_bwd_fine_kernel, dim3(views.total_tiles * parts), dim3(FINE_NT), fine_lds_bytes(true), s,
+                       reinterpret_cast<const float4*>(srec), hl, views, st, t_final, last, dl, n, d_rec, d_masks,
+                       parts);
+}
+
 template <int TW, int TH, int PPT>
 void hybrid_bwd_t(hipStream_t s, int num_cus, const float* srec, const HybridLists& hl, const ViewSet& views,
                   const DevSettings& st, const float* t_final, const int32_t* last, const float* dl, int64_t n,
@@ -1511,7 +2116,9 @@ void hybrid_bwd_t(hipStream_t s, int num_cus, const float* srec, const HybridLis
     int grid = (int)views.total_tiles;
     if (queue) {
         static int cache[4] = {0, 0, 0, 0};
-        grid = min(cached_grid(cache, hybrid_bwd_kernel<TW, TH, PPT>, TW * TH / PPT, num_cus, st.batch), grid);
+        grid = min(cached_grid(cache, hybrid_bwd_kernel<TW, TH, PPT>, TW * TH / PPT, num_cus, st.batch,
+                               lds_bytes(st.batch)),
+                   grid);
     }
     hipLaunchKernelGGL((hybrid_bwd_kernel<TW, TH, PPT>), dim3(grid), dim3(TW * TH / PPT), lds_bytes(st.batch), s,
                        reinterpret_cast<const float4*>(srec), hl, views, st, t_final, last, dl, n, d_rec, d_masks,
@@ -1553,6 +2160,27 @@ unsigned blocks_of(int64_t n) { return (unsigned)((n + 255) / 256); }
 
 }  // namespace
 
+// Which compositing kernels a forward (and its backward) takes: those for
+// small splats or the tile-wide ones.  Measured, tile-wide / small-splat time
+// of forward and backward together (16x16 tiles; the library's default
+// settings, and batches of 128 with 2 and 4 pixels per thread, persistent):
+//   up to 900 tiles, splats of every size: 1.26 (screen-filling scenes of 800
+//   tiles) to 7.4 (64 tiles); 950 tiles, screen-filling: 0.90 and 1.23
+//   2,500 tiles, share of large splats' tiles 0.07 / 0.72 / 1.0: 4.1, 4.9 /
+//   3.7, 2.4 / 1.1, 1.6;  1,600 tiles of a screen-filling scene (0.94): 0.78,
+//   0.82;  10,000 tiles, 0.07 / 0.72 / 0.96: 1.9, 2.0 / 1.4, 1.7 / 0.7, 1.0
+//   20,000 tiles, 0.08 / 0.73: 1.05, 1.15 / 0.7, 1.0;  40,000 tiles: 0.6
+// So the line lies at 896 tiles, or at 12,288 tiles where splats larger than
+// LARGE_RADIUS hold at most three quarters of the footprint tiles.  Tiles of
+// other sizes count by their pixels.
+constexpr int64_t FINE_PIXELS_ANY = 896 * 256, FINE_PIXELS_SMALL = 12288 * 256;
+
+bool fine_needs_sizes(int64_t pixels) { return pixels > FINE_PIXELS_ANY && pixels <= FINE_PIXELS_SMALL; }
+
+bool use_fine(int64_t pixels, uint64_t tiles_all, uint64_t tiles_large) {
+    return pixels <= FINE_PIXELS_ANY || (pixels <= FINE_PIXELS_SMALL && 4 * tiles_large <= 3 * tiles_all);
+}
+
 bool composite_config_supported(const CompositeConfig& c) {
 #define MGS_MATCH(A, B, P) \
     if (c.tile_w == A && c.tile_h == B && c.ppt == P) return true;
@@ -1563,38 +2191,40 @@ bool composite_config_supported(const CompositeConfig& c) {
 
 void launch_permute_classify(hipStream_t stream, const uint32_t* order, const uint32_t* skeys, const float* rec,
                              int64_t R, int64_t n, const ViewSet& views, const DevSettings& st, uint32_t* cnt,
-                             uint64_t* tmask, float* srec, uint32_t* part) {
+                             uint64_t* tmask, float* srec, uint32_t* part, bool sizes) {
     if (R == 0) return;
     const unsigned nb = blocks_of(R);
     hipLaunchKernelGGL(permute_classify_kernel, dim3(nb), dim3(256), 0, stream, order, skeys,
                        reinterpret_cast<const float4*>(rec), R, n, views, st, cnt, tmask,
-                       reinterpret_cast<float4*>(srec), part);
+                       reinterpret_cast<float4*>(srec), part, sizes ? 1 : 0);
 }
 
-// part: 2 nb + 4 nb u32 counts (per workgroup, per wave), then (8-byte
-// aligned) the list offsets: per wave, per group (3 totals and the offset)
+// part: 2 nb + 4 nb + 2 nb u32 counts (per workgroup, per wave, per
+// workgroup), then (8-byte aligned) the list offsets: per wave, per group (5
+// totals and the offset)
 namespace {
 int64_t waves_of(int64_t R) { return (int64_t)blocks_of(R) * 4; }
 int64_t groups_of(int64_t R) { return (waves_of(R) + LO_GROUP - 1) / LO_GROUP; }
-size_t counts_bytes(int64_t R) { return ((size_t)blocks_of(R) * 24 + 15) / 8 * 8; }
+size_t counts_bytes(int64_t R) { return ((size_t)blocks_of(R) * 32 + 15) / 8 * 8; }
 ListOffsets list_offsets(uint32_t* part, int64_t R) {
     char* p = reinterpret_cast<char*>(part) + counts_bytes(R);
     ListOffsets lo;
     lo.wave_rel = reinterpret_cast<uint64_t*>(p);
     lo.group_tot = lo.wave_rel + waves_of(R);
-    lo.group_off = lo.group_tot + 3 * groups_of(R);
+    lo.group_off = lo.group_tot + 5 * groups_of(R);
     return lo;
 }
 }  // namespace
 
-size_t classify_parts_bytes(int64_t R) { return counts_bytes(R) + (size_t)(waves_of(R) + 4 * groups_of(R)) * 8 + 8; }
+size_t classify_parts_bytes(int64_t R) { return counts_bytes(R) + (size_t)(waves_of(R) + 6 * groups_of(R)) * 8 + 8; }
 
-void launch_list_offsets(hipStream_t stream, uint32_t* part, int64_t R, uint64_t* total, uint64_t* wide_counts) {
+void launch_list_offsets(hipStream_t stream, uint32_t* part, int64_t R, uint64_t* total, uint64_t* wide_counts,
+                         bool sizes) {
     const ListOffsets lo = list_offsets(part, R);
     const int64_t ng = R > 0 ? groups_of(R) : 0;
     if (ng > 0)
         hipLaunchKernelGGL(list_offsets_group_kernel, dim3((unsigned)ng), dim3(LO_GROUP), 0, stream, part,
-                           (int64_t)blocks_of(R), waves_of(R), lo);
+                           (int64_t)blocks_of(R), waves_of(R), lo, sizes ? 1 : 0);
     hipLaunchKernelGGL(list_offsets_total_kernel, dim3(1), dim3(LO_GROUP), 0, stream, ng, lo, total, wide_counts);
 }
 
@@ -1619,14 +2249,14 @@ void launch_tile_order(hipStream_t stream, const uint32_t* key, uint32_t tiles, 
 
 void launch_tile_setup(hipStream_t stream, const uint32_t* ranges, const ViewSet& views, int batch,
                        const uint32_t* key, uint32_t* cost, uint32_t* cur_off, uint64_t* cur_need, uint32_t* blk,
-                       uint32_t* hist_cursor, uint32_t* order) {
+                       uint32_t* hist_cursor, uint32_t* order, uint32_t* nbatch) {
     const uint32_t T = views.total_tiles;
     if (T == 0) return;
     hipLaunchKernelGGL(batch_caps_kernel, dim3(blocks_of(T)), dim3(256), 0, stream,
                        reinterpret_cast<const uint2*>(ranges), views, batch, key, cost, cur_off, blk, hist_cursor);
     hipLaunchKernelGGL(order_offsets_kernel, dim3(blocks_of(T)), dim3(256), 0, stream, key, (const uint32_t*)cost, T,
                        (const uint32_t*)hist_cursor, hist_cursor + 256, order, cur_off, (const uint32_t*)blk,
-                       cur_need);
+                       cur_need, nbatch);
 }
 
 void launch_hybrid_fwd(hipStream_t stream, const CompositeConfig& cfg, const float* srec, const HybridBuffers& bufs,
@@ -1635,6 +2265,18 @@ void launch_hybrid_fwd(hipStream_t stream, const CompositeConfig& cfg, const flo
                        uint32_t* imp_max) {
     if (views.total_tiles == 0) return;
     const HybridLists hl = make_lists(bufs);
+    if (bufs.fine) {
+        if (imp_sum && imp_max)
+            hybrid_fwd_fine<false, true>(stream, srec, hl, views, st, images, t_final, last, nullptr, nullptr, n,
+                                         imp_sum, imp_max);
+        else if (stats && evals)
+            hybrid_fwd_fine<true, false>(stream, srec, hl, views, st, images, t_final, last, stats, evals, n, nullptr,
+                                         nullptr);
+        else
+            hybrid_fwd_fine<false, false>(stream, srec, hl, views, st, images, t_final, last, nullptr, nullptr, n,
+                                          nullptr, nullptr);
+        return;
+    }
 #define MGS_HFWD(A, B, P)                                                                                          \
     if (cfg.tile_w == A && cfg.tile_h == B && cfg.ppt == P) {                                                      \
         hybrid_fwd_t<A, B, P>(stream, num_cus, srec, hl, views, st, images, t_final, last, stats, evals, queue, n, \
@@ -1651,6 +2293,10 @@ void launch_hybrid_bwd(hipStream_t stream, const CompositeConfig& cfg, const flo
                        int num_cus) {
     if (views.total_tiles == 0) return;
     const HybridLists hl = make_lists(bufs);
+    if (bufs.fine) {
+        hybrid_bwd_fine(stream, srec, hl, views, st, t_final, last, dl_dimages, n, d_rec, d_masks);
+        return;
+    }
 #define MGS_HBWD(A, B, P)                                                                                       \
     if (cfg.tile_w == A && cfg.tile_h == B && cfg.ppt == P) {                                                   \
         hybrid_bwd_t<A, B, P>(stream, num_cus, srec, hl, views, st, t_final, last, dl_dimages, n, d_rec, d_masks, \

@@ -97,11 +97,18 @@ bool composite_config_supported(const CompositeConfig& c);
 size_t classify_parts_bytes(int64_t R);
 void launch_permute_classify(hipStream_t stream, const uint32_t* order, const uint32_t* skeys, const float* rec,
                              int64_t R, int64_t n, const ViewSet& views, const DevSettings& st, uint32_t* cnt,
-                             uint64_t* tmask, float* srec, uint32_t* part);
+                             uint64_t* tmask, float* srec, uint32_t* part, bool sizes);
 // From the classification's per-workgroup counts: each workgroup's first list
 // entry, the entry total (device u64 *total) and wide_counts (device u64):
-// [0] = wide records, [2] = their region entries
-void launch_list_offsets(hipStream_t stream, uint32_t* part, int64_t R, uint64_t* total, uint64_t* wide_counts);
+// [0] = wide records, [2] = their region entries, and with sizes (as given to
+// the classification; else 0) [3] = tiles of all footprints, [4] = of those
+// of large splats
+void launch_list_offsets(hipStream_t stream, uint32_t* part, int64_t R, uint64_t* total, uint64_t* wide_counts,
+                         bool sizes);
+// The rule that picks the compositing kernels (pixels over all views; the two
+// counts above, needed where fine_needs_sizes).
+bool fine_needs_sizes(int64_t pixels);
+bool use_fine(int64_t pixels, uint64_t tiles_all, uint64_t tiles_large);
 void launch_duplicate_lists(hipStream_t stream, const float* srec, const uint32_t* cnt_sorted,
                             const uint64_t* tmask, uint32_t* part, int64_t R,
                             int64_t n, const ViewSet& views, const DevSettings& st, uint32_t* keys, uint32_t* vals,
@@ -117,9 +124,10 @@ void launch_tile_order(hipStream_t stream, const uint32_t* key, uint32_t tiles, 
 // the entries of its two lists in units of 8, at most 255), and the tile
 // order by descending key (key[t], or the cost key when key is null).
 // hist_cursor: [512] u32, zero before; blk: blocks of 256 tiles, u32 scratch.
+// nbatch (which key may be) is cleared once the order is taken.
 void launch_tile_setup(hipStream_t stream, const uint32_t* ranges, const ViewSet& views, int batch,
                        const uint32_t* key, uint32_t* cost, uint32_t* cur_off, uint64_t* cur_need, uint32_t* blk,
-                       uint32_t* hist_cursor, uint32_t* order);
+                       uint32_t* hist_cursor, uint32_t* order, uint32_t* nbatch);
 struct HybridBuffers {
     const uint32_t* vals;        // list entries (sorted positions), (cell, position) order
     const uint32_t* ranges;      // [tiles + regions, 2]
@@ -136,6 +144,7 @@ struct HybridBuffers {
     double* drec_clear;          // optional: FP64 per-record gradient accumulator the forward clears
     uint64_t drec_clear_n2;      // its size in pairs of doubles
     const uint32_t* order;       // optional [tiles]: the order in which a persistent launch takes the tiles
+    bool fine;                   // the kernels for small splats (the same for a forward and its backward)
 };
 // stats [P, 4] (examined, blended, blended with mask 0, last + 1) and evals
 // [P, 4] (evaluated, evaluated up to the last blended entry, 0, 0) are
