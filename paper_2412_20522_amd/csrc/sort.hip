@@ -102,6 +102,9 @@ constexpr int sort_tile() {
 }
 constexpr int SORT_TILE_MIN = NT * 8;  // the smallest sort tile (sizes the histograms)
 constexpr int64_t MAX_SORT_SEGMENTS = 16;  // segments of a segmented sort (one per view)
+constexpr int64_t SHORT_MAX = 16384;       // longest segment sorted in one workgroup's LDS
+// segments of up to this many blocks need no row scan
+constexpr int64_t OWN_SCAN_BLOCKS = 96;
 
 // Keys per workgroup of the sort: the host's chunk for a known count; with a
 // device-side live count, the live keys are spread evenly over the nb
@@ -282,7 +285,9 @@ __device__ __forceinline__ SortSeg sort_seg(int64_t K, int64_t seg_len, int64_t 
 // a wave with equal digits rarely hit one LDS counter: 4 for the list
 // entries' cell keys (digits clustered in the second pass), 1 for the
 // depth keys
-template <typename KeyT, int COPIES>
+// BLOCKMAJOR: hist[(segment nbs + block) RADIX + digit] instead, for a scatter
+// that adds up its segment's rows itself (radix_downsweep_kernel<.., true>)
+template <typename KeyT, int COPIES, bool BLOCKMAJOR>
 __global__ void __launch_bounds__(NT) radix_upsweep_kernel(const KeyT* __restrict__ keys, int64_t Kcap,
                                                             const uint64_t* __restrict__ K_dev, int shift,
                                                             uint32_t* __restrict__ hist, int64_t nb, int64_t chunk,
@@ -336,7 +341,8 @@ __global__ void __launch_bounds__(NT) radix_upsweep_kernel(const KeyT* __restric
     uint32_t s = 0;
 #pragma unroll
     for (int i = 0; i < (NT / 64) * COPIES; ++i) s += h[i][d];
-    hist[(sg.seg * RADIX + d) * nbs + sg.bl] = s;
+    if constexpr (BLOCKMAJOR) hist[(sg.seg * nbs + sg.bl) * RADIX + d] = s;
+    else hist[(sg.seg * RADIX + d) * nbs + sg.bl] = s;
 }
 
 // Exclusive prefix of every (segment, digit) row of the block histograms
@@ -379,7 +385,10 @@ constexpr int sort_dt() {
 
 // Threads t < RADIX own digit t in the digit steps; the per-wave digit
 // counts (at most 64 x 8 per wave, prefixes at most the tile) fit 16 bits.
-template <typename KeyT>
+// OWN_SCAN: no row scan ran; row_pre holds the block-major histogram, and each
+// workgroup adds up its segment's counts (two threads per digit), which costs
+// less than a launch while a segment has few blocks.
+template <typename KeyT, bool OWN_SCAN>
 __global__ void __launch_bounds__(sort_dt<KeyT>()) __attribute__((amdgpu_waves_per_eu(sizeof(KeyT) == 8 ? 1 : 6)))
 radix_downsweep_kernel(
     const KeyT* __restrict__ keys_in, const uint32_t* __restrict__ vals_in, KeyT* __restrict__ keys_out,
@@ -406,9 +415,36 @@ radix_downsweep_kernel(
     const bool dig = threadIdx.x < RADIX;
     {
         const int64_t row = sg.seg * RADIX + (dig ? threadIdx.x : 0);
-        uint32_t tot;
-        const uint32_t below = block_exclusive_scan_n<uint32_t, DT>(dig ? row_tot[row] : 0u, scan_sh, &tot);
-        if (dig) gstart[threadIdx.x] = (uint32_t)(sg.seg * seg_len) + below + row_pre[row * nbs + sg.bl];
+        uint32_t tot, pre, own;
+        if constexpr (OWN_SCAN) {
+            constexpr int PER = DT / RADIX;  // threads per digit, over every PER-th block
+            const uint32_t* h = row_pre + sg.seg * nbs * RADIX + threadIdx.x % RADIX;
+            const int64_t b0 = threadIdx.x / RADIX;
+            pre = own = 0;
+#pragma unroll 8
+            for (int64_t b = b0; b < nbs; b += PER) {
+                const uint32_t c = h[b * RADIX];
+                own += c;
+                pre += b < sg.bl ? c : 0u;
+            }
+            if constexpr (PER > 1) {
+                static_assert(PER == 2, "one partner per digit");
+                if (!dig) {
+                    dstart[threadIdx.x - RADIX] = pre;
+                    gstart[threadIdx.x - RADIX] = own;
+                }
+                __syncthreads();
+                if (dig) {
+                    pre += dstart[threadIdx.x];
+                    own += gstart[threadIdx.x];
+                }
+            }
+        } else {
+            pre = dig ? row_pre[row * nbs + sg.bl] : 0u;
+            own = row_tot[row];
+        }
+        const uint32_t below = block_exclusive_scan_n<uint32_t, DT>(dig ? own : 0u, scan_sh, &tot);
+        if (dig) gstart[threadIdx.x] = (uint32_t)(sg.seg * seg_len) + below + pre;
     }
     for (int64_t base = cbeg; base < cend; base += STILE) {
     const int nvalid = (int)min((int64_t)STILE, cend - base);
@@ -494,6 +530,102 @@ radix_downsweep_kernel(
     const uint32_t pad = (threadIdx.x == RADIX - 1) ? (uint32_t)(STILE - nvalid) : 0u;
     if (dig) gstart[threadIdx.x] += digit_total - pad;
     __syncthreads();
+    }
+}
+
+// ---------------------------------------------------------------------------
+// short 32-bit sorts: one workgroup per segment, all passes in LDS
+// ---------------------------------------------------------------------------
+
+// At most 1024 IPW keys per segment.  The multi-block sort takes three
+// launches of 3 to 7 us per pass whatever the size; this one holds keys and
+// values in LDS and takes 3 to 5 us per pass (4096 keys, four passes: 59 ->
+// 16 us).  Ranking as in radix_downsweep_kernel; keys past the live count are
+// all ones and stay behind every valid key.
+constexpr int SHORT_DT = 1024;
+template <int IPW>
+__global__ void __launch_bounds__(SHORT_DT) radix_short_kernel(uint32_t* __restrict__ keys, uint32_t* __restrict__ vals,
+                                                                int64_t Kcap, const uint64_t* __restrict__ K_dev,
+                                                                int begin_bit, int end_bit, int64_t seg_len) {
+    constexpr int NW = SHORT_DT / 64;
+    __shared__ uint32_t sk[SHORT_DT * IPW];
+    __shared__ uint32_t sv[SHORT_DT * IPW];
+    __shared__ uint16_t wcnt[NW][RADIX];
+    __shared__ uint32_t dstart[RADIX];
+    __shared__ uint32_t scan_sh[NW];
+    const int64_t K = live_count(Kcap, K_dev);
+    const int64_t beg = (int64_t)blockIdx.x * seg_len;
+    const int n = (int)min(seg_len, K - beg);
+    if (n <= 0) return;  // uniform
+    const int t = threadIdx.x, w = t >> 6, lane = lane_id();
+    const bool dig = t < RADIX;
+    // wave w owns the span [64 w rounds, 64 (w + 1) rounds) of the segment
+    const int rounds = (n + SHORT_DT - 1) / SHORT_DT;
+    const int l0 = w * rounds * 64 + lane;
+    uint32_t key[IPW], val[IPW], rank[IPW];
+#pragma unroll
+    for (int j = 0; j < IPW; ++j) {
+        const int i = l0 + j * 64;
+        const bool in = j < rounds && i < n;
+        key[j] = in ? keys[beg + i] : 0xffffffffu;
+        val[j] = in ? vals[beg + i] : 0u;
+    }
+    const uint64_t lt = lanemask_lt();
+    for (int shift = begin_bit; shift < end_bit; shift += 8) {
+        for (int i = t; i < NW * RADIX; i += SHORT_DT) (&wcnt[0][0])[i] = 0u;
+        __syncthreads();
+#pragma unroll
+        for (int j = 0; j < IPW; ++j) {
+            if (j >= rounds) break;
+            const uint32_t d = digit_of(key[j], shift);
+            uint64_t peers = ~0ull;
+#pragma unroll
+            for (int b = 0; b < 8; ++b) {
+                const uint64_t bal = ballot(((d >> b) & 1u) != 0);
+                peers &= ((d >> b) & 1u) ? bal : ~bal;
+            }
+            const uint32_t before = wcnt[w][d];
+            rank[j] = before + (uint32_t)__popcll(peers & lt);
+            if (lane == __ffsll((long long)peers) - 1) wcnt[w][d] = (uint16_t)(before + (uint32_t)__popcll(peers));
+        }
+        __syncthreads();
+        uint32_t run = 0;
+        if (dig) {
+#pragma unroll
+            for (int i = 0; i < NW; ++i) {
+                const uint32_t c = wcnt[i][t];
+                wcnt[i][t] = (uint16_t)run;
+                run += c;
+            }
+        }
+        uint32_t tot;
+        const uint32_t ds = block_exclusive_scan_n<uint32_t, SHORT_DT>(run, scan_sh, &tot);
+        if (dig) dstart[t] = ds;
+        __syncthreads();
+#pragma unroll
+        for (int j = 0; j < IPW; ++j) {
+            if (j >= rounds) break;
+            const uint32_t d = digit_of(key[j], shift);
+            const uint32_t pos = dstart[d] + wcnt[w][d] + rank[j];
+            sk[pos] = key[j];
+            sv[pos] = val[j];
+        }
+        __syncthreads();
+#pragma unroll
+        for (int j = 0; j < IPW; ++j) {
+            if (j >= rounds) break;
+            key[j] = sk[l0 + j * 64];
+            val[j] = sv[l0 + j * 64];
+        }
+        __syncthreads();  // sk, sv are written again by the next pass
+    }
+#pragma unroll
+    for (int j = 0; j < IPW; ++j) {
+        const int i = l0 + j * 64;
+        if (j < rounds && i < n) {
+            keys[beg + i] = key[j];
+            vals[beg + i] = val[j];
+        }
     }
 }
 
@@ -632,6 +764,22 @@ void radix_sort_t(hipStream_t stream, KeyT* keys, uint32_t* vals, KeyT* keys_alt
     *out_in_alt = false;
     if (K <= 1 && !K_dev) return;
     if (end_bit <= begin_bit) return;
+    if constexpr (sizeof(KeyT) == 4) {
+        // short segments: one launch, in place (the lines between 8 and 16
+        // keys per thread and at SHORT_MAX are those of its LDS)
+        const int64_t sl = seg_len > 0 && seg_len < K && !K_dev ? seg_len : K;
+        const unsigned ns = (unsigned)((K + sl - 1) / sl);
+        if (sl <= SHORT_DT * 8) {
+            hipLaunchKernelGGL(radix_short_kernel<8>, dim3(ns), dim3(SHORT_DT), 0, stream, keys, vals, K, K_dev,
+                               begin_bit, end_bit, sl);
+            return;
+        }
+        if (sl <= SHORT_MAX) {
+            hipLaunchKernelGGL(radix_short_kernel<16>, dim3(ns), dim3(SHORT_DT), 0, stream, keys, vals, K, K_dev,
+                               begin_bit, end_bit, sl);
+            return;
+        }
+    }
     // about SORT_BLOCKS workgroups, each over a contiguous chunk of whole
     // tiles of one segment
     constexpr int64_t STILE = sort_tile<KeyT>();
@@ -654,19 +802,28 @@ void radix_sort_t(hipStream_t stream, KeyT* keys, uint32_t* vals, KeyT* keys_alt
     uint32_t* vin = vals;
     KeyT* kout = keys_alt;
     uint32_t* vout = vals_alt;
+    const bool own_scan = nbs <= OWN_SCAN_BLOCKS;
     for (int shift = begin_bit; shift < end_bit; shift += 8) {
-        if (segmented)
-            hipLaunchKernelGGL((radix_upsweep_kernel<KeyT, 1>), dim3((unsigned)nb), dim3(NT), 0, stream, kin, K, K_dev,
-                               shift, hist, nb, chunk, seg_arg, nbs);
-        else
-            hipLaunchKernelGGL((radix_upsweep_kernel<KeyT, 4>), dim3((unsigned)nb), dim3(NT), 0, stream, kin, K, K_dev,
-                               shift, hist, nb, chunk, seg_arg, nbs);
-        hipLaunchKernelGGL(radix_rowscan_kernel, dim3((unsigned)rows), dim3(NT), 0, stream, (const uint32_t*)hist,
-                           nbs, row_pre, row_tot);
-        hipLaunchKernelGGL(radix_downsweep_kernel<KeyT>, dim3((unsigned)nb), dim3(sort_dt<KeyT>()), 0, stream, kin, vin,
-                           kout, vout,
-                           K, K_dev, shift, (const uint32_t*)row_pre, (const uint32_t*)row_tot, nb, chunk, seg_arg,
-                           nbs);
+#define MGS_UPSWEEP(C, B)                                                                                           \
+    hipLaunchKernelGGL((radix_upsweep_kernel<KeyT, C, B>), dim3((unsigned)nb), dim3(NT), 0, stream, kin, K, K_dev, \
+                       shift, hist, nb, chunk, seg_arg, nbs)
+#define MGS_DOWNSWEEP(O, P)                                                                                          \
+    hipLaunchKernelGGL((radix_downsweep_kernel<KeyT, O>), dim3((unsigned)nb), dim3(sort_dt<KeyT>()), 0, stream, kin, \
+                       vin, kout, vout, K, K_dev, shift, (const uint32_t*)P, (const uint32_t*)row_tot, nb, chunk,    \
+                       seg_arg, nbs)
+        if (own_scan) {
+            if (segmented) MGS_UPSWEEP(1, true);
+            else MGS_UPSWEEP(4, true);
+            MGS_DOWNSWEEP(true, hist);
+        } else {
+            if (segmented) MGS_UPSWEEP(1, false);
+            else MGS_UPSWEEP(4, false);
+            hipLaunchKernelGGL(radix_rowscan_kernel, dim3((unsigned)rows), dim3(NT), 0, stream, (const uint32_t*)hist,
+                               nbs, row_pre, row_tot);
+            MGS_DOWNSWEEP(false, row_pre);
+        }
+#undef MGS_UPSWEEP
+#undef MGS_DOWNSWEEP
         KeyT* tk = kin; kin = kout; kout = tk;
         uint32_t* tv = vin; vin = vout; vout = tv;
         *out_in_alt = !*out_in_alt;

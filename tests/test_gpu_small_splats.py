@@ -111,3 +111,34 @@ def test_tile_wide_kernels_match_oracle(tile, fwd_ppt, bwd_ppt, wide):
                        ("masks", g.masks, op.bwd.d_mask)]:
         e = U.rel_err(x.cpu().numpy(), y)
         assert e <= 2e-3, (name, e)
+
+
+@pytest.mark.parametrize("n", [1, 64, 1025, 8192, 8193, 16384, 16385, 40_000])
+@pytest.mark.parametrize("views", [1, 3])
+def test_depth_order_and_lists_over_the_sort_variants(n, views):
+    """Record order and list entries around the sizes where the sorts change
+    between one workgroup with 8 or 16 keys per thread and several blocks."""
+    from paper_2412_20522_amd import maskgs as M
+    from paper_2412_20522_amd.raster import Rasterizer
+    s = scenegen.small_scene(n, 70, 50, seed=900 + n, sh_degree=0, log_scale_mean=-4.0, n_views=views)
+    s["means"][: n // 3] = s["means"][n // 3: 2 * (n // 3)]  # equal depths: ties by record id
+    rast = Rasterizer(0, **_settings((8, 8), sh_degree=0, wide_tiles=4))
+    dev = U.to_device(s)
+    frame = rast.acquire_frame()
+    rast.forward(frame, {k: dev[k] for k in U.PARAM_KEYS}, dev["masks"], s["cameras"])
+    ex = {k: M.mgs_frame_export(rast.ctx, frame, k) for k in ("order", "depth", "tiles", "values", "ranges")}
+    torch.cuda.synchronize()
+    K = rast.stats(frame)["n_instances"]
+    rast.release_frame(frame)
+    bits, tiles, order = U.u32(ex["depth"]), U.u32(ex["tiles"]), U.u32(ex["order"])
+    key = np.where(tiles > 0, bits, np.uint32(0xffffffff))
+    for v in range(views):
+        want = np.argsort(key[v * n:(v + 1) * n], kind="stable") + v * n
+        assert np.array_equal(order[v * n:(v + 1) * n], want)
+    r = U.u32(ex["ranges"]).reshape(-1, 2).astype(np.int64)
+    vals = U.u32(ex["values"]).astype(np.int64)[:K]
+    r = r[r[:, 1] > r[:, 0]]
+    assert (r[:, 1] - r[:, 0]).sum() == K and np.array_equal(r[1:, 0], r[:-1, 1]) and (K == 0 or r[0, 0] == 0)
+    step = np.diff(vals) > 0
+    step[r[1:, 0] - 1] = True  # positions ascend within a cell
+    assert step.all()
