@@ -294,11 +294,12 @@ struct mgs_frame {
     DevBuf keys, vals, keys_alt, vals_alt, ranges, caps, tcost, order, order_b, cur_off, nbatch, cur, cur_stg, stg,
         t_final, last, stats, evals;
     bool have_stats = false;  // the last forward wrote the per-pixel work counters
-    DevBuf d_rec, dm_acc, rsort_tmp, sort_tmp, misc, queue, sum_tmp;  // d_rec, dm_acc: FP64
+    DevBuf d_rec, rsort_tmp, sort_tmp, misc, queue, sum_tmp;  // d_rec: FP64, R rows, then the masks' n sums
     DevBuf imp_acc;  // FP64 sums of the importance forward
-    // d_rec is all zeros from the forward compositing (which clears it) to
-    // the backward that accumulates into it; false after a backward and
-    // after (re)allocation (a backward then fills it first)
+    // d_rec, the backward's queue and its order's histogram are all zeros from
+    // the forward (which clears them) to the backward that uses them; false
+    // after a backward and after (re)allocation (a backward then clears them
+    // first)
     bool drec_zero = false;
     // views of the last forward, whose per-tile batch counts (nbatch) order
     // the tiles of the next forward over the same views
@@ -308,27 +309,39 @@ struct mgs_frame {
     // the forward before it over the same views); the backward then reuses
     // that order
     bool fwd_order_measured = false;
-    // misc: flags (u32) at 0, list entry count (u64) at 8, wide record count
+    // misc: flags (2 u32) at 0, list entry count (u64) at 8, wide record count
     // (u64) at 16, checkpoint count (u64) at 24, region entry count (u64) at
     // 32, footprint tiles of all and of large splats (u64) at 40 and 48,
-    // staged-entry counter (u32) at 192; the tile orders' histogram and
-    // cursors (2 x 256 u32) from 256
+    // staged-entry counter (u32) at 192; the histogram and cursors (2 x 256
+    // u32) of the forward's tile order from 256, of the backward's from 2304
     uint64_t* h_pinned = nullptr;  // read-back of misc
+    uint64_t* h_device = nullptr;  // the same memory as the device sees it
     uint32_t* keys_sorted() { return (uint32_t*)(sorted_in_alt ? keys_alt.p : keys.p); }
     uint32_t* vals_sorted() { return (uint32_t*)(sorted_in_alt ? vals_alt.p : vals.p); }
     uint32_t* record_order() { return (uint32_t*)(order_in_alt ? rvals_alt.p : rvals.p); }
-    uint32_t* flags() { return (uint32_t*)misc.p; }
+    // device flags: one of two words.  A plain forward uses the word that the
+    // one before it left cleared and clears the other; a fixed workspace (whose
+    // launches a graph may replay) keeps to word 0 and clears it itself.
+    int flag_word = 0;
+    bool flag_clear[2] = {false, false};
+    uint32_t* flag_words() { return (uint32_t*)misc.p; }
+    uint32_t* flags() { return flag_words() + flag_word; }
+    uint32_t flags_read() const { return (uint32_t)(h_pinned[0] >> (32 * flag_word)); }
     uint64_t* total() { return (uint64_t*)((char*)misc.p + 8); }
     uint64_t* wide_counts() { return (uint64_t*)((char*)misc.p + 16); }
     uint64_t* cur_need() { return (uint64_t*)((char*)misc.p + 24); }
     uint32_t* stg_count() { return (uint32_t*)((char*)misc.p + 192); }
     uint32_t* order_hist() { return (uint32_t*)((char*)misc.p + 256); }
+    uint32_t* order_hist_b() { return order_hist() + 512; }
+    uint32_t* queue_f() { return persistent ? (uint32_t*)queue.p : nullptr; }
+    uint32_t* queue_b() { return persistent ? (uint32_t*)queue.p + 32 : nullptr; }
+    double* dm_acc() { return (double*)d_rec.p + (size_t)R * DREC; }
     HybridBuffers hybrid(bool clear_drec = false) {
         const uint64_t cap = reserved ? (uint64_t)cur_cap : (uint64_t)std::min(cur.bytes / 16, cur_stg.bytes / 8);
         const uint64_t scap = reserved ? (uint64_t)stg_cap : (uint64_t)(stg.bytes / 8);
-        // pairs of doubles covering the R x DREC accumulator (the allocation
-        // has 8 bytes of slack for an odd count)
-        const uint64_t n2 = clear_drec ? ((uint64_t)R * DREC + 1) / 2 : 0;
+        // pairs of doubles covering the accumulators (the allocation has 8
+        // bytes of slack for an odd count)
+        const uint64_t n2 = clear_drec ? ((uint64_t)R * DREC + (uint64_t)n + 1) / 2 : 0;
         return HybridBuffers{vals_sorted(), (const uint32_t*)ranges.p, (uint32_t*)cur.p, (const uint32_t*)cur_off.p, (uint32_t*)nbatch.p, cur_need(), cap,
                              flags(), (uint32_t*)cur_stg.p, (uint32_t*)stg.p, stg_count(), scap,
                              clear_drec ? (double*)d_rec.p : nullptr, n2, (const uint32_t*)order.p, fine};
@@ -406,7 +419,14 @@ mgs_status mgs_frame_create(mgs_ctx* ctx, mgs_frame** out) {
         delete f;
         return fail(ctx, MGS_ERR_OOM, "pinned host allocation");
     }
-    if (grow(ctx, f->misc, 256 + 2048) != MGS_OK) {
+    if (hipHostGetDevicePointer((void**)&f->h_device, f->h_pinned, 0) != hipSuccess) {
+        (void)hipHostFree(f->h_pinned);
+        delete f;
+        return fail(ctx, MGS_ERR_HIP, "device address of pinned memory");
+    }
+    // (zeroed: the staged-entry counter is read before it is first written)
+    if (grow(ctx, f->misc, 256 + 4096) != MGS_OK || hipMemset(f->misc.p, 0, f->misc.bytes) != hipSuccess) {
+        release(f->misc);
         (void)hipHostFree(f->h_pinned);
         delete f;
         return MGS_ERR_OOM;
@@ -423,7 +443,7 @@ mgs_status mgs_frame_destroy(mgs_frame* f) {
                       &f->keys,     &f->vals,      &f->keys_alt, &f->vals_alt,  &f->ranges,
                       &f->caps,     &f->tcost,     &f->order,     &f->order_b,   &f->cur_off,   &f->nbatch,   &f->cur,       &f->cur_stg,   &f->stg,
                       &f->t_final,  &f->last,
-                      &f->stats,    &f->evals,     &f->d_rec,     &f->dm_acc,    &f->rsort_tmp, &f->sort_tmp,
+                      &f->stats,    &f->evals,     &f->d_rec,     &f->rsort_tmp, &f->sort_tmp,
                       &f->misc,     &f->queue,     &f->sum_tmp,  &f->imp_acc};
     for (DevBuf* b : bufs) release(*b);
     if (f->h_pinned) (void)hipHostFree(f->h_pinned);
@@ -459,7 +479,7 @@ static mgs_status grow_nbatch(mgs_frame* f, size_t bytes) {
 // known to be zero.
 static mgs_status grow_drec(mgs_frame* f) {
     const size_t before = f->d_rec.p ? f->d_rec.bytes : 0;  // grow reallocates only to a larger size
-    const mgs_status s = grow(f->ctx, f->d_rec, (size_t)f->R * DREC * 8 + 8);
+    const mgs_status s = grow(f->ctx, f->d_rec, ((size_t)f->R * DREC + (size_t)f->n) * 8 + 8);
     if (s != MGS_OK || f->d_rec.bytes != before) f->drec_zero = false;
     return s;
 }
@@ -487,7 +507,7 @@ mgs_status mgs_frame_reserve(mgs_frame* f, mgs_stream stream_, double slack) {
     const size_t kb = (size_t)K_cap * 4 + 16;
     if ((s = grow(ctx, f->keys, kb)) || (s = grow(ctx, f->vals, kb)) || (s = grow(ctx, f->keys_alt, kb)) ||
         (s = grow(ctx, f->vals_alt, kb)) || (s = grow(ctx, f->sort_tmp, sort_scratch_bytes(K_cap))) ||
-        (s = grow(ctx, f->cur, (size_t)cur_cap * 16 + 16)) || (s = grow_drec(f)) || (s = grow(ctx, f->dm_acc, (size_t)f->n * 8 + 8)) ||
+        (s = grow(ctx, f->cur, (size_t)cur_cap * 16 + 16)) || (s = grow_drec(f)) ||
         (s = grow(ctx, f->cur_stg, (size_t)cur_cap * 8 + 8)) || (s = grow(ctx, f->stg, (size_t)stg_cap * 8 + 8)))
         return s;
     f->stg_cap = stg_cap;
@@ -507,7 +527,7 @@ mgs_status mgs_frame_check(mgs_frame* f, mgs_stream stream_) {
     if (!f->have_forward) return fail(ctx, MGS_ERR_STATE, "no forward on this frame");
     MGS_HIP(ctx, hipMemcpyAsync(f->h_pinned, f->misc.p, 32, hipMemcpyDeviceToHost, stream));
     MGS_HIP(ctx, hipStreamSynchronize(stream));
-    const uint32_t flags = (uint32_t)(f->h_pinned[0] & 0xffffffffu);
+    const uint32_t flags = f->flags_read();
     const uint64_t K = f->h_pinned[1], W = f->h_pinned[2], C = f->h_pinned[3];
     f->W = (int64_t)W;
     if (f->reserved) f->K = (int64_t)std::min<uint64_t>(K, (uint64_t)f->K_cap);
@@ -574,7 +594,9 @@ mgs_status forward_impl(mgs_frame* f, mgs_stream stream_, const mgs_gaussians* g
         (s = grow(ctx, f->stats, (size_t)P * 16)) || (s = grow(ctx, f->evals, (size_t)P * 16)) ||
         (s = grow(ctx, f->rsort_tmp, sort_scratch_bytes(R))) || (s = grow(ctx, f->queue, 256)))
         return s;
-    launch_fill_u32(stream, f->flags(), 10, 0u);  // flags and the counters up to byte 40
+    f->flag_word = f->reserved ? 0 : f->flag_word ^ 1;
+    if (f->reserved || !f->flag_clear[f->flag_word]) launch_fill_u32(stream, f->flags(), 1, 0u);
+    f->flag_clear[f->flag_word] = false;
     {
         StageTimer t(ctx, stream, MGS_STAGE_PROJECT);
         // the radius stays in the records (B.w); the export reads it there
@@ -604,7 +626,8 @@ mgs_status forward_impl(mgs_frame* f, mgs_stream stream_, const mgs_gaussians* g
         // list offsets: one scan over the classification's per-workgroup
         // counts; the duplication adds the counts within its workgroup
         StageTimer t(ctx, stream, MGS_STAGE_SCAN);
-        launch_list_offsets(stream, (uint32_t*)f->cls_part.p, R, f->total(), f->wide_counts(), sizes);
+        launch_list_offsets(stream, (uint32_t*)f->cls_part.p, R, f->total(), f->wide_counts(), sizes, f->flag_words(),
+                            f->stg_count(), f->reserved ? nullptr : f->h_device);
     }
     MGS_CHECK_LAUNCH(ctx);
     const int64_t B = st->batch_depth;
@@ -617,10 +640,10 @@ mgs_status forward_impl(mgs_frame* f, mgs_stream stream_, const mgs_gaussians* g
         K_dev = f->total();
     } else {
         // the one synchronisation of the plain path: the list entry counts
-        // size the sort and the batch checkpoints
-        MGS_HIP(ctx, hipMemcpyAsync(f->h_pinned, f->misc.p, 200, hipMemcpyDeviceToHost, stream));
+        // size the sort and the batch checkpoints (written to pinned memory by
+        // the kernel that forms them)
         MGS_HIP(ctx, hipStreamSynchronize(stream));
-        const uint32_t flags = (uint32_t)(f->h_pinned[0] & 0xffffffffu);
+        const uint32_t flags = f->flags_read();
         const uint64_t K = f->h_pinned[1];
         const uint64_t W = f->h_pinned[2], KW = f->h_pinned[4];
         if (flags & FLAG_NONFINITE) return fail(ctx, MGS_ERR_NONFINITE, "non-finite projected geometry");
@@ -647,34 +670,38 @@ mgs_status forward_impl(mgs_frame* f, mgs_stream stream_, const mgs_gaussians* g
         if ((s = grow(ctx, f->stg, (size_t)want * 8 + 8))) return s;
     }
     f->capacity = (int64_t)std::min<size_t>(f->keys.bytes / 4, f->vals.bytes / 4);
+    // the duplication's launch also clears the ranges, the tile orders'
+    // histograms and cursors, the staged-entry counter, the persistent queues
+    // and, in the plain path, the next forward's flags
+    const FillSpan zero[] = {{(uint32_t*)f->ranges.p, 2 * (T + NR), 0u},
+                             {f->order_hist(), 1024, 0u},
+                             {f->stg_count(), 1, 0u},
+                             {f->queue_f(), 1, 0u},
+                             {f->queue_b(), 1, 0u},
+                             {f->reserved ? nullptr : f->flag_words() + (f->flag_word ^ 1), 1, 0u}};
     {
         StageTimer t(ctx, stream, MGS_STAGE_DUPLICATE);
         launch_duplicate_lists(stream, (const float*)f->srec.p, (const uint32_t*)f->cnt_sorted.p,
                                (const uint64_t*)f->tmask.p,
                                (uint32_t*)f->cls_part.p, R, f->n, f->views, f->st, (uint32_t*)f->keys.p,
-                               (uint32_t*)f->vals.p, f->K, f->flags());
+                               (uint32_t*)f->vals.p, f->K, f->flags(), zero, (int)(sizeof zero / sizeof *zero));
     }
+    if (!f->reserved) f->flag_clear[f->flag_word ^ 1] = true;
     // entries are already in (depth, record) order: a stable sort on the cell
     // bits alone gives the (cell, depth, record) order
     f->sort_passes = f->K > 1 ? (f->tile_bits + 7) / 8 : 0;
-    bool in_alt = false;
+    bool in_alt = false, have_ranges = false;
     {
         StageTimer t(ctx, stream, MGS_STAGE_SORT);
-        launch_radix_sort32(stream, (uint32_t*)f->keys.p, (uint32_t*)f->vals.p, (uint32_t*)f->keys_alt.p,
-                            (uint32_t*)f->vals_alt.p, f->K, K_dev, 0, 8 * f->sort_passes, f->sort_tmp.p, &in_alt);
+        have_ranges = launch_radix_sort32(stream, (uint32_t*)f->keys.p, (uint32_t*)f->vals.p,
+                                          (uint32_t*)f->keys_alt.p, (uint32_t*)f->vals_alt.p, f->K, K_dev, 0,
+                                          8 * f->sort_passes, f->sort_tmp.p, &in_alt, (uint32_t*)f->ranges.p, T + NR);
     }
     f->sorted_in_alt = in_alt;
-    uint32_t* queue = f->persistent ? (uint32_t*)f->queue.p : nullptr;
     {
         StageTimer t(ctx, stream, MGS_STAGE_RANGES);
-        // one launch clears the ranges, the tile order's histogram and
-        // cursors, the staged-entry counter and the persistent queue
-        const FillSpan zero[4] = {{(uint32_t*)f->ranges.p, 2 * (T + NR), 0u},
-                                  {f->order_hist(), 512, 0u},
-                                  {f->stg_count(), 1, 0u},
-                                  {queue, 1, 0u}};
-        launch_fill_spans(stream, zero, 4);
-        launch_tile_ranges32(stream, f->keys_sorted(), f->K, K_dev, T + NR, (uint32_t*)f->ranges.p, true);
+        if (!have_ranges)
+            launch_tile_ranges32(stream, f->keys_sorted(), f->K, K_dev, T + NR, (uint32_t*)f->ranges.p, true);
         // the forward takes the most expensive tiles first: by the batches the
         // last forward over the same views took, else by list length
         const bool measured = f->order_valid && std::memcmp(&f->order_views, &f->views, sizeof(ViewSet)) == 0;
@@ -698,7 +725,7 @@ mgs_status forward_impl(mgs_frame* f, mgs_stream stream_, const mgs_gaussians* g
         f->have_stats = st->stats != 0 && !imp;
         launch_hybrid_fwd(stream, f->cfg_fwd, (const float*)f->srec.p, f->hybrid(true), f->views, f->st, images,
                           (float*)f->t_final.p, (int32_t*)f->last.p, f->have_stats ? (int32_t*)f->stats.p : nullptr,
-                          f->have_stats ? (int32_t*)f->evals.p : nullptr, queue, ctx->num_cus, f->n,
+                          f->have_stats ? (int32_t*)f->evals.p : nullptr, f->queue_f(), ctx->num_cus, f->n,
                           imp ? (double*)f->imp_acc.p : nullptr, imp ? (uint32_t*)imp_max : nullptr);
     }
     if (imp) launch_round_f64(stream, (const double*)f->imp_acc.p, imp_sum, f->n);
@@ -741,27 +768,20 @@ mgs_status mgs_backward(mgs_frame* f, mgs_stream stream_, const float* dl_dimage
     mgs_status s;
     // per-record 2D gradients and mask gradients accumulate in FP64: a wide
     // splat takes atomics from thousands of tiles whose partial sums cancel
-    if ((s = grow_drec(f)) || (s = grow(ctx, f->dm_acc, (size_t)f->n * 8 + 8))) return s;
-    uint32_t* queue = nullptr;
-    if (!f->drec_zero) {
-        // +0.0 in every double: normally the forward compositing has cleared
-        // the accumulator; a second backward after one forward, or a new
-        // allocation, fills it here
-        launch_fill_u32(stream, (uint32_t*)f->d_rec.p, f->d_rec.bytes / 4, 0u);
-    }
-    f->drec_zero = false;  // this backward accumulates into it
-    if (f->persistent) queue = (uint32_t*)f->queue.p;
+    if ((s = grow_drec(f))) return s;
     // the tile order: the forward's when it came from measured batch counts
     // (a scheduling choice: the order decides no result), else by this
     // forward's batch counts
     const bool own_order = !f->fwd_order_measured;
-    {
-        // one launch clears the FP64 mask gradients, the persistent queue and
-        // the tile order's histogram and cursors
-        const FillSpan zero[3] = {{(uint32_t*)f->dm_acc.p, 2 * f->n, 0u}, {queue, 1, 0u},
-                                  {own_order ? f->order_hist() : nullptr, 512, 0u}};
-        launch_fill_spans(stream, zero, 3);
+    if (!f->drec_zero) {
+        // +0.0 in every double: normally the forward has cleared the
+        // accumulators, the queue and the order's histogram; a second backward
+        // after one forward, or a new allocation, clears them here
+        launch_fill_u32(stream, (uint32_t*)f->d_rec.p, f->d_rec.bytes / 4, 0u);
+        const FillSpan zero[] = {{f->queue_b(), 1, 0u}, {f->order_hist_b(), 512, 0u}};
+        launch_fill_spans(stream, zero, 2);
     }
+    f->drec_zero = false;  // this backward accumulates into it
     HybridBuffers hb = f->hybrid();
     {
         StageTimer t(ctx, stream, MGS_STAGE_COMPOSITE_BWD);
@@ -769,7 +789,7 @@ mgs_status mgs_backward(mgs_frame* f, mgs_stream stream_, const float* dl_dimage
         // batches (the backward replays them)
         const uint32_t T = f->views.total_tiles;
         if (own_order) {
-            launch_tile_order(stream, (const uint32_t*)f->nbatch.p, T, f->order_hist(), (uint32_t*)f->order_b.p,
+            launch_tile_order(stream, (const uint32_t*)f->nbatch.p, T, f->order_hist_b(), (uint32_t*)f->order_b.p,
                               true);
             hb.order = (const uint32_t*)f->order_b.p;
         } else {
@@ -777,12 +797,11 @@ mgs_status mgs_backward(mgs_frame* f, mgs_stream stream_, const float* dl_dimage
         }
         launch_hybrid_bwd(stream, f->cfg_bwd, (const float*)f->srec.p, hb, f->views, f->st,
                           (const float*)f->t_final.p, (const int32_t*)f->last.p, dl_dimages, f->n,
-                          (double*)f->d_rec.p, (double*)f->dm_acc.p, queue, ctx->num_cus);
+                          (double*)f->d_rec.p, f->dm_acc(), f->queue_b(), ctx->num_cus);
     }
     {
         StageTimer t(ctx, stream, MGS_STAGE_PROJECT_BWD);
-        launch_project_bwd64(stream, f->g, f->views, f->st, (double*)f->d_rec.p, (const double*)f->dm_acc.p,
-                             *grads, (const uint32_t*)f->tiles.p);
+        launch_project_bwd64(stream, f->g, f->views, f->st, (double*)f->d_rec.p, f->dm_acc(), *grads, (const uint32_t*)f->tiles.p);
     }
     MGS_CHECK_LAUNCH(ctx);
     return MGS_OK;

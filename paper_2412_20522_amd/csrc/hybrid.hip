@@ -438,9 +438,35 @@ __global__ void __launch_bounds__(LO_GROUP) list_offsets_group_kernel(const uint
     }
 }
 
-__global__ void __launch_bounds__(LO_GROUP) list_offsets_total_kernel(int64_t ng, ListOffsets lo,
-                                                                     uint64_t* __restrict__ total,
-                                                                     uint64_t* __restrict__ wide) {
+// What step 2 leaves: on the device, and (host, optional) in pinned host
+// memory with the flag words and the staged-entry counter, so that the plain
+// path's one read needs no copy.
+struct ListTotals {
+    uint64_t* total;
+    uint64_t* wide;
+    const uint32_t* flags;   // two words
+    const uint32_t* staged;
+    uint64_t* host;
+};
+// thread k of the workgroup holds total k (0: entries, 1 .. 4: as group_tot)
+__device__ __forceinline__ void put_totals(const ListTotals& o, int k, uint64_t v) {
+    if (k > 4) return;
+    const int w = k <= 1 ? 0 : k;  // place in wide
+    if (k == 0) *o.total = v;
+    else o.wide[w] = v;
+    if (o.host) {
+        if (k == 0) {
+            o.host[1] = v;
+            o.host[0] = (uint64_t)o.flags[0] | (uint64_t)o.flags[1] << 32;
+            o.host[24] = *o.staged;
+        } else {
+            o.host[2 + w] = v;
+        }
+        __threadfence_system();
+    }
+}
+
+__global__ void __launch_bounds__(LO_GROUP) list_offsets_total_kernel(int64_t ng, ListOffsets lo, ListTotals out) {
     __shared__ uint64_t s_w[LO_GROUP / 64][5];
     const int t = threadIdx.x, lane = lane_id(), wid = t >> 6;
     uint64_t carry = 0, sum[4] = {0, 0, 0, 0};
@@ -474,11 +500,64 @@ __global__ void __launch_bounds__(LO_GROUP) list_offsets_total_kernel(int64_t ng
         if (lane == 0) s_w[wid][1 + k] = sum[k];
     }
     __syncthreads();
-    if (t == 0) *total = carry;
-    if (t < 4) {
-        uint64_t tot = 0;
-        for (int v = 0; v < LO_GROUP / 64; ++v) tot += s_w[v][1 + t];
-        wide[t == 0 ? 0 : t + 1] = tot;
+    if (t < 5) {
+        uint64_t tot = carry;
+        if (t > 0) {
+            tot = 0;
+            for (int v = 0; v < LO_GROUP / 64; ++v) tot += s_w[v][t];
+        }
+        put_totals(out, t, tot);
+    }
+}
+
+// Both steps in one workgroup, for at most LO_ONE groups: a group takes about
+// as long here as the launch it saves (4.6 us).
+constexpr int64_t LO_ONE = 4;
+__global__ void __launch_bounds__(LO_GROUP) list_offsets_one_kernel(const uint32_t* __restrict__ part, int64_t nb,
+                                                                   int64_t nw, int64_t ng, ListOffsets lo, int sizes,
+                                                                   ListTotals out) {
+    __shared__ uint64_t s_w[LO_GROUP / 64][5];
+    const int t = threadIdx.x, lane = lane_id(), wid = t >> 6;
+    uint64_t carry = 0, sum[4] = {0, 0, 0, 0};
+    for (int64_t b = t; b < nb; b += LO_GROUP) {
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+            if (k < 2 || sizes) sum[k] += part[(k < 2 ? k : k + 4) * nb + b];
+    }
+    for (int64_t g = 0; g < ng; ++g) {
+        const int64_t w = g * LO_GROUP + t;
+        const uint64_t c = w < nw ? part[2 * nb + w] : 0u;
+        uint64_t x = c;
+#pragma unroll
+        for (int d = 1; d < 64; d <<= 1) {
+            const uint64_t y = __shfl_up(x, d);
+            if (lane >= d) x += y;
+        }
+        if (lane == 63) s_w[wid][0] = x;
+        __syncthreads();
+        uint64_t wo = 0, tot = 0;
+        for (int v = 0; v < LO_GROUP / 64; ++v) {
+            if (v < wid) wo += s_w[v][0];
+            tot += s_w[v][0];
+        }
+        if (w < nw) lo.wave_rel[w] = wo + x - c;
+        if (t == 0) lo.group_off[g] = carry;
+        carry += tot;
+        __syncthreads();  // s_w is written again
+    }
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        for (int off = 32; off > 0; off >>= 1) sum[k] += __shfl_xor(sum[k], off);
+        if (lane == 0) s_w[wid][1 + k] = sum[k];
+    }
+    __syncthreads();
+    if (t < 5) {
+        uint64_t tot = carry;
+        if (t > 0) {
+            tot = 0;
+            for (int v = 0; v < LO_GROUP / 64; ++v) tot += s_w[v][t];
+        }
+        put_totals(out, t, tot);
     }
 }
 
@@ -532,7 +611,11 @@ __device__ __forceinline__ int wave_max_scan(int x) {
 __global__ void __launch_bounds__(256) duplicate_kernel(
     const float4* __restrict__ srec, const uint32_t* __restrict__ cnt_sorted,
     const uint64_t* __restrict__ tmask, ListOffsets lo, int64_t R, int64_t n, ViewSet views, DevSettings st,
-    uint32_t* __restrict__ keys, uint32_t* __restrict__ vals, int64_t capacity, uint32_t* __restrict__ flags) {
+    uint32_t* __restrict__ keys, uint32_t* __restrict__ vals, int64_t capacity, uint32_t* __restrict__ flags,
+    FillSet fs) {
+    // the clears of the later stages ride along (a launch of their own: 4 us)
+    for (int64_t f = (int64_t)blockIdx.x * 256 + threadIdx.x; f < fs.total; f += (int64_t)gridDim.x * 256)
+        fill_element(fs, f);
     __shared__ uint32_t s_first[256];
     __shared__ uint32_t s_rel[256];
     __shared__ unsigned long long s_mask[256];
@@ -838,6 +921,81 @@ __global__ void __launch_bounds__(256) order_offsets_kernel(const uint32_t* key,
     __syncthreads();
     if (i < n) {
         order[s_base[b] + rank] = i;
+        nbatch[i] = 0u;  // (key may be the same array: read above by this thread only)
+    }
+}
+
+// batch_caps_kernel and order_offsets_kernel in one workgroup, for at most
+// SETUP_ONE tiles (2,500 tiles: 8.4 -> 5 us, and one launch fewer).
+constexpr int SETUP_DT = 1024, SETUP_PER = 4;
+constexpr uint32_t SETUP_ONE = SETUP_DT * SETUP_PER;
+__global__ void __launch_bounds__(SETUP_DT) tile_setup_kernel(const uint2* __restrict__ ranges, ViewSet views, int batch,
+                                                               const uint32_t* key, uint32_t* __restrict__ cost,
+                                                               uint32_t* __restrict__ cur_off,
+                                                               uint64_t* __restrict__ cur_need,
+                                                               uint32_t* __restrict__ order, uint32_t* nbatch) {
+    __shared__ uint32_t h[256];
+    __shared__ uint32_t s_w[SETUP_DT / 64];
+    __shared__ uint32_t s_bin[4];
+    const int t = threadIdx.x, lane = lane_id(), wid = t >> 6;
+    if (t < 256) h[t] = 0u;
+    __syncthreads();
+    uint32_t c[SETUP_PER], bin[SETUP_PER];
+#pragma unroll
+    for (int k = 0; k < SETUP_PER; ++k) {
+        const uint32_t i = (uint32_t)(k * SETUP_DT + t);
+        c[k] = 0u;
+        bin[k] = 0u;
+        if (i >= views.total_tiles) continue;
+        int vi = 0;
+        while (vi + 1 < views.n_views && i >= views.v[vi + 1].tile_off) ++vi;
+        const DevView& cam = views.v[vi];
+        const uint32_t lt = i - cam.tile_off;
+        const int tx = (int)(lt % (uint32_t)cam.grid_w), ty = (int)(lt / (uint32_t)cam.grid_w);
+        const uint2 r1 = ranges[i], r2 = ranges[region_of_tile(tx, ty, cam, views)];
+        const uint32_t len1 = r1.y - r1.x, len2 = r2.y - r2.x;
+        c[k] = 2u * ((len1 + batch - 1) / batch + (len2 + batch - 1) / batch) + 2u;
+        const uint32_t ck = min((len1 + len2) >> 3, 255u);
+        cost[i] = ck;
+        bin[k] = 255u - min(key ? key[i] : ck, 255u);
+        atomicAdd(&h[bin[k]], 1u);
+    }
+    // checkpoint offsets: exclusive prefix over the tiles in index order
+    uint64_t carry = 0;
+#pragma unroll
+    for (int k = 0; k < SETUP_PER; ++k) {
+        const uint32_t i = (uint32_t)(k * SETUP_DT + t);
+        const uint32_t x = wave_add_scan(c[k]);
+        if (lane == 63) s_w[wid] = x;
+        __syncthreads();
+        uint32_t wo = 0, tot = 0;
+        for (int v = 0; v < SETUP_DT / 64; ++v) {
+            if (v < wid) wo += s_w[v];
+            tot += s_w[v];
+        }
+        if (i < views.total_tiles) cur_off[i] = (uint32_t)carry + wo + x - c[k];
+        carry += tot;
+        __syncthreads();  // s_w is written again
+    }
+    if (t == 0) *cur_need = carry;
+    // bin starts, then the tiles in descending cost (ties in any order)
+    uint32_t n = 0, x = 0;
+    if (t < 256) {
+        n = h[t];
+        x = wave_add_scan(n);
+        if (lane == 63) s_bin[wid] = x;
+    }
+    __syncthreads();
+    if (t < 256) {
+        for (int v = 0; v < wid; ++v) x += s_bin[v];
+        h[t] = x - n;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < SETUP_PER; ++k) {
+        const uint32_t i = (uint32_t)(k * SETUP_DT + t);
+        if (i >= views.total_tiles) continue;
+        order[atomicAdd(&h[bin[k]], 1u)] = i;
         nbatch[i] = 0u;  // (key may be the same array: read above by this thread only)
     }
 }
@@ -1151,8 +1309,8 @@ struct HybridLists {
     uint2* stg;                // null: the backward merges again
     uint32_t* stg_count;
     uint64_t stg_cap;
-    double* drec_clear;        // the backward's FP64 accumulator, cleared by the forward
-    uint64_t drec_clear_n2;    // its size in pairs of doubles
+    double* drec_clear;        // the backward's FP64 accumulators, cleared by the forward
+    uint64_t drec_clear_n2;    // their size in pairs of doubles
     const uint32_t* order;     // optional: tile taken at each queue position
 };
 
@@ -2219,23 +2377,32 @@ ListOffsets list_offsets(uint32_t* part, int64_t R) {
 size_t classify_parts_bytes(int64_t R) { return counts_bytes(R) + (size_t)(waves_of(R) + 6 * groups_of(R)) * 8 + 8; }
 
 void launch_list_offsets(hipStream_t stream, uint32_t* part, int64_t R, uint64_t* total, uint64_t* wide_counts,
-                         bool sizes) {
+                         bool sizes, const uint32_t* flags, const uint32_t* staged, uint64_t* host) {
     const ListOffsets lo = list_offsets(part, R);
-    const int64_t ng = R > 0 ? groups_of(R) : 0;
+    const ListTotals out{total, wide_counts, flags, staged, host};
+    const int64_t ng = R > 0 ? groups_of(R) : 0, nb = (int64_t)blocks_of(R);
+    if (ng > 0 && ng <= LO_ONE) {
+        hipLaunchKernelGGL(list_offsets_one_kernel, dim3(1), dim3(LO_GROUP), 0, stream, part, nb, waves_of(R), ng, lo,
+                           sizes ? 1 : 0, out);
+        return;
+    }
     if (ng > 0)
-        hipLaunchKernelGGL(list_offsets_group_kernel, dim3((unsigned)ng), dim3(LO_GROUP), 0, stream, part,
-                           (int64_t)blocks_of(R), waves_of(R), lo, sizes ? 1 : 0);
-    hipLaunchKernelGGL(list_offsets_total_kernel, dim3(1), dim3(LO_GROUP), 0, stream, ng, lo, total, wide_counts);
+        hipLaunchKernelGGL(list_offsets_group_kernel, dim3((unsigned)ng), dim3(LO_GROUP), 0, stream, part, nb,
+                           waves_of(R), lo, sizes ? 1 : 0);
+    hipLaunchKernelGGL(list_offsets_total_kernel, dim3(1), dim3(LO_GROUP), 0, stream, ng, lo, out);
 }
 
 void launch_duplicate_lists(hipStream_t stream, const float* srec, const uint32_t* cnt_sorted,
                             const uint64_t* tmask, uint32_t* part, int64_t R,
                             int64_t n, const ViewSet& views, const DevSettings& st, uint32_t* keys, uint32_t* vals,
-                            int64_t capacity, uint32_t* flags) {
-    if (R == 0) return;
+                            int64_t capacity, uint32_t* flags, const FillSpan* fill, int fill_count) {
+    if (R == 0) {
+        launch_fill_spans(stream, fill, fill_count);
+        return;
+    }
     hipLaunchKernelGGL(duplicate_kernel, dim3(blocks_of(R)), dim3(256), 0, stream,
                        reinterpret_cast<const float4*>(srec), cnt_sorted, tmask, list_offsets(part, R), R,
-                       n, views, st, keys, vals, capacity, flags);
+                       n, views, st, keys, vals, capacity, flags, make_fill_set(fill, fill_count));
 }
 
 void launch_tile_order(hipStream_t stream, const uint32_t* key, uint32_t tiles, uint32_t* hist_cursor,
@@ -2252,6 +2419,12 @@ void launch_tile_setup(hipStream_t stream, const uint32_t* ranges, const ViewSet
                        uint32_t* hist_cursor, uint32_t* order, uint32_t* nbatch) {
     const uint32_t T = views.total_tiles;
     if (T == 0) return;
+    if (T <= SETUP_ONE) {
+        hipLaunchKernelGGL(tile_setup_kernel, dim3(1), dim3(SETUP_DT), 0, stream,
+                           reinterpret_cast<const uint2*>(ranges), views, batch, key, cost, cur_off, cur_need, order,
+                           nbatch);
+        return;
+    }
     hipLaunchKernelGGL(batch_caps_kernel, dim3(blocks_of(T)), dim3(256), 0, stream,
                        reinterpret_cast<const uint2*>(ranges), views, batch, key, cost, cur_off, blk, hist_cursor);
     hipLaunchKernelGGL(order_offsets_kernel, dim3(blocks_of(T)), dim3(256), 0, stream, key, (const uint32_t*)cost, T,

@@ -54,10 +54,11 @@ void launch_radix_sort(hipStream_t stream, uint64_t* keys, uint32_t* vals, uint6
 void launch_tile_ranges(hipStream_t stream, const uint64_t* keys, int64_t K, const uint64_t* K_dev,
                         int64_t total_tiles, uint32_t* ranges);
 // 32-bit keys sorted on bits [begin_bit, end_bit) (stable), and the tile
-// ranges of 32-bit tile keys
-void launch_radix_sort32(hipStream_t stream, uint32_t* keys, uint32_t* vals, uint32_t* keys_alt, uint32_t* vals_alt,
+// ranges of 32-bit tile keys.  With ranges (cleared, nbins of them), a sort in
+// one workgroup also writes them; returns whether it did.
+bool launch_radix_sort32(hipStream_t stream, uint32_t* keys, uint32_t* vals, uint32_t* keys_alt, uint32_t* vals_alt,
                          int64_t K, const uint64_t* K_dev, int begin_bit, int end_bit, void* scratch,
-                         bool* out_in_alt);
+                         bool* out_in_alt, uint32_t* ranges = nullptr, int64_t nbins = 0);
 // Stable sort of 32-bit keys (all bits) within consecutive segments of
 // seg_len keys each (at most 16 segments; the last may be shorter).
 void launch_radix_sort_segmented(hipStream_t stream, uint32_t* keys, uint32_t* vals, uint32_t* keys_alt,
@@ -68,12 +69,32 @@ void launch_tile_ranges32(hipStream_t stream, const uint32_t* keys, int64_t K, c
 void launch_fill_u32(hipStream_t stream, uint32_t* p, int64_t n, uint32_t value);
 // Several u32 fills in one launch (at most FILL_SPANS; null or empty spans
 // are skipped).
-constexpr int FILL_SPANS = 4;
+constexpr int FILL_SPANS = 8;
 struct FillSpan {
     uint32_t* p;
     int64_t n;
     uint32_t value;
 };
+// Spans as a kernel argument: element i of their concatenation belongs to the
+// first span whose end exceeds it.
+struct FillSet {
+    uint32_t* p[FILL_SPANS];
+    int64_t end[FILL_SPANS];  // cumulative element counts
+    uint32_t v[FILL_SPANS];
+    int64_t total;
+    int count;
+};
+FillSet make_fill_set(const FillSpan* spans, int count);
+__device__ __forceinline__ void fill_element(const FillSet& fs, int64_t i) {
+    int64_t start = 0;
+    for (int k = 0; k < fs.count; ++k) {
+        if (i < fs.end[k]) {
+            fs.p[k][i - start] = fs.v[k];
+            return;
+        }
+        start = fs.end[k];
+    }
+}
 void launch_fill_spans(hipStream_t stream, const FillSpan* spans, int count);
 void launch_fill_f32(hipStream_t stream, float* p, int64_t n, float value);
 // Column sums of an [n, 4] int32 array into out_dev[4] (u64); scratch holds
@@ -102,17 +123,20 @@ void launch_permute_classify(hipStream_t stream, const uint32_t* order, const ui
 // entry, the entry total (device u64 *total) and wide_counts (device u64):
 // [0] = wide records, [2] = their region entries, and with sizes (as given to
 // the classification; else 0) [3] = tiles of all footprints, [4] = of those
-// of large splats
+// of large splats; host (optional, pinned memory the device can write)
+// receives for the host [0] = the two flag words, [1] = the entry total, [2] ..
+// [6] = wide_counts, [24] = *staged
 void launch_list_offsets(hipStream_t stream, uint32_t* part, int64_t R, uint64_t* total, uint64_t* wide_counts,
-                         bool sizes);
+                         bool sizes, const uint32_t* flags, const uint32_t* staged, uint64_t* host);
 // The rule that picks the compositing kernels (pixels over all views; the two
 // counts above, needed where fine_needs_sizes).
 bool fine_needs_sizes(int64_t pixels);
 bool use_fine(int64_t pixels, uint64_t tiles_all, uint64_t tiles_large);
+// (fill: the spans the later stages need cleared, set in the same launch)
 void launch_duplicate_lists(hipStream_t stream, const float* srec, const uint32_t* cnt_sorted,
                             const uint64_t* tmask, uint32_t* part, int64_t R,
                             int64_t n, const ViewSet& views, const DevSettings& st, uint32_t* keys, uint32_t* vals,
-                            int64_t capacity, uint32_t* flags);
+                            int64_t capacity, uint32_t* flags, const FillSpan* fill, int fill_count);
 // Tile order of a persistent launch: the tiles by descending cost key
 // (key[t] in 0..255, ties in any order), so that the most expensive start
 // first.  hist_cursor: [512] u32 of scratch (cleared here unless cleared).
@@ -141,8 +165,8 @@ struct HybridBuffers {
     uint32_t* stg;               // [stg_cap, 2] staged entries; null: the backward merges again
     uint32_t* stg_count;         // device counter of staged entries (zeroed before the forward)
     uint64_t stg_cap;
-    double* drec_clear;          // optional: FP64 per-record gradient accumulator the forward clears
-    uint64_t drec_clear_n2;      // its size in pairs of doubles
+    double* drec_clear;          // optional: FP64 gradient accumulators (per record, then the masks') the forward clears
+    uint64_t drec_clear_n2;      // their size in pairs of doubles
     const uint32_t* order;       // optional [tiles]: the order in which a persistent launch takes the tiles
     bool fine;                   // the kernels for small splats (the same for a forward and its backward)
 };

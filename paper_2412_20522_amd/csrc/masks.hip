@@ -227,18 +227,55 @@ __global__ void __launch_bounds__(RNT) finish_sum_kernel(const double* __restric
     }
 }
 
+// Sum and mean of at most SUM_ONE values in one workgroup (a second launch
+// costs more).
+constexpr int SUM_DT = 1024;
+constexpr int64_t SUM_ONE = 16384;
+__global__ void __launch_bounds__(SUM_DT) sum_one_kernel(const float* __restrict__ a, int64_t n, double scale,
+                                                          float* __restrict__ out_f) {
+    __shared__ double sh[SUM_DT / 64];
+    double s = 0.0;
+    for (int64_t i = threadIdx.x; i < n; i += SUM_DT) s += (double)a[i];
+    s = block_sum_double(s, sh);
+    if (threadIdx.x == 0) {
+        const double m = s * scale;
+        *out_f = (float)(m * m);
+    }
+}
+
+// sum(M) for the gradient of L_m comes from every workgroup itself: over the
+// masks (m_hard, at most SUM_ONE of them), or over the np partial sums of
+// partial_sum_kernel.  loss_m (optional): (mean M)^2.
 __global__ void __launch_bounds__(RNT) mask_grad_kernel(const float* __restrict__ d_masks,
                                                          const float* __restrict__ y_soft, int64_t n, float tau,
                                                          float lambda_m, const float* __restrict__ lambda_scale,
-                                                         const double* __restrict__ sum_m,
-                                                         float* __restrict__ d_scores) {
+                                                         const float* __restrict__ m_hard,
+                                                         const double* __restrict__ partial, int np,
+                                                         float* __restrict__ d_scores, float* __restrict__ loss_m) {
+    __shared__ double sh[RNT / 64];
+    __shared__ double s_sum;
+    double s = 0.0;
+    if (np > 0) {
+        for (int i = threadIdx.x; i < np; i += RNT) s += partial[i];
+    } else {
+        for (int64_t i = threadIdx.x; i < n; i += RNT) s += (double)m_hard[i];
+    }
+    s = block_sum_double(s, sh);
+    if (threadIdx.x == 0) {
+        s_sum = s;
+        if (loss_m && blockIdx.x == 0) {
+            const double m = s * (1.0 / (double)n);
+            *loss_m = (float)(m * m);
+        }
+    }
+    __syncthreads();
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n) return;
     // the weight of L_m in L (Eq. 8), optionally scaled by a device value (the
     // incoming gradient of L_m under autograd)
     if (lambda_scale) lambda_m *= *lambda_scale;
     // d L_m / d M_i = 2 mean(M) / n
-    const float dlm = (float)(2.0 * (*sum_m) / ((double)n * (double)n));
+    const float dlm = (float)(2.0 * s_sum / ((double)n * (double)n));
     const float y = y_soft[i];
     const float g = (d_masks[i] + lambda_m * dlm) * y * (1.f - y) / tau;
     reinterpret_cast<float2*>(d_scores)[i] = make_float2(g, -g);
@@ -384,33 +421,32 @@ void launch_compact_rows(hipStream_t stream, const uint32_t* keep, const uint32_
     }
 }
 
-// (mean M)^2 into loss_m (optional); the double sum of M stays in the
-// scratch for the gradient.
-static const double* mask_sum(hipStream_t stream, const float* m_hard, int64_t n, float* loss_m, void* scratch) {
+void launch_mask_loss(hipStream_t stream, const float* m_hard, int64_t n, float* loss_m, void* scratch) {
+    if (n == 0) {
+        launch_fill_f32(stream, loss_m, 1, 0.f);
+        return;
+    }
+    if (n <= SUM_ONE) {
+        hipLaunchKernelGGL(sum_one_kernel, dim3(1), dim3(SUM_DT), 0, stream, m_hard, n, 1.0 / (double)n, loss_m);
+        return;
+    }
     double* partial = reinterpret_cast<double*>(scratch);
     double* total = partial + REDUCE_BLOCKS;
     const int nb = (int)std::min<int64_t>(REDUCE_BLOCKS, (n + RNT - 1) / RNT);
     hipLaunchKernelGGL(partial_sum_kernel, dim3(nb), dim3(RNT), 0, stream, m_hard, n, partial);
     hipLaunchKernelGGL(finish_sum_kernel, dim3(1), dim3(RNT), 0, stream, (const double*)partial, nb, 1.0 / (double)n,
                        total, loss_m, 1);
-    return total;
-}
-
-void launch_mask_loss(hipStream_t stream, const float* m_hard, int64_t n, float* loss_m, void* scratch) {
-    if (n == 0) {
-        launch_fill_f32(stream, loss_m, 1, 0.f);
-        return;
-    }
-    (void)mask_sum(stream, m_hard, n, loss_m, scratch);
 }
 
 void launch_mask_grad(hipStream_t stream, const float* d_masks, const float* m_hard, const float* y_soft, int64_t n,
                       float tau, float lambda_m, const float* lambda_scale, float* d_scores, float* loss_m,
                       void* scratch) {
     if (n == 0) return;
-    const double* total = mask_sum(stream, m_hard, n, loss_m, scratch);
+    double* partial = reinterpret_cast<double*>(scratch);
+    const int np = n <= SUM_ONE ? 0 : (int)std::min<int64_t>(REDUCE_BLOCKS, (n + RNT - 1) / RNT);
+    if (np > 0) hipLaunchKernelGGL(partial_sum_kernel, dim3(np), dim3(RNT), 0, stream, m_hard, n, partial);
     hipLaunchKernelGGL(mask_grad_kernel, dim3((unsigned)((n + RNT - 1) / RNT)), dim3(RNT), 0, stream, d_masks, y_soft,
-                       n, tau, lambda_m, lambda_scale, total, d_scores);
+                       n, tau, lambda_m, lambda_scale, m_hard, (const double*)partial, np, d_scores, loss_m);
 }
 
 void launch_l1_loss_grad(hipStream_t stream, const float* images, const float* targets, int64_t m, float* d_images,

@@ -541,12 +541,14 @@ radix_downsweep_kernel(
 // launches of 3 to 7 us per pass whatever the size; this one holds keys and
 // values in LDS and takes 3 to 5 us per pass (4096 keys, four passes: 59 ->
 // 16 us).  Ranking as in radix_downsweep_kernel; keys past the live count are
-// all ones and stay behind every valid key.
+// all ones and stay behind every valid key.  ranges (optional, cleared; one
+// segment): [start, end) of every key below nbins, as tile_ranges_kernel.
 constexpr int SHORT_DT = 1024;
 template <int IPW>
 __global__ void __launch_bounds__(SHORT_DT) radix_short_kernel(uint32_t* __restrict__ keys, uint32_t* __restrict__ vals,
                                                                 int64_t Kcap, const uint64_t* __restrict__ K_dev,
-                                                                int begin_bit, int end_bit, int64_t seg_len) {
+                                                                int begin_bit, int end_bit, int64_t seg_len,
+                                                                uint2* __restrict__ ranges, uint32_t nbins) {
     constexpr int NW = SHORT_DT / 64;
     __shared__ uint32_t sk[SHORT_DT * IPW];
     __shared__ uint32_t sv[SHORT_DT * IPW];
@@ -625,6 +627,14 @@ __global__ void __launch_bounds__(SHORT_DT) radix_short_kernel(uint32_t* __restr
         if (j < rounds && i < n) {
             keys[beg + i] = key[j];
             vals[beg + i] = val[j];
+            if (ranges) {  // sk still holds the sorted keys
+                const uint32_t c = key[j], p = i > 0 ? sk[i - 1] : 0u;
+                if (i == 0 || p != c) {
+                    if (i > 0 && p < nbins) ranges[p].y = (uint32_t)i;
+                    if (c < nbins) ranges[c].x = (uint32_t)i;
+                }
+                if (i == n - 1 && c < nbins) ranges[c].y = (uint32_t)n;
+            }
         }
     }
 }
@@ -695,25 +705,9 @@ __global__ void __launch_bounds__(256) fill_u32_kernel(uint32_t* __restrict__ p,
     if (i < n) p[i] = v;
 }
 
-// Up to FILL_SPANS u32 spans in one launch: element i of the concatenation
-// belongs to the first span whose end exceeds it.
-struct FillSet {
-    uint32_t* p[FILL_SPANS];
-    int64_t end[FILL_SPANS];  // cumulative element counts
-    uint32_t v[FILL_SPANS];
-    int count;
-};
-
+// Up to FILL_SPANS u32 spans in one launch
 __global__ void __launch_bounds__(256) fill_set_kernel(FillSet fs) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    int64_t start = 0;
-    for (int k = 0; k < fs.count; ++k) {
-        if (i < fs.end[k]) {
-            fs.p[k][i - start] = fs.v[k];
-            return;
-        }
-        start = fs.end[k];
-    }
+    fill_element(fs, (int64_t)blockIdx.x * blockDim.x + threadIdx.x);
 }
 
 __global__ void __launch_bounds__(256) fill_f32_kernel(float* __restrict__ p, int64_t n, float v) {
@@ -757,27 +751,28 @@ __global__ void __launch_bounds__(NT) sum_i32x4_partial_kernel(const int4* __res
 
 // seg_len > 0: the keys form segments of seg_len keys, each sorted on its own
 // (no device-side count then); otherwise one segment.
+// ranges, nbins: as launch_radix_sort32; returns whether they were written.
 template <typename KeyT>
-void radix_sort_t(hipStream_t stream, KeyT* keys, uint32_t* vals, KeyT* keys_alt, uint32_t* vals_alt, int64_t K,
+bool radix_sort_t(hipStream_t stream, KeyT* keys, uint32_t* vals, KeyT* keys_alt, uint32_t* vals_alt, int64_t K,
                   const uint64_t* K_dev, int begin_bit, int end_bit, void* scratch, bool* out_in_alt,
-                  int64_t seg_len = 0) {
+                  int64_t seg_len = 0, uint32_t* ranges = nullptr, int64_t nbins = 0) {
     *out_in_alt = false;
-    if (K <= 1 && !K_dev) return;
-    if (end_bit <= begin_bit) return;
+    if (K <= 1 && !K_dev) return false;
+    if (end_bit <= begin_bit) return false;
     if constexpr (sizeof(KeyT) == 4) {
         // short segments: one launch, in place (the lines between 8 and 16
         // keys per thread and at SHORT_MAX are those of its LDS)
         const int64_t sl = seg_len > 0 && seg_len < K && !K_dev ? seg_len : K;
         const unsigned ns = (unsigned)((K + sl - 1) / sl);
-        if (sl <= SHORT_DT * 8) {
-            hipLaunchKernelGGL(radix_short_kernel<8>, dim3(ns), dim3(SHORT_DT), 0, stream, keys, vals, K, K_dev,
-                               begin_bit, end_bit, sl);
-            return;
-        }
         if (sl <= SHORT_MAX) {
-            hipLaunchKernelGGL(radix_short_kernel<16>, dim3(ns), dim3(SHORT_DT), 0, stream, keys, vals, K, K_dev,
-                               begin_bit, end_bit, sl);
-            return;
+            uint2* r = ns == 1 ? reinterpret_cast<uint2*>(ranges) : nullptr;
+#define MGS_SHORT(I)                                                                                               \
+    hipLaunchKernelGGL(radix_short_kernel<I>, dim3(ns), dim3(SHORT_DT), 0, stream, keys, vals, K, K_dev, begin_bit, \
+                       end_bit, sl, r, (uint32_t)nbins)
+            if (sl <= SHORT_DT * 8) MGS_SHORT(8);
+            else MGS_SHORT(16);
+#undef MGS_SHORT
+            return r != nullptr;
         }
     }
     // about SORT_BLOCKS workgroups, each over a contiguous chunk of whole
@@ -828,6 +823,7 @@ void radix_sort_t(hipStream_t stream, KeyT* keys, uint32_t* vals, KeyT* keys_alt
         uint32_t* tv = vin; vin = vout; vout = tv;
         *out_in_alt = !*out_in_alt;
     }
+    return false;
 }
 
 }  // namespace
@@ -895,10 +891,11 @@ void launch_radix_sort(hipStream_t stream, uint64_t* keys, uint32_t* vals, uint6
     radix_sort_t<uint64_t>(stream, keys, vals, keys_alt, vals_alt, K, K_dev, 0, key_bits, scratch, out_in_alt);
 }
 
-void launch_radix_sort32(hipStream_t stream, uint32_t* keys, uint32_t* vals, uint32_t* keys_alt, uint32_t* vals_alt,
+bool launch_radix_sort32(hipStream_t stream, uint32_t* keys, uint32_t* vals, uint32_t* keys_alt, uint32_t* vals_alt,
                          int64_t K, const uint64_t* K_dev, int begin_bit, int end_bit, void* scratch,
-                         bool* out_in_alt) {
-    radix_sort_t<uint32_t>(stream, keys, vals, keys_alt, vals_alt, K, K_dev, begin_bit, end_bit, scratch, out_in_alt);
+                         bool* out_in_alt, uint32_t* ranges, int64_t nbins) {
+    return radix_sort_t<uint32_t>(stream, keys, vals, keys_alt, vals_alt, K, K_dev, begin_bit, end_bit, scratch,
+                                  out_in_alt, 0, ranges, nbins);
 }
 
 void launch_radix_sort_segmented(hipStream_t stream, uint32_t* keys, uint32_t* vals, uint32_t* keys_alt,
@@ -929,19 +926,23 @@ void launch_fill_u32(hipStream_t stream, uint32_t* p, int64_t n, uint32_t value)
     hipLaunchKernelGGL(fill_u32_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, stream, p, n, value);
 }
 
-void launch_fill_spans(hipStream_t stream, const FillSpan* spans, int count) {
+FillSet make_fill_set(const FillSpan* spans, int count) {
     FillSet fs{};
-    int64_t total = 0;
     for (int k = 0; k < count && fs.count < FILL_SPANS; ++k) {
         if (!spans[k].p || spans[k].n <= 0) continue;
-        total += spans[k].n;
+        fs.total += spans[k].n;
         fs.p[fs.count] = spans[k].p;
-        fs.end[fs.count] = total;
+        fs.end[fs.count] = fs.total;
         fs.v[fs.count] = spans[k].value;
         ++fs.count;
     }
-    if (total == 0) return;
-    hipLaunchKernelGGL(fill_set_kernel, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, stream, fs);
+    return fs;
+}
+
+void launch_fill_spans(hipStream_t stream, const FillSpan* spans, int count) {
+    const FillSet fs = make_fill_set(spans, count);
+    if (fs.total == 0) return;
+    hipLaunchKernelGGL(fill_set_kernel, dim3((unsigned)((fs.total + 255) / 256)), dim3(256), 0, stream, fs);
 }
 
 void launch_round_f64(hipStream_t stream, const double* in, float* out, int64_t n) {

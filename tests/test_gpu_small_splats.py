@@ -113,7 +113,7 @@ def test_tile_wide_kernels_match_oracle(tile, fwd_ppt, bwd_ppt, wide):
         assert e <= 2e-3, (name, e)
 
 
-@pytest.mark.parametrize("n", [1, 64, 1025, 8192, 8193, 16384, 16385, 40_000])
+@pytest.mark.parametrize("n", [1, 64, 1025, 8192, 8193, 16384, 16385, 40_000, 300_000])
 @pytest.mark.parametrize("views", [1, 3])
 def test_depth_order_and_lists_over_the_sort_variants(n, views):
     """Record order and list entries around the sizes where the sorts change
@@ -142,3 +142,54 @@ def test_depth_order_and_lists_over_the_sort_variants(n, views):
     step = np.diff(vals) > 0
     step[r[1:, 0] - 1] = True  # positions ascend within a cell
     assert step.all()
+
+
+@pytest.mark.parametrize("persistent", [0, 1])
+def test_tile_setup_in_one_workgroup_equals_several(persistent):
+    """4096 tiles take the one-workgroup set-up; one tile more (a second view
+    of one pixel) the two-kernel one: same images, also on a workspace fixed
+    from each set-up's checkpoint count."""
+    from paper_2412_20522_amd.raster import Rasterizer
+    s = scenegen.small_scene(20_000, 1024, 1024, seed=77, sh_degree=1, log_scale_mean=-2.5)
+    dev = U.to_device(s)
+    params = {k: dev[k] for k in U.PARAM_KEYS}
+    rast = Rasterizer(0, **_settings((16, 16), persistent=persistent, wide_tiles=8))
+    one = s["cameras"]
+    two = one + [scenegen.orbit_camera(4.0, 10.0, 0.0, 1, 1)]
+    out = []
+    for cams in (one, two):
+        frame = rast.acquire_frame()
+        plain = rast.forward(frame, params, dev["masks"], cams)[:3 * 1024 * 1024].clone()
+        again = rast.forward(frame, params, dev["masks"], cams)[:3 * 1024 * 1024].clone()  # measured order
+        rast.reserve(frame, 1.0)
+        fixed = rast.forward(frame, params, dev["masks"], cams)[:3 * 1024 * 1024].clone()
+        rast.check(frame)
+        rast.reserve(frame, 0)
+        rast.release_frame(frame)
+        out += [plain, again, fixed]
+    torch.cuda.synchronize()
+    for x in out[1:]:
+        assert torch.equal(x, out[0])
+
+
+@pytest.mark.parametrize("n", [1, 255, 256, 16_384, 16_385, 300_001])
+def test_mask_loss_and_gradient_over_the_reduction_variants(n):
+    from paper_2412_20522_amd import maskgs as M
+    from paper_2412_20522_amd.raster import Rasterizer
+    rng = np.random.default_rng(n)
+    m = (rng.uniform(size=n) < 0.6).astype(np.float32)
+    y, d = rng.uniform(size=n).astype(np.float32), rng.normal(size=n).astype(np.float32)
+    ctx = Rasterizer(0).ctx
+    t = {k: torch.from_numpy(v).cuda() for k, v in (("m", m), ("y", y), ("d", d))}
+    loss, loss2, out = torch.full((1,), -1.0, device="cuda"), torch.full((1,), -1.0, device="cuda"), \
+        torch.empty(n, 2, device="cuda")
+    M.mgs_mask_loss(ctx, t["m"], loss)
+    M.mgs_mask_grad(ctx, t["d"], t["m"], t["y"], 0.5, 0.3, out, loss_m=loss2)
+    torch.cuda.synchronize()
+    want = m.astype(np.float64).mean() ** 2
+    assert abs(loss.item() - want) <= 2e-7 * want and loss.item() == loss2.item()
+    y64 = y.astype(np.float64)
+    g = (d + 0.3 * 2.0 * m.sum(dtype=np.float64) / n ** 2) * y64 * (1.0 - y64) / 0.5
+    o = out.cpu().numpy().astype(np.float64)
+    # a few FP32 roundings of the sum and the product
+    assert np.all(np.abs(o[:, 0] - g) <= 1e-6 * (np.abs(g) + np.abs(d) + 1.0)) and np.array_equal(o[:, 1], -o[:, 0])
