@@ -91,7 +91,8 @@ typedef struct {
     float bg[3];             /* background colour */
     int32_t exact_mode;      /* 1: alpha_min = 0, t_min = 0, no Q cut, every valid
                                 Gaussian in every tile (for calculus tests) */
-    int32_t persistent;      /* 1: compositing pops tiles from a device queue */
+    int32_t persistent;      /* accepted, without effect: every launch takes the
+                                tiles most expensive first */
     int32_t fwd_ppt;         /* pixels per thread in forward compositing: 1, 2 or 4
                                 (tile_w * tile_h / ppt threads per workgroup, a
                                 multiple of 64) */

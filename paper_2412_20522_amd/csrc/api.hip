@@ -18,7 +18,6 @@ using namespace mgs;
 
 struct mgs_ctx {
     int device = 0;
-    int num_cus = 256;
     void* scan_noalloc = nullptr;  // this device's address of the scratch of mgs_scan_noalloc
     std::string err;
     // per-stage timing
@@ -275,7 +274,6 @@ struct mgs_frame {
     ViewSet views{};
     DevSettings st{};
     CompositeConfig cfg_fwd{}, cfg_bwd{};
-    int persistent = 0;
     bool fine = false;  // composited by the kernels for small splats (use_fine)
     int n_views = 0;
     int64_t n = 0, R = 0, P = 0, K = 0, W = 0, total_tiles = 0, capacity = 0;
@@ -294,9 +292,9 @@ struct mgs_frame {
     DevBuf keys, vals, keys_alt, vals_alt, ranges, caps, tcost, order, order_b, cur_off, nbatch, cur, cur_stg, stg,
         t_final, last, stats, evals;
     bool have_stats = false;  // the last forward wrote the per-pixel work counters
-    DevBuf d_rec, rsort_tmp, sort_tmp, misc, queue, sum_tmp;  // d_rec: FP64, R rows, then the masks' n sums
+    DevBuf d_rec, rsort_tmp, sort_tmp, misc, sum_tmp;  // d_rec: FP64, R rows, then the masks' n sums
     DevBuf imp_acc;  // FP64 sums of the importance forward
-    // d_rec, the backward's queue and its order's histogram are all zeros from
+    // d_rec and the backward's order's histogram are all zeros from
     // the forward (which clears them) to the backward that uses them; false
     // after a backward and after (re)allocation (a backward then clears them
     // first)
@@ -312,7 +310,7 @@ struct mgs_frame {
     // misc: flags (2 u32) at 0, list entry count (u64) at 8, wide record count
     // (u64) at 16, checkpoint count (u64) at 24, region entry count (u64) at
     // 32, footprint tiles of all and of large splats (u64) at 40 and 48,
-    // staged-entry counter (u32) at 192; the histogram and cursors (2 x 256
+    // staged-entry counters (2 u32) at 192; the histogram and cursors (2 x 256
     // u32) of the forward's tile order from 256, of the backward's from 2304
     uint64_t* h_pinned = nullptr;  // read-back of misc
     uint64_t* h_device = nullptr;  // the same memory as the device sees it
@@ -333,8 +331,6 @@ struct mgs_frame {
     uint32_t* stg_count() { return (uint32_t*)((char*)misc.p + 192); }
     uint32_t* order_hist() { return (uint32_t*)((char*)misc.p + 256); }
     uint32_t* order_hist_b() { return order_hist() + 512; }
-    uint32_t* queue_f() { return persistent ? (uint32_t*)queue.p : nullptr; }
-    uint32_t* queue_b() { return persistent ? (uint32_t*)queue.p + 32 : nullptr; }
     double* dm_acc() { return (double*)d_rec.p + (size_t)R * DREC; }
     HybridBuffers hybrid(bool clear_drec = false) {
         const uint64_t cap = reserved ? (uint64_t)cur_cap : (uint64_t)std::min(cur.bytes / 16, cur_stg.bytes / 8);
@@ -398,7 +394,6 @@ mgs_status mgs_create(int device, mgs_ctx** out) {
     if (!c) return fail(nullptr, MGS_ERR_OOM, "context allocation");
     c->device = device;
     c->scan_noalloc = noalloc;
-    c->num_cus = prop.multiProcessorCount;
     *out = c;
     return MGS_OK;
 }
@@ -424,7 +419,7 @@ mgs_status mgs_frame_create(mgs_ctx* ctx, mgs_frame** out) {
         delete f;
         return fail(ctx, MGS_ERR_HIP, "device address of pinned memory");
     }
-    // (zeroed: the staged-entry counter is read before it is first written)
+    // (zeroed: the staged-entry counters are read before they are first written)
     if (grow(ctx, f->misc, 256 + 4096) != MGS_OK || hipMemset(f->misc.p, 0, f->misc.bytes) != hipSuccess) {
         release(f->misc);
         (void)hipHostFree(f->h_pinned);
@@ -444,7 +439,7 @@ mgs_status mgs_frame_destroy(mgs_frame* f) {
                       &f->caps,     &f->tcost,     &f->order,     &f->order_b,   &f->cur_off,   &f->nbatch,   &f->cur,       &f->cur_stg,   &f->stg,
                       &f->t_final,  &f->last,
                       &f->stats,    &f->evals,     &f->d_rec,     &f->rsort_tmp, &f->sort_tmp,
-                      &f->misc,     &f->queue,     &f->sum_tmp,  &f->imp_acc};
+                      &f->misc,     &f->sum_tmp,  &f->imp_acc};
     for (DevBuf* b : bufs) release(*b);
     if (f->h_pinned) (void)hipHostFree(f->h_pinned);
     delete f;
@@ -498,7 +493,7 @@ mgs_status mgs_frame_reserve(mgs_frame* f, mgs_stream stream_, double slack) {
     MGS_HIP(ctx, hipMemcpyAsync(f->h_pinned, f->misc.p, 200, hipMemcpyDeviceToHost, stream));
     MGS_HIP(ctx, hipStreamSynchronize(stream));
     const double K = (double)f->h_pinned[1], C = (double)f->h_pinned[3];
-    const double S = (double)(f->h_pinned[24] & 0xffffffffu);
+    const double S = (double)(f->h_pinned[24] & 0xffffffffu) + (double)(f->h_pinned[24] >> 32);
     const int64_t K_cap = (int64_t)std::ceil(K * slack) + 4096;
     const int64_t cur_cap = (int64_t)std::ceil(C * slack) + 4096;
     const int64_t stg_cap = std::min<int64_t>((int64_t)std::ceil(S * slack) + 4096, 0xffffffffll);
@@ -565,7 +560,6 @@ mgs_status forward_impl(mgs_frame* f, mgs_stream stream_, const mgs_gaussians* g
     f->st = make_settings(st);
     f->cfg_fwd = CompositeConfig{st->tile_w, st->tile_h, st->fwd_ppt};
     f->cfg_bwd = CompositeConfig{st->tile_w, st->tile_h, st->bwd_ppt};
-    f->persistent = st->persistent;
     f->total_tiles = f->views.total_tiles;
     // the plain path picks the compositing kernels from this forward's splat
     // sizes, read with the list counts; a fixed workspace keeps the choice of
@@ -592,7 +586,7 @@ mgs_status forward_impl(mgs_frame* f, mgs_stream stream_, const mgs_gaussians* g
         (s = grow(ctx, f->cur_off, (size_t)T * 4 + 4)) || (s = grow_nbatch(f, (size_t)T * 4 + 4)) ||
         (s = grow(ctx, f->t_final, (size_t)P * 4)) || (s = grow(ctx, f->last, (size_t)P * 4)) ||
         (s = grow(ctx, f->stats, (size_t)P * 16)) || (s = grow(ctx, f->evals, (size_t)P * 16)) ||
-        (s = grow(ctx, f->rsort_tmp, sort_scratch_bytes(R))) || (s = grow(ctx, f->queue, 256)))
+        (s = grow(ctx, f->rsort_tmp, sort_scratch_bytes(R))))
         return s;
     f->flag_word = f->reserved ? 0 : f->flag_word ^ 1;
     if (f->reserved || !f->flag_clear[f->flag_word]) launch_fill_u32(stream, f->flags(), 1, 0u);
@@ -664,20 +658,21 @@ mgs_status forward_impl(mgs_frame* f, mgs_stream stream_, const mgs_gaussians* g
             return s;
         // the entries staged for the backward: room for the previous forward's
         // count with a margin (a batch that does not fit is merged again)
-        const uint64_t prev = f->h_pinned[24] & 0xffffffffu;
-        const uint64_t want = std::min<uint64_t>(std::max<uint64_t>((uint64_t)P, prev + prev / 4), 0xffffffffull);
-        // (the count includes the unused tails of the workgroups' chunks)
-        if ((s = grow(ctx, f->stg, (size_t)want * 8 + 8))) return s;
+        const uint64_t prev = f->h_pinned[24];
+        const uint64_t want =
+            std::min<uint64_t>(std::max<uint64_t>((uint64_t)P + staged_first((uint32_t)T),
+                                                  prev + prev / 4),
+                               0xffffffffull);
+        // (the count includes the unused tails of the workgroups' chunks; the
+        // kernels for small splats keep no staged list)
+        if (!f->fine && (s = grow(ctx, f->stg, (size_t)want * 8 + 8))) return s;
     }
     f->capacity = (int64_t)std::min<size_t>(f->keys.bytes / 4, f->vals.bytes / 4);
     // the duplication's launch also clears the ranges, the tile orders'
-    // histograms and cursors, the staged-entry counter, the persistent queues
-    // and, in the plain path, the next forward's flags
+    // histograms and cursors, the staged-entry counter and, in the plain path, the next forward's flags
     const FillSpan zero[] = {{(uint32_t*)f->ranges.p, 2 * (T + NR), 0u},
                              {f->order_hist(), 1024, 0u},
-                             {f->stg_count(), 1, 0u},
-                             {f->queue_f(), 1, 0u},
-                             {f->queue_b(), 1, 0u},
+                             {f->stg_count(), 2, 0u},
                              {f->reserved ? nullptr : f->flag_words() + (f->flag_word ^ 1), 1, 0u}};
     {
         StageTimer t(ctx, stream, MGS_STAGE_DUPLICATE);
@@ -725,7 +720,7 @@ mgs_status forward_impl(mgs_frame* f, mgs_stream stream_, const mgs_gaussians* g
         f->have_stats = st->stats != 0 && !imp;
         launch_hybrid_fwd(stream, f->cfg_fwd, (const float*)f->srec.p, f->hybrid(true), f->views, f->st, images,
                           (float*)f->t_final.p, (int32_t*)f->last.p, f->have_stats ? (int32_t*)f->stats.p : nullptr,
-                          f->have_stats ? (int32_t*)f->evals.p : nullptr, f->queue_f(), ctx->num_cus, f->n,
+                          f->have_stats ? (int32_t*)f->evals.p : nullptr, f->n,
                           imp ? (double*)f->imp_acc.p : nullptr, imp ? (uint32_t*)imp_max : nullptr);
     }
     if (imp) launch_round_f64(stream, (const double*)f->imp_acc.p, imp_sum, f->n);
@@ -775,11 +770,10 @@ mgs_status mgs_backward(mgs_frame* f, mgs_stream stream_, const float* dl_dimage
     const bool own_order = !f->fwd_order_measured;
     if (!f->drec_zero) {
         // +0.0 in every double: normally the forward has cleared the
-        // accumulators, the queue and the order's histogram; a second backward
+        // accumulators and the order's histogram; a second backward
         // after one forward, or a new allocation, clears them here
         launch_fill_u32(stream, (uint32_t*)f->d_rec.p, f->d_rec.bytes / 4, 0u);
-        const FillSpan zero[] = {{f->queue_b(), 1, 0u}, {f->order_hist_b(), 512, 0u}};
-        launch_fill_spans(stream, zero, 2);
+        launch_fill_u32(stream, f->order_hist_b(), 512, 0u);
     }
     f->drec_zero = false;  // this backward accumulates into it
     HybridBuffers hb = f->hybrid();
@@ -797,7 +791,7 @@ mgs_status mgs_backward(mgs_frame* f, mgs_stream stream_, const float* dl_dimage
         }
         launch_hybrid_bwd(stream, f->cfg_bwd, (const float*)f->srec.p, hb, f->views, f->st,
                           (const float*)f->t_final.p, (const int32_t*)f->last.p, dl_dimages, f->n,
-                          (double*)f->d_rec.p, f->dm_acc(), f->queue_b(), ctx->num_cus);
+                          (double*)f->d_rec.p, f->dm_acc());
     }
     {
         StageTimer t(ctx, stream, MGS_STAGE_PROJECT_BWD);

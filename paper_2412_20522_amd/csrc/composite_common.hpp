@@ -73,24 +73,4 @@ __device__ __forceinline__ bool eval_entry(const float4& A, const float4& B, flo
     return (qs >= k.qs_max) & (e.alpha >= k.amin);
 }
 
-// Persistent launches pop tile ids from a device counter; plain launches
-// own tile blockIdx.x.
-__device__ __forceinline__ uint32_t next_tile(uint32_t* queue, uint32_t* s_tile, uint32_t fixed) {
-    if (!queue) return fixed;
-    __syncthreads();
-    if (threadIdx.x == 0) *s_tile = atomicAdd(queue, 1u);
-    __syncthreads();
-    return *s_tile;
-}
-
-// Workgroups a persistent launch needs to fill the device: resident blocks
-// per CU at the kernel's register and LDS use, times the CU count.
-template <typename Kernel>
-inline int persistent_grid(Kernel k, int block, int num_cus, size_t dyn_lds = 0) {
-    int per_cu = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k, block, dyn_lds) != hipSuccess || per_cu <= 0)
-        per_cu = 4;
-    return per_cu * num_cus;
-}
-
 }  // namespace mgs

@@ -29,6 +29,8 @@
 // began; the backward replays the same batches in reverse from those
 // checkpoints, so the merge is deterministic and nothing per pixel beyond the
 // final transmittance and the last blended entry is stored.
+#include <algorithm>
+
 #include "common.hpp"
 #include "composite_common.hpp"
 #include "kernels.hpp"
@@ -445,7 +447,7 @@ struct ListTotals {
     uint64_t* total;
     uint64_t* wide;
     const uint32_t* flags;   // two words
-    const uint32_t* staged;
+    const uint32_t* staged;  // two words
     uint64_t* host;
 };
 // thread k of the workgroup holds total k (0: entries, 1 .. 4: as group_tot)
@@ -458,7 +460,7 @@ __device__ __forceinline__ void put_totals(const ListTotals& o, int k, uint64_t 
         if (k == 0) {
             o.host[1] = v;
             o.host[0] = (uint64_t)o.flags[0] | (uint64_t)o.flags[1] << 32;
-            o.host[24] = *o.staged;
+            o.host[24] = (uint64_t)o.staged[0] + o.staged[1];
         } else {
             o.host[2 + w] = v;
         }
@@ -820,9 +822,9 @@ __global__ void __launch_bounds__(256) batch_caps_kernel(const uint2* __restrict
     if (h[tid]) atomicAdd(&hist[tid], h[tid]);
 }
 
-// Queue order of the tiles, most expensive first, so that the last tiles a
-// persistent launch takes are cheap (its tail is the cost of the tiles
-// still running when the queue runs dry).  A counting sort on a per-tile
+// Launch order of the tiles, most expensive first, so that the last
+// workgroups to start are cheap (a launch's tail is the cost of the tiles
+// still running when none is left to start).  A counting sort on a per-tile
 // cost key (0..255, descending): order_hist_kernel adds every workgroup's
 // histogram of the keys into hist[256]; order_place_kernel scans hist for the
 // bins' starts, takes for each of its bins a run of slots with one atomic
@@ -1104,6 +1106,15 @@ __device__ __forceinline__ void stage_entry(const Lds& L, int j, const float4* _
     put_entry<FINE>(L, j, srec[3 * p], srec[3 * p + 1], srec[3 * p + 2], k, qx0, qy0, height, st);
 }
 
+// A value equal in all lanes, in a scalar register.
+__device__ __forceinline__ int uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }
+__device__ __forceinline__ uint32_t uniform(uint32_t v) { return (uint32_t)uniform((int)v); }
+__device__ __forceinline__ uint2 uniform(uint2 v) { return make_uint2(uniform(v.x), uniform(v.y)); }
+
+// Hides where a value comes from: what is computed from it is computed again
+// behind this point, not kept in (spilled) registers from before it.
+__device__ __forceinline__ void opaque(int& v) { asm volatile("" : "+v"(v)); }
+
 // Stages the next (at most `batch`) entries of the tile's merged list in LDS.
 // Every thread of the block calls it; the result is uniform.  The first
 // stream is the tile's narrow list, the second its region list, of which
@@ -1116,7 +1127,9 @@ template <bool FINE>
 __device__ Batch merge_batch(const Lds& L, const uint32_t* __restrict__ vals, const float4* __restrict__ srec,
                              int i1, int e1, int i2, int e2, int batch, int tcx, int tcy, const TileBox& tb,
                              const DevView& cam, const DevSettings& st, int kbase, int qx0 = 0, int qy0 = 0) {
-    const int t = threadIdx.x, NT = blockDim.x;
+    int t = threadIdx.x;
+    opaque(t);
+    const int NT = blockDim.x;
     if (st.tile_cull && i2 >= e2) {
         // no region entries left: the next narrow entries are the batch
         const int M = min(batch, e1 - i1);
@@ -1126,7 +1139,7 @@ __device__ Batch merge_batch(const Lds& L, const uint32_t* __restrict__ vals, co
             stage_entry<FINE>(L, j, srec, p, kbase + j, qx0, qy0, cam.height, st);
         }
         __syncthreads();
-        return Batch{M, M, M, 0};
+        return Batch{uniform(M), uniform(M), uniform(M), 0};
     }
     const int cX = min(batch, e1 - i1), cY = min(batch, e2 - i2);
     for (int l = t; l < cX; l += NT) L.xk[l] = vals[i1 + l];
@@ -1194,7 +1207,7 @@ __device__ Batch merge_batch(const Lds& L, const uint32_t* __restrict__ vals, co
     if (st.tile_cull) {
         for (int j = t; j < M; j += NT) stage_entry<FINE>(L, j, srec, L.m[j], kbase + j, qx0, qy0, cam.height, st);
         __syncthreads();
-        return Batch{M, M, nX, nYr};
+        return Batch{uniform(M), uniform(M), uniform(nX), uniform(nYr)};
     }
     const int run = (M + NT - 1) / NT;  // contiguous entries per thread (<= MAXB / 64)
     uint32_t keep = 0, nkeep = 0;
@@ -1217,7 +1230,7 @@ __device__ Batch merge_batch(const Lds& L, const uint32_t* __restrict__ vals, co
         ++p;
     }
     __syncthreads();
-    return Batch{(int)Mc, M, nX, nYr};
+    return Batch{uniform((int)Mc), uniform(M), uniform(nX), uniform(nYr)};
 }
 
 // Wave totals of ten per-lane quantities, each left in the lanes that
@@ -1288,10 +1301,14 @@ __device__ __forceinline__ void pixel_of(int t, int i, const TileGeom& tg, int& 
     y = tg.ty0 + (b / (TW / 8)) * 8 + (l >> 3);
 }
 
-// Staged-list chunks: a persistent workgroup composites many tiles, a plain
-// one a single tile.
-constexpr uint32_t STG_CHUNK_PERSISTENT = 4096;
-constexpr uint32_t STG_CHUNK = 256;
+// Staged-list chunks: a workgroup's first one is its own by its index, further
+// ones come from the global counter (with every workgroup of a launch at that
+// counter at its start, forward compositing waits).
+constexpr uint32_t STG_FIRST = 256;
+constexpr uint32_t STG_CHUNK = 512;
+// words of Lds::wsum behind the scan's: next free entry of the workgroup's
+// chunk, entries left in it, where the batch's entries go (all ones: nowhere)
+constexpr int STG_BASE = 8, STG_LEFT = 9, STG_OFF = 10;
 
 struct HybridLists {
     const uint32_t* vals;      // list entries (sorted positions) in (cell, position) order
@@ -1307,33 +1324,43 @@ struct HybridLists {
     // entry (sorted position, index within the merged batch)
     uint2* cur_stg;
     uint2* stg;                // null: the backward merges again
-    uint32_t* stg_count;
+    uint32_t* stg_count;       // two words: entries taken from the counter, entries of the first chunks
     uint64_t stg_cap;
     double* drec_clear;        // the backward's FP64 accumulators, cleared by the forward
     uint64_t drec_clear_n2;    // their size in pairs of doubles
-    const uint32_t* order;     // optional: tile taken at each queue position
+    const uint32_t* order;     // optional: tile of each workgroup
 };
 
-// Both compositing kernels are built for at least five waves per SIMD (at
-// most 96 registers), the forward with up to two pixels per thread for seven
-// (72 registers): both spill a few values at most, and all run faster than
-// with fewer waves (measured on the batched workload: forward 0.65 -> 0.63
-// ms at four pixels per thread, 0.62 -> 0.58 ms at two; backward 1.02 ->
-// 0.99 ms; eight waves for the forward spill more and are slower).
+// Tile-wide compositing, one workgroup per tile in launch order.  Both kernels
+// are bound by instruction issue, and take no loop over a device queue: with
+// the loop, the launch's arguments stay live in registers across it, and
+// resident workgroups that pop one counter wait for each other.  What the tile
+// and the batch determine is read into scalar registers (`uniform`), so that a
+// thread holds its pixels and the entry only: 55 registers for the forward at
+// two pixels per thread (72 and spills before), 90 for the backward at four.
+// Measured on splats of an unbounded scene, batches of 128, two pixels per
+// thread forward and four backward, queue loop -> now: 4,346 tiles forward 143
+// -> 64 us, backward 186 -> 152 us; 8,664 tiles 222 -> 134 and 317 -> 252 us;
+// 24,937 tiles 432 -> 341 and 663 -> 585 us (of the forward, the tests every
+// 16 entries as a loop of their own: 69 -> 64, 147 -> 134 and 362 -> 341 us).
+// With the counters, batches of 256, one workgroup per tile before and after:
+// 4,346 tiles 107 -> 86 us, 24,937 tiles 512 -> 480 us.
+// Waves per SIMD the register use is held to: forward eight (seven with the
+// counters, which at eight spill: 485 -> 505 us at 24,937 tiles), backward
+// five (six spill at four pixels per thread: 254 -> 268 us at 8,664 tiles).
 // STATS: write the per-pixel work counters (stats_out, eval_out).
 // IMP: accumulate every Gaussian's blending weights M alpha T over the
 // pixels it enters: the wave's sum (FP64 atomic) into imp_sum and its
 // maximum (as float bits, the weights being non-negative) into imp_max.
 template <int TW, int TH, int PPT, bool STATS, bool IMP>
-__global__ void __launch_bounds__(TW * TH / PPT, PPT >= 4 ? 5 : 7) hybrid_fwd_kernel(
+__global__ void __launch_bounds__(TW * TH / PPT, PPT >= 4 ? 5 : STATS ? 7 : 8) hybrid_fwd_kernel(
     const float4* __restrict__ srec, HybridLists hl, ViewSet views, DevSettings st, float* __restrict__ images,
     float* __restrict__ t_final, int32_t* __restrict__ last_out, int4* __restrict__ stats_out,
-    int4* __restrict__ eval_out, uint32_t* __restrict__ queue, int64_t n, double* __restrict__ imp_sum,
+    int4* __restrict__ eval_out, int64_t n, double* __restrict__ imp_sum,
     uint32_t* __restrict__ imp_max) {
     constexpr int NT = TW * TH / PPT;
     extern __shared__ __align__(16) char smem[];
-    __shared__ uint32_t s_tile;
-    const int t = threadIdx.x;
+    int t = threadIdx.x;
     const int batch = st.batch;
     const Lds L = carve(smem, batch);
     const EvalConsts ek = eval_consts(st);
@@ -1342,81 +1369,86 @@ __global__ void __launch_bounds__(TW * TH / PPT, PPT >= 4 ? 5 : 7) hybrid_fwd_ke
         return;
     }
     // staged-list chunk of this workgroup (used by thread 0 only)
-    const uint32_t chunk = queue ? STG_CHUNK_PERSISTENT : STG_CHUNK;
-    uint32_t cbase = 0, cused = chunk;
-    for (;;) {
-        const uint32_t q = next_tile(queue, &s_tile, blockIdx.x);
-        if (q >= views.total_tiles) break;
-        const uint32_t tile = hl.order ? hl.order[q] : q;
-        const TileGeom tg = tile_geom(views, tile, TW, TH);
-        const DevView& cam = views.v[tg.vi];
-        float px[PPT], py[PPT], T[PPT], C0[PPT], C1[PPT], C2[PPT];
-        // stopk: the entry at which the pixel stopped, -1 while it runs
-        // (and 0 for a pixel outside the view, which never runs): the
-        // pixel's done flag, tested with one compare per slot and entry; its
-        // value changes only when the pixel stops
-        int last[PPT], stopk[PPT], nblend[PPT], nmasked[PPT], nev[PPT], nev_last[PPT];
-        bool inside[PPT];
+    if (hl.stg && t == 0) {
+        L.wsum[STG_BASE] = blockIdx.x * STG_FIRST;
+        L.wsum[STG_LEFT] = STG_FIRST;
+        if (blockIdx.x == 0) hl.stg_count[1] = gridDim.x * STG_FIRST;
+    }
+    const uint32_t tile = uniform(hl.order ? hl.order[blockIdx.x] : blockIdx.x);
+    const TileGeom tg = tile_geom(views, tile, TW, TH);
+    const DevView& cam = views.v[tg.vi];
+    float px[PPT], py[PPT], T[PPT], C0[PPT], C1[PPT], C2[PPT];
+    // stopk: the entry at which the pixel stopped, -1 while it runs
+    // (and 0 for a pixel outside the view, which never runs): the
+    // pixel's done flag, tested with one compare per slot and entry; its
+    // value changes only when the pixel stops
+    // (STATS: nev, nev_last: staged entries up to the one at which the
+    // pixel stopped and up to the one it blended last, from the entry's
+    // place in the staged order, so that an entry a pixel skips costs no
+    // counter; staged: entries staged in the batches before)
+    int last[PPT], stopk[PPT], nblend[PPT], nmasked[PPT], nev[PPT], nev_last[PPT];
+    int staged = 0;
 #pragma unroll
-        for (int i = 0; i < PPT; ++i) {
-            int x, y;
-            pixel_of<TW, PPT>(t, i, tg, x, y);
-            inside[i] = x < cam.width && y < cam.height;
-            px[i] = (float)x + 0.5f;
-            py[i] = (float)y + 0.5f;
-            T[i] = 1.f;
-            C0[i] = C1[i] = C2[i] = 0.f;
-            last[i] = -1;
-            stopk[i] = inside[i] ? -1 : 0;
-            nblend[i] = nmasked[i] = nev[i] = nev_last[i] = 0;
+    for (int i = 0; i < PPT; ++i) {
+        int x, y;
+        pixel_of<TW, PPT>(t, i, tg, x, y);
+        const bool inside = x < cam.width && y < cam.height;
+        px[i] = (float)x + 0.5f;
+        py[i] = (float)y + 0.5f;
+        T[i] = 1.f;
+        C0[i] = C1[i] = C2[i] = 0.f;
+        last[i] = -1;
+        stopk[i] = inside ? -1 : 0;
+        nblend[i] = nmasked[i] = nev[i] = nev_last[i] = 0;
+    }
+    const int tcx = tg.tx0 / TW, tcy = tg.ty0 / TH;
+    const uint2 r1 = uniform(hl.ranges[tile]);
+    const uint2 r2 = uniform(hl.ranges[region_of_tile(tcx, tcy, cam, views)]);
+    const int e1 = (int)r1.y, e2 = (int)r2.y;
+    int i1 = (int)r1.x, i2 = (int)r2.x, m = 0, b = 0;
+    const TileBox tb{(float)tg.tx0 + 0.5f, (float)min(tg.tx0 + TW, cam.width) - 0.5f, (float)tg.ty0 + 0.5f,
+                     (float)min(tg.ty0 + TH, cam.height) - 0.5f};
+    uint4* cur = hl.cur + uniform(hl.cur_off[tile]);
+    while (i1 < e1 || i2 < e2) {
+        bool active = false;
+#pragma unroll
+        for (int i = 0; i < PPT; ++i) active |= stopk[i] < 0;
+        if (!__syncthreads_or(active)) break;
+        if (t == 0) cur[b] = make_uint4((uint32_t)i1, (uint32_t)i2, (uint32_t)m, 0u);
+        const Batch bt =
+            merge_batch<false>(L, hl.vals, srec, i1, e1, i2, e2, batch, tcx, tcy, tb, cam, st, m);
+        // room for the staged entries in the list kept for the backward:
+        // thread 0 sub-allocates from a chunk the workgroup took from the
+        // global counter (one atomic per chunk, not per batch)
+        if (hl.stg && t == 0) {
+            uint32_t cbase = L.wsum[STG_BASE], cleft = L.wsum[STG_LEFT];
+            if ((uint32_t)bt.M > cleft) {
+                cbase = gridDim.x * STG_FIRST + atomicAdd(hl.stg_count, STG_CHUNK);
+                cleft = STG_CHUNK;
+            }
+            const uint32_t off = (uint64_t)cbase + (uint64_t)bt.M <= hl.stg_cap ? cbase : 0xffffffffu;
+            L.wsum[STG_OFF] = off;
+            L.wsum[STG_BASE] = cbase + (uint32_t)bt.M;
+            L.wsum[STG_LEFT] = cleft - (uint32_t)bt.M;
+            hl.cur_stg[hl.cur_off[tile] + b] = make_uint2(off, (uint32_t)bt.M);
         }
-        const int tcx = tg.tx0 / TW, tcy = tg.ty0 / TH;
-        const uint2 r1 = hl.ranges[tile];
-        const uint2 r2 = hl.ranges[region_of_tile(tcx, tcy, cam, views)];
-        const int e1 = (int)r1.y, e2 = (int)r2.y;
-        int i1 = (int)r1.x, i2 = (int)r2.x, m = 0, b = 0;
-        const TileBox tb{(float)tg.tx0 + 0.5f, (float)min(tg.tx0 + TW, cam.width) - 0.5f, (float)tg.ty0 + 0.5f,
-                         (float)min(tg.ty0 + TH, cam.height) - 0.5f};
-        uint4* cur = hl.cur + hl.cur_off[tile];
-        while (i1 < e1 || i2 < e2) {
-            bool active = false;
+        for (int j0 = 0; j0 < bt.M; j0 += 16) {
+            // the wave leaves the batch once all its pixels are done,
+            // tested every 16 entries (a done pixel's slot costs only
+            // its skip; a test per entry costs more than it saves)
+            active = false;
 #pragma unroll
             for (int i = 0; i < PPT; ++i) active |= stopk[i] < 0;
-            if (!__syncthreads_or(active)) break;
-            if (t == 0) cur[b] = make_uint4((uint32_t)i1, (uint32_t)i2, (uint32_t)m, 0u);
-            const Batch bt =
-                merge_batch<false>(L, hl.vals, srec, i1, e1, i2, e2, batch, tcx, tcy, tb, cam, st, m);
-            // room for the staged entries in the list kept for the backward:
-            // thread 0 sub-allocates from a chunk the workgroup took from the
-            // global counter (one atomic per chunk, not per batch)
-            uint32_t my_off = 0;
-            if (hl.stg && t == 0) {
-                if (cused + (uint32_t)bt.M > chunk) {
-                    cbase = atomicAdd(hl.stg_count, chunk);
-                    cused = 0;
-                }
-                my_off = cbase + cused;
-                cused += (uint32_t)bt.M;
-            }
-            // uniform: a scalar loop bound
-            const int Mb = __builtin_amdgcn_readfirstlane(bt.M);
-            for (int j = 0; j < Mb; ++j) {
-                // the wave leaves the batch once all its pixels are done,
-                // tested every 16 entries (a done pixel's slot costs only
-                // its skip; a test per entry costs more than it saves)
-                if ((j & 15) == 0) {
-                    active = false;
-#pragma unroll
-                    for (int i = 0; i < PPT; ++i) active |= stopk[i] < 0;
-                    if (!__any(active)) break;
-                }
+            if (!__any(active)) break;
+            const int j1 = min(j0 + 16, bt.M);
+            int j = j0;
+            do {
                 const float4 A = L.E[3 * j], B = L.E[3 * j + 1], Cc = L.E[3 * j + 2];
                 const int k = __float_as_int(B.w);  // index in the tile's full list
                 float isum = 0.f, imax = 0.f;
 #pragma unroll
                 for (int i = 0; i < PPT; ++i) {
                     if (stopk[i] >= 0) continue;
-                    if (STATS) ++nev[i];
                     Eval e;
                     if (!eval_entry(A, B, px[i], py[i], ek, e)) continue;
                     const float ma = B.z * e.alpha;
@@ -1425,6 +1457,7 @@ __global__ void __launch_bounds__(TW * TH / PPT, PPT >= 4 ? 5 : 7) hybrid_fwd_ke
                     const bool stop = test < st.t_min;
                     stopk[i] = stop ? k : stopk[i];
                     asm volatile("" : "+v"(stopk[i]));  // keeps the select here
+                    if (STATS) nev[i] = staged + j + 1;  // the last entry that passed the cuts
                     if (stop) continue;
                     const float wgt = ma * T[i];
                     C0[i] += wgt * Cc.x;
@@ -1450,65 +1483,61 @@ __global__ void __launch_bounds__(TW * TH / PPT, PPT >= 4 ? 5 : 7) hybrid_fwd_ke
                         atomicMax(imp_max + g, __float_as_uint(wm));
                     }
                 }
-            }
-            active = false;
+            } while (++j < j1);
+        }
+        active = false;
 #pragma unroll
-            for (int i = 0; i < PPT; ++i) active |= stopk[i] < 0;
-            if (hl.stg) {
-                if (t == 0) {
-                    const uint32_t off = (uint64_t)my_off + (uint64_t)bt.M <= hl.stg_cap ? my_off : 0xffffffffu;
-                    L.wsum[8] = off;
-                    hl.cur_stg[hl.cur_off[tile] + b] = make_uint2(off, (uint32_t)bt.M);
-                }
-                __syncthreads();
-                const uint32_t off = L.wsum[8];
-                if (off != 0xffffffffu) {
-                    for (int p = t; p < bt.M; p += NT) {
-                        const uint32_t jj = __float_as_uint(L.E[3 * p + 1].w) - (uint32_t)m;
-                        hl.stg[off + p] = make_uint2(L.m[jj], jj);
-                    }
+        for (int i = 0; i < PPT; ++i) active |= stopk[i] < 0;
+        if (hl.stg) {
+            __syncthreads();
+            const uint32_t off = L.wsum[STG_OFF];
+            if (off != 0xffffffffu) {
+                for (int p = t; p < bt.M; p += NT) {
+                    const uint32_t jj = __float_as_uint(L.E[3 * p + 1].w) - (uint32_t)m;
+                    hl.stg[off + p] = make_uint2(L.m[jj], jj);
                 }
             }
-            i1 += bt.nX;
-            i2 += bt.nYraw;
-            m += bt.Mfull;
-            ++b;
-            __syncthreads();  // the next batch overwrites the LDS
         }
-        if (t == 0) hl.nbatch[tile] = (uint32_t)b;
-        if (hl.drec_clear) {
-            // the backward's FP64 accumulator of per-record gradients is
-            // cleared here, one slice per tile: this kernel is bound by VALU
-            // issue and leaves HBM bandwidth idle, the projection backward
-            // (HBM-bound) then only reads the rows
-            const uint64_t per = (hl.drec_clear_n2 + views.total_tiles - 1) / views.total_tiles;
-            const uint64_t q0 = (uint64_t)tile * per;
-            const uint64_t q1 = min(q0 + per, hl.drec_clear_n2);
-            double2* z = reinterpret_cast<double2*>(hl.drec_clear);
-            for (uint64_t q = q0 + (uint64_t)t; q < q1; q += NT) z[q] = make_double2(0.0, 0.0);
-        }
+        i1 += bt.nX;
+        i2 += bt.nYraw;
+        m += bt.Mfull;
+        if (STATS) staged += bt.M;
+        ++b;
+        __syncthreads();  // the next batch overwrites the LDS
+    }
+    opaque(t);
+    if (t == 0) hl.nbatch[tile] = (uint32_t)b;
+    if (hl.drec_clear) {
+        // the backward's FP64 accumulator of per-record gradients is
+        // cleared here, one slice per tile: this kernel is bound by VALU
+        // issue and leaves HBM bandwidth idle, the projection backward
+        // (HBM-bound) then only reads the rows
+        const uint64_t per = (hl.drec_clear_n2 + views.total_tiles - 1) / views.total_tiles;
+        const uint64_t q0 = (uint64_t)tile * per;
+        const uint64_t q1 = min(q0 + per, hl.drec_clear_n2);
+        double2* z = reinterpret_cast<double2*>(hl.drec_clear);
+        for (uint64_t q = q0 + (uint64_t)t; q < q1; q += NT) z[q] = make_double2(0.0, 0.0);
+    }
 #pragma unroll
-        for (int i = 0; i < PPT; ++i) {
-            if (!inside[i]) continue;
-            int x, y;
-            pixel_of<TW, PPT>(t, i, tg, x, y);
-            const int64_t pv = (int64_t)cam.width * cam.height;
-            const int64_t loc = (int64_t)y * cam.width + x;
-            float* im = images + 3 * (int64_t)cam.px_off;
-            im[loc] = C0[i] + T[i] * st.bg[0];
-            im[pv + loc] = C1[i] + T[i] * st.bg[1];
-            im[2 * pv + loc] = C2[i] + T[i] * st.bg[2];
-            const int64_t p = (int64_t)cam.px_off + loc;
-            t_final[p] = T[i];
-            last_out[p] = last[i];
-            // a pixel that never stopped saw the whole merged list (m entries);
-            // entries it evaluated are those of the list that can reach the tile
-            if (STATS) {
-                stats_out[p] = make_int4(stopk[i] >= 0 ? stopk[i] + 1 : m, nblend[i], nmasked[i], last[i] + 1);
-                eval_out[p] = make_int4(nev[i], nev_last[i], 0, 0);
-            }
+    for (int i = 0; i < PPT; ++i) {
+        int x, y;
+        pixel_of<TW, PPT>(t, i, tg, x, y);
+        if (x >= cam.width || y >= cam.height) continue;
+        const int64_t pv = (int64_t)cam.width * cam.height;
+        const int64_t loc = (int64_t)y * cam.width + x;
+        float* im = images + 3 * (int64_t)cam.px_off;
+        im[loc] = C0[i] + T[i] * st.bg[0];
+        im[pv + loc] = C1[i] + T[i] * st.bg[1];
+        im[2 * pv + loc] = C2[i] + T[i] * st.bg[2];
+        const int64_t p = (int64_t)cam.px_off + loc;
+        t_final[p] = T[i];
+        last_out[p] = last[i];
+        // a pixel that never stopped saw the whole merged list (m entries);
+        // entries it evaluated are those of the list that can reach the tile
+        if (STATS) {
+            stats_out[p] = make_int4(stopk[i] >= 0 ? stopk[i] + 1 : m, nblend[i], nmasked[i], last[i] + 1);
+            eval_out[p] = make_int4(stopk[i] >= 0 ? nev[i] : staged, nev_last[i], 0, 0);
         }
-        if (!queue) break;
     }
 }
 
@@ -1516,10 +1545,9 @@ template <int TW, int TH, int PPT>
 __global__ void __launch_bounds__(TW * TH / PPT, 5) hybrid_bwd_kernel(
     const float4* __restrict__ srec, HybridLists hl, ViewSet views, DevSettings st, const float* __restrict__ t_final,
     const int32_t* __restrict__ last_in, const float* __restrict__ dl_dimages, int64_t n, double* __restrict__ d_rec,
-    double* __restrict__ d_masks, uint32_t* __restrict__ queue) {
+    double* __restrict__ d_masks) {
     constexpr int NT = TW * TH / PPT;
     extern __shared__ __align__(16) char smem[];
-    __shared__ uint32_t s_tile;
     __shared__ int s_top;
     const int t = threadIdx.x;
     const int lane = lane_id();
@@ -1534,151 +1562,146 @@ __global__ void __launch_bounds__(TW * TH / PPT, 5) hybrid_bwd_kernel(
     const int qi = swap10_quantity(lane);
     const float qscale = (qi == 2 || qi == 4) ? 0.5f * QSCALE : 1.f;
     if (*hl.cur_need > hl.cur_cap) return;  // the forward reported it
-    for (;;) {
-        const uint32_t q = next_tile(queue, &s_tile, blockIdx.x);
-        if (q >= views.total_tiles) break;
-        const uint32_t tile = hl.order ? hl.order[q] : q;
-        const TileGeom tg = tile_geom(views, tile, TW, TH);
-        const DevView& cam = views.v[tg.vi];
-        const int64_t rec_base = (int64_t)tg.vi * n;
-        // s = w . b: the loss weights of the pixel dotted with the colour
-        // composited behind the current entry (scaled by its transmittance)
-        float px[PPT], py[PPT], T[PPT], Tf[PPT], w0[PPT], w1[PPT], w2[PPT], wbg[PPT], sb[PPT];
-        int lastk[PPT];
-        int mylast = -1;
-        const int64_t pv = (int64_t)cam.width * cam.height;
+    const uint32_t tile = uniform(hl.order ? hl.order[blockIdx.x] : blockIdx.x);
+    const TileGeom tg = tile_geom(views, tile, TW, TH);
+    const DevView& cam = views.v[tg.vi];
+    const int64_t rec_base = (int64_t)tg.vi * n;
+    // s = w . b: the loss weights of the pixel dotted with the colour
+    // composited behind the current entry (scaled by its transmittance)
+    float px[PPT], py[PPT], T[PPT], Tf[PPT], w0[PPT], w1[PPT], w2[PPT], wbg[PPT], sb[PPT];
+    int lastk[PPT];
+    int mylast = -1;
+    const int64_t pv = (int64_t)cam.width * cam.height;
 #pragma unroll
-        for (int i = 0; i < PPT; ++i) {
-            int x, y;
-            pixel_of<TW, PPT>(t, i, tg, x, y);
-            px[i] = (float)x + 0.5f;
-            py[i] = (float)y + 0.5f;
-            sb[i] = 0.f;
-            if (x < cam.width && y < cam.height) {
-                const int64_t loc = (int64_t)y * cam.width + x;
-                const int64_t p = (int64_t)cam.px_off + loc;
-                const float* dl = dl_dimages + 3 * (int64_t)cam.px_off;
-                lastk[i] = last_in[p];
-                Tf[i] = t_final[p];
-                w0[i] = dl[loc];
-                w1[i] = dl[pv + loc];
-                w2[i] = dl[2 * pv + loc];
-            } else {
-                lastk[i] = -1;
-                Tf[i] = 1.f;
-                w0[i] = w1[i] = w2[i] = 0.f;
-            }
-            T[i] = Tf[i];
-            wbg[i] = w0[i] * bg0 + w1[i] * bg1 + w2[i] * bg2;
-            mylast = max(mylast, lastk[i]);
+    for (int i = 0; i < PPT; ++i) {
+        int x, y;
+        pixel_of<TW, PPT>(t, i, tg, x, y);
+        px[i] = (float)x + 0.5f;
+        py[i] = (float)y + 0.5f;
+        sb[i] = 0.f;
+        if (x < cam.width && y < cam.height) {
+            const int64_t loc = (int64_t)y * cam.width + x;
+            const int64_t p = (int64_t)cam.px_off + loc;
+            const float* dl = dl_dimages + 3 * (int64_t)cam.px_off;
+            lastk[i] = last_in[p];
+            Tf[i] = t_final[p];
+            w0[i] = dl[loc];
+            w1[i] = dl[pv + loc];
+            w2[i] = dl[2 * pv + loc];
+        } else {
+            lastk[i] = -1;
+            Tf[i] = 1.f;
+            w0[i] = w1[i] = w2[i] = 0.f;
         }
-        for (int off = 32; off > 0; off >>= 1) mylast = max(mylast, __shfl_xor(mylast, off));
-        if (t == 0) s_top = -1;
-        __syncthreads();
-        if (lane == 0) atomicMax(&s_top, mylast);
-        __syncthreads();
-        const int top = s_top;
-        const uint4* cur = hl.cur + hl.cur_off[tile];
-        const int tcx = tg.tx0 / TW, tcy = tg.ty0 / TH;
-        const uint2 r1 = hl.ranges[tile];
-        const uint2 r2 = hl.ranges[region_of_tile(tcx, tcy, cam, views)];
-        const TileBox tb{(float)tg.tx0 + 0.5f, (float)min(tg.tx0 + TW, cam.width) - 0.5f, (float)tg.ty0 + 0.5f,
-                         (float)min(tg.ty0 + TH, cam.height) - 0.5f};
-        // the batch holding the largest last-blended entry, then backwards
-        int bstar = -1;
-        if (top >= 0) {
-            const int nb = (int)hl.nbatch[tile];
-            for (int b = 0; b < nb; ++b)
-                if ((int)cur[b].z <= top) bstar = b;
-        }
-        const uint2* cstg = hl.stg ? hl.cur_stg + hl.cur_off[tile] : nullptr;
-        // per-entry partial sums of this lane's pixels; zero between entries
-        // (reset after each reduction), so no per-entry initialisation
-        float gu = 0.f, gv = 0.f, ga = 0.f, gb = 0.f, gc = 0.f, go = 0.f, gr = 0.f, gg = 0.f, gbl = 0.f, gm = 0.f;
-        for (int b = bstar; b >= 0; --b) {
-            const uint4 c = cur[b];
-            const int m = (int)c.z;
-            const uint2 cs = cstg ? cstg[b] : make_uint2(0xffffffffu, 0u);
-            int Mb;
-            if (cs.x != 0xffffffffu) {
-                // the entries the forward staged for this batch
-                Mb = (int)cs.y;
-                for (int p = t; p < Mb; p += NT) {
-                    const uint2 e = hl.stg[cs.x + p];
-                    const size_t i = e.x;
-                    float4 B = stage_b(srec[3 * i + 1]);
-                    B.w = __int_as_float(m + (int)e.y);
-                    L.E[3 * p] = stage_a(srec[3 * i]);
-                    L.E[3 * p + 1] = B;
-                    L.E[3 * p + 2] = srec[3 * i + 2];
-                }
-                __syncthreads();
-            } else {
-                Mb = merge_batch<false>(L, hl.vals, srec, (int)c.x, (int)r1.y, (int)c.y, (int)r2.y, batch, tcx,
-                                            tcy, tb, cam, st, m).M;
+        T[i] = Tf[i];
+        wbg[i] = w0[i] * bg0 + w1[i] * bg1 + w2[i] * bg2;
+        mylast = max(mylast, lastk[i]);
+    }
+    for (int off = 32; off > 0; off >>= 1) mylast = max(mylast, __shfl_xor(mylast, off));
+    if (t == 0) s_top = -1;
+    __syncthreads();
+    if (lane == 0) atomicMax(&s_top, mylast);
+    __syncthreads();
+    const int top = uniform(s_top);
+    const uint4* cur = hl.cur + uniform(hl.cur_off[tile]);
+    const int tcx = tg.tx0 / TW, tcy = tg.ty0 / TH;
+    const uint2 r1 = uniform(hl.ranges[tile]);
+    const uint2 r2 = uniform(hl.ranges[region_of_tile(tcx, tcy, cam, views)]);
+    const TileBox tb{(float)tg.tx0 + 0.5f, (float)min(tg.tx0 + TW, cam.width) - 0.5f, (float)tg.ty0 + 0.5f,
+                     (float)min(tg.ty0 + TH, cam.height) - 0.5f};
+    // the batch holding the largest last-blended entry, then backwards
+    int bstar = -1;
+    if (top >= 0) {
+        const int nb = (int)hl.nbatch[tile];
+        for (int b = 0; b < nb; ++b)
+            if ((int)cur[b].z <= top) bstar = b;
+    }
+    const uint2* cstg = hl.stg ? hl.cur_stg + uniform(hl.cur_off[tile]) : nullptr;
+    // per-entry partial sums of this lane's pixels; zero between entries
+    // (reset after each reduction), so no per-entry initialisation
+    float gu = 0.f, gv = 0.f, ga = 0.f, gb = 0.f, gc = 0.f, go = 0.f, gr = 0.f, gg = 0.f, gbl = 0.f, gm = 0.f;
+    for (int b = bstar; b >= 0; --b) {
+        const uint4 c = cur[b];
+        const int m = (int)c.z;
+        const uint2 cs = cstg ? cstg[b] : make_uint2(0xffffffffu, 0u);
+        int Mb;
+        if (cs.x != 0xffffffffu) {
+            // the entries the forward staged for this batch
+            Mb = (int)cs.y;
+            for (int p = t; p < Mb; p += NT) {
+                const uint2 e = hl.stg[cs.x + p];
+                const size_t i = e.x;
+                float4 B = stage_b(srec[3 * i + 1]);
+                B.w = __int_as_float(m + (int)e.y);
+                L.E[3 * p] = stage_a(srec[3 * i]);
+                L.E[3 * p + 1] = B;
+                L.E[3 * p + 2] = srec[3 * i + 2];
             }
-            for (int j = Mb - 1; j >= 0; --j) {
-                const float4 A = L.E[3 * j], B = L.E[3 * j + 1], Cc = L.E[3 * j + 2];
-                const int k = __float_as_int(B.w);  // index in the tile's full list
-                if (k > top) continue;                  // uniform: past every pixel's last entry
-                const float M = B.z;
-                const float okq = B.y * QSCALE_NINV;
-                bool any = false;
+            __syncthreads();
+        } else {
+            Mb = merge_batch<false>(L, hl.vals, srec, (int)c.x, (int)r1.y, (int)c.y, (int)r2.y, batch, tcx,
+                                        tcy, tb, cam, st, m).M;
+        }
+        for (int j = Mb - 1; j >= 0; --j) {
+            const float4 A = L.E[3 * j], B = L.E[3 * j + 1], Cc = L.E[3 * j + 2];
+            const int k = __float_as_int(B.w);  // index in the tile's full list
+            if (k > top) continue;                  // uniform: past every pixel's last entry
+            const float M = B.z;
+            const float okq = B.y * QSCALE_NINV;
+            bool any = false;
 #pragma unroll
-                for (int i = 0; i < PPT; ++i) {
-                    if (k > lastk[i]) continue;
-                    Eval e;
-                    if (!eval_entry(A, B, px[i], py[i], ek, e)) continue;
-                    any = true;
-                    const float ma = M * e.alpha;
-                    const float one_m = 1.f - ma;
-                    const float inv = __builtin_amdgcn_rcpf(one_m);
-                    const float Ti = T[i] * inv;
-                    const float d = fmaf(w0[i], Cc.x, fmaf(w1[i], Cc.y, w2[i] * Cc.z)) - sb[i];
-                    const float X = Ti * d - Tf[i] * inv * wbg[i];
-                    gm += e.alpha * X;
-                    const float wt = ma * Ti;
-                    gr += wt * w0[i];
-                    gg += wt * w1[i];
-                    gbl += wt * w2[i];
-                    if (e.oG <= ek.amax) {
-                        // dL/dalpha = M X, dL/dQ = -o G M X / 2; with a' = QSCALE a,
-                        // gamma' = QSCALE gamma: dL/du = kq a' t, dL/dv =
-                        // kq (beta a' t + gamma' dy), dL/dbeta = kq a' t dy, and
-                        // dL/da, dL/dgamma are QSCALE / 2 times the sums of kq t^2,
-                        // kq dy^2, where kq = 2 dL/dQ / QSCALE
-                        const float GdA = e.G * (M * X);
-                        go += GdA;
-                        const float kq = GdA * okq;
-                        const float kapt = kq * e.apt;
-                        gu += kapt;
-                        gv += kq * fmaf(A.w, e.apt, e.gdy);
-                        gb += kapt * e.dy;
-                        ga += (kq * e.t) * e.t;
-                        gc += (kq * e.dy) * e.dy;
-                    }
-                    sb[i] = fmaf(ma, d, sb[i]);
-                    T[i] = Ti;
+            for (int i = 0; i < PPT; ++i) {
+                if (k > lastk[i]) continue;
+                Eval e;
+                if (!eval_entry(A, B, px[i], py[i], ek, e)) continue;
+                any = true;
+                const float ma = M * e.alpha;
+                const float one_m = 1.f - ma;
+                const float inv = __builtin_amdgcn_rcpf(one_m);
+                const float Ti = T[i] * inv;
+                const float d = fmaf(w0[i], Cc.x, fmaf(w1[i], Cc.y, w2[i] * Cc.z)) - sb[i];
+                const float X = Ti * d - Tf[i] * inv * wbg[i];
+                gm += e.alpha * X;
+                const float wt = ma * Ti;
+                gr += wt * w0[i];
+                gg += wt * w1[i];
+                gbl += wt * w2[i];
+                if (e.oG <= ek.amax) {
+                    // dL/dalpha = M X, dL/dQ = -o G M X / 2; with a' = QSCALE a,
+                    // gamma' = QSCALE gamma: dL/du = kq a' t, dL/dv =
+                    // kq (beta a' t + gamma' dy), dL/dbeta = kq a' t dy, and
+                    // dL/da, dL/dgamma are QSCALE / 2 times the sums of kq t^2,
+                    // kq dy^2, where kq = 2 dL/dQ / QSCALE
+                    const float GdA = e.G * (M * X);
+                    go += GdA;
+                    const float kq = GdA * okq;
+                    const float kapt = kq * e.apt;
+                    gu += kapt;
+                    gv += kq * fmaf(A.w, e.apt, e.gdy);
+                    gb += kapt * e.dy;
+                    ga += (kq * e.t) * e.t;
+                    gc += (kq * e.dy) * e.dy;
                 }
-                if (__any(any)) {
-                    const uint32_t r = __float_as_uint(Cc.w);
-                    const int64_t g = (int64_t)r - rec_base;
-                    if (M != 0.f) {
-                        // ten lanes receive the wave totals, quantity qi each
-                        const float v[10] = {gu, gv, ga, gb, gc, go, gr, gg, gbl, gm};
-                        const float x = wave_sum_swap10(v, lane) * qscale;
-                        if ((unsigned)qi < (unsigned)DREC) atomicAdd(d_rec + (size_t)r * DREC + qi, (double)x);
-                        else if (qi == DREC) atomicAdd(d_masks + g, (double)x);
-                    } else {
-                        const float sm = wave_sum(gm);
-                        if (lane == 0) atomicAdd(d_masks + g, (double)sm);
-                    }
-                    gu = gv = ga = gb = gc = go = gr = gg = gbl = gm = 0.f;
-                }
+                sb[i] = fmaf(ma, d, sb[i]);
+                T[i] = Ti;
             }
-            __syncthreads();  // the next batch overwrites the LDS
+            if (__any(any)) {
+                const uint32_t r = __float_as_uint(Cc.w);
+                const int64_t g = (int64_t)r - rec_base;
+                if (M != 0.f) {
+                    // ten lanes receive the wave totals, quantity qi each
+                    const float v[10] = {gu, gv, ga, gb, gc, go, gr, gg, gbl, gm};
+                    const float x = wave_sum_swap10(v, lane) * qscale;
+                    if ((unsigned)qi < (unsigned)DREC) atomicAdd(d_rec + (size_t)r * DREC + qi, (double)x);
+                    else if (qi == DREC) atomicAdd(d_masks + g, (double)x);
+                } else {
+                    const float sm = wave_sum(gm);
+                    if (lane == 0) atomicAdd(d_masks + g, (double)sm);
+                }
+                gu = gv = ga = gb = gc = go = gr = gg = gbl = gm = 0.f;
+            }
         }
-        if (!queue) break;
+        __syncthreads();  // the next batch overwrites the LDS
     }
 }
 
@@ -1701,7 +1724,7 @@ __global__ void __launch_bounds__(TW * TH / PPT, 5) hybrid_bwd_kernel(
 // thread: 200 k small splats at 800x800, forward 304 -> 80 us, backward 449 ->
 // 112 us; 4096 splats at 128x128, 216 -> 33 and 336 -> 44 us.  Bound by VALU
 // issue where a few parts hold long lists.  Launches are plain (one workgroup
-// per part, the tiles in queue order): a loop over a device queue keeps the
+// per part, the tiles in launch order): a loop over a device queue keeps the
 // kernel arguments live and spills (forward 97 -> 80 us without it).
 constexpr int FINE_NT = 256;
 constexpr int FINE_BATCH = 256;  // entries per batch: one per thread
@@ -1749,7 +1772,7 @@ constexpr size_t fine_lds_bytes(bool bwd) {
     return lds_bytes(FINE_BATCH) + (FINE_NT / 64) * FINE_LIST * 2 + (bwd ? FINE_BATCH * 40 : 0);
 }
 
-// Part q of a launch over the 8x8 parts of every tile, tiles in queue order.
+// Part q of a launch over the 8x8 parts of every tile, tiles in launch order.
 struct FinePart {
     uint32_t tile;
     TileGeom tg;
@@ -1874,13 +1897,13 @@ __global__ void __launch_bounds__(FINE_NT, 6) hybrid_fwd_fine_kernel(
     int last = -1, stopk = 0x7fffffff, nblend = 0, nmasked = 0, nev = 0x7fffffff, nev_last = 0, staged = 0;
     bool run = inside;
     const int tcx = tg.tx0 / st.tile_w, tcy = tg.ty0 / st.tile_h;
-    const uint2 r1 = hl.ranges[tile];
-    const uint2 r2 = hl.ranges[region_of_tile(tcx, tcy, cam, views)];
+    const uint2 r1 = uniform(hl.ranges[tile]);
+    const uint2 r2 = uniform(hl.ranges[region_of_tile(tcx, tcy, cam, views)]);
     const int e1 = (int)r1.y, e2 = (int)r2.y;
     int i1 = (int)r1.x, i2 = (int)r2.x, m = 0, b = 0;
     const TileBox tb{(float)tg.tx0 + 0.5f, (float)min(tg.tx0 + st.tile_w, cam.width) - 0.5f,
                      (float)tg.ty0 + 0.5f, (float)min(tg.ty0 + st.tile_h, cam.height) - 0.5f};
-    uint4* cur = hl.cur + hl.cur_off[tile];
+    uint4* cur = hl.cur + uniform(hl.cur_off[tile]);
     FineStream fs;
     fs.have = false;
     while (i1 < e1 || i2 < e2) {
@@ -2089,11 +2112,11 @@ __global__ void __launch_bounds__(FINE_NT, 5) hybrid_bwd_fine_kernel(
     __syncthreads();
     if (lane == 0) atomicMax(&s_top, wlast);
     __syncthreads();
-    const int top = s_top;
-    const uint4* cur = hl.cur + hl.cur_off[tile];
+    const int top = uniform(s_top);
+    const uint4* cur = hl.cur + uniform(hl.cur_off[tile]);
     const int tcx = tg.tx0 / st.tile_w, tcy = tg.ty0 / st.tile_h;
-    const uint2 r1 = hl.ranges[tile];
-    const uint2 r2 = hl.ranges[region_of_tile(tcx, tcy, cam, views)];
+    const uint2 r1 = uniform(hl.ranges[tile]);
+    const uint2 r2 = uniform(hl.ranges[region_of_tile(tcx, tcy, cam, views)]);
     const TileBox tb{(float)tg.tx0 + 0.5f, (float)min(tg.tx0 + st.tile_w, cam.width) - 0.5f,
                      (float)tg.ty0 + 0.5f, (float)min(tg.ty0 + st.tile_h, cam.height) - 0.5f};
     // the batch holding the largest last-blended entry (the batches'
@@ -2207,44 +2230,28 @@ __global__ void __launch_bounds__(FINE_NT, 5) hybrid_bwd_fine_kernel(
     }
 }
 
-// Persistent grid per batch depth (index log2(batch / 32)).
-template <typename Kernel>
-int cached_grid(int (&cache)[4], Kernel k, int block, int num_cus, int batch, size_t lds) {
-    const int idx = batch <= 32 ? 0 : batch <= 64 ? 1 : batch <= 128 ? 2 : 3;
-    if (!cache[idx]) cache[idx] = persistent_grid(k, block, num_cus, lds);
-    return cache[idx];
-}
-
 template <int TW, int TH, int PPT, bool STATS, bool IMP>
-void hybrid_fwd_s(hipStream_t s, int num_cus, const float* srec, const HybridLists& hl, const ViewSet& views,
+void hybrid_fwd_s(hipStream_t s, const float* srec, const HybridLists& hl, const ViewSet& views,
                   const DevSettings& st, float* images, float* t_final, int32_t* last, int32_t* stats,
-                  int32_t* evals, uint32_t* queue, int64_t n, double* imp_sum, uint32_t* imp_max) {
-    int grid = (int)views.total_tiles;
-    if (queue) {
-        static int cache[4] = {0, 0, 0, 0};
-        grid = min(cached_grid(cache, hybrid_fwd_kernel<TW, TH, PPT, STATS, IMP>, TW * TH / PPT, num_cus,
-                               st.batch, lds_bytes(st.batch)),
-                   grid);
-    }
-    hipLaunchKernelGGL((hybrid_fwd_kernel<TW, TH, PPT, STATS, IMP>), dim3(grid), dim3(TW * TH / PPT),
+                  int32_t* evals, int64_t n, double* imp_sum, uint32_t* imp_max) {
+    hipLaunchKernelGGL((hybrid_fwd_kernel<TW, TH, PPT, STATS, IMP>), dim3(views.total_tiles), dim3(TW * TH / PPT),
                        lds_bytes(st.batch), s, reinterpret_cast<const float4*>(srec), hl, views, st, images, t_final,
-                       last, reinterpret_cast<int4*>(stats), reinterpret_cast<int4*>(evals), queue, n, imp_sum,
-                       imp_max);
+                       last, reinterpret_cast<int4*>(stats), reinterpret_cast<int4*>(evals), n, imp_sum, imp_max);
 }
 
 template <int TW, int TH, int PPT>
-void hybrid_fwd_t(hipStream_t s, int num_cus, const float* srec, const HybridLists& hl, const ViewSet& views,
+void hybrid_fwd_t(hipStream_t s, const float* srec, const HybridLists& hl, const ViewSet& views,
                   const DevSettings& st, float* images, float* t_final, int32_t* last, int32_t* stats,
-                  int32_t* evals, uint32_t* queue, int64_t n, double* imp_sum, uint32_t* imp_max) {
+                  int32_t* evals, int64_t n, double* imp_sum, uint32_t* imp_max) {
     if (imp_sum && imp_max)
-        hybrid_fwd_s<TW, TH, PPT, false, true>(s, num_cus, srec, hl, views, st, images, t_final, last, nullptr,
-                                               nullptr, queue, n, imp_sum, imp_max);
+        hybrid_fwd_s<TW, TH, PPT, false, true>(s, srec, hl, views, st, images, t_final, last, nullptr,
+                                               nullptr, n, imp_sum, imp_max);
     else if (stats && evals)
-        hybrid_fwd_s<TW, TH, PPT, true, false>(s, num_cus, srec, hl, views, st, images, t_final, last, stats, evals,
-                                               queue, n, nullptr, nullptr);
+        hybrid_fwd_s<TW, TH, PPT, true, false>(s, srec, hl, views, st, images, t_final, last, stats, evals,
+                                               n, nullptr, nullptr);
     else
-        hybrid_fwd_s<TW, TH, PPT, false, false>(s, num_cus, srec, hl, views, st, images, t_final, last, nullptr,
-                                                nullptr, queue, n, nullptr, nullptr);
+        hybrid_fwd_s<TW, TH, PPT, false, false>(s, srec, hl, views, st, images, t_final, last, nullptr,
+                                                nullptr, n, nullptr, nullptr);
 }
 
 template <bool STATS, bool IMP>
@@ -2268,19 +2275,11 @@ void hybrid_bwd_fine(hipStream_t s, const float* srec, const HybridLists& hl, co
 }
 
 template <int TW, int TH, int PPT>
-void hybrid_bwd_t(hipStream_t s, int num_cus, const float* srec, const HybridLists& hl, const ViewSet& views,
+void hybrid_bwd_t(hipStream_t s, const float* srec, const HybridLists& hl, const ViewSet& views,
                   const DevSettings& st, const float* t_final, const int32_t* last, const float* dl, int64_t n,
-                  double* d_rec, double* d_masks, uint32_t* queue) {
-    int grid = (int)views.total_tiles;
-    if (queue) {
-        static int cache[4] = {0, 0, 0, 0};
-        grid = min(cached_grid(cache, hybrid_bwd_kernel<TW, TH, PPT>, TW * TH / PPT, num_cus, st.batch,
-                               lds_bytes(st.batch)),
-                   grid);
-    }
-    hipLaunchKernelGGL((hybrid_bwd_kernel<TW, TH, PPT>), dim3(grid), dim3(TW * TH / PPT), lds_bytes(st.batch), s,
-                       reinterpret_cast<const float4*>(srec), hl, views, st, t_final, last, dl, n, d_rec, d_masks,
-                       queue);
+                  double* d_rec, double* d_masks) {
+    hipLaunchKernelGGL((hybrid_bwd_kernel<TW, TH, PPT>), dim3(views.total_tiles), dim3(TW * TH / PPT), lds_bytes(st.batch), s,
+                       reinterpret_cast<const float4*>(srec), hl, views, st, t_final, last, dl, n, d_rec, d_masks);
 }
 
 #define MGS_HYBRID_SHAPES(X) \
@@ -2321,7 +2320,7 @@ unsigned blocks_of(int64_t n) { return (unsigned)((n + 255) / 256); }
 // Which compositing kernels a forward (and its backward) takes: those for
 // small splats or the tile-wide ones.  Measured, tile-wide / small-splat time
 // of forward and backward together (16x16 tiles; the library's default
-// settings, and batches of 128 with 2 and 4 pixels per thread, persistent):
+// settings, and batches of 128 with 2 and 4 pixels per thread):
 //   up to 900 tiles, splats of every size: 1.26 (screen-filling scenes of 800
 //   tiles) to 7.4 (64 tiles); 950 tiles, screen-filling: 0.90 and 1.23
 //   2,500 tiles, share of large splats' tiles 0.07 / 0.72 / 1.0: 4.1, 4.9 /
@@ -2338,6 +2337,8 @@ bool fine_needs_sizes(int64_t pixels) { return pixels > FINE_PIXELS_ANY && pixel
 bool use_fine(int64_t pixels, uint64_t tiles_all, uint64_t tiles_large) {
     return pixels <= FINE_PIXELS_ANY || (pixels <= FINE_PIXELS_SMALL && 4 * tiles_large <= 3 * tiles_all);
 }
+
+uint64_t staged_first(uint32_t tiles) { return (uint64_t)tiles * STG_FIRST; }
 
 bool composite_config_supported(const CompositeConfig& c) {
 #define MGS_MATCH(A, B, P) \
@@ -2434,7 +2435,7 @@ void launch_tile_setup(hipStream_t stream, const uint32_t* ranges, const ViewSet
 
 void launch_hybrid_fwd(hipStream_t stream, const CompositeConfig& cfg, const float* srec, const HybridBuffers& bufs,
                        const ViewSet& views, const DevSettings& st, float* images, float* t_final, int32_t* last,
-                       int32_t* stats, int32_t* evals, uint32_t* queue, int num_cus, int64_t n, double* imp_sum,
+                       int32_t* stats, int32_t* evals, int64_t n, double* imp_sum,
                        uint32_t* imp_max) {
     if (views.total_tiles == 0) return;
     const HybridLists hl = make_lists(bufs);
@@ -2450,11 +2451,11 @@ void launch_hybrid_fwd(hipStream_t stream, const CompositeConfig& cfg, const flo
                                           nullptr, nullptr);
         return;
     }
-#define MGS_HFWD(A, B, P)                                                                                          \
-    if (cfg.tile_w == A && cfg.tile_h == B && cfg.ppt == P) {                                                      \
-        hybrid_fwd_t<A, B, P>(stream, num_cus, srec, hl, views, st, images, t_final, last, stats, evals, queue, n, \
-                              imp_sum, imp_max);                                                                   \
-        return;                                                                                                    \
+#define MGS_HFWD(A, B, P)                                                                               \
+    if (cfg.tile_w == A && cfg.tile_h == B && cfg.ppt == P) {                                           \
+        hybrid_fwd_t<A, B, P>(stream, srec, hl, views, st, images, t_final, last, stats, evals, n,      \
+                              imp_sum, imp_max);                                                        \
+        return;                                                                                         \
     }
     MGS_HYBRID_SHAPES(MGS_HFWD)
 #undef MGS_HFWD
@@ -2462,19 +2463,17 @@ void launch_hybrid_fwd(hipStream_t stream, const CompositeConfig& cfg, const flo
 
 void launch_hybrid_bwd(hipStream_t stream, const CompositeConfig& cfg, const float* srec, const HybridBuffers& bufs,
                        const ViewSet& views, const DevSettings& st, const float* t_final, const int32_t* last,
-                       const float* dl_dimages, int64_t n, double* d_rec, double* d_masks, uint32_t* queue,
-                       int num_cus) {
+                       const float* dl_dimages, int64_t n, double* d_rec, double* d_masks) {
     if (views.total_tiles == 0) return;
     const HybridLists hl = make_lists(bufs);
     if (bufs.fine) {
         hybrid_bwd_fine(stream, srec, hl, views, st, t_final, last, dl_dimages, n, d_rec, d_masks);
         return;
     }
-#define MGS_HBWD(A, B, P)                                                                                       \
-    if (cfg.tile_w == A && cfg.tile_h == B && cfg.ppt == P) {                                                   \
-        hybrid_bwd_t<A, B, P>(stream, num_cus, srec, hl, views, st, t_final, last, dl_dimages, n, d_rec, d_masks, \
-                              queue);                                                                           \
-        return;                                                                                                 \
+#define MGS_HBWD(A, B, P)                                                                               \
+    if (cfg.tile_w == A && cfg.tile_h == B && cfg.ppt == P) {                                           \
+        hybrid_bwd_t<A, B, P>(stream, srec, hl, views, st, t_final, last, dl_dimages, n, d_rec, d_masks); \
+        return;                                                                                         \
     }
     MGS_HYBRID_SHAPES(MGS_HBWD)
 #undef MGS_HBWD

@@ -106,6 +106,9 @@ struct CompositeConfig {
     int tile_w, tile_h, ppt;  // pixels per thread; threads per block = tile_w * tile_h / ppt
 };
 bool composite_config_supported(const CompositeConfig& c);
+// Entries of the staged list that a forward's workgroups hold without asking
+// for them (at most).
+uint64_t staged_first(uint32_t tiles);
 
 // hybrid binning: records in (view, depth, record) order are copied once
 // ("sorted records": radius in B.w, record id bits in C.w); narrow records
@@ -125,7 +128,7 @@ void launch_permute_classify(hipStream_t stream, const uint32_t* order, const ui
 // the classification; else 0) [3] = tiles of all footprints, [4] = of those
 // of large splats; host (optional, pinned memory the device can write)
 // receives for the host [0] = the two flag words, [1] = the entry total, [2] ..
-// [6] = wide_counts, [24] = *staged
+// [6] = wide_counts, [24] = staged[0] + staged[1]
 void launch_list_offsets(hipStream_t stream, uint32_t* part, int64_t R, uint64_t* total, uint64_t* wide_counts,
                          bool sizes, const uint32_t* flags, const uint32_t* staged, uint64_t* host);
 // The rule that picks the compositing kernels (pixels over all views; the two
@@ -137,7 +140,7 @@ void launch_duplicate_lists(hipStream_t stream, const float* srec, const uint32_
                             const uint64_t* tmask, uint32_t* part, int64_t R,
                             int64_t n, const ViewSet& views, const DevSettings& st, uint32_t* keys, uint32_t* vals,
                             int64_t capacity, uint32_t* flags, const FillSpan* fill, int fill_count);
-// Tile order of a persistent launch: the tiles by descending cost key
+// Launch order of the tiles: the tiles by descending cost key
 // (key[t] in 0..255, ties in any order), so that the most expensive start
 // first.  hist_cursor: [512] u32 of scratch (cleared here unless cleared).
 void launch_tile_order(hipStream_t stream, const uint32_t* key, uint32_t tiles, uint32_t* hist_cursor,
@@ -163,11 +166,11 @@ struct HybridBuffers {
     uint32_t* flags;             // device flags (capacity)
     uint32_t* cur_stg;           // [checkpoints, 2] staged-list offset (or ~0) and count
     uint32_t* stg;               // [stg_cap, 2] staged entries; null: the backward merges again
-    uint32_t* stg_count;         // device counter of staged entries (zeroed before the forward)
+    uint32_t* stg_count;         // [2], zeroed before the forward: entries of the staged list in use
     uint64_t stg_cap;
     double* drec_clear;          // optional: FP64 gradient accumulators (per record, then the masks') the forward clears
     uint64_t drec_clear_n2;      // their size in pairs of doubles
-    const uint32_t* order;       // optional [tiles]: the order in which a persistent launch takes the tiles
+    const uint32_t* order;       // optional [tiles]: tile of each workgroup
     bool fine;                   // the kernels for small splats (the same for a forward and its backward)
 };
 // stats [P, 4] (examined, blended, blended with mask 0, last + 1) and evals
@@ -177,13 +180,12 @@ struct HybridBuffers {
 // null: per-Gaussian sum and maximum of the blending weights M alpha T.
 void launch_hybrid_fwd(hipStream_t stream, const CompositeConfig& cfg, const float* srec, const HybridBuffers& bufs,
                        const ViewSet& views, const DevSettings& st, float* images, float* t_final, int32_t* last,
-                       int32_t* stats, int32_t* evals, uint32_t* queue, int num_cus, int64_t n = 0,
+                       int32_t* stats, int32_t* evals, int64_t n = 0,
                        double* imp_sum = nullptr, uint32_t* imp_max = nullptr);
 void launch_round_f64(hipStream_t stream, const double* in, float* out, int64_t n);
 void launch_hybrid_bwd(hipStream_t stream, const CompositeConfig& cfg, const float* srec, const HybridBuffers& bufs,
                        const ViewSet& views, const DevSettings& st, const float* t_final, const int32_t* last,
-                       const float* dl_dimages, int64_t n, double* d_rec, double* d_masks, uint32_t* queue,
-                       int num_cus);
+                       const float* dl_dimages, int64_t n, double* d_rec, double* d_masks);
 
 // masks, loss, optimiser
 size_t reduce_scratch_bytes(int64_t n);
