@@ -2321,16 +2321,17 @@ unsigned blocks_of(int64_t n) { return (unsigned)((n + 255) / 256); }
 // small splats or the tile-wide ones.  Measured, tile-wide / small-splat time
 // of forward and backward together (16x16 tiles; the library's default
 // settings, and batches of 128 with 2 and 4 pixels per thread):
-//   up to 900 tiles, splats of every size: 1.26 (screen-filling scenes of 800
-//   tiles) to 7.4 (64 tiles); 950 tiles, screen-filling: 0.90 and 1.23
-//   2,500 tiles, share of large splats' tiles 0.07 / 0.72 / 1.0: 4.1, 4.9 /
-//   3.7, 2.4 / 1.1, 1.6;  1,600 tiles of a screen-filling scene (0.94): 0.78,
-//   0.82;  10,000 tiles, 0.07 / 0.72 / 0.96: 1.9, 2.0 / 1.4, 1.7 / 0.7, 1.0
-//   20,000 tiles, 0.08 / 0.73: 1.05, 1.15 / 0.7, 1.0;  40,000 tiles: 0.6
-// So the line lies at 896 tiles, or at 12,288 tiles where splats larger than
+//   192 and 600 tiles, splats of every size: 0.97 (600 tiles of a scene of
+//   screen-filling splats) to 7.4;  960 tiles, screen-filling: 0.65 to 1.07
+//   1,750 tiles, share of large splats' tiles 0.07 / 0.72 / 0.94: 3.5, 3.6 /
+//   3.1, 3.0 / 0.6, 0.7;  3,300 tiles, 0.18 / 0.89 / 0.97: 2.0, 2.1 / 2.0, 2.4
+//   / 0.55, 0.42;  5,400 tiles, 0.13 / 0.84 / 0.96: 1.4, 1.4 / 1.4, 1.7 / 0.5,
+//   0.4;  8,800 tiles, 0.10 / 0.79: 0.96, 0.91 / 0.94, 1.15;  16,000 tiles,
+//   0.29: 0.6, 0.5
+// So the line lies at 640 tiles, or at 7,168 tiles where splats larger than
 // LARGE_RADIUS hold at most three quarters of the footprint tiles.  Tiles of
 // other sizes count by their pixels.
-constexpr int64_t FINE_PIXELS_ANY = 896 * 256, FINE_PIXELS_SMALL = 12288 * 256;
+constexpr int64_t FINE_PIXELS_ANY = 640 * 256, FINE_PIXELS_SMALL = 7168 * 256;
 
 bool fine_needs_sizes(int64_t pixels) { return pixels > FINE_PIXELS_ANY && pixels <= FINE_PIXELS_SMALL; }
 
