@@ -138,26 +138,28 @@ struct Cells {
     int x0, y0, w;
     uint32_t area;   // 0: the record is listed nowhere
     int cw, ch;      // cell size in pixels
+    int h;
 };
 
 __device__ __forceinline__ Cells cells_of(const float4& A, const float4& B, bool wide, const DevView& cam,
                                           const DevSettings& st) {
-    Cells c{0, 0, 1, 0u, st.tile_w, st.tile_h};
+    Cells c{0, 0, 1, 0u, st.tile_w, st.tile_h, 0};
     const Rect q = rect_of(A.x, A.y, B.w, cam, st);
     if (q.x1 < q.x0 || q.y1 < q.y0) return c;
     if (wide) {
         c.x0 = q.x0 / REGION;
         c.y0 = q.y0 / REGION;
         c.w = q.x1 / REGION - c.x0 + 1;
-        c.area = (uint32_t)c.w * (uint32_t)(q.y1 / REGION - c.y0 + 1);
+        c.h = q.y1 / REGION - c.y0 + 1;
         c.cw = REGION * st.tile_w;
         c.ch = REGION * st.tile_h;
     } else {
         c.x0 = q.x0;
         c.y0 = q.y0;
         c.w = q.x1 - q.x0 + 1;
-        c.area = (uint32_t)c.w * (uint32_t)(q.y1 - q.y0 + 1);
+        c.h = q.y1 - q.y0 + 1;
     }
+    c.area = (uint32_t)c.w * (uint32_t)c.h;
     return c;
 }
 
@@ -275,10 +277,50 @@ __device__ __forceinline__ uint32_t block_mask(const float4& A, const float4& B,
     return mask;
 }
 
-// With culling, the kept cells of a rectangle of at most CULL_MAX cells
-// travel from the classification to the duplication as a bit mask (bit j:
-// cell j, row-major); larger rectangles have their rows recomputed.
+// A value equal in all lanes, in a scalar register.
+__device__ __forceinline__ int uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }
+__device__ __forceinline__ uint32_t uniform(uint32_t v) { return (uint32_t)uniform((int)v); }
+__device__ __forceinline__ uint2 uniform(uint2 v) { return make_uint2(uniform(v.x), uniform(v.y)); }
+
+// Inclusive maximum scan over the 64 lanes of a wave, for values >= -1:
+// shifts within each 16-lane row, then the broadcasts of lane 15 into rows
+// 1 and 3 and of lane 31 into rows 2 and 3 (a lane with no source keeps -1).
+__device__ __forceinline__ int wave_max_scan(int x) {
+    x = max(x, __builtin_amdgcn_update_dpp(-1, x, 0x111, 0xf, 0xf, false));  // row_shr 1
+    x = max(x, __builtin_amdgcn_update_dpp(-1, x, 0x112, 0xf, 0xf, false));  // row_shr 2
+    x = max(x, __builtin_amdgcn_update_dpp(-1, x, 0x114, 0xf, 0xf, false));  // row_shr 4
+    x = max(x, __builtin_amdgcn_update_dpp(-1, x, 0x118, 0xf, 0xf, false));  // row_shr 8
+    x = max(x, __builtin_amdgcn_update_dpp(-1, x, 0x142, 0xa, 0xf, false));  // row_bcast 15
+    x = max(x, __builtin_amdgcn_update_dpp(-1, x, 0x143, 0xc, 0xf, false));  // row_bcast 31
+    return x;
+}
+
+// Owner of each of the slots [w0, w0 + 64) of a wave, one per lane: items (one
+// per lane, at most; has: this lane's holds slots) own consecutive runs of
+// slots, item `lane` from slot `first` on; the owner is the last item whose
+// first slot is at or before the slot.  Every item marks its first slot in the
+// wave's 64 words, a running maximum fills the rest; carry: the last owner of
+// the slots before (-1 at first).  LDS operations of one wave complete in
+// program order.
+__device__ __forceinline__ int slot_owner(int* words, int lane, bool has, uint32_t first, uint32_t w0, int& carry) {
+    words[lane] = -1;
+    __builtin_amdgcn_wave_barrier();
+    if (has && first - w0 < 64u) words[first - w0] = lane;  // (first below w0 wraps)
+    __builtin_amdgcn_wave_barrier();
+    const int own = max(wave_max_scan(words[lane]), carry);
+    carry = __builtin_amdgcn_readlane(own, 63);
+    __builtin_amdgcn_wave_barrier();
+    return own;
+}
+
+// What the classification hands to the duplication per listed position (x:
+// key of the first cell; y: row stride of the keys << 14).  A rectangle of at
+// most CULL_MAX cells: y also width and height << 7, (z, w) the kept cells as
+// a bit mask (bit j: cell j, row-major).  A larger one: y also CELLS_LARGE, z
+// first column and row << 16, w width and height << 16; its rows are found
+// again.  (Grids have at most 2048 x 2048 cells.)
 constexpr uint32_t CULL_MAX = 64;
+constexpr uint32_t CELLS_LARGE = 0x80000000u;
 // Key of an emitted slot the duplication could not fill: past every cell,
 // so it sorts last and no range includes it.
 constexpr uint32_t KEY_NONE = 0xffffffffu;
@@ -304,12 +346,24 @@ __device__ __forceinline__ float4 shfl4(const float4& v, int src) {
 // 2^22 tiles each): the compositing's choice of kernel.
 // A record without tiles (key all ones, sorted last in its view) is listed
 // nowhere: it gets no copy, which nothing uses.
+// Bound by the gather of the records (8 views of 1 M, 70 % listed: 0.82 GB, 159
+// us at the copy rate).  The wave loads its records three lanes to each, and
+// walks their rows 64 at a time: with a record per lane throughout, the lanes
+// wait for the one with most rows.  227 -> 209 us (8.5e7 -> 6.3e7 vector
+// instructions of a wave), 1.5 M records of one view 41.5 -> 40.6 us, though
+// the duplication now gets the rectangle too (16 bytes for 8).
 __global__ void __launch_bounds__(256) permute_classify_kernel(
     const uint32_t* __restrict__ order, const uint32_t* __restrict__ skeys, const float4* __restrict__ rec,
     int64_t R, int64_t n, ViewSet views, DevSettings st, uint32_t* __restrict__ cnt_out,
-    uint64_t* __restrict__ tmask, float4* __restrict__ srec,
+    uint4* __restrict__ cells, float4* __restrict__ srec,
     uint32_t* __restrict__ part, int sizes) {
     __shared__ uint32_t s_part[4][4];
+    // per wave 3 x 64: its records as they are laid out, then for the walk over
+    // rows, per record: RowCull (two), columns, rows and the view's size
+    __shared__ float4 s_rec[3 * 256];
+    __shared__ uint32_t s_cnt[256];
+    __shared__ unsigned long long s_mask[256];
+    __shared__ int s_own[256];
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     const int lane = lane_id();
     const bool live = i < R;
@@ -320,44 +374,105 @@ __global__ void __launch_bounds__(256) permute_classify_kernel(
     // both loads of the position in one round trip, then the record
     const uint32_t key = live ? skeys[i] : 0xffffffffu;
     const uint32_t r = live ? order[i] : 0u;
-    if (live && key != 0xffffffffu) {
-        // one gather of the record (radius in B.w, tile count in C.w)
-        A = rec[3 * (size_t)r];
-        B = rec[3 * (size_t)r + 1];
-        uint4 C = reinterpret_cast<const uint4*>(rec)[3 * (size_t)r + 2];
-        c = C.w;
-        vi = (int)((uint32_t)i / (uint32_t)n);  // positions are below 2^32
-        wide = c > views.v[vi].wide_min;
-        C.w = r;
-        srec[3 * i] = A;
-        srec[3 * i + 1] = B;
-        reinterpret_cast<uint4*>(srec)[3 * i + 2] = C;
+    const bool has = live && key != 0xffffffffu;
+    float4* wrec = s_rec + 3 * (threadIdx.x & ~63u);
+    if (ballot(has)) {
+        // the wave's records (radius in B.w, tile count in C.w), three
+        // neighbouring lanes to a record: a load touches 22 records' lines
+        // instead of 64, and the copy's stores are contiguous
+        const uint32_t rid = has ? r : 0xffffffffu;
+        float4* out4 = srec + 3 * (i - lane);
+        float4 v[3];
+#pragma unroll
+        for (int j = 0; j < 3; ++j) {
+            const int q = j * 64 + lane, part = q % 3;
+            const uint32_t rq = (uint32_t)__shfl((int)rid, q / 3);
+            v[j] = make_float4(0.f, 0.f, 0.f, 0.f);
+            if (rq != 0xffffffffu) v[j] = rec[3 * (size_t)rq + part];
+        }
+#pragma unroll
+        for (int j = 0; j < 3; ++j) {
+            const int q = j * 64 + lane;
+            const uint32_t rq = (uint32_t)__shfl((int)rid, q / 3);
+            wrec[q] = v[j];
+            if (q % 3 == 2) v[j].w = __uint_as_float(rq);
+            if (rq != 0xffffffffu) out4[q] = v[j];
+        }
+        __builtin_amdgcn_wave_barrier();
+        A = wrec[3 * lane];
+        B = wrec[3 * lane + 1];
+        c = __float_as_uint(wrec[3 * lane + 2].w);
+        if (has) {
+            vi = (int)((uint32_t)i / (uint32_t)n);  // positions are below 2^32
+            wide = c > views.v[vi].wide_min;
+        }
+        __builtin_amdgcn_wave_barrier();
     }
-    Cells cl{0, 0, 1, 0u, st.tile_w, st.tile_h};
+    Cells cl{0, 0, 1, 0u, st.tile_w, st.tile_h, 0};
     if (live && c > 0) cl = cells_of(A, B, wide, views.v[vi], st);
     uint32_t cnt = cl.area;
-    uint64_t mask = 0;
-    if (st.tile_cull && cl.area > 0) {
-        const RowCull rc = row_prep(A, B, st);
-        const int width = views.v[vi].width, height = views.v[vi].height;  // loaded once, not per row
-        const int rows = (int)(cl.area / (uint32_t)cl.w);
-        cnt = 0;
-        for (int ry = 0; ry < rows; ++ry) {
-            int lo, hi;
-            if (!row_cells(rc, cl.y0 + ry, cl.cw, cl.ch, cl.x0, cl.x0 + cl.w - 1, width, height, lo, hi)) continue;
-            cnt += (uint32_t)(hi - lo + 1);
-            if (cl.area <= CULL_MAX) {
-                // bits ry w + (lo - x0) .. ry w + (hi - x0)
-                const uint32_t b0 = (uint32_t)(ry * cl.w + (lo - cl.x0)), nb = (uint32_t)(hi - lo + 1);
-                mask |= (nb >= 64 ? ~0ull : ((1ull << nb) - 1ull)) << b0;
-            }
+    uint64_t mask = cl.area >= 64u ? ~0ull : (1ull << cl.area) - 1ull;
+    if (st.tile_cull) {
+        // the rows of the wave's records, one per lane and round
+        const int t = threadIdx.x, wb = t & ~63;
+        const uint32_t rows = cl.area > 0 ? (uint32_t)cl.h : 0u;
+        const uint32_t x = wave_add_scan(rows);
+        const uint32_t total = (uint32_t)__builtin_amdgcn_readlane((int)x, 63), first = x - rows;
+        if (rows) {
+            const RowCull rc = row_prep(A, B, st);
+            wrec[lane] = make_float4(rc.u, rc.v, rc.beta, rc.gamma);
+            wrec[64 + lane] = make_float4(rc.inva, rc.cut, rc.H, rc.eyR);
+            reinterpret_cast<uint4*>(wrec)[128 + lane] =
+                make_uint4(first, (uint32_t)cl.x0 | (uint32_t)cl.y0 << 16,
+                           (uint32_t)cl.w | (uint32_t)rc.mode << 16 | (wide ? 1u << 18 : 0u),
+                           (uint32_t)views.v[vi].width | (uint32_t)views.v[vi].height << 16);
         }
+        s_cnt[t] = 0u;
+        s_mask[t] = 0ull;
+        int carry = -1;
+        for (uint32_t w0 = 0; w0 < total; w0 += 64) {
+            const int own = slot_owner(s_own + wb, lane, rows > 0, first, w0, carry), k = wb + own;
+            const uint32_t e = w0 + (uint32_t)lane;
+            if (e >= total) continue;
+            const float4 p0 = wrec[own], p1 = wrec[64 + own];
+            const uint4 g = reinterpret_cast<const uint4*>(wrec)[128 + own];
+            const int ry = (int)(e - g.x), w = (int)(g.z & 0xffffu), x0 = (int)(g.y & 0xffffu);
+            const RowCull rc{p0.x, p0.y, p0.z, p0.w, p1.x, p1.y, p1.z, p1.w, (int)(g.z >> 16) & 3};
+            const int scale = (g.z >> 18) & 1u ? REGION : 1;
+            int lo, hi;
+            if (!row_cells(rc, (int)(g.y >> 16) + ry, scale * st.tile_w, scale * st.tile_h, x0, x0 + w - 1,
+                           (int)(g.w & 0xffffu), (int)(g.w >> 16), lo, hi))
+                continue;
+            const uint32_t nb = (uint32_t)(hi - lo + 1);
+            atomicAdd(&s_cnt[k], nb);
+            // bits ry w + (lo - x0) .. ry w + (hi - x0); of no use past 64 cells
+            const uint32_t b0 = (uint32_t)(ry * w + (lo - x0));
+            if (b0 < 64u) atomicOr(&s_mask[k], (nb >= 64 ? ~0ull : ((1ull << nb) - 1ull)) << b0);
+        }
+        __builtin_amdgcn_wave_barrier();
+        cnt = s_cnt[t];
+        mask = s_mask[t];
     }
     if (live) {
-        // the wide flag rides in bit 31 (counts stay below 2^24); the cull
-        // mask is kept only for positions with entries
+        // the wide flag rides in bit 31 (counts stay below 2^24); the cells
+        // are kept only for positions with entries
         cnt_out[i] = cnt | (wide ? CNT_WIDE : 0u);
-        if (cnt != 0) tmask[i] = mask;
+        if (cnt != 0) {
+            const DevView& cam = views.v[vi];
+            uint4 o;
+            o.x = cell_key(wide, cl.x0, cl.y0, cam, views);
+            o.y = (uint32_t)(wide ? cam.reg_w : cam.grid_w) << 14;
+            if (cl.area <= CULL_MAX) {
+                o.y |= (uint32_t)cl.w | (uint32_t)cl.h << 7;
+                o.z = (uint32_t)mask;
+                o.w = (uint32_t)(mask >> 32);
+            } else {
+                o.y |= CELLS_LARGE;
+                o.z = (uint32_t)cl.x0 | (uint32_t)cl.y0 << 16;
+                o.w = (uint32_t)cl.w | (uint32_t)cl.h << 16;
+            }
+            cells[i] = o;
+        }
     }
     // wide records and their list entries of the workgroup (no atomics: one
     // address updated by every wave serialises)
@@ -563,211 +678,128 @@ __global__ void __launch_bounds__(LO_GROUP) list_offsets_one_kernel(const uint32
     }
 }
 
-// Position of the r-th (0-based) set bit of m; r < popcount(m).
-__device__ __forceinline__ uint32_t select_bit(uint64_t m, uint32_t r) {
-    uint32_t pos = 0;
-    uint32_t x = (uint32_t)m;
-    uint32_t c = (uint32_t)__popc(x);
-    if (r >= c) {
-        r -= c;
-        x = (uint32_t)(m >> 32);
-        pos = 32;
-    }
-#pragma unroll
-    for (int sh = 16; sh >= 1; sh >>= 1) {
-        c = (uint32_t)__popc(x & ((1u << sh) - 1u));
-        if (r >= c) {
-            r -= c;
-            x >>= sh;
-            pos += (uint32_t)sh;
-        }
-    }
-    return pos;
-}
-
-// Inclusive maximum scan over the 64 lanes of a wave, for values >= -1:
-// shifts within each 16-lane row, then the broadcasts of lane 15 into rows
-// 1 and 3 and of lane 31 into rows 2 and 3 (a lane with no source keeps -1).
-__device__ __forceinline__ int wave_max_scan(int x) {
-    x = max(x, __builtin_amdgcn_update_dpp(-1, x, 0x111, 0xf, 0xf, false));  // row_shr 1
-    x = max(x, __builtin_amdgcn_update_dpp(-1, x, 0x112, 0xf, 0xf, false));  // row_shr 2
-    x = max(x, __builtin_amdgcn_update_dpp(-1, x, 0x114, 0xf, 0xf, false));  // row_shr 4
-    x = max(x, __builtin_amdgcn_update_dpp(-1, x, 0x118, 0xf, 0xf, false));  // row_shr 8
-    x = max(x, __builtin_amdgcn_update_dpp(-1, x, 0x142, 0xa, 0xf, false));  // row_bcast 15
-    x = max(x, __builtin_amdgcn_update_dpp(-1, x, 0x143, 0xc, 0xf, false));  // row_bcast 31
-    return x;
-}
-
 // List entries in sorted-position order: cell keys (tile or region ids) as
-// keys, positions as values, for the cells the classification counted.  The
-// outputs of a wave's records are contiguous, so each wave walks them 64
-// slots at a time with every lane busy and consecutive lanes writing
-// consecutive entries.  The owner of a slot is the last record whose first
-// slot is at or before it: every record marks its first slot (records with
-// entries start at distinct slots), and a running maximum over the slots
-// fills the rest.  Record-local rank -> cell by selecting the rank-th bit of
-// the cull mask (the rank itself without culling).  Culled rectangles of
-// more than CULL_MAX cells re-derive their rows, one row per lane.  Writes
-// never leave a record's counted slots; a slot the emission does not fill
-// gets KEY_NONE.  No step waits on another wave.
+// keys, positions as values, for the cells the classification counted.  Each
+// wave walks its records' rows 64 at a time, one per lane: a row's kept cells
+// are one run, read off the record's cell mask, or found again where the
+// rectangle has more than CULL_MAX cells.  It then walks the runs' entries 64
+// at a time, so that every lane is busy and consecutive lanes write
+// consecutive entries.  Bound by VALU issue where lists are short: selecting
+// each entry's cell as the r-th bit of its mask, deriving every rectangle again
+// from the record, and one large record at a time, this took 187 us for 8
+// views of 1 M records (20.2 M entries), 63 us for 1.5 M (4.1 M) and 32 us for
+// 300 k (1.6 M); walking runs 104, 23 and 14 us (20.2 M entries: 41 us of
+// traffic for them, 27 us for the cells).  Writes never leave the wave's counted slots; a slot
+// the emission does not fill gets KEY_NONE.  No step waits on another wave.
 __global__ void __launch_bounds__(256) duplicate_kernel(
     const float4* __restrict__ srec, const uint32_t* __restrict__ cnt_sorted,
-    const uint64_t* __restrict__ tmask, ListOffsets lo, int64_t R, int64_t n, ViewSet views, DevSettings st,
+    const uint4* __restrict__ cells, ListOffsets lo, int64_t R, int64_t n, ViewSet views, DevSettings st,
     uint32_t* __restrict__ keys, uint32_t* __restrict__ vals, int64_t capacity, uint32_t* __restrict__ flags,
     FillSet fs) {
     // the clears of the later stages ride along (a launch of their own: 4 us)
     for (int64_t f = (int64_t)blockIdx.x * 256 + threadIdx.x; f < fs.total; f += (int64_t)gridDim.x * 256)
         fill_element(fs, f);
-    __shared__ uint32_t s_first[256];
-    __shared__ uint32_t s_rel[256];
+    __shared__ uint4 s_c[256];   // per record: first row | flags, key, width | stride << 16, column | row << 16
     __shared__ unsigned long long s_mask[256];
-    __shared__ uint2 s_geo[256];
+    __shared__ float4 s_p0[256], s_p1[256];  // large records: RowCull, in part
+    __shared__ int2 s_wh[256];               // ... and the view's size
+    __shared__ uint2 s_run[256];             // per row: key of its first entry less the entry's slot, position
     __shared__ int s_own[256];
+    constexpr uint32_t LARGE = 1u << 24, MODE = 25, WIDE = 1u << 27;  // flags beside the first row (below 2^24)
     const int t = threadIdx.x;
     const int64_t i0 = (int64_t)blockIdx.x * blockDim.x;
     const int64_t i = i0 + t;
     const int lane = lane_id();
     const int wb = t & ~63;  // the wave's first thread
-    Cells cl{0, 0, 1, 0u, st.tile_w, st.tile_h};
     uint32_t cnt = 0;
-    int vi = 0;
     bool wide = false;
-    uint64_t mask = 0;
-    float4 A = make_float4(0.f, 0.f, 0.f, 0.f), B = A;
-    const bool cull = st.tile_cull != 0;
     if (i < R) {
         const uint32_t cw = cnt_sorted[i];
         cnt = cw & ~CNT_WIDE;
         wide = (cw & CNT_WIDE) != 0;
     }
-    // the copy and the mask of a position without entries (never written)
-    // are not used: positions listed nowhere sort last in their view, so
-    // whole waves of them load nothing more
-    if (__any(cnt != 0) && i < R) {
-        A = srec[3 * i];
-        B = srec[3 * i + 1];
-        if (cull) mask = tmask[i];
-    }
-    // the record's view, loaded once: cell (x0 + rx, y0 + ry) has key
-    // key0 + ry stride + rx
-    uint32_t key0 = 0, stride = 0;
-    int width = 0, height = 0;
+    if (!ballot(cnt != 0)) return;  // (no barrier below is the workgroup's)
+    uint32_t rows = 0;
+    uint4 c = make_uint4(0u, 0u, 0u, 0u);
     if (cnt != 0) {
-        vi = (int)((uint32_t)i / (uint32_t)n);  // positions are below 2^32
-        const DevView& cam = views.v[vi];
-        cl = cells_of(A, B, wide, cam, st);
-        key0 = cell_key(wide, cl.x0, cl.y0, cam, views);
-        stride = (uint32_t)(wide ? cam.reg_w : cam.grid_w);
-        width = cam.width;
-        height = cam.height;
+        c = cells[i];
+        rows = c.y & CELLS_LARGE ? c.w >> 16 : (c.y >> 7) & 0x7fu;
     }
-    if (cnt == 0 || cl.area > CULL_MAX) mask = 0;
-    const bool flat = cnt > 0 && (!cull || cl.area <= CULL_MAX);
-    // start of the wave's output: its offset within its group of waves plus
-    // the group's
-    const int64_t wave = i0 / 64 + (t >> 6);
-    const int64_t base = (int64_t)(lo.wave_rel[wave] + lo.group_off[wave / LO_GROUP]);
-    bool overflow = false;
-    // the record's first entry: the wave's start plus the entries of the
-    // wave's earlier positions (below 2^32, see the classification)
-    uint32_t rel;
-    {
-        // inclusive scans over the wave: all entries (ax), flat slots (x)
-        const uint32_t x = wave_add_scan(flat ? cnt : 0u), ax = wave_add_scan(cnt);
-        rel = ax - cnt;
-        // first slot of each record among the wave's flat slots
-        const uint32_t first = x - (flat ? cnt : 0u);
-        const uint32_t total = (uint32_t)__builtin_amdgcn_readlane((int)x, 63);
-        s_first[t] = first;
-        s_rel[t] = rel;
-        s_mask[t] = mask;
-        s_geo[t] = make_uint2(key0, (uint32_t)cl.w | (stride << 16));
-        int carry = -1;
-        for (uint32_t w0 = 0; w0 < total; w0 += 64) {
-            // LDS operations of one wave complete in program order
-            s_own[t] = -1;
-            __builtin_amdgcn_wave_barrier();
-            if (flat && first >= w0 && first < w0 + 64u) s_own[wb + (int)(first - w0)] = lane;
-            __builtin_amdgcn_wave_barrier();
-            const int own = max(wave_max_scan(s_own[t]), carry);
-            carry = __builtin_amdgcn_readlane(own, 63);
-            __builtin_amdgcn_wave_barrier();
-            const uint32_t e = w0 + (uint32_t)lane;
-            if (e >= total) continue;
-            const int k = wb + own;
-            const uint32_t r = e - s_first[k];
-            const uint2 g = s_geo[k];
-            const uint32_t w = g.y & 0xffffu, kstride = g.y >> 16;
-            const uint64_t km = s_mask[k];
-            const int64_t o = base + (int64_t)s_rel[k] + (int64_t)r;
-            uint32_t key = KEY_NONE;
-            if (!cull || r < (uint32_t)__popcll(km)) {
-                const uint32_t j = cull ? select_bit(km, r) : r;
-                // with culling j < 64 and w <= 64: (j + 1/2) / w is at least
-                // 1/128 from an integer, far beyond the product's rounding
-                const uint32_t ry = cull ? (uint32_t)(((float)j + 0.5f) * __builtin_amdgcn_rcpf((float)w)) : j / w;
-                const uint32_t rx = j - ry * w;
-                key = g.x + ry * kstride + rx;
+    const uint32_t rx = wave_add_scan(rows), ax = wave_add_scan(cnt);
+    const uint32_t total_rows = (uint32_t)__builtin_amdgcn_readlane((int)rx, 63), first = rx - rows;
+    const uint32_t total = (uint32_t)__builtin_amdgcn_readlane((int)ax, 63);
+    if (cnt != 0) {
+        const uint32_t stride = (c.y & ~CELLS_LARGE) >> 14;
+        if (c.y & CELLS_LARGE) {
+            uint32_t fl = LARGE | (wide ? WIDE : 0u);
+            if (st.tile_cull) {
+                const DevView& cam = views.v[(uint32_t)i / (uint32_t)n];  // positions are below 2^32
+                const RowCull rc = row_prep(srec[3 * i], srec[3 * i + 1], st);
+                s_p0[t] = make_float4(rc.u, rc.v, rc.beta, rc.gamma);
+                s_p1[t] = make_float4(rc.inva, rc.cut, rc.H, rc.eyR);
+                s_wh[t] = make_int2(cam.width, cam.height);
+                fl |= (uint32_t)rc.mode << MODE;
             }
-            if (o < capacity) {
-                keys[o] = key;
-                vals[o] = key == KEY_NONE ? 0u : (uint32_t)(i0 + k);
-            } else {
-                overflow = true;
-            }
+            s_c[t] = make_uint4(first | fl, c.x, (c.w & 0xffffu) | stride << 16, c.z);
+        } else {
+            s_c[t] = make_uint4(first, c.x, (c.y & 0x7fu) | stride << 16, 0u);
+            s_mask[t] = (unsigned long long)c.w << 32 | c.z;
         }
     }
-    // culled rectangles of more than CULL_MAX cells: the rows again, one row
-    // per lane; each row is a contiguous run of cells placed by a prefix sum
-    uint64_t pending = __ballot(cnt > 0 && !flat);
-    while (pending) {
-        const int src = __ffsll((long long)pending) - 1;
-        pending &= pending - 1;
-        const uint32_t barea = __shfl(cl.area, src), bcnt = __shfl(cnt, src);
-        const uint32_t bi = (uint32_t)__shfl((int)(uint32_t)i, src);
-        const int bx0 = __shfl(cl.x0, src), by0 = __shfl(cl.y0, src), bw = __shfl(cl.w, src);
-        const int bcw = __shfl(cl.cw, src), bch = __shfl(cl.ch, src);
-        const int bwidth = __shfl(width, src), bheight = __shfl(height, src);
-        const uint32_t bkey0 = (uint32_t)__shfl((int)key0, src), bstride = (uint32_t)__shfl((int)stride, src);
-        const int64_t bo = base + (int64_t)(uint32_t)__shfl((int)rel, src);
-        const int64_t end = bo + bcnt;
-        const RowCull rc = row_prep(shfl4(A, src), shfl4(B, src), st);
-        const int rows = (int)(barea / (uint32_t)bw);
-        int64_t rbase = bo;
-        for (int r0 = 0; r0 < rows && rbase < end; r0 += 64) {
-            const int ry = r0 + lane;
-            int lo = 0, hi = -1;
-            if (ry < rows && !row_cells(rc, by0 + ry, bcw, bch, bx0, bx0 + bw - 1, bwidth, bheight, lo, hi))
-                hi = lo - 1;
-            if (ry >= rows) hi = lo - 1;
-            const int nrow = hi - lo + 1;
-            int incl = nrow;
-#pragma unroll
-            for (int d = 1; d < 64; d <<= 1) {
-                const int y = __shfl_up(incl, d);
-                if (lane >= d) incl += y;
-            }
-            int64_t o = rbase + (incl - nrow);
-            for (int cx = lo; cx <= hi && o < end; ++cx, ++o) {
-                if (o < capacity) {
-                    keys[o] = bkey0 + (uint32_t)ry * bstride + (uint32_t)(cx - bx0);
-                    vals[o] = bi;
-                } else {
-                    overflow = true;
+    // the wave's slots: its offset within its group of waves plus the group's
+    const int64_t wave = uniform((int)(i0 / 64) + (t >> 6));
+    const int64_t base = (int64_t)(lo.wave_rel[wave] + lo.group_off[wave / LO_GROUP]);
+    const uint32_t lim = (uint32_t)max((int64_t)0, min((int64_t)total, capacity - base));
+    uint32_t* kw = keys + base;
+    uint32_t* vw = vals + base;
+    uint32_t out = 0;
+    int rcarry = -1;
+    for (uint32_t r0 = 0; r0 < total_rows; r0 += 64) {
+        const int k = wb + slot_owner(s_own + wb, lane, rows > 0, first, r0, rcarry);
+        uint32_t nrun = 0, key = 0;
+        if (r0 + (uint32_t)lane < total_rows) {
+            const uint4 g = s_c[k];
+            const uint32_t ry = r0 + (uint32_t)lane - (g.x & 0xffffffu), w = g.z & 0xffffu;
+            key = g.y + ry * (g.z >> 16);
+            if (!(g.x & LARGE)) {
+                const uint64_t m = (s_mask[k] >> (ry * w)) & (w >= 64u ? ~0ull : (1ull << w) - 1ull);
+                nrun = (uint32_t)__popcll(m);
+                key += (uint32_t)__builtin_ctzll(m | 1ull << 63);
+            } else if (!st.tile_cull) {
+                nrun = w;
+            } else {
+                const float4 p0 = s_p0[k], p1 = s_p1[k];
+                const int2 wh = s_wh[k];
+                const RowCull rc{p0.x, p0.y, p0.z, p0.w, p1.x, p1.y, p1.z, p1.w, (int)(g.x >> MODE) & 3};
+                const int scale = g.x & WIDE ? REGION : 1, x0 = (int)(g.w & 0xffffu);
+                int cl, ch;
+                if (row_cells(rc, (int)((g.w >> 16) + ry), scale * st.tile_w, scale * st.tile_h, x0, x0 + (int)w - 1,
+                              wh.x, wh.y, cl, ch)) {
+                    nrun = (uint32_t)(ch - cl + 1);
+                    key += (uint32_t)(cl - x0);
                 }
             }
-            rbase += __shfl(incl, 63);
         }
-        for (int64_t o = rbase + lane; o < end; o += 64) {
-            if (o < capacity) {
-                keys[o] = KEY_NONE;
-                vals[o] = 0u;
-            } else {
-                overflow = true;
+        const uint32_t nx = wave_add_scan(nrun), nfirst = nx - nrun;
+        const uint32_t ntot = (uint32_t)__builtin_amdgcn_readlane((int)nx, 63);
+        s_run[t] = make_uint2(key - nfirst, (uint32_t)(i0 + k));
+        int ecarry = -1;
+        for (uint32_t e0 = 0; e0 < ntot; e0 += 64) {
+            const uint2 run = s_run[wb + slot_owner(s_own + wb, lane, nrun > 0, nfirst, e0, ecarry)];
+            const uint32_t e = e0 + (uint32_t)lane, o = out + e;
+            if (e < ntot && o < lim) {
+                kw[o] = run.x + e;
+                vw[o] = run.y;
             }
         }
+        __builtin_amdgcn_wave_barrier();  // s_run is written again
+        out += ntot;
     }
-    if (overflow) atomicOr(flags, FLAG_CAPACITY);
+    for (uint32_t o = out + (uint32_t)lane; o < lim; o += 64) {
+        kw[o] = KEY_NONE;
+        vw[o] = 0u;
+    }
+    if (lim < total && lane == 0) atomicOr(flags, FLAG_CAPACITY);
 }
 
 // Upper bound on the batches a tile can take: a batch either emits `batch`
@@ -1105,11 +1137,6 @@ __device__ __forceinline__ void stage_entry(const Lds& L, int j, const float4* _
                                             int qx0, int qy0, int height, const DevSettings& st) {
     put_entry<FINE>(L, j, srec[3 * p], srec[3 * p + 1], srec[3 * p + 2], k, qx0, qy0, height, st);
 }
-
-// A value equal in all lanes, in a scalar register.
-__device__ __forceinline__ int uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }
-__device__ __forceinline__ uint32_t uniform(uint32_t v) { return (uint32_t)uniform((int)v); }
-__device__ __forceinline__ uint2 uniform(uint2 v) { return make_uint2(uniform(v.x), uniform(v.y)); }
 
 // Hides where a value comes from: what is computed from it is computed again
 // behind this point, not kept in (spilled) registers from before it.
@@ -2351,11 +2378,11 @@ bool composite_config_supported(const CompositeConfig& c) {
 
 void launch_permute_classify(hipStream_t stream, const uint32_t* order, const uint32_t* skeys, const float* rec,
                              int64_t R, int64_t n, const ViewSet& views, const DevSettings& st, uint32_t* cnt,
-                             uint64_t* tmask, float* srec, uint32_t* part, bool sizes) {
+                             uint32_t* cells, float* srec, uint32_t* part, bool sizes) {
     if (R == 0) return;
     const unsigned nb = blocks_of(R);
     hipLaunchKernelGGL(permute_classify_kernel, dim3(nb), dim3(256), 0, stream, order, skeys,
-                       reinterpret_cast<const float4*>(rec), R, n, views, st, cnt, tmask,
+                       reinterpret_cast<const float4*>(rec), R, n, views, st, cnt, reinterpret_cast<uint4*>(cells),
                        reinterpret_cast<float4*>(srec), part, sizes ? 1 : 0);
 }
 
@@ -2395,7 +2422,7 @@ void launch_list_offsets(hipStream_t stream, uint32_t* part, int64_t R, uint64_t
 }
 
 void launch_duplicate_lists(hipStream_t stream, const float* srec, const uint32_t* cnt_sorted,
-                            const uint64_t* tmask, uint32_t* part, int64_t R,
+                            const uint32_t* cells, uint32_t* part, int64_t R,
                             int64_t n, const ViewSet& views, const DevSettings& st, uint32_t* keys, uint32_t* vals,
                             int64_t capacity, uint32_t* flags, const FillSpan* fill, int fill_count) {
     if (R == 0) {
@@ -2403,7 +2430,8 @@ void launch_duplicate_lists(hipStream_t stream, const float* srec, const uint32_
         return;
     }
     hipLaunchKernelGGL(duplicate_kernel, dim3(blocks_of(R)), dim3(256), 0, stream,
-                       reinterpret_cast<const float4*>(srec), cnt_sorted, tmask, list_offsets(part, R), R,
+                       reinterpret_cast<const float4*>(srec), cnt_sorted, reinterpret_cast<const uint4*>(cells),
+                       list_offsets(part, R), R,
                        n, views, st, keys, vals, capacity, flags, make_fill_set(fill, fill_count));
 }
 

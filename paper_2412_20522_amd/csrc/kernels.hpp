@@ -121,7 +121,7 @@ uint64_t staged_first(uint32_t tiles);
 size_t classify_parts_bytes(int64_t R);
 void launch_permute_classify(hipStream_t stream, const uint32_t* order, const uint32_t* skeys, const float* rec,
                              int64_t R, int64_t n, const ViewSet& views, const DevSettings& st, uint32_t* cnt,
-                             uint64_t* tmask, float* srec, uint32_t* part, bool sizes);
+                             uint32_t* cells, float* srec, uint32_t* part, bool sizes);
 // From the classification's per-workgroup counts: each workgroup's first list
 // entry, the entry total (device u64 *total) and wide_counts (device u64):
 // [0] = wide records, [2] = their region entries, and with sizes (as given to
@@ -137,7 +137,7 @@ bool fine_needs_sizes(int64_t pixels);
 bool use_fine(int64_t pixels, uint64_t tiles_all, uint64_t tiles_large);
 // (fill: the spans the later stages need cleared, set in the same launch)
 void launch_duplicate_lists(hipStream_t stream, const float* srec, const uint32_t* cnt_sorted,
-                            const uint64_t* tmask, uint32_t* part, int64_t R,
+                            const uint32_t* cells, uint32_t* part, int64_t R,
                             int64_t n, const ViewSet& views, const DevSettings& st, uint32_t* keys, uint32_t* vals,
                             int64_t capacity, uint32_t* flags, const FillSpan* fill, int fill_count);
 // Launch order of the tiles: the tiles by descending cost key

@@ -144,6 +144,43 @@ def test_depth_order_and_lists_over_the_sort_variants(n, views):
     assert step.all()
 
 
+@pytest.mark.parametrize("size", [(60, 70), (300, 130), (1030, 520)])
+@pytest.mark.parametrize("wide", [-1, 4, 40])
+@pytest.mark.parametrize("n", [3, 64, 1500])
+def test_lists_of_rectangles_around_the_cell_mask(size, wide, n):
+    """Splats of a cell to the whole view: rectangles up to 64 cells go from
+    the classification to the duplication as a mask, larger ones row by row.
+    Without culling every cell of every rectangle is listed; with it the lists
+    are the ones of the image: the same bits."""
+    from paper_2412_20522_amd import maskgs as M
+    from paper_2412_20522_amd.raster import Rasterizer
+    w, h = size
+    s = scenegen.small_scene(n, w, h, seed=920 + n, sh_degree=0, log_scale_mean=-2.5)
+    s["log_scales"] += np.random.default_rng(1).uniform(-2, 3, (n, 1)).astype(np.float32)  # radii over 2 decades
+    s["opacity_logits"][:] = -3.0
+    dev = U.to_device(s)
+    params = {k: dev[k] for k in U.PARAM_KEYS}
+    img = []
+    for cull in (0, 1):
+        rast = Rasterizer(0, **_settings((8, 8), sh_degree=0, tile_cull=cull, wide_tiles=wide))
+        frame = rast.acquire_frame()
+        img.append(rast.forward(frame, params, dev["masks"], s["cameras"]).clone())
+        ex = {k: M.mgs_frame_export(rast.ctx, frame, k) for k in ("tiles", "values", "ranges")}
+        torch.cuda.synchronize()
+        K = rast.stats(frame)["n_instances"]
+        rast.release_frame(frame)
+        if wide < 0 and cull == 0:
+            assert K == int(U.u32(ex["tiles"]).astype(np.int64).sum())
+        r = U.u32(ex["ranges"]).reshape(-1, 2).astype(np.int64)
+        vals = U.u32(ex["values"]).astype(np.int64)[:K]
+        r = r[r[:, 1] > r[:, 0]]
+        assert (r[:, 1] - r[:, 0]).sum() == K
+        step = np.diff(vals) > 0
+        step[r[1:, 0] - 1] = True  # positions ascend within a cell
+        assert step.all()
+    assert torch.equal(img[0], img[1])
+
+
 @pytest.mark.parametrize("persistent", [0, 1])
 def test_tile_setup_in_one_workgroup_equals_several(persistent):
     """4096 tiles take the one-workgroup set-up; one tile more (a second view
