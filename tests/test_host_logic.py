@@ -134,6 +134,30 @@ def test_prune_cadence():
     assert sum(1 for it in due if it > 15_000) == 5
 
 
+def test_fp32_gumbel_bounds_decide_pruning_draws_like_the_exact_rule():
+    """The kernel's thresholds: FP32, less 1e-5, against the uniforms without
+    their half step.  Neither contradicts the double-precision rule, and the
+    gap's form d + log(log u1 / log u0) decides like the difference of the two
+    Gumbel samples."""
+    rng = np.random.default_rng(32)
+    g = lambda u: -np.log(-np.log(u))
+    f = np.float32
+    k = np.arange(0, 2 ** 24, 97)
+    u_grid, u_f = (k + 0.5) / 16777216.0, k.astype(f) * f(2.0 ** -24)
+    u_min = 0.5 / 16777216.0
+    with np.errstate(over="ignore"):
+        for d in (-90.0, -25.0, -12.0, -8.0, -1.5, -0.3, 0.0, 0.7, 3.0, 8.0, 12.0, 25.0, 90.0):
+            s0, s1 = d / 2, -d / 2
+            t0 = np.exp(-np.exp(f(d) - f(-2.8523629))) - f(1e-5)
+            t1 = np.exp(-np.exp(-f(d) - f(-2.8523629))) - f(1e-5)
+            for other in ((rng.integers(0, 2 ** 24, k.size) + 0.5) / 16777216.0, np.full(k.size, u_min)):
+                zero = (s0 + g(u_grid)) > (s1 + g(other))
+                one = (s0 + g(other)) > (s1 + g(u_grid))
+                assert not np.any(zero[u_f < t0]), d
+                assert np.all(one[u_f < t1]), d
+                assert np.array_equal(zero, d + np.log(np.log(other) / np.log(u_grid)) > 0.0), d
+
+
 def test_gumbel_bound_decides_pruning_draws_like_the_exact_rule():
     """The pruning draws settle most draws by comparing the uniforms with two
     per-Gaussian thresholds: g(u) = -log(-log u) increases with u and is at
