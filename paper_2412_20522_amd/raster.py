@@ -11,7 +11,6 @@ blended entry is kept.
 """
 from __future__ import annotations
 
-import weakref
 from dataclasses import dataclass
 from typing import Optional, Sequence
 
@@ -171,6 +170,22 @@ class Rasterizer:
         return m, y
 
 
+class _FrameLease:
+    """A pooled frame, given back once: by release(), or when the lease (held
+    by one autograd node) is freed."""
+    __slots__ = ("rasterizer", "frame")
+
+    def __init__(self, rasterizer: Rasterizer, frame):
+        self.rasterizer, self.frame = rasterizer, frame
+
+    def release(self) -> None:
+        frame, self.frame = self.frame, None
+        if frame is not None:
+            self.rasterizer.release_frame(frame)
+
+    __del__ = release
+
+
 class MaskedRasterize(torch.autograd.Function):
     """images, mask_loss = MaskedRasterize.apply(means, log_scales, quats,
     opacity_logits, sh, mask_scores, rasterizer, cams, tau, seed, step,
@@ -213,7 +228,7 @@ class MaskedRasterize(torch.autograd.Function):
         ctx.tau = tau
         # a pooled frame goes back to the pool once: after the backward, or
         # when this node is freed without one
-        ctx.release = weakref.finalize(ctx, rasterizer.release_frame, fr) if own else None
+        ctx.lease = _FrameLease(rasterizer, fr) if own else None
         ctx.save_for_backward(m_hard, y_soft)
         rasterizer.last_masks = m_hard
         return images, mask_loss
@@ -226,8 +241,8 @@ class MaskedRasterize(torch.autograd.Function):
             n_px = M.mgs_frame_get_stats(ctx.frame)["n_pixels"]
             dl_dimages = torch.zeros(3 * n_px, dtype=torch.float32, device=m_hard.device)
         g = r.backward(ctx.frame, ctx.params, dl_dimages.contiguous())
-        if ctx.release is not None:
-            ctx.release()
+        if ctx.lease is not None:
+            ctx.lease.release()
         ctx.frame = None
         d_scores = torch.empty(m_hard.shape[0], 2, dtype=torch.float32, device=m_hard.device)
         if dl_dmask_loss is None:
