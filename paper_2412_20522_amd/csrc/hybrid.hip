@@ -1296,6 +1296,22 @@ __device__ __forceinline__ float row_total(float x) {
     return x + dpp_xor1(x);
 }
 
+// the same for maxima
+__device__ __forceinline__ float halves_pair_max(float a, float b) {
+    const auto s = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+    return fmaxf(__uint_as_float(s[0]), __uint_as_float(s[1]));
+}
+__device__ __forceinline__ float rows_pair_max(float a, float b) {
+    const auto s = __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+    return fmaxf(__uint_as_float(s[0]), __uint_as_float(s[1]));
+}
+__device__ __forceinline__ float row_max(float x) {
+    x = fmaxf(x, dpp_ror8(x));
+    x = fmaxf(x, dpp_ror4(x));
+    x = fmaxf(x, dpp_xor2(x));
+    return fmaxf(x, dpp_xor1(x));
+}
+
 // Quantity whose wave total lane holds after wave_sum_swap10 (-1: none).
 // Column 0 of the rows holds quantities 0, 2, 1, 3 (rows 0 to 3), column 1
 // quantities 4, 6, 5, 7, column 2 of rows 0 and 2 quantities 8 and 9.
@@ -1377,8 +1393,9 @@ struct HybridLists {
 // five (six spill at four pixels per thread: 254 -> 268 us at 8,664 tiles).
 // STATS: write the per-pixel work counters (stats_out, eval_out).
 // IMP: accumulate every Gaussian's blending weights M alpha T over the
-// pixels it enters: the wave's sum (FP64 atomic) into imp_sum and its
-// maximum (as float bits, the weights being non-negative) into imp_max.
+// pixels it enters: the tile's sum (of FP32 sums over the waves, in FP64) into
+// imp_sum and its maximum (as float bits, the weights being non-negative) into
+// imp_max.
 template <int TW, int TH, int PPT, bool STATS, bool IMP>
 __global__ void __launch_bounds__(TW * TH / PPT, PPT >= 4 ? 5 : STATS ? 7 : 8) hybrid_fwd_kernel(
     const float4* __restrict__ srec, HybridLists hl, ViewSet views, DevSettings st, float* __restrict__ images,
@@ -1386,6 +1403,14 @@ __global__ void __launch_bounds__(TW * TH / PPT, PPT >= 4 ? 5 : STATS ? 7 : 8) h
     int4* __restrict__ eval_out, int64_t n, double* __restrict__ imp_sum,
     uint32_t* __restrict__ imp_max) {
     constexpr int NT = TW * TH / PPT;
+    // entries per round: with IMP four, whose reductions over the wave share
+    // their steps (2 views of 400 k Gaussians: 154 -> IMPT us against one)
+    constexpr int ROUND = IMP ? 4 : 1;
+    // IMP: the batch's sums and maxima over the tile, added to the Gaussians'
+    // once per tile, a lane to an entry (138 -> 102 us against atomics of
+    // every wave and round); zero between batches
+    __shared__ double s_isum[IMP ? MAXB : 1];
+    __shared__ uint32_t s_imax[IMP ? MAXB : 1];
     extern __shared__ __align__(16) char smem[];
     int t = threadIdx.x;
     const int batch = st.batch;
@@ -1403,6 +1428,12 @@ __global__ void __launch_bounds__(TW * TH / PPT, PPT >= 4 ? 5 : STATS ? 7 : 8) h
     }
     const uint32_t tile = uniform(hl.order ? hl.order[blockIdx.x] : blockIdx.x);
     const TileGeom tg = tile_geom(views, tile, TW, TH);
+    if constexpr (IMP) {
+        for (int p = t; p < MAXB; p += NT) {
+            s_isum[p] = 0.0;
+            s_imax[p] = 0u;
+        }
+    }
     const DevView& cam = views.v[tg.vi];
     float px[PPT], py[PPT], T[PPT], C0[PPT], C1[PPT], C2[PPT];
     // stopk: the entry at which the pixel stopped, -1 while it runs
@@ -1470,47 +1501,62 @@ __global__ void __launch_bounds__(TW * TH / PPT, PPT >= 4 ? 5 : STATS ? 7 : 8) h
             const int j1 = min(j0 + 16, bt.M);
             int j = j0;
             do {
-                const float4 A = L.E[3 * j], B = L.E[3 * j + 1], Cc = L.E[3 * j + 2];
-                const int k = __float_as_int(B.w);  // index in the tile's full list
-                float isum = 0.f, imax = 0.f;
+                float isum[ROUND], imax[ROUND];
 #pragma unroll
-                for (int i = 0; i < PPT; ++i) {
-                    if (stopk[i] >= 0) continue;
-                    Eval e;
-                    if (!eval_entry(A, B, px[i], py[i], ek, e)) continue;
-                    const float ma = B.z * e.alpha;
-                    const float test = T[i] * (1.f - ma);
-                    // one select, not a branch with copies on both sides
-                    const bool stop = test < st.t_min;
-                    stopk[i] = stop ? k : stopk[i];
-                    asm volatile("" : "+v"(stopk[i]));  // keeps the select here
-                    if (STATS) nev[i] = staged + j + 1;  // the last entry that passed the cuts
-                    if (stop) continue;
-                    const float wgt = ma * T[i];
-                    C0[i] += wgt * Cc.x;
-                    C1[i] += wgt * Cc.y;
-                    C2[i] += wgt * Cc.z;
-                    T[i] = test;
-                    last[i] = k;
-                    if (STATS) {
-                        ++nblend[i];
-                        nmasked[i] += B.z == 0.f;
-                        nev_last[i] = nev[i];
-                    }
-                    if (IMP) {
-                        isum += wgt;
-                        imax = fmaxf(imax, wgt);
+                for (int u = 0; u < ROUND; ++u) {
+                    const int je = j + u;
+                    isum[u] = imax[u] = 0.f;
+                    if (u > 0 && je >= j1) continue;  // uniform
+                    const float4 A = L.E[3 * je], B = L.E[3 * je + 1], Cc = L.E[3 * je + 2];
+                    const int k = __float_as_int(B.w);  // index in the tile's full list
+#pragma unroll
+                    for (int i = 0; i < PPT; ++i) {
+                        if (stopk[i] >= 0) continue;
+                        Eval e;
+                        if (!eval_entry(A, B, px[i], py[i], ek, e)) continue;
+                        const float ma = B.z * e.alpha;
+                        const float test = T[i] * (1.f - ma);
+                        // one select, not a branch with copies on both sides
+                        const bool stop = test < st.t_min;
+                        stopk[i] = stop ? k : stopk[i];
+                        asm volatile("" : "+v"(stopk[i]));  // keeps the select here
+                        if (STATS) nev[i] = staged + je + 1;  // the last entry that passed the cuts
+                        if (stop) continue;
+                        const float wgt = ma * T[i];
+                        C0[i] += wgt * Cc.x;
+                        C1[i] += wgt * Cc.y;
+                        C2[i] += wgt * Cc.z;
+                        T[i] = test;
+                        last[i] = k;
+                        if (STATS) {
+                            ++nblend[i];
+                            nmasked[i] += B.z == 0.f;
+                            nev_last[i] = nev[i];
+                        }
+                        if (IMP) {
+                            isum[u] += wgt;
+                            imax[u] = fmaxf(imax[u], wgt);
+                        }
                     }
                 }
-                if (IMP && __any(isum > 0.f)) {
-                    const float ws = wave_sum(isum), wm = wave_max(imax);
-                    if (lane_id() == 0) {
-                        const int64_t g = (int64_t)__float_as_uint(Cc.w) - (int64_t)tg.vi * n;
-                        atomicAdd(imp_sum + g, (double)ws);
-                        atomicMax(imp_max + g, __float_as_uint(wm));
+                if constexpr (IMP) {
+                    // the four entries' sums and maxima over the wave, each
+                    // entry's in one row, whose first lane adds them
+                    if (ballot((isum[0] > 0.f) | (isum[1] > 0.f) | (isum[2] > 0.f) | (isum[3] > 0.f))) {
+                        const float ws = row_total(rows_pair(halves_pair(isum[0], isum[1]),
+                                                             halves_pair(isum[2], isum[3])));
+                        const float wm = row_max(rows_pair_max(halves_pair_max(imax[0], imax[1]),
+                                                               halves_pair_max(imax[2], imax[3])));
+                        const int row = lane_id() >> 4;  // rows: entries 0, 2, 1, 3
+                        const int je = j + (row >> 1) + 2 * (row & 1);
+                        if ((lane_id() & 15) == 0 && je < j1 && !(ws <= 0.f)) {
+                            atomicAdd(&s_isum[je], (double)ws);
+                            atomicMax(&s_imax[je], __float_as_uint(wm));
+                        }
                     }
                 }
-            } while (++j < j1);
+                j += ROUND;
+            } while (j < j1);
         }
         active = false;
 #pragma unroll
@@ -1523,6 +1569,18 @@ __global__ void __launch_bounds__(TW * TH / PPT, PPT >= 4 ? 5 : STATS ? 7 : 8) h
                     const uint32_t jj = __float_as_uint(L.E[3 * p + 1].w) - (uint32_t)m;
                     hl.stg[off + p] = make_uint2(L.m[jj], jj);
                 }
+            }
+        }
+        if constexpr (IMP) {
+            __syncthreads();
+            for (int p = t; p < bt.M; p += NT) {
+                const double ws = s_isum[p];
+                if (ws == 0.0) continue;
+                const int64_t g = (int64_t)__float_as_uint(L.E[3 * p + 2].w) - (int64_t)tg.vi * n;
+                atomicAdd(imp_sum + g, ws);
+                atomicMax(imp_max + g, s_imax[p]);
+                s_isum[p] = 0.0;
+                s_imax[p] = 0u;
             }
         }
         i1 += bt.nX;
@@ -1784,12 +1842,6 @@ __device__ __forceinline__ int rows_add(int x) {
     return (int)(b[0] + b[1]);
 }
 // maximum over the 16 lanes of each row, in every lane of the row
-__device__ __forceinline__ float row_max(float x) {
-    x = fmaxf(x, dpp_ror8(x));
-    x = fmaxf(x, dpp_ror4(x));
-    x = fmaxf(x, dpp_xor2(x));
-    return fmaxf(x, dpp_xor1(x));
-}
 
 // LDS of one workgroup after the staging area of lds_bytes: per wave the
 // block's list (byte offsets of its entries in L.E, two rounds of padding)

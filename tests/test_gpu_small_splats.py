@@ -181,6 +181,35 @@ def test_lists_of_rectangles_around_the_cell_mask(size, wide, n):
     assert torch.equal(img[0], img[1])
 
 
+@pytest.mark.parametrize("tile,ppt,batch", [((16, 16), 1, 32), ((16, 16), 2, 128), ((16, 16), 4, 256), ((8, 8), 1, 64),
+                                            ((32, 8), 2, 64)])
+@pytest.mark.parametrize("n", [1, 3, 5, 900])
+def test_importance_of_the_tile_wide_kernels(tile, ppt, batch, n):
+    """Lists shorter than a round of four entries, with remainders and over
+    several batches, one to four waves to a tile: the scores are those of the
+    kernels for small splats to FP32 sums in another order (at most 256 weights
+    each: 256 x 2^-24), and the maxima the same bits."""
+    from paper_2412_20522_amd.raster import Rasterizer
+    s = scenegen.small_scene(n, 131, 77, seed=930 + n, sh_degree=0, log_scale_mean=-2.0, opacity_mean=-2.0)
+    s["masks"][::5] = 0.5
+    away = _big()
+    away["viewmat"] = np.array(away["viewmat"], np.float64).reshape(4, 4)
+    away["viewmat"][2, 3] -= 1e4  # everything behind this view: the tiles count, nothing is in them
+    dev = U.to_device(s)
+    params = {k: dev[k] for k in U.PARAM_KEYS}
+    rast = Rasterizer(0, **_settings(tile, sh_degree=0, fwd_ppt=ppt, batch_depth=batch, stats=0))
+    out = []
+    for cams in ([s["cameras"][0]], [s["cameras"][0], away]):
+        frame = rast.acquire_frame()
+        img, isum, imax = rast.forward_importance(frame, params, dev["masks"], cams)
+        torch.cuda.synchronize()
+        rast.release_frame(frame)
+        out.append((img[:3 * 131 * 77].cpu().numpy(), isum.cpu().numpy(), imax.cpu().numpy()))
+    (i0, s0, m0), (i1, s1, m1) = out
+    assert np.array_equal(i0, i1) and np.array_equal(m0, m1)
+    assert (np.abs(s0 - s1) <= 256 * 2.0 ** -24 * np.abs(s0)).all() and (s0.max() > 0)
+
+
 @pytest.mark.parametrize("persistent", [0, 1])
 def test_tile_setup_in_one_workgroup_equals_several(persistent):
     """4096 tiles take the one-workgroup set-up; one tile more (a second view
