@@ -314,7 +314,7 @@ struct mgs_frame {
     // u32) of the forward's tile order from 256, of the backward's from 2304
     uint64_t* h_pinned = nullptr;  // read-back of misc
     uint64_t* h_device = nullptr;  // the same memory as the device sees it
-    uint32_t* keys_sorted() { return (uint32_t*)(sorted_in_alt ? keys_alt.p : keys.p); }
+    const void* keys_sorted() { return sorted_in_alt ? keys_alt.p : keys.p; }
     uint32_t* vals_sorted() { return (uint32_t*)(sorted_in_alt ? vals_alt.p : vals.p); }
     uint32_t* record_order() { return (uint32_t*)(order_in_alt ? rvals_alt.p : rvals.p); }
     // device flags: one of two words.  A plain forward uses the word that the
@@ -668,17 +668,23 @@ mgs_status forward_impl(mgs_frame* f, mgs_stream stream_, const mgs_gaussians* g
         if (!f->fine && (s = grow(ctx, f->stg, (size_t)want * 8 + 8))) return s;
     }
     f->capacity = (int64_t)std::min<size_t>(f->keys.bytes / 4, f->vals.bytes / 4);
+    const bool imp = imp_sum != nullptr;
+    if (imp && (s = grow(ctx, f->imp_acc, (size_t)f->n * 8 + 8))) return s;
+    const bool keys16 = cell_keys16(f->K, T + NR);
     // the duplication's launch also clears the ranges, the tile orders'
-    // histograms and cursors, the staged-entry counter and, in the plain path, the next forward's flags
+    // histograms and cursors, the staged-entry counter, the importance sums
+    // and, in the plain path, the next forward's flags
     const FillSpan zero[] = {{(uint32_t*)f->ranges.p, 2 * (T + NR), 0u},
                              {f->order_hist(), 1024, 0u},
                              {f->stg_count(), 2, 0u},
-                             {f->reserved ? nullptr : f->flag_words() + (f->flag_word ^ 1), 1, 0u}};
+                             {f->reserved ? nullptr : f->flag_words() + (f->flag_word ^ 1), 1, 0u},
+                             {imp ? (uint32_t*)f->imp_acc.p : nullptr, 2 * f->n, 0u},
+                             {imp ? (uint32_t*)imp_max : nullptr, f->n, 0u}};
     {
         StageTimer t(ctx, stream, MGS_STAGE_DUPLICATE);
         launch_duplicate_lists(stream, (const float*)f->srec.p, (const uint32_t*)f->cnt_sorted.p,
                                (const uint32_t*)f->cells.p,
-                               (uint32_t*)f->cls_part.p, R, f->n, f->views, f->st, (uint32_t*)f->keys.p,
+                               (uint32_t*)f->cls_part.p, R, f->n, f->views, f->st, f->keys.p, keys16,
                                (uint32_t*)f->vals.p, f->K, f->flags(), zero, (int)(sizeof zero / sizeof *zero));
     }
     if (!f->reserved) f->flag_clear[f->flag_word ^ 1] = true;
@@ -688,15 +694,15 @@ mgs_status forward_impl(mgs_frame* f, mgs_stream stream_, const mgs_gaussians* g
     bool in_alt = false, have_ranges = false;
     {
         StageTimer t(ctx, stream, MGS_STAGE_SORT);
-        have_ranges = launch_radix_sort32(stream, (uint32_t*)f->keys.p, (uint32_t*)f->vals.p,
-                                          (uint32_t*)f->keys_alt.p, (uint32_t*)f->vals_alt.p, f->K, K_dev, 0,
-                                          8 * f->sort_passes, f->sort_tmp.p, &in_alt, (uint32_t*)f->ranges.p, T + NR);
+        have_ranges = launch_cell_sort(stream, f->keys.p, (uint32_t*)f->vals.p, f->keys_alt.p,
+                                       (uint32_t*)f->vals_alt.p, keys16, f->K, K_dev, 8 * f->sort_passes,
+                                       f->sort_tmp.p, &in_alt, (uint32_t*)f->ranges.p, T + NR);
     }
     f->sorted_in_alt = in_alt;
     {
         StageTimer t(ctx, stream, MGS_STAGE_RANGES);
         if (!have_ranges)
-            launch_tile_ranges32(stream, f->keys_sorted(), f->K, K_dev, T + NR, (uint32_t*)f->ranges.p, true);
+            launch_cell_ranges(stream, f->keys_sorted(), keys16, f->K, K_dev, T + NR, (uint32_t*)f->ranges.p);
         // the forward takes the most expensive tiles first: by the batches the
         // last forward over the same views took, else by list length
         const bool measured = f->order_valid && std::memcmp(&f->order_views, &f->views, sizeof(ViewSet)) == 0;
@@ -705,12 +711,6 @@ mgs_status forward_impl(mgs_frame* f, mgs_stream stream_, const mgs_gaussians* g
                           measured ? (const uint32_t*)f->nbatch.p : nullptr, (uint32_t*)f->tcost.p,
                           (uint32_t*)f->cur_off.p, f->cur_need(), (uint32_t*)f->caps.p, f->order_hist(),
                           (uint32_t*)f->order.p, (uint32_t*)f->nbatch.p);
-    }
-    const bool imp = imp_sum != nullptr;
-    if (imp) {
-        if ((s = grow(ctx, f->imp_acc, (size_t)f->n * 8 + 8))) return s;
-        launch_fill_u32(stream, (uint32_t*)f->imp_acc.p, 2 * f->n, 0u);
-        launch_fill_u32(stream, (uint32_t*)imp_max, f->n, 0u);
     }
     // the compositing clears the backward's accumulator (sized here; a fixed
     // workspace already holds it)

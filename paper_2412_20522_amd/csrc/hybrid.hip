@@ -694,8 +694,8 @@ __global__ void __launch_bounds__(LO_GROUP) list_offsets_one_kernel(const uint32
 __global__ void __launch_bounds__(256) duplicate_kernel(
     const float4* __restrict__ srec, const uint32_t* __restrict__ cnt_sorted,
     const uint4* __restrict__ cells, ListOffsets lo, int64_t R, int64_t n, ViewSet views, DevSettings st,
-    uint32_t* __restrict__ keys, uint32_t* __restrict__ vals, int64_t capacity, uint32_t* __restrict__ flags,
-    FillSet fs) {
+    void* __restrict__ keys, bool keys16, uint32_t* __restrict__ vals, int64_t capacity,
+    uint32_t* __restrict__ flags, FillSet fs) {
     // the clears of the later stages ride along (a launch of their own: 4 us)
     for (int64_t f = (int64_t)blockIdx.x * 256 + threadIdx.x; f < fs.total; f += (int64_t)gridDim.x * 256)
         fill_element(fs, f);
@@ -750,7 +750,8 @@ __global__ void __launch_bounds__(256) duplicate_kernel(
     const int64_t wave = uniform((int)(i0 / 64) + (t >> 6));
     const int64_t base = (int64_t)(lo.wave_rel[wave] + lo.group_off[wave / LO_GROUP]);
     const uint32_t lim = (uint32_t)max((int64_t)0, min((int64_t)total, capacity - base));
-    uint32_t* kw = keys + base;
+    uint32_t* kw = reinterpret_cast<uint32_t*>(keys) + base;
+    uint16_t* kh = reinterpret_cast<uint16_t*>(keys) + base;
     uint32_t* vw = vals + base;
     uint32_t out = 0;
     int rcarry = -1;
@@ -788,7 +789,8 @@ __global__ void __launch_bounds__(256) duplicate_kernel(
             const uint2 run = s_run[wb + slot_owner(s_own + wb, lane, nrun > 0, nfirst, e0, ecarry)];
             const uint32_t e = e0 + (uint32_t)lane, o = out + e;
             if (e < ntot && o < lim) {
-                kw[o] = run.x + e;
+                if (keys16) kh[o] = (uint16_t)(run.x + e);
+                else kw[o] = run.x + e;
                 vw[o] = run.y;
             }
         }
@@ -796,7 +798,8 @@ __global__ void __launch_bounds__(256) duplicate_kernel(
         out += ntot;
     }
     for (uint32_t o = out + (uint32_t)lane; o < lim; o += 64) {
-        kw[o] = KEY_NONE;
+        if (keys16) kh[o] = (uint16_t)KEY_NONE;
+        else kw[o] = KEY_NONE;
         vw[o] = 0u;
     }
     if (lim < total && lane == 0) atomicOr(flags, FLAG_CAPACITY);
@@ -2475,8 +2478,9 @@ void launch_list_offsets(hipStream_t stream, uint32_t* part, int64_t R, uint64_t
 
 void launch_duplicate_lists(hipStream_t stream, const float* srec, const uint32_t* cnt_sorted,
                             const uint32_t* cells, uint32_t* part, int64_t R,
-                            int64_t n, const ViewSet& views, const DevSettings& st, uint32_t* keys, uint32_t* vals,
-                            int64_t capacity, uint32_t* flags, const FillSpan* fill, int fill_count) {
+                            int64_t n, const ViewSet& views, const DevSettings& st, void* keys, bool keys16,
+                            uint32_t* vals, int64_t capacity, uint32_t* flags, const FillSpan* fill,
+                            int fill_count) {
     if (R == 0) {
         launch_fill_spans(stream, fill, fill_count);
         return;
@@ -2484,7 +2488,7 @@ void launch_duplicate_lists(hipStream_t stream, const float* srec, const uint32_
     hipLaunchKernelGGL(duplicate_kernel, dim3(blocks_of(R)), dim3(256), 0, stream,
                        reinterpret_cast<const float4*>(srec), cnt_sorted, reinterpret_cast<const uint4*>(cells),
                        list_offsets(part, R), R,
-                       n, views, st, keys, vals, capacity, flags, make_fill_set(fill, fill_count));
+                       n, views, st, keys, keys16, vals, capacity, flags, make_fill_set(fill, fill_count));
 }
 
 void launch_tile_order(hipStream_t stream, const uint32_t* key, uint32_t tiles, uint32_t* hist_cursor,

@@ -16,6 +16,7 @@
 // digit's row of them, then a stable scatter); it has no inter-block spin
 // waits, so it needs no forward-progress guarantee between workgroups.
 #include <mutex>
+#include <type_traits>
 
 #include "common.hpp"
 #include "kernels.hpp"
@@ -234,6 +235,10 @@ __device__ __forceinline__ int64_t live_count(int64_t K, const uint64_t* K_dev) 
     return (int64_t)(k < (uint64_t)K ? k : (uint64_t)K);
 }
 
+// Keys in registers (16-bit ones take a whole one).
+template <typename KeyT>
+using KeyReg = std::conditional_t<sizeof(KeyT) == 2, uint32_t, KeyT>;
+
 template <typename KeyT>
 __device__ __forceinline__ uint32_t digit_of(KeyT k, int shift) {
     return (uint32_t)(k >> shift) & (RADIX - 1);
@@ -309,7 +314,12 @@ __global__ void __launch_bounds__(NT) radix_upsweep_kernel(const KeyT* __restric
         KeyT k[VEC];
         int nv = 0;
         if (i0 + VEC <= cend) {
-            if constexpr (VEC == 4) {
+            if constexpr (VEC == 8) {
+                const uint4 q = *reinterpret_cast<const uint4*>(keys + i0);
+                const uint32_t qs[4] = {q.x, q.y, q.z, q.w};
+#pragma unroll
+                for (int v = 0; v < VEC; ++v) k[v] = (KeyT)(qs[v / 2] >> (16 * (v & 1)));
+            } else if constexpr (VEC == 4) {
                 const uint4 q = *reinterpret_cast<const uint4*>(keys + i0);
                 k[0] = q.x; k[1] = q.y; k[2] = q.z; k[3] = q.w;
             } else {
@@ -453,7 +463,7 @@ radix_downsweep_kernel(
 
     // wave w owns the contiguous span [w * 64 SIPT, (w + 1) * 64 SIPT) of the tile;
     // round j covers 64 consecutive items, lane l the (j * 64 + l)-th
-    KeyT key[SIPT];
+    KeyReg<KeyT> key[SIPT];
     uint32_t val[SIPT];
     uint32_t rank[SIPT];
     // one address per array: the rounds are constant offsets from it
@@ -466,7 +476,7 @@ radix_downsweep_kernel(
             key[j] = kp[j * 64];
             val[j] = vp[j * 64];
         } else {
-            key[j] = ~(KeyT)0;  // digit 255 at every shift, ranked after every valid item
+            key[j] = ~(KeyReg<KeyT>)0;  // digit 255 at every shift, ranked after every valid item
             val[j] = 0u;
         }
     }
@@ -514,7 +524,7 @@ radix_downsweep_kernel(
     for (int j = 0; j < SIPT; ++j) {
         const uint32_t d = digit_of(key[j], shift);
         const uint32_t pos = dstart[d] + wcnt[w][d] + rank[j];
-        sk[pos] = key[j];
+        sk[pos] = (KeyT)key[j];
         sv[pos] = val[j];
     }
     __syncthreads();
@@ -667,8 +677,10 @@ __global__ void __launch_bounds__(256) tile_ranges_kernel(const KeyT* __restrict
 }
 
 // The same for 32-bit keys, four consecutive keys per thread (one 16-byte
-// load of keys 4 j .. 4 j + 3 and the key before them).
-__global__ void __launch_bounds__(256) tile_ranges4_kernel(const uint32_t* __restrict__ keys, int64_t Kcap,
+// load of keys 4 j .. 4 j + 3 and the key before them), or 16-bit ones (8
+// bytes).
+template <typename KeyT>
+__global__ void __launch_bounds__(256) tile_ranges4_kernel(const KeyT* __restrict__ keys, int64_t Kcap,
                                                             const uint64_t* __restrict__ K_dev, uint64_t nbins,
                                                             uint2* __restrict__ ranges) {
     const int64_t K = live_count(Kcap, K_dev);
@@ -676,8 +688,13 @@ __global__ void __launch_bounds__(256) tile_ranges4_kernel(const uint32_t* __res
     if (k0 >= K) return;
     uint32_t v[4];
     if (k0 + 4 <= K) {
-        const uint4 q = *reinterpret_cast<const uint4*>(keys + k0);
-        v[0] = q.x; v[1] = q.y; v[2] = q.z; v[3] = q.w;
+        if constexpr (sizeof(KeyT) == 2) {
+            const uint2 q = *reinterpret_cast<const uint2*>(keys + k0);
+            v[0] = q.x & 0xffffu; v[1] = q.x >> 16; v[2] = q.y & 0xffffu; v[3] = q.y >> 16;
+        } else {
+            const uint4 q = *reinterpret_cast<const uint4*>(keys + k0);
+            v[0] = q.x; v[1] = q.y; v[2] = q.z; v[3] = q.w;
+        }
     } else {
 #pragma unroll
         for (int i = 0; i < 4; ++i) v[i] = k0 + i < K ? keys[k0 + i] : 0u;
@@ -751,7 +768,7 @@ __global__ void __launch_bounds__(NT) sum_i32x4_partial_kernel(const int4* __res
 
 // seg_len > 0: the keys form segments of seg_len keys, each sorted on its own
 // (no device-side count then); otherwise one segment.
-// ranges, nbins: as launch_radix_sort32; returns whether they were written.
+// ranges, nbins: as launch_cell_sort; returns whether they were written.
 template <typename KeyT>
 bool radix_sort_t(hipStream_t stream, KeyT* keys, uint32_t* vals, KeyT* keys_alt, uint32_t* vals_alt, int64_t K,
                   const uint64_t* K_dev, int begin_bit, int end_bit, void* scratch, bool* out_in_alt,
@@ -891,11 +908,16 @@ void launch_radix_sort(hipStream_t stream, uint64_t* keys, uint32_t* vals, uint6
     radix_sort_t<uint64_t>(stream, keys, vals, keys_alt, vals_alt, K, K_dev, 0, key_bits, scratch, out_in_alt);
 }
 
-bool launch_radix_sort32(hipStream_t stream, uint32_t* keys, uint32_t* vals, uint32_t* keys_alt, uint32_t* vals_alt,
-                         int64_t K, const uint64_t* K_dev, int begin_bit, int end_bit, void* scratch,
-                         bool* out_in_alt, uint32_t* ranges, int64_t nbins) {
-    return radix_sort_t<uint32_t>(stream, keys, vals, keys_alt, vals_alt, K, K_dev, begin_bit, end_bit, scratch,
-                                  out_in_alt, 0, ranges, nbins);
+bool cell_keys16(int64_t K, int64_t cells) { return cells < 0xffff && K > SHORT_MAX; }
+
+bool launch_cell_sort(hipStream_t stream, void* keys, uint32_t* vals, void* keys_alt, uint32_t* vals_alt, bool keys16,
+                      int64_t K, const uint64_t* K_dev, int bits, void* scratch, bool* out_in_alt, uint32_t* ranges,
+                      int64_t nbins) {
+    if (keys16)
+        return radix_sort_t<uint16_t>(stream, (uint16_t*)keys, vals, (uint16_t*)keys_alt, vals_alt, K, K_dev, 0, bits,
+                                      scratch, out_in_alt);
+    return radix_sort_t<uint32_t>(stream, (uint32_t*)keys, vals, (uint32_t*)keys_alt, vals_alt, K, K_dev, 0, bits,
+                                  scratch, out_in_alt, 0, ranges, nbins);
 }
 
 void launch_radix_sort_segmented(hipStream_t stream, uint32_t* keys, uint32_t* vals, uint32_t* keys_alt,
@@ -912,13 +934,18 @@ void launch_tile_ranges(hipStream_t stream, const uint64_t* keys, int64_t K, con
                        K_dev, 32, (uint64_t)total_tiles, reinterpret_cast<uint2*>(ranges));
 }
 
-void launch_tile_ranges32(hipStream_t stream, const uint32_t* keys, int64_t K, const uint64_t* K_dev,
-                          int64_t total_tiles, uint32_t* ranges, bool cleared) {
-    if (!cleared) launch_fill_u32(stream, ranges, 2 * total_tiles, 0u);
+void launch_cell_ranges(hipStream_t stream, const void* keys, bool keys16, int64_t K, const uint64_t* K_dev,
+                        int64_t cells, uint32_t* ranges) {
     if (K == 0) return;
     // keys come from the library's own buffers (16-byte aligned)
-    hipLaunchKernelGGL(tile_ranges4_kernel, dim3((unsigned)((K + 1023) / 1024)), dim3(256), 0, stream, keys, K, K_dev,
-                       (uint64_t)total_tiles, reinterpret_cast<uint2*>(ranges));
+    const dim3 grid((unsigned)((K + 1023) / 1024));
+    uint2* r = reinterpret_cast<uint2*>(ranges);
+    if (keys16)
+        hipLaunchKernelGGL(tile_ranges4_kernel<uint16_t>, grid, dim3(256), 0, stream, (const uint16_t*)keys, K, K_dev,
+                           (uint64_t)cells, r);
+    else
+        hipLaunchKernelGGL(tile_ranges4_kernel<uint32_t>, grid, dim3(256), 0, stream, (const uint32_t*)keys, K, K_dev,
+                           (uint64_t)cells, r);
 }
 
 void launch_fill_u32(hipStream_t stream, uint32_t* p, int64_t n, uint32_t value) {

@@ -144,6 +144,48 @@ def test_depth_order_and_lists_over_the_sort_variants(n, views):
     assert step.all()
 
 
+@pytest.mark.parametrize("w,h", [(1928, 2024), (1928, 2032), (2048, 2048)])
+@pytest.mark.parametrize("cull", [0, 1])
+def test_lists_on_both_sides_of_16_bit_cell_keys(w, h, cull):
+    """60,973 and 61,214 tiles of 8x8 with 3,904 regions (64,877 and 65,118
+    cells, 16-bit keys), 65,536 tiles with 4,096 (32-bit): every cell's list
+    holds the records whose rectangle reaches it."""
+    from paper_2412_20522_amd import maskgs as M
+    from paper_2412_20522_amd.raster import Rasterizer
+    n = 30_000
+    s = scenegen.small_scene(n, w, h, seed=940, sh_degree=0, log_scale_mean=-4.0)
+    s["means"][::7] *= 3.0  # some near the edges and outside
+    dev = U.to_device(s)
+    rast = Rasterizer(0, **_settings((8, 8), sh_degree=0, tile_cull=cull, wide_tiles=-1))
+    frame = rast.acquire_frame()
+    rast.forward(frame, {k: dev[k] for k in U.PARAM_KEYS}, dev["masks"], s["cameras"])
+    ex = {k: M.mgs_frame_export(rast.ctx, frame, k) for k in ("records", "radius", "order", "tiles", "values", "ranges")}
+    torch.cuda.synchronize()
+    K, T = rast.stats(frame)["n_instances"], rast.stats(frame)["total_tiles"]
+    rast.release_frame(frame)
+    assert K > 16384 and T == ((w + 7) // 8) * ((h + 7) // 8)
+    order, tiles = U.u32(ex["order"]), U.u32(ex["tiles"]).astype(np.int64)
+    r = U.u32(ex["ranges"]).reshape(-1, 2).astype(np.int64)[:T]
+    vals = U.u32(ex["values"]).astype(np.int64)[:K]
+    length = r[:, 1] - r[:, 0]
+    assert length.sum() == K and (length >= 0).all()
+    cell = np.full(K, -1, np.int64)
+    for c in np.flatnonzero(length):
+        cell[r[c, 0]:r[c, 1]] = c
+        assert (np.diff(vals[r[c, 0]:r[c, 1]]) > 0).all()
+    assert (cell >= 0).all()
+    rec = ex["records"].cpu().numpy().reshape(-1, 12).astype(np.float64)
+    rad = ex["radius"].cpu().numpy().astype(np.float64)
+    g = order[vals]
+    gw, gh = (w + 7) // 8, (h + 7) // 8
+    lo = lambda c, k: np.maximum(np.floor((rec[g, c] - rad[g]) / 8), 0)
+    hi = lambda c, k: np.minimum(np.floor((rec[g, c] + rad[g]) / 8), k - 1)
+    cx, cy = cell % gw, cell // gw
+    assert ((cx >= lo(0, gw)) & (cx <= hi(0, gw)) & (cy >= lo(1, gh)) & (cy <= hi(1, gh))).all()
+    if not cull:
+        assert K == tiles.sum() and np.array_equal(np.bincount(g, minlength=n), tiles)
+
+
 @pytest.mark.parametrize("size", [(60, 70), (300, 130), (1030, 520)])
 @pytest.mark.parametrize("wide", [-1, 4, 40])
 @pytest.mark.parametrize("n", [3, 64, 1500])
