@@ -518,10 +518,25 @@ struct ListOffsets {
     uint64_t* group_off;  // [groups]
 };
 
+// Inclusive sums within each 16 lanes, and a lane's value in every lane.
+__device__ __forceinline__ uint64_t waves_scan(uint64_t x) {
+    static_assert(LO_GROUP / 64 == 16, "one lane per wave");
+#pragma unroll
+    for (int d = 1; d < 16; d <<= 1) {
+        const uint64_t y = __shfl_up(x, d, 16);
+        if ((lane_id() & 15) >= d) x += y;
+    }
+    return x;
+}
+__device__ __forceinline__ uint64_t read_lane(uint64_t x, int l) {
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)x, l);
+    return (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(x >> 32), l) << 32 | lo;
+}
+
 __global__ void __launch_bounds__(LO_GROUP) list_offsets_group_kernel(const uint32_t* __restrict__ part, int64_t nb,
                                                                      int64_t nw, ListOffsets lo, int sizes) {
     __shared__ uint64_t s_w[LO_GROUP / 64][5];
-    const int t = threadIdx.x, lane = lane_id(), wid = t >> 6;
+    const int t = threadIdx.x, lane = lane_id(), wid = uniform(t >> 6);
     const int64_t w = (int64_t)blockIdx.x * LO_GROUP + t;  // this thread's wave
     const uint64_t c = w < nw ? part[2 * nb + w] : 0u;
     // the group's classification workgroups: LO_GROUP / 4 of them
@@ -545,11 +560,11 @@ __global__ void __launch_bounds__(LO_GROUP) list_offsets_group_kernel(const uint
         if (lane == 0) s_w[wid][1 + k] = sum[k];
     }
     __syncthreads();
-    uint64_t wo = 0;
-    for (int v = 0; v < wid; ++v) wo += s_w[v][0];
-    if (w < nw) lo.wave_rel[w] = wo + x - c;
+    const uint64_t ws = waves_scan(s_w[lane & 15][0]);
+    if (w < nw) lo.wave_rel[w] = (wid > 0 ? read_lane(ws, wid - 1) : 0u) + x - c;
     if (t < 5) {
         uint64_t tot = 0;
+#pragma unroll
         for (int v = 0; v < LO_GROUP / 64; ++v) tot += s_w[v][t];
         lo.group_tot[5 * blockIdx.x + t] = tot;
     }
@@ -585,7 +600,7 @@ __device__ __forceinline__ void put_totals(const ListTotals& o, int k, uint64_t 
 
 __global__ void __launch_bounds__(LO_GROUP) list_offsets_total_kernel(int64_t ng, ListOffsets lo, ListTotals out) {
     __shared__ uint64_t s_w[LO_GROUP / 64][5];
-    const int t = threadIdx.x, lane = lane_id(), wid = t >> 6;
+    const int t = threadIdx.x, lane = lane_id(), wid = uniform(t >> 6);
     uint64_t carry = 0, sum[4] = {0, 0, 0, 0};
     for (int64_t base = 0; base < ng; base += LO_GROUP) {
         const int64_t g = base + t;
@@ -602,13 +617,9 @@ __global__ void __launch_bounds__(LO_GROUP) list_offsets_total_kernel(int64_t ng
         }
         if (lane == 63) s_w[wid][0] = x;
         __syncthreads();
-        uint64_t wo = 0, tot = 0;
-        for (int v = 0; v < LO_GROUP / 64; ++v) {
-            if (v < wid) wo += s_w[v][0];
-            tot += s_w[v][0];
-        }
-        if (g < ng) lo.group_off[g] = carry + wo + x - c;
-        carry += tot;
+        const uint64_t ws = waves_scan(s_w[lane & 15][0]);
+        if (g < ng) lo.group_off[g] = carry + (wid > 0 ? read_lane(ws, wid - 1) : 0u) + x - c;
+        carry += read_lane(ws, 15);
         __syncthreads();  // s_w is written again by the next round
     }
 #pragma unroll
@@ -621,46 +632,61 @@ __global__ void __launch_bounds__(LO_GROUP) list_offsets_total_kernel(int64_t ng
         uint64_t tot = carry;
         if (t > 0) {
             tot = 0;
+#pragma unroll
             for (int v = 0; v < LO_GROUP / 64; ++v) tot += s_w[v][t];
         }
         put_totals(out, t, tot);
     }
 }
 
-// Both steps in one workgroup, for at most LO_ONE groups: a group takes about
-// as long here as the launch it saves (4.6 us).
+// Both steps in one workgroup, for at most LO_ONE groups, whose loads and scans
+// go side by side (10.4 -> 8.9 us for four; the two launches: 10.3 us; a second
+// round of groups: 12.6 us).
 constexpr int64_t LO_ONE = 4;
+constexpr int LO_ROUND = 4;
 __global__ void __launch_bounds__(LO_GROUP) list_offsets_one_kernel(const uint32_t* __restrict__ part, int64_t nb,
                                                                    int64_t nw, int64_t ng, ListOffsets lo, int sizes,
                                                                    ListTotals out) {
     __shared__ uint64_t s_w[LO_GROUP / 64][5];
-    const int t = threadIdx.x, lane = lane_id(), wid = t >> 6;
+    const int t = threadIdx.x, lane = lane_id(), wid = uniform(t >> 6);
     uint64_t carry = 0, sum[4] = {0, 0, 0, 0};
     for (int64_t b = t; b < nb; b += LO_GROUP) {
 #pragma unroll
         for (int k = 0; k < 4; ++k)
             if (k < 2 || sizes) sum[k] += part[(k < 2 ? k : k + 4) * nb + b];
     }
-    for (int64_t g = 0; g < ng; ++g) {
-        const int64_t w = g * LO_GROUP + t;
-        const uint64_t c = w < nw ? part[2 * nb + w] : 0u;
-        uint64_t x = c;
+    __shared__ uint64_t s_g[LO_GROUP / 64][LO_ROUND];
+    for (int64_t g0 = 0; g0 < ng; g0 += LO_ROUND) {
+        // the groups' loads and scans side by side
+        uint64_t c[LO_ROUND], x[LO_ROUND];
+#pragma unroll
+        for (int j = 0; j < LO_ROUND; ++j) {
+            const int64_t w = (g0 + j) * LO_GROUP + t;
+            x[j] = c[j] = w < nw ? part[2 * nb + w] : 0u;
+        }
 #pragma unroll
         for (int d = 1; d < 64; d <<= 1) {
-            const uint64_t y = __shfl_up(x, d);
-            if (lane >= d) x += y;
+#pragma unroll
+            for (int j = 0; j < LO_ROUND; ++j) {
+                const uint64_t y = __shfl_up(x[j], d);
+                if (lane >= d) x[j] += y;
+            }
         }
-        if (lane == 63) s_w[wid][0] = x;
+#pragma unroll
+        for (int j = 0; j < LO_ROUND; ++j)
+            if (lane == 63) s_g[wid][j] = x[j];
         __syncthreads();
-        uint64_t wo = 0, tot = 0;
-        for (int v = 0; v < LO_GROUP / 64; ++v) {
-            if (v < wid) wo += s_w[v][0];
-            tot += s_w[v][0];
+        // lanes 16 j + v: the inclusive sums of group j's waves up to v
+        const uint64_t ws = waves_scan(s_g[lane & 15][lane >> 4]);
+#pragma unroll
+        for (int j = 0; j < LO_ROUND; ++j) {
+            const int64_t w = (g0 + j) * LO_GROUP + t;
+            const uint64_t wo = wid > 0 ? read_lane(ws, 16 * j + wid - 1) : 0u;
+            if (w < nw) lo.wave_rel[w] = wo + x[j] - c[j];
+            if (t == 0 && g0 + j < ng) lo.group_off[g0 + j] = carry;
+            carry += read_lane(ws, 16 * j + 15);
         }
-        if (w < nw) lo.wave_rel[w] = wo + x - c;
-        if (t == 0) lo.group_off[g] = carry;
-        carry += tot;
-        __syncthreads();  // s_w is written again
+        __syncthreads();  // s_g is written again
     }
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
@@ -672,6 +698,7 @@ __global__ void __launch_bounds__(LO_GROUP) list_offsets_one_kernel(const uint32
         uint64_t tot = carry;
         if (t > 0) {
             tot = 0;
+#pragma unroll
             for (int v = 0; v < LO_GROUP / 64; ++v) tot += s_w[v][t];
         }
         put_totals(out, t, tot);
@@ -963,8 +990,9 @@ __global__ void __launch_bounds__(256) order_offsets_kernel(const uint32_t* key,
 }
 
 // batch_caps_kernel and order_offsets_kernel in one workgroup, for at most
-// SETUP_ONE tiles (2,500 tiles: 8.4 -> 5 us, and one launch fewer).
-constexpr int SETUP_DT = 1024, SETUP_PER = 4;
+// SETUP_ONE tiles (64 tiles 4 us, 478 tiles 5.2 us; 2,500 tiles 8.5 us, 4,080
+// tiles 11.5 us, where the two launches take 8 to 9 us).
+constexpr int SETUP_DT = 1024, SETUP_PER = 2;
 constexpr uint32_t SETUP_ONE = SETUP_DT * SETUP_PER;
 __global__ void __launch_bounds__(SETUP_DT) tile_setup_kernel(const uint2* __restrict__ ranges, ViewSet views, int batch,
                                                                const uint32_t* key, uint32_t* __restrict__ cost,
@@ -978,23 +1006,29 @@ __global__ void __launch_bounds__(SETUP_DT) tile_setup_kernel(const uint2* __res
     if (t < 256) h[t] = 0u;
     __syncthreads();
     uint32_t c[SETUP_PER], bin[SETUP_PER];
+    uint2 r1[SETUP_PER], r2[SETUP_PER];
 #pragma unroll
-    for (int k = 0; k < SETUP_PER; ++k) {
-        const uint32_t i = (uint32_t)(k * SETUP_DT + t);
-        c[k] = 0u;
-        bin[k] = 0u;
-        if (i >= views.total_tiles) continue;
+    for (int k = 0; k < SETUP_PER; ++k) {  // the loads first
+        const uint32_t i = min((uint32_t)(k * SETUP_DT + t), views.total_tiles - 1u);
         int vi = 0;
         while (vi + 1 < views.n_views && i >= views.v[vi + 1].tile_off) ++vi;
         const DevView& cam = views.v[vi];
         const uint32_t lt = i - cam.tile_off;
-        const int tx = (int)(lt % (uint32_t)cam.grid_w), ty = (int)(lt / (uint32_t)cam.grid_w);
-        const uint2 r1 = ranges[i], r2 = ranges[region_of_tile(tx, ty, cam, views)];
-        const uint32_t len1 = r1.y - r1.x, len2 = r2.y - r2.x;
+        const int ty = (int)(lt / (uint32_t)cam.grid_w), tx = (int)(lt - (uint32_t)ty * (uint32_t)cam.grid_w);
+        r1[k] = ranges[i];
+        r2[k] = ranges[region_of_tile(tx, ty, cam, views)];
+        bin[k] = key ? key[i] : 0u;
+    }
+#pragma unroll
+    for (int k = 0; k < SETUP_PER; ++k) {
+        const uint32_t i = (uint32_t)(k * SETUP_DT + t);
+        c[k] = 0u;
+        if (i >= views.total_tiles) continue;
+        const uint32_t len1 = r1[k].y - r1[k].x, len2 = r2[k].y - r2[k].x;
         c[k] = 2u * ((len1 + batch - 1) / batch + (len2 + batch - 1) / batch) + 2u;
         const uint32_t ck = min((len1 + len2) >> 3, 255u);
         cost[i] = ck;
-        bin[k] = 255u - min(key ? key[i] : ck, 255u);
+        bin[k] = 255u - min(key ? bin[k] : ck, 255u);
         atomicAdd(&h[bin[k]], 1u);
     }
     // checkpoint offsets: exclusive prefix over the tiles in index order

@@ -104,8 +104,10 @@ constexpr int sort_tile() {
 constexpr int SORT_TILE_MIN = NT * 8;  // the smallest sort tile (sizes the histograms)
 constexpr int64_t MAX_SORT_SEGMENTS = 16;  // segments of a segmented sort (one per view)
 constexpr int64_t SHORT_MAX = 16384;       // longest segment sorted in one workgroup's LDS
-// segments of up to this many blocks need no row scan
-constexpr int64_t OWN_SCAN_BLOCKS = 96;
+// Segments of up to this many blocks need no row scan: 98 blocks, a pass's
+// launches 16.7 us with their own sums, 18.7 with a row scan; 160 blocks 17 and
+// 17, 366 blocks 28 and 24 us.
+constexpr int64_t OWN_SCAN_BLOCKS = 128;
 
 // Keys per workgroup of the sort: the host's chunk for a known count; with a
 // device-side live count, the live keys are spread evenly over the nb
@@ -431,11 +433,28 @@ radix_downsweep_kernel(
             const uint32_t* h = row_pre + sg.seg * nbs * RADIX + threadIdx.x % RADIX;
             const int64_t b0 = threadIdx.x / RADIX;
             pre = own = 0;
-#pragma unroll 8
-            for (int64_t b = b0; b < nbs; b += PER) {
-                const uint32_t c = h[b * RADIX];
-                own += c;
-                pre += b < sg.bl ? c : 0u;
+            constexpr uint32_t ROUND = 8;  // loads in flight
+            const uint32_t n = (uint32_t)nbs, bl = (uint32_t)sg.bl;
+            uint32_t b = (uint32_t)b0;
+            for (; b + PER * (ROUND - 1) < n; b += PER * ROUND) {
+                uint32_t c[ROUND];
+#pragma unroll
+                for (uint32_t j = 0; j < ROUND; ++j) c[j] = h[(b + PER * j) * RADIX];
+#pragma unroll
+                for (uint32_t j = 0; j < ROUND; ++j) {
+                    own += c[j];
+                    pre += b + PER * j < bl ? c[j] : 0u;
+                }
+            }
+            if (b < n) {
+                uint32_t c[ROUND];
+#pragma unroll
+                for (uint32_t j = 0; j < ROUND; ++j) c[j] = b + PER * j < n ? h[(b + PER * j) * RADIX] : 0u;
+#pragma unroll
+                for (uint32_t j = 0; j < ROUND; ++j) {
+                    own += c[j];
+                    pre += b + PER * j < bl ? c[j] : 0u;
+                }
             }
             if constexpr (PER > 1) {
                 static_assert(PER == 2, "one partner per digit");

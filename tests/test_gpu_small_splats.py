@@ -254,11 +254,11 @@ def test_importance_of_the_tile_wide_kernels(tile, ppt, batch, n):
 
 @pytest.mark.parametrize("persistent", [0, 1])
 def test_tile_setup_in_one_workgroup_equals_several(persistent):
-    """4096 tiles take the one-workgroup set-up; one tile more (a second view
+    """2048 tiles take the one-workgroup set-up; one tile more (a second view
     of one pixel) the two-kernel one: same images, also on a workspace fixed
     from each set-up's checkpoint count."""
     from paper_2412_20522_amd.raster import Rasterizer
-    s = scenegen.small_scene(20_000, 1024, 1024, seed=77, sh_degree=1, log_scale_mean=-2.5)
+    s = scenegen.small_scene(20_000, 1024, 512, seed=77, sh_degree=1, log_scale_mean=-2.5)
     dev = U.to_device(s)
     params = {k: dev[k] for k in U.PARAM_KEYS}
     rast = Rasterizer(0, **_settings((16, 16), persistent=persistent, wide_tiles=8))
@@ -267,10 +267,10 @@ def test_tile_setup_in_one_workgroup_equals_several(persistent):
     out = []
     for cams in (one, two):
         frame = rast.acquire_frame()
-        plain = rast.forward(frame, params, dev["masks"], cams)[:3 * 1024 * 1024].clone()
-        again = rast.forward(frame, params, dev["masks"], cams)[:3 * 1024 * 1024].clone()  # measured order
+        plain = rast.forward(frame, params, dev["masks"], cams)[:3 * 1024 * 512].clone()
+        again = rast.forward(frame, params, dev["masks"], cams)[:3 * 1024 * 512].clone()  # measured order
         rast.reserve(frame, 1.0)
-        fixed = rast.forward(frame, params, dev["masks"], cams)[:3 * 1024 * 1024].clone()
+        fixed = rast.forward(frame, params, dev["masks"], cams)[:3 * 1024 * 512].clone()
         rast.check(frame)
         rast.reserve(frame, 0)
         rast.release_frame(frame)
