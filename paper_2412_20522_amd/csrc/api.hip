@@ -328,6 +328,7 @@ struct mgs_frame {
     uint64_t* total() { return (uint64_t*)((char*)misc.p + 8); }
     uint64_t* wide_counts() { return (uint64_t*)((char*)misc.p + 16); }
     uint64_t* cur_need() { return (uint64_t*)((char*)misc.p + 24); }
+    uint32_t* live() { return (uint32_t*)((char*)misc.p + 64); }  // per view: records with tiles
     uint32_t* stg_count() { return (uint32_t*)((char*)misc.p + 192); }
     uint32_t* order_hist() { return (uint32_t*)((char*)misc.p + 256); }
     uint32_t* order_hist_b() { return order_hist() + 512; }
@@ -595,7 +596,7 @@ mgs_status forward_impl(mgs_frame* f, mgs_stream stream_, const mgs_gaussians* g
         StageTimer t(ctx, stream, MGS_STAGE_PROJECT);
         // the radius stays in the records (B.w); the export reads it there
         launch_project_fwd(stream, *g, f->views, f->st, (float*)f->rec.p, (float*)f->depth.p, nullptr,
-                           (uint32_t*)f->tiles.p, f->flags(), (uint32_t*)f->rkeys.p, (uint32_t*)f->rvals.p);
+                           (uint32_t*)f->tiles.p, f->flags(), (uint32_t*)f->rkeys.p);
     }
     {
         // records in (view, depth, record) order, those without tiles last in
@@ -606,11 +607,13 @@ mgs_status forward_impl(mgs_frame* f, mgs_stream stream_, const mgs_gaussians* g
         // view's segment of n records: the order of 64-bit (view, depth) keys
         // in 4 passes instead of 5
         bool alt = false;
-        launch_radix_sort_segmented(stream, (uint32_t*)f->rkeys.p, (uint32_t*)f->rvals.p, (uint32_t*)f->rkeys_alt.p,
-                                    (uint32_t*)f->rvals_alt.p, R, f->n, f->rsort_tmp.p, &alt);
+        const bool live = launch_depth_sort(stream, (uint32_t*)f->rkeys.p, (uint32_t*)f->rvals.p,
+                                            (uint32_t*)f->rkeys_alt.p, (uint32_t*)f->rvals_alt.p, R, f->n,
+                                            f->rsort_tmp.p, &alt, f->live());
         f->order_in_alt = alt;
         launch_permute_classify(stream, f->record_order(),
                                 (const uint32_t*)(f->order_in_alt ? f->rkeys_alt.p : f->rkeys.p),
+                                live ? f->live() : nullptr,
                                 (const float*)f->rec.p, R, f->n, f->views, f->st,
                                 (uint32_t*)f->cnt_sorted.p,
                                 (uint32_t*)f->cells.p, (float*)f->srec.p,

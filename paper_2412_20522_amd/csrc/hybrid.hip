@@ -344,7 +344,8 @@ __device__ __forceinline__ float4 shfl4(const float4& v, int src) {
 // With sizes, also per workgroup the tiles of all footprints and those of
 // splats larger than LARGE_RADIUS (part[6 nb + b], part[7 nb + b]; at most
 // 2^22 tiles each): the compositing's choice of kernel.
-// A record without tiles (key all ones, sorted last in its view) is listed
+// A record without tiles (key all ones, last in its view: from lives[view] on,
+// if given) is listed
 // nowhere: it gets no copy, which nothing uses.
 // Bound by the gather of the records (8 views of 1 M, 70 % listed: 0.82 GB, 159
 // us at the copy rate).  The wave loads its records three lanes to each, and
@@ -353,8 +354,8 @@ __device__ __forceinline__ float4 shfl4(const float4& v, int src) {
 // instructions of a wave), 1.5 M records of one view 41.5 -> 40.6 us, though
 // the duplication now gets the rectangle too (16 bytes for 8).
 __global__ void __launch_bounds__(256) permute_classify_kernel(
-    const uint32_t* __restrict__ order, const uint32_t* __restrict__ skeys, const float4* __restrict__ rec,
-    int64_t R, int64_t n, ViewSet views, DevSettings st, uint32_t* __restrict__ cnt_out,
+    const uint32_t* __restrict__ order, const uint32_t* __restrict__ skeys, const uint32_t* __restrict__ lives,
+    const float4* __restrict__ rec, int64_t R, int64_t n, ViewSet views, DevSettings st, uint32_t* __restrict__ cnt_out,
     uint4* __restrict__ cells, float4* __restrict__ srec,
     uint32_t* __restrict__ part, int sizes) {
     __shared__ uint32_t s_part[4][4];
@@ -372,9 +373,10 @@ __global__ void __launch_bounds__(256) permute_classify_kernel(
     bool wide = false;
     int vi = 0;
     // both loads of the position in one round trip, then the record
-    const uint32_t key = live ? skeys[i] : 0xffffffffu;
+    if (live && lives) vi = (int)((uint32_t)i / (uint32_t)n);  // positions are below 2^32
+    const bool has =
+        live && (lives ? (uint32_t)i - (uint32_t)vi * (uint32_t)n < lives[vi] : skeys[i] != 0xffffffffu);
     const uint32_t r = live ? order[i] : 0u;
-    const bool has = live && key != 0xffffffffu;
     float4* wrec = s_rec + 3 * (threadIdx.x & ~63u);
     if (ballot(has)) {
         // the wave's records (radius in B.w, tile count in C.w), three
@@ -403,7 +405,7 @@ __global__ void __launch_bounds__(256) permute_classify_kernel(
         B = wrec[3 * lane + 1];
         c = __float_as_uint(wrec[3 * lane + 2].w);
         if (has) {
-            vi = (int)((uint32_t)i / (uint32_t)n);  // positions are below 2^32
+            vi = (int)((uint32_t)i / (uint32_t)n);
             wide = c > views.v[vi].wide_min;
         }
         __builtin_amdgcn_wave_barrier();
@@ -2465,12 +2467,12 @@ bool composite_config_supported(const CompositeConfig& c) {
     return false;
 }
 
-void launch_permute_classify(hipStream_t stream, const uint32_t* order, const uint32_t* skeys, const float* rec,
-                             int64_t R, int64_t n, const ViewSet& views, const DevSettings& st, uint32_t* cnt,
+void launch_permute_classify(hipStream_t stream, const uint32_t* order, const uint32_t* skeys, const uint32_t* live,
+                             const float* rec, int64_t R, int64_t n, const ViewSet& views, const DevSettings& st, uint32_t* cnt,
                              uint32_t* cells, float* srec, uint32_t* part, bool sizes) {
     if (R == 0) return;
     const unsigned nb = blocks_of(R);
-    hipLaunchKernelGGL(permute_classify_kernel, dim3(nb), dim3(256), 0, stream, order, skeys,
+    hipLaunchKernelGGL(permute_classify_kernel, dim3(nb), dim3(256), 0, stream, order, skeys, live,
                        reinterpret_cast<const float4*>(rec), R, n, views, st, cnt, reinterpret_cast<uint4*>(cells),
                        reinterpret_cast<float4*>(srec), part, sizes ? 1 : 0);
 }

@@ -10,12 +10,11 @@
 namespace mgs {
 
 // projection (radius optional: the record's B.w holds it too)
-// rkeys, rvals (optional, both or neither): the keys of the per-view depth
-// order of the records (depth bits, all ones for records without tiles) and
-// the record ids
+// rkeys (optional): the keys of the per-view depth order of the records (depth
+// bits, all ones for records without tiles)
 void launch_project_fwd(hipStream_t stream, const mgs_gaussians& g, const ViewSet& views, const DevSettings& st,
                         float* rec, float* depth, float* radius, uint32_t* tiles, uint32_t* flags,
-                        uint32_t* rkeys = nullptr, uint32_t* rvals = nullptr);
+                        uint32_t* rkeys = nullptr);
 // out[r] = field `field` (0..11) of record r (the radius is field 7, B.w)
 void launch_record_field(hipStream_t stream, const float* rec, int64_t R, int field, float* out);
 void launch_project_bwd(hipStream_t stream, const mgs_gaussians& g, const ViewSet& views, const DevSettings& st,
@@ -64,10 +63,13 @@ bool cell_keys16(int64_t K, int64_t cells);
 bool launch_cell_sort(hipStream_t stream, void* keys, uint32_t* vals, void* keys_alt, uint32_t* vals_alt, bool keys16,
                       int64_t K, const uint64_t* K_dev, int bits, void* scratch, bool* out_in_alt, uint32_t* ranges,
                       int64_t nbins);
-// Stable sort of 32-bit keys (all bits) within consecutive segments of
-// seg_len keys each (at most 16 segments; the last may be shorter).
-void launch_radix_sort_segmented(hipStream_t stream, uint32_t* keys, uint32_t* vals, uint32_t* keys_alt,
-                                 uint32_t* vals_alt, int64_t K, int64_t seg_len, void* scratch, bool* out_in_alt);
+// Stable sort of the indices 0 .. K - 1 (written to vals) by their 32-bit keys
+// within consecutive segments of seg_len keys each (at most 16 segments; the
+// last may be shorter).  Keys of all ones come last in their segment.  Returns
+// whether live[segment] was written: the number of other keys, behind which
+// the sorted keys hold anything; if not, all keys are there, sorted.
+bool launch_depth_sort(hipStream_t stream, uint32_t* keys, uint32_t* vals, uint32_t* keys_alt, uint32_t* vals_alt,
+                       int64_t K, int64_t seg_len, void* scratch, bool* out_in_alt, uint32_t* live);
 void launch_cell_ranges(hipStream_t stream, const void* keys, bool keys16, int64_t K, const uint64_t* K_dev,
                         int64_t cells, uint32_t* ranges);
 void launch_fill_u32(hipStream_t stream, uint32_t* p, int64_t n, uint32_t value);
@@ -123,8 +125,9 @@ uint64_t staged_first(uint32_t tiles);
 // the classification) and list offsets (by launch_list_offsets, read by the
 // duplication)
 size_t classify_parts_bytes(int64_t R);
-void launch_permute_classify(hipStream_t stream, const uint32_t* order, const uint32_t* skeys, const float* rec,
-                             int64_t R, int64_t n, const ViewSet& views, const DevSettings& st, uint32_t* cnt,
+// skeys, live: as launch_depth_sort left them; live null if not written
+void launch_permute_classify(hipStream_t stream, const uint32_t* order, const uint32_t* skeys, const uint32_t* live,
+                             const float* rec, int64_t R, int64_t n, const ViewSet& views, const DevSettings& st, uint32_t* cnt,
                              uint32_t* cells, float* srec, uint32_t* part, bool sizes);
 // From the classification's per-workgroup counts: each workgroup's first list
 // entry, the entry total (device u64 *total) and wide_counts (device u64):

@@ -144,6 +144,35 @@ def test_depth_order_and_lists_over_the_sort_variants(n, views):
     assert step.all()
 
 
+@pytest.mark.parametrize("n,views", [(16_385, 1), (500_003, 1), (1_400_001, 3), (4_001_792, 1)])
+@pytest.mark.parametrize("dead", ["none", "some", "runs", "last", "all"])
+def test_depth_order_with_records_that_reach_no_tile(n, views, dead):
+    """Positions of the records with tiles by (depth, record), the others
+    behind them by record: below and above the size from which the first pass
+    drops the others, over segments of whole and broken tiles of the sort."""
+    from paper_2412_20522_amd import maskgs as M
+    from paper_2412_20522_amd.raster import Rasterizer
+    s = scenegen.small_scene(n, 70, 50, seed=910, sh_degree=0, log_scale_mean=-7.0, n_views=views)
+    s["means"][: n // 3] = s["means"][n // 3: 2 * (n // 3)]  # equal depths
+    far = np.zeros(n, bool)
+    far[{"none": slice(0, 0), "some": slice(0, None, 3), "runs": slice(n // 5, n // 2), "last": slice(n - 5000, None),
+         "all": slice(None)}[dead]] = True
+    s["means"][far] = (1e4, -1e4, 1e4)  # outside every view
+    rast = Rasterizer(0, **_settings((8, 8), sh_degree=0, wide_tiles=4, stats=0))
+    dev = U.to_device(s)
+    frame = rast.acquire_frame()
+    rast.forward(frame, {k: dev[k] for k in U.PARAM_KEYS}, dev["masks"], s["cameras"])
+    ex = {k: M.mgs_frame_export(rast.ctx, frame, k) for k in ("order", "depth", "tiles")}
+    torch.cuda.synchronize()
+    rast.release_frame(frame)
+    bits, tiles, order = U.u32(ex["depth"]), U.u32(ex["tiles"]), U.u32(ex["order"])
+    assert (tiles.reshape(views, n)[:, far] == 0).all()
+    key = np.where(tiles > 0, bits, np.uint32(0xffffffff))
+    for v in range(views):
+        want = np.argsort(key[v * n:(v + 1) * n], kind="stable") + v * n
+        assert np.array_equal(order[v * n:(v + 1) * n], want)
+
+
 @pytest.mark.parametrize("w,h", [(1928, 2024), (1928, 2032), (2048, 2048)])
 @pytest.mark.parametrize("cull", [0, 1])
 def test_lists_on_both_sides_of_16_bit_cell_keys(w, h, cull):
