@@ -30,6 +30,7 @@
 // checkpoints, so the merge is deterministic and nothing per pixel beyond the
 // final transmittance and the last blended entry is stored.
 #include <algorithm>
+#include <type_traits>
 
 #include "common.hpp"
 #include "composite_common.hpp"
@@ -1665,12 +1666,25 @@ __global__ void __launch_bounds__(TW * TH / PPT, PPT >= 4 ? 5 : STATS ? 7 : 8) h
     }
 }
 
-template <int TW, int TH, int PPT>
+// SUM (several waves to a tile): the waves' totals of BWD_ROUND entries meet in
+// LDS and are added to the accumulators once per tile and entry, a lane to a
+// quantity.  Where all tiles run at once they reach the same splats, the last
+// of their lists, at the same time, and the atomics wait for each other; with
+// more tiles they drift apart, and the barriers cost more.  Two pixels per
+// thread, batches of 256, splats of an unbounded scene, every wave for itself /
+// summed: 1,000 tiles 91 / 90 us, 4,346 tiles 238 / 170, 4,108 tiles 232 / 200,
+// 6,004 tiles 247 / 252, 7,110 tiles 315 / 284, 8,664 tiles 328 / 349, 24,937
+// tiles 800 / 906 us.
+constexpr int BWD_ROUND = 32;
+constexpr uint32_t SUM_TILES = 5632;
+template <int TW, int TH, int PPT, bool SUM>
 __global__ void __launch_bounds__(TW * TH / PPT, 5) hybrid_bwd_kernel(
     const float4* __restrict__ srec, HybridLists hl, ViewSet views, DevSettings st, const float* __restrict__ t_final,
     const int32_t* __restrict__ last_in, const float* __restrict__ dl_dimages, int64_t n, double* __restrict__ d_rec,
     double* __restrict__ d_masks) {
-    constexpr int NT = TW * TH / PPT;
+    constexpr int NT = TW * TH / PPT, NW = SUM ? NT / 64 : 1;
+    // SUM: the waves' totals of BWD_ROUND entries; zero between rounds
+    __shared__ float s_acc[SUM ? NW * BWD_ROUND * 10 : 1];
     extern __shared__ __align__(16) char smem[];
     __shared__ int s_top;
     const int t = threadIdx.x;
@@ -1740,6 +1754,9 @@ __global__ void __launch_bounds__(TW * TH / PPT, 5) hybrid_bwd_kernel(
         for (int b = 0; b < nb; ++b)
             if ((int)cur[b].z <= top) bstar = b;
     }
+    float* acc = s_acc + (SUM ? (t >> 6) * BWD_ROUND * 10 : 0);
+    if constexpr (SUM)
+        for (int i = t; i < NW * BWD_ROUND * 10; i += NT) s_acc[i] = 0.f;
     const uint2* cstg = hl.stg ? hl.cur_stg + uniform(hl.cur_off[tile]) : nullptr;
     // per-entry partial sums of this lane's pixels; zero between entries
     // (reset after each reduction), so no per-entry initialisation
@@ -1766,64 +1783,91 @@ __global__ void __launch_bounds__(TW * TH / PPT, 5) hybrid_bwd_kernel(
             Mb = merge_batch<false>(L, hl.vals, srec, (int)c.x, (int)r1.y, (int)c.y, (int)r2.y, batch, tcx,
                                         tcy, tb, cam, st, m).M;
         }
-        for (int j = Mb - 1; j >= 0; --j) {
-            const float4 A = L.E[3 * j], B = L.E[3 * j + 1], Cc = L.E[3 * j + 2];
-            const int k = __float_as_int(B.w);  // index in the tile's full list
-            if (k > top) continue;                  // uniform: past every pixel's last entry
-            const float M = B.z;
-            const float okq = B.y * QSCALE_NINV;
-            bool any = false;
+        for (int j1 = Mb; j1 > 0; j1 -= BWD_ROUND) {
+            const int j0 = SUM ? max(j1 - BWD_ROUND, 0) : 0;
+            for (int j = j1 - 1; j >= j0; --j) {
+                const float4 A = L.E[3 * j], B = L.E[3 * j + 1], Cc = L.E[3 * j + 2];
+                const int k = __float_as_int(B.w);  // index in the tile's full list
+                if (k > top) continue;                  // uniform: past every pixel's last entry
+                const float M = B.z;
+                const float okq = B.y * QSCALE_NINV;
+                bool any = false;
 #pragma unroll
-            for (int i = 0; i < PPT; ++i) {
-                if (k > lastk[i]) continue;
-                Eval e;
-                if (!eval_entry(A, B, px[i], py[i], ek, e)) continue;
-                any = true;
-                const float ma = M * e.alpha;
-                const float one_m = 1.f - ma;
-                const float inv = __builtin_amdgcn_rcpf(one_m);
-                const float Ti = T[i] * inv;
-                const float d = fmaf(w0[i], Cc.x, fmaf(w1[i], Cc.y, w2[i] * Cc.z)) - sb[i];
-                const float X = Ti * d - Tf[i] * inv * wbg[i];
-                gm += e.alpha * X;
-                const float wt = ma * Ti;
-                gr += wt * w0[i];
-                gg += wt * w1[i];
-                gbl += wt * w2[i];
-                if (e.oG <= ek.amax) {
-                    // dL/dalpha = M X, dL/dQ = -o G M X / 2; with a' = QSCALE a,
-                    // gamma' = QSCALE gamma: dL/du = kq a' t, dL/dv =
-                    // kq (beta a' t + gamma' dy), dL/dbeta = kq a' t dy, and
-                    // dL/da, dL/dgamma are QSCALE / 2 times the sums of kq t^2,
-                    // kq dy^2, where kq = 2 dL/dQ / QSCALE
-                    const float GdA = e.G * (M * X);
-                    go += GdA;
-                    const float kq = GdA * okq;
-                    const float kapt = kq * e.apt;
-                    gu += kapt;
-                    gv += kq * fmaf(A.w, e.apt, e.gdy);
-                    gb += kapt * e.dy;
-                    ga += (kq * e.t) * e.t;
-                    gc += (kq * e.dy) * e.dy;
+                for (int i = 0; i < PPT; ++i) {
+                    if (k > lastk[i]) continue;
+                    Eval e;
+                    if (!eval_entry(A, B, px[i], py[i], ek, e)) continue;
+                    any = true;
+                    const float ma = M * e.alpha;
+                    const float one_m = 1.f - ma;
+                    const float inv = __builtin_amdgcn_rcpf(one_m);
+                    const float Ti = T[i] * inv;
+                    const float d = fmaf(w0[i], Cc.x, fmaf(w1[i], Cc.y, w2[i] * Cc.z)) - sb[i];
+                    const float X = Ti * d - Tf[i] * inv * wbg[i];
+                    gm += e.alpha * X;
+                    const float wt = ma * Ti;
+                    gr += wt * w0[i];
+                    gg += wt * w1[i];
+                    gbl += wt * w2[i];
+                    if (e.oG <= ek.amax) {
+                        // dL/dalpha = M X, dL/dQ = -o G M X / 2; with a' = QSCALE a,
+                        // gamma' = QSCALE gamma: dL/du = kq a' t, dL/dv =
+                        // kq (beta a' t + gamma' dy), dL/dbeta = kq a' t dy, and
+                        // dL/da, dL/dgamma are QSCALE / 2 times the sums of kq t^2,
+                        // kq dy^2, where kq = 2 dL/dQ / QSCALE
+                        const float GdA = e.G * (M * X);
+                        go += GdA;
+                        const float kq = GdA * okq;
+                        const float kapt = kq * e.apt;
+                        gu += kapt;
+                        gv += kq * fmaf(A.w, e.apt, e.gdy);
+                        gb += kapt * e.dy;
+                        ga += (kq * e.t) * e.t;
+                        gc += (kq * e.dy) * e.dy;
+                    }
+                    sb[i] = fmaf(ma, d, sb[i]);
+                    T[i] = Ti;
                 }
-                sb[i] = fmaf(ma, d, sb[i]);
-                T[i] = Ti;
-            }
-            if (__any(any)) {
-                const uint32_t r = __float_as_uint(Cc.w);
-                const int64_t g = (int64_t)r - rec_base;
-                if (M != 0.f) {
-                    // ten lanes receive the wave totals, quantity qi each
-                    const float v[10] = {gu, gv, ga, gb, gc, go, gr, gg, gbl, gm};
-                    const float x = wave_sum_swap10(v, lane) * qscale;
-                    if ((unsigned)qi < (unsigned)DREC) atomicAdd(d_rec + (size_t)r * DREC + qi, (double)x);
-                    else if (qi == DREC) atomicAdd(d_masks + g, (double)x);
-                } else {
-                    const float sm = wave_sum(gm);
-                    if (lane == 0) atomicAdd(d_masks + g, (double)sm);
+                if (__any(any)) {
+                    const uint32_t r = __float_as_uint(Cc.w);
+                    const int64_t g = (int64_t)r - rec_base;
+                    if (M != 0.f) {
+                        // ten lanes receive the wave totals, quantity qi each
+                        const float v[10] = {gu, gv, ga, gb, gc, go, gr, gg, gbl, gm};
+                        const float x = wave_sum_swap10(v, lane) * qscale;
+                        if constexpr (SUM) {
+                            if (qi >= 0) acc[(j - j0) * 10 + qi] = x;
+                        } else {
+                            if ((unsigned)qi < (unsigned)DREC) atomicAdd(d_rec + (size_t)r * DREC + qi, (double)x);
+                            else if (qi == DREC) atomicAdd(d_masks + g, (double)x);
+                        }
+                    } else {
+                        const float sm = wave_sum(gm);
+                        if (lane == 0) {
+                            if constexpr (SUM) acc[(j - j0) * 10 + DREC] = sm;
+                            else atomicAdd(d_masks + g, (double)sm);
+                        }
+                    }
+                    gu = gv = ga = gb = gc = go = gr = gg = gbl = gm = 0.f;
                 }
-                gu = gv = ga = gb = gc = go = gr = gg = gbl = gm = 0.f;
+        
             }
+            if constexpr (!SUM) break;  // the whole batch
+            __syncthreads();
+            for (int i = t; i < (j1 - j0) * 10; i += NT) {
+                double x = 0.0;
+#pragma unroll
+                for (int w = 0; w < NW; ++w) {
+                    x += (double)s_acc[w * BWD_ROUND * 10 + i];
+                    s_acc[w * BWD_ROUND * 10 + i] = 0.f;
+                }
+                if (x == 0.0) continue;
+                const int j = i / 10, q = i - j * 10;
+                const uint32_t r = __float_as_uint(L.E[3 * (j0 + j) + 2].w);
+                if (q < DREC) atomicAdd(d_rec + (size_t)r * DREC + q, x);
+                else atomicAdd(d_masks + ((int64_t)r - rec_base), x);
+            }
+            __syncthreads();
         }
         __syncthreads();  // the next batch overwrites the LDS
     }
@@ -2396,8 +2440,15 @@ template <int TW, int TH, int PPT>
 void hybrid_bwd_t(hipStream_t s, const float* srec, const HybridLists& hl, const ViewSet& views,
                   const DevSettings& st, const float* t_final, const int32_t* last, const float* dl, int64_t n,
                   double* d_rec, double* d_masks) {
-    hipLaunchKernelGGL((hybrid_bwd_kernel<TW, TH, PPT>), dim3(views.total_tiles), dim3(TW * TH / PPT), lds_bytes(st.batch), s,
-                       reinterpret_cast<const float4*>(srec), hl, views, st, t_final, last, dl, n, d_rec, d_masks);
+    auto launch = [&](auto sum) {
+        hipLaunchKernelGGL((hybrid_bwd_kernel<TW, TH, PPT, decltype(sum)::value>), dim3(views.total_tiles),
+                           dim3(TW * TH / PPT), lds_bytes(st.batch), s, reinterpret_cast<const float4*>(srec), hl, views,
+                           st, t_final, last, dl, n, d_rec, d_masks);
+    };
+    if constexpr (TW * TH / PPT > 64) {
+        if (views.total_tiles <= SUM_TILES) return launch(std::true_type{});
+    }
+    launch(std::false_type{});
 }
 
 #define MGS_HYBRID_SHAPES(X) \

@@ -252,6 +252,33 @@ def test_lists_of_rectangles_around_the_cell_mask(size, wide, n):
     assert torch.equal(img[0], img[1])
 
 
+@pytest.mark.parametrize("tile,ppt,batch", [((16, 16), 1, 256), ((16, 16), 2, 128), ((16, 8), 1, 32), ((32, 8), 1, 64),
+                                            ((32, 8), 2, 128)])
+@pytest.mark.parametrize("n", [1, 33, 700])
+def test_backward_sums_over_the_waves_of_a_tile(tile, ppt, batch, n):
+    """Large splats over 1,575 to 3,150 tiles, where the waves' totals meet in
+    LDS, against the same view beside one whose tiles make every wave add its
+    own: the same FP32 totals in FP64 sums, so gradients to a few roundings.
+    Lists below and above a round of 32 entries and a batch."""
+    from paper_2412_20522_amd.raster import Rasterizer
+    w, h = 1000, 400
+    s = scenegen.small_scene(n, w, h, seed=950 + n, sh_degree=1, log_scale_mean=-0.3, opacity_mean=-3.0)
+    s["masks"][::4] = 0.0  # masked entries return dL/dM alone
+    away = _big()
+    away["viewmat"] = np.array(away["viewmat"], np.float64).reshape(4, 4)
+    away["viewmat"][2, 3] -= 1e4  # everything behind this view: the tiles count, nothing is in them
+    dl = np.random.default_rng(6).normal(size=3 * w * h).astype(np.float32)
+    rast = Rasterizer(0)
+    kw = dict(fwd_ppt=ppt, bwd_ppt=ppt, batch_depth=batch, wide_tiles=8)
+    a, ga = _run(rast, s, s["cameras"], dl, **_settings(tile, **kw))
+    b, gb = _run(rast, s, [s["cameras"][0], away], dl, **_settings(tile, **kw))
+    for k in a:
+        assert np.array_equal(a[k], b[k]), k
+    for k in ("means", "log_scales", "quats", "opacity_logits", "sh", "masks"):
+        x, y = getattr(ga, k).cpu().numpy(), getattr(gb, k).cpu().numpy()
+        assert U.rel_err(x, y) <= 1e-6 or np.abs(x - y).max() <= 1e-9, (k, U.rel_err(x, y))
+
+
 @pytest.mark.parametrize("tile,ppt,batch", [((16, 16), 1, 32), ((16, 16), 2, 128), ((16, 16), 4, 256), ((8, 8), 1, 64),
                                             ((32, 8), 2, 64)])
 @pytest.mark.parametrize("n", [1, 3, 5, 900])
