@@ -252,6 +252,29 @@ def test_lists_of_rectangles_around_the_cell_mask(size, wide, n):
     assert torch.equal(img[0], img[1])
 
 
+@pytest.mark.parametrize("n", [1, 255, 1023, 1025, 9000])
+@pytest.mark.parametrize("shift", [0, 1])
+def test_compaction_over_row_widths(n, shift):
+    """Rows of one to four units and wider, of 16-, 8- and 4-byte units (the
+    pointers off by one float too), around a workgroup's rows: the bits of
+    boolean indexing, and nothing behind the kept rows."""
+    from paper_2412_20522_amd import maskgs as M
+    from paper_2412_20522_amd.raster import Rasterizer
+    rast = Rasterizer(0)
+    g = torch.Generator(device="cuda").manual_seed(n)
+    keep = (torch.rand(n, generator=g, device="cuda") < 0.4).to(torch.int32)
+    ins, outs = [], []
+    for w in (1, 2, 3, 4, 5, 6, 8, 16, 20, 48, 49, 1030):
+        ins.append(torch.randn(n * w + shift, generator=g, device="cuda")[shift:].view(n, w))
+        outs.append(torch.full((n * w + shift,), -7.0, device="cuda")[shift:].view(n, w))
+    kept = torch.zeros(1, dtype=torch.int64, device="cuda")
+    M.mgs_compact_rows(rast.ctx, keep, ins, outs, n_kept=kept)
+    k = int(keep.sum())
+    assert int(kept) == k
+    for a, b in zip(ins, outs):
+        assert torch.equal(b[:k], a[keep.bool()]) and bool((b[k:] == -7.0).all())
+
+
 @pytest.mark.parametrize("tile,ppt,batch", [((16, 16), 1, 256), ((16, 16), 2, 128), ((16, 8), 1, 32), ((32, 8), 1, 64),
                                             ((32, 8), 2, 128)])
 @pytest.mark.parametrize("n", [1, 33, 700])
