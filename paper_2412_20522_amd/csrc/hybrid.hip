@@ -116,13 +116,6 @@ __device__ __forceinline__ bool may_touch(const float4& A, const float4& B, cons
     return touch_test(touch_prep(A, B, st), tb);
 }
 
-// Pixel-centre box of cell (cx, cy) of a grid of cw x ch pixel cells.
-__device__ __forceinline__ TileBox cell_box(int cx, int cy, int cw, int ch, const DevView& cam) {
-    const int x0 = cx * cw, y0 = cy * ch;
-    return TileBox{(float)x0 + 0.5f, (float)min(x0 + cw, cam.width) - 0.5f, (float)y0 + 0.5f,
-                   (float)min(y0 + ch, cam.height) - 0.5f};
-}
-
 // ---------------------------------------------------------------------------
 // binning: (view, depth) order of records, sorted records, per-tile and
 // per-region lists, batch checkpoints
@@ -330,10 +323,6 @@ constexpr uint32_t KEY_NONE = 0xffffffffu;
 constexpr uint32_t CNT_WIDE = 0x80000000u;
 // Splats of a larger radius (pixels) cover most of the tiles they reach.
 constexpr float LARGE_RADIUS = 24.f;
-
-__device__ __forceinline__ float4 shfl4(const float4& v, int src) {
-    return make_float4(__shfl(v.x, src), __shfl(v.y, src), __shfl(v.z, src), __shfl(v.w, src));
-}
 
 // Sorted position i holds record order[i] with depth key skeys[i]; positions
 // [v n, (v + 1) n) belong to view v.  Writes the sorted record copy (radius in
