@@ -128,6 +128,17 @@ void release(DevBuf& b) {
     b.bytes = 0;
 }
 
+// The capture that a stream records into, as a number (0: none).
+unsigned long long capture_id(hipStream_t stream) {
+    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+    unsigned long long id = 0;
+    if (hipStreamGetCaptureInfo(stream, &status, &id) != hipSuccess) {
+        (void)hipGetLastError();
+        return 0;
+    }
+    return status == hipStreamCaptureStatusActive ? id + 1 : 0;
+}
+
 bool valid_tile(int w, int h) {
     return (w == 8 && h == 8) || (w == 16 && h == 8) || (w == 16 && h == 16) || (w == 32 && h == 8);
 }
@@ -294,11 +305,16 @@ struct mgs_frame {
     bool have_stats = false;  // the last forward wrote the per-pixel work counters
     DevBuf d_rec, rsort_tmp, sort_tmp, misc, sum_tmp;  // d_rec: FP64, R rows, then the masks' n sums
     DevBuf imp_acc;  // FP64 sums of the importance forward
-    // d_rec and the backward's order's histogram are all zeros from
-    // the forward (which clears them) to the backward that uses them; false
-    // after a backward and after (re)allocation (a backward then clears them
-    // first)
+    // d_rec is all zeros from the forward (which clears it) to the backward
+    // that accumulates into it; false after a backward and after
+    // (re)allocation (a backward then clears it first)
     bool drec_zero = false;
+    // ... in stream order: a forward that was captured clears where its graph
+    // runs, so it serves the backwards of the same capture (0: none).  Replays
+    // of a captured backward are not seen here: once there is one, an eager
+    // backward clears for itself
+    unsigned long long drec_capture = 0;
+    bool bwd_captured = false;
     // views of the last forward, whose per-tile batch counts (nbatch) order
     // the tiles of the next forward over the same views
     ViewSet order_views{};
@@ -341,7 +357,7 @@ struct mgs_frame {
         const uint64_t n2 = clear_drec ? ((uint64_t)R * DREC + (uint64_t)n + 1) / 2 : 0;
         return HybridBuffers{vals_sorted(), (const uint32_t*)ranges.p, (uint32_t*)cur.p, (const uint32_t*)cur_off.p, (uint32_t*)nbatch.p, cur_need(), cap,
                              flags(), (uint32_t*)cur_stg.p, (uint32_t*)stg.p, stg_count(), scap,
-                             clear_drec ? (double*)d_rec.p : nullptr, n2, (const uint32_t*)order.p, fine};
+                             clear_drec ? (double*)d_rec.p : nullptr, n2, (const uint32_t*)order.p, order_hist_b(), fine};
     }
 };
 
@@ -674,11 +690,11 @@ mgs_status forward_impl(mgs_frame* f, mgs_stream stream_, const mgs_gaussians* g
     const bool imp = imp_sum != nullptr;
     if (imp && (s = grow(ctx, f->imp_acc, (size_t)f->n * 8 + 8))) return s;
     const bool keys16 = cell_keys16(f->K, T + NR);
-    // the duplication's launch also clears the ranges, the tile orders'
-    // histograms and cursors, the staged-entry counter, the importance sums
+    // the duplication's launch also clears the ranges, the forward's tile
+    // order's histogram and cursors, the staged-entry counter, the importance sums
     // and, in the plain path, the next forward's flags
     const FillSpan zero[] = {{(uint32_t*)f->ranges.p, 2 * (T + NR), 0u},
-                             {f->order_hist(), 1024, 0u},
+                             {f->order_hist(), 512, 0u},
                              {f->stg_count(), 2, 0u},
                              {f->reserved ? nullptr : f->flag_words() + (f->flag_word ^ 1), 1, 0u},
                              {imp ? (uint32_t*)f->imp_acc.p : nullptr, 2 * f->n, 0u},
@@ -731,6 +747,7 @@ mgs_status forward_impl(mgs_frame* f, mgs_stream stream_, const mgs_gaussians* g
     if (t_final_out)
         MGS_HIP(ctx, hipMemcpyAsync(t_final_out, f->t_final.p, (size_t)P * 4, hipMemcpyDeviceToDevice, stream));
     f->drec_zero = true;
+    f->drec_capture = capture_id(stream);
     f->have_forward = true;
     f->order_views = f->views;  // nbatch now holds this forward's batch counts
     f->order_valid = true;
@@ -771,14 +788,16 @@ mgs_status mgs_backward(mgs_frame* f, mgs_stream stream_, const float* dl_dimage
     // (a scheduling choice: the order decides no result), else by this
     // forward's batch counts
     const bool own_order = !f->fwd_order_measured;
-    if (!f->drec_zero) {
+    const unsigned long long capture = capture_id(stream);
+    if (!f->drec_zero || f->drec_capture != capture || (capture == 0 && f->bwd_captured)) {
         // +0.0 in every double: normally the forward has cleared the
-        // accumulators and the order's histogram; a second backward
-        // after one forward, or a new allocation, clears them here
+        // accumulators; a second backward after one forward, a new
+        // allocation, or a backward in another graph than its forward clears
+        // them here
         launch_fill_u32(stream, (uint32_t*)f->d_rec.p, f->d_rec.bytes / 4, 0u);
-        launch_fill_u32(stream, f->order_hist_b(), 512, 0u);
     }
     f->drec_zero = false;  // this backward accumulates into it
+    f->bwd_captured |= capture != 0;
     HybridBuffers hb = f->hybrid();
     {
         StageTimer t(ctx, stream, MGS_STAGE_COMPOSITE_BWD);

@@ -178,6 +178,7 @@ struct HybridBuffers {
     double* drec_clear;          // optional: FP64 gradient accumulators (per record, then the masks') the forward clears
     uint64_t drec_clear_n2;      // their size in pairs of doubles
     const uint32_t* order;       // optional [tiles]: tile of each workgroup
+    uint32_t* order_hist;        // [512] that the backward compositing clears (launch_tile_order's)
     bool fine;                   // the kernels for small splats (the same for a forward and its backward)
 };
 // stats [P, 4] (examined, blended, blended with mask 0, last + 1) and evals
