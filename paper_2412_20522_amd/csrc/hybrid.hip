@@ -35,6 +35,7 @@
 #include "common.hpp"
 #include "composite_common.hpp"
 #include "kernels.hpp"
+#include "staged.hpp"
 
 namespace mgs {
 namespace {
@@ -569,7 +570,7 @@ struct ListTotals {
     uint64_t* total;
     uint64_t* wide;
     const uint32_t* flags;   // two words
-    const uint32_t* staged;  // two words
+    const uint64_t* staged;  // two
     uint64_t* host;
 };
 // thread k of the workgroup holds total k (0: entries, 1 .. 4: as group_tot)
@@ -582,7 +583,7 @@ __device__ __forceinline__ void put_totals(const ListTotals& o, int k, uint64_t 
         if (k == 0) {
             o.host[1] = v;
             o.host[0] = (uint64_t)o.flags[0] | (uint64_t)o.flags[1] << 32;
-            o.host[24] = (uint64_t)o.staged[0] + o.staged[1];
+            o.host[24] = o.staged[0] + o.staged[1];
         } else {
             o.host[2 + w] = v;
         }
@@ -1373,14 +1374,11 @@ __device__ __forceinline__ void pixel_of(int t, int i, const TileGeom& tg, int& 
     y = tg.ty0 + (b / (TW / 8)) * 8 + (l >> 3);
 }
 
-// Staged-list chunks: a workgroup's first one is its own by its index, further
-// ones come from the global counter (with every workgroup of a launch at that
-// counter at its start, forward compositing waits).
-constexpr uint32_t STG_FIRST = 256;
-constexpr uint32_t STG_CHUNK = 512;
-// words of Lds::wsum behind the scan's: next free entry of the workgroup's
-// chunk, entries left in it, where the batch's entries go (all ones: nowhere)
-constexpr int STG_BASE = 8, STG_LEFT = 9, STG_OFF = 10;
+// Words of Lds::wsum behind the scan's, of the workgroup's staged-list chunk:
+// next free entry (two words), entries left, where the batch's entries go
+// (STG_NOWHERE: nowhere).  (The batch is a multiple of 32, so that the two
+// words are 8-byte aligned.)
+constexpr int STG_BASE = 8, STG_LEFT = 10, STG_OFF = 11;
 
 struct HybridLists {
     const uint32_t* vals;      // list entries (sorted positions) in (cell, position) order
@@ -1396,8 +1394,9 @@ struct HybridLists {
     // entry (sorted position, index within the merged batch)
     uint2* cur_stg;
     uint2* stg;                // null: the backward merges again
-    uint32_t* stg_count;       // two words: entries taken from the counter, entries of the first chunks
+    uint64_t* stg_count;       // two: entries taken from the counter, entries of the first chunks
     uint64_t stg_cap;
+    uint32_t stg_first;        // entries of each workgroup's first chunk (staged_first)
     double* drec_clear;        // the backward's FP64 accumulators, cleared by the forward
     uint64_t drec_clear_n2;    // their size in pairs of doubles
     const uint32_t* order;     // optional: tile of each workgroup
@@ -1452,9 +1451,9 @@ __global__ void __launch_bounds__(TW * TH / PPT, PPT >= 4 ? 5 : STATS ? 7 : 8) h
     }
     // staged-list chunk of this workgroup (used by thread 0 only)
     if (hl.stg && t == 0) {
-        L.wsum[STG_BASE] = blockIdx.x * STG_FIRST;
-        L.wsum[STG_LEFT] = STG_FIRST;
-        if (blockIdx.x == 0) hl.stg_count[1] = gridDim.x * STG_FIRST;
+        *reinterpret_cast<uint64_t*>(L.wsum + STG_BASE) = (uint64_t)blockIdx.x * hl.stg_first;
+        L.wsum[STG_LEFT] = hl.stg_first;
+        if (blockIdx.x == 0) hl.stg_count[1] = (uint64_t)gridDim.x * hl.stg_first;
     }
     const uint32_t tile = uniform(hl.order ? hl.order[blockIdx.x] : blockIdx.x);
     const TileGeom tg = tile_geom(views, tile, TW, TH);
@@ -1509,14 +1508,17 @@ __global__ void __launch_bounds__(TW * TH / PPT, PPT >= 4 ? 5 : STATS ? 7 : 8) h
         // thread 0 sub-allocates from a chunk the workgroup took from the
         // global counter (one atomic per chunk, not per batch)
         if (hl.stg && t == 0) {
-            uint32_t cbase = L.wsum[STG_BASE], cleft = L.wsum[STG_LEFT];
+            uint64_t* const base = reinterpret_cast<uint64_t*>(L.wsum + STG_BASE);
+            uint64_t cbase = *base;
+            uint32_t cleft = L.wsum[STG_LEFT];
             if ((uint32_t)bt.M > cleft) {
-                cbase = gridDim.x * STG_FIRST + atomicAdd(hl.stg_count, STG_CHUNK);
+                cbase = (uint64_t)gridDim.x * hl.stg_first +
+                        atomicAdd(reinterpret_cast<unsigned long long*>(hl.stg_count), (unsigned long long)STG_CHUNK);
                 cleft = STG_CHUNK;
             }
-            const uint32_t off = (uint64_t)cbase + (uint64_t)bt.M <= hl.stg_cap ? cbase : 0xffffffffu;
+            const uint32_t off = staged_offset(cbase, (uint32_t)bt.M, hl.stg_cap);
             L.wsum[STG_OFF] = off;
-            L.wsum[STG_BASE] = cbase + (uint32_t)bt.M;
+            *base = cbase + (uint32_t)bt.M;
             L.wsum[STG_LEFT] = cleft - (uint32_t)bt.M;
             hl.cur_stg[hl.cur_off[tile] + b] = make_uint2(off, (uint32_t)bt.M);
         }
@@ -1594,7 +1596,7 @@ __global__ void __launch_bounds__(TW * TH / PPT, PPT >= 4 ? 5 : STATS ? 7 : 8) h
         if (hl.stg) {
             __syncthreads();
             const uint32_t off = L.wsum[STG_OFF];
-            if (off != 0xffffffffu) {
+            if (off != STG_NOWHERE) {
                 for (int p = t; p < bt.M; p += NT) {
                     const uint32_t jj = __float_as_uint(L.E[3 * p + 1].w) - (uint32_t)m;
                     hl.stg[off + p] = make_uint2(L.m[jj], jj);
@@ -1764,9 +1766,9 @@ __global__ void __launch_bounds__(TW * TH / PPT, 5) hybrid_bwd_kernel(
     for (int b = bstar; b >= 0; --b) {
         const uint4 c = cur[b];
         const int m = (int)c.z;
-        const uint2 cs = cstg ? cstg[b] : make_uint2(0xffffffffu, 0u);
+        const uint2 cs = cstg ? cstg[b] : make_uint2(STG_NOWHERE, 0u);
         int Mb;
-        if (cs.x != 0xffffffffu) {
+        if (cs.x != STG_NOWHERE) {
             // the entries the forward staged for this batch
             Mb = (int)cs.y;
             for (int p = t; p < Mb; p += NT) {
@@ -2499,6 +2501,7 @@ HybridLists make_lists(const HybridBuffers& b) {
     hl.order = b.order;
     hl.order_hist = b.order_hist;
     hl.stg_cap = b.stg_cap;
+    hl.stg_first = b.stg_first;
     hl.drec_clear = b.drec_clear;
     hl.drec_clear_n2 = b.drec_clear_n2;
     return hl;
@@ -2529,8 +2532,6 @@ bool fine_needs_sizes(int64_t pixels) { return pixels > FINE_PIXELS_ANY && pixel
 bool use_fine(int64_t pixels, uint64_t tiles_all, uint64_t tiles_large) {
     return pixels <= FINE_PIXELS_ANY || (pixels <= FINE_PIXELS_SMALL && 4 * tiles_large <= 3 * tiles_all);
 }
-
-uint64_t staged_first(uint32_t tiles) { return (uint64_t)tiles * STG_FIRST; }
 
 bool composite_config_supported(const CompositeConfig& c) {
 #define MGS_MATCH(A, B, P) \
@@ -2570,7 +2571,7 @@ ListOffsets list_offsets(uint32_t* part, int64_t R) {
 size_t classify_parts_bytes(int64_t R) { return counts_bytes(R) + (size_t)(waves_of(R) + 6 * groups_of(R)) * 8 + 8; }
 
 void launch_list_offsets(hipStream_t stream, uint32_t* part, int64_t R, uint64_t* total, uint64_t* wide_counts,
-                         bool sizes, const uint32_t* flags, const uint32_t* staged, uint64_t* host) {
+                         bool sizes, const uint32_t* flags, const uint64_t* staged, uint64_t* host) {
     const ListOffsets lo = list_offsets(part, R);
     const ListTotals out{total, wide_counts, flags, staged, host};
     const int64_t ng = R > 0 ? groups_of(R) : 0, nb = (int64_t)blocks_of(R);
