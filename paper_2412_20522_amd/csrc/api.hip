@@ -358,7 +358,7 @@ struct mgs_frame {
         const uint64_t n2 = clear_drec ? ((uint64_t)R * DREC + (uint64_t)n + 1) / 2 : 0;
         return HybridBuffers{vals_sorted(), (const uint32_t*)ranges.p, (uint32_t*)cur.p, (const uint32_t*)cur_off.p, (uint32_t*)nbatch.p, cur_need(), cap,
                              flags(), (uint32_t*)cur_stg.p, (uint32_t*)stg.p, stg_count(), scap, staged_first((uint64_t)total_tiles),
-                             clear_drec ? (double*)d_rec.p : nullptr, n2, (const uint32_t*)order.p, order_hist_b(), fine};
+                             clear_drec ? (double*)d_rec.p : nullptr, n2, (const uint32_t*)order.p, fine};
     }
 };
 
@@ -816,7 +816,8 @@ mgs_status mgs_backward(mgs_frame* f, mgs_stream stream_, const float* dl_dimage
     }
     {
         StageTimer t(ctx, stream, MGS_STAGE_PROJECT_BWD);
-        launch_project_bwd64(stream, f->g, f->views, f->st, (double*)f->d_rec.p, f->dm_acc(), *grads, (const uint32_t*)f->tiles.p);
+        launch_project_bwd64(stream, f->g, f->views, f->st, (double*)f->d_rec.p, f->dm_acc(), *grads,
+                             (const uint32_t*)f->tiles.p, f->order_hist_b());
     }
     MGS_CHECK_LAUNCH(ctx);
     return MGS_OK;

@@ -1400,7 +1400,6 @@ struct HybridLists {
     double* drec_clear;        // the backward's FP64 accumulators, cleared by the forward
     uint64_t drec_clear_n2;    // their size in pairs of doubles
     const uint32_t* order;     // optional: tile of each workgroup
-    uint32_t* order_hist;      // [512]: the backward's order's histogram and cursors, which it clears
 };
 
 // Tile-wide compositing, one workgroup per tile in launch order.  Both kernels
@@ -1658,15 +1657,6 @@ __global__ void __launch_bounds__(TW * TH / PPT, PPT >= 4 ? 5 : STATS ? 7 : 8) h
     }
 }
 
-// The backward's tile order is taken from a histogram that has to be zero
-// before it (launch_tile_order).  The compositing behind it leaves it zero
-// again, whatever happens between two backwards: an eager one, a replay of a
-// captured one, another forward or none.
-__device__ __forceinline__ void clear_order_hist(const HybridLists& hl, int t, int nt) {
-    if (blockIdx.x == 0)
-        for (int i = t; i < 512; i += nt) hl.order_hist[i] = 0u;
-}
-
 // SUM (several waves to a tile): the waves' totals of BWD_ROUND entries meet in
 // LDS and are added to the accumulators once per tile and entry, a lane to a
 // quantity.  Where all tiles run at once they reach the same splats, the last
@@ -1700,7 +1690,6 @@ __global__ void __launch_bounds__(TW * TH / PPT, 5) hybrid_bwd_kernel(
     // pixel loop)
     const int qi = swap10_quantity(lane);
     const float qscale = (qi == 2 || qi == 4) ? 0.5f * QSCALE : 1.f;
-    clear_order_hist(hl, t, NT);
     if (*hl.cur_need > hl.cur_cap) return;  // the forward reported it
     const uint32_t tile = uniform(hl.order ? hl.order[blockIdx.x] : blockIdx.x);
     const TileGeom tg = tile_geom(views, tile, TW, TH);
@@ -2264,7 +2253,6 @@ __global__ void __launch_bounds__(FINE_NT, 5) hybrid_bwd_fine_kernel(
     float* acc = reinterpret_cast<float*>(smem + lds_bytes(FINE_BATCH) + (FINE_NT / 64) * FINE_LIST * 2);
     const int qi = fold10_quantity(col);
     const EvalConsts ek = eval_consts(st);
-    clear_order_hist(hl, t, FINE_NT);
     if (*hl.cur_need > hl.cur_cap) return;  // the forward reported it
     for (int i = t; i < FINE_BATCH * 10; i += FINE_NT) acc[i] = 0.f;
     const uint32_t q = blockIdx.x;
@@ -2499,7 +2487,6 @@ HybridLists make_lists(const HybridBuffers& b) {
     hl.stg = reinterpret_cast<uint2*>(b.stg);
     hl.stg_count = b.stg_count;
     hl.order = b.order;
-    hl.order_hist = b.order_hist;
     hl.stg_cap = b.stg_cap;
     hl.stg_first = b.stg_first;
     hl.drec_clear = b.drec_clear;

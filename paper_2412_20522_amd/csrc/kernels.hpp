@@ -21,10 +21,11 @@ void launch_project_bwd(hipStream_t stream, const mgs_gaussians& g, const ViewSe
                         const float* d_rec, const mgs_gradients& out);
 // Whole path: FP64 per-record gradients (zeroed by the forward compositing
 // before the backward accumulates them); dm_acc (FP64 mask gradients) is
-// rounded into out.d_masks.
+// rounded into out.d_masks.  order_hist: the [512] words of the backward's
+// tile order (launch_tile_order), left zero for the next backward.
 void launch_project_bwd64(hipStream_t stream, const mgs_gaussians& g, const ViewSet& views, const DevSettings& st,
                           double* d_rec, const double* dm_acc, const mgs_gradients& out,
-                          const uint32_t* tiles);
+                          const uint32_t* tiles, uint32_t* order_hist);
 
 // scan / binning / sort / ranges
 size_t scan_scratch_bytes(int64_t n);
@@ -176,7 +177,6 @@ struct HybridBuffers {
     double* drec_clear;          // optional: FP64 gradient accumulators (per record, then the masks') the forward clears
     uint64_t drec_clear_n2;      // their size in pairs of doubles
     const uint32_t* order;       // optional [tiles]: tile of each workgroup
-    uint32_t* order_hist;        // [512] that the backward compositing clears (launch_tile_order's)
     bool fine;                   // the kernels for small splats (the same for a forward and its backward)
 };
 // stats [P, 4] (examined, blended, blended with mask 0, last + 1) and evals
