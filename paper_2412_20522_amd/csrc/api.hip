@@ -329,6 +329,7 @@ struct mgs_frame {
     // 32, footprint tiles of all and of large splats (u64) at 40 and 48,
     // staged-entry counters (2 u64) at 192; the histogram and cursors (2 x 256
     // u32) of the forward's tile order from 256, of the backward's from 2304
+    bool misc_cleared = false;     // by the first forward
     uint64_t* h_pinned = nullptr;  // read-back of misc
     uint64_t* h_device = nullptr;  // the same memory as the device sees it
     const void* keys_sorted() { return sorted_in_alt ? keys_alt.p : keys.p; }
@@ -437,9 +438,7 @@ mgs_status mgs_frame_create(mgs_ctx* ctx, mgs_frame** out) {
         delete f;
         return fail(ctx, MGS_ERR_HIP, "device address of pinned memory");
     }
-    // (zeroed: the staged-entry counters are read before they are first written)
-    if (grow(ctx, f->misc, 256 + 4096) != MGS_OK || hipMemset(f->misc.p, 0, f->misc.bytes) != hipSuccess) {
-        release(f->misc);
+    if (grow(ctx, f->misc, 256 + 4096) != MGS_OK) {
         (void)hipHostFree(f->h_pinned);
         delete f;
         return MGS_ERR_OOM;
@@ -606,6 +605,13 @@ mgs_status forward_impl(mgs_frame* f, mgs_stream stream_, const mgs_gaussians* g
         (s = grow(ctx, f->stats, (size_t)P * 16)) || (s = grow(ctx, f->evals, (size_t)P * 16)) ||
         (s = grow(ctx, f->rsort_tmp, sort_scratch_bytes(R))))
         return s;
+    if (!f->misc_cleared) {
+        // before the first use, on the stream of that use (one that does not
+        // wait for the null stream, possibly): the staged-entry counters and
+        // the backward's histogram are read before a forward has written them
+        launch_fill_u32(stream, (uint32_t*)f->misc.p, f->misc.bytes / 4, 0u);
+        f->misc_cleared = f->flag_clear[0] = f->flag_clear[1] = true;
+    }
     f->flag_word = f->reserved ? 0 : f->flag_word ^ 1;
     if (f->reserved || !f->flag_clear[f->flag_word]) launch_fill_u32(stream, f->flags(), 1, 0u);
     f->flag_clear[f->flag_word] = false;

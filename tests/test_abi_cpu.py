@@ -92,3 +92,12 @@ def test_create_fails_cleanly_without_gfx950():
     with pytest.raises(M.MaskGSError):
         M.mgs_create(0)
     assert M.mgs_last_error(None)
+
+
+def test_library_queues_nothing_on_the_null_stream():
+    """Every fill and copy names the caller's stream: one on the null stream is
+    not ordered with a caller's non-blocking stream."""
+    src = os.path.join(ROOT, "paper_2412_20522_amd", "csrc")
+    for name in sorted(os.listdir(src)):
+        txt = re.sub(r"//[^\n]*", "", open(os.path.join(src, name)).read())
+        assert not re.search(r"\bhip(Memset|Memcpy)(D8|D16|D32|2D|3D|DtoD|DtoH|HtoD|ToSymbol|FromSymbol)?\s*\(", txt), name

@@ -116,3 +116,35 @@ def test_seventeen_views_are_refused(rast):
         assert M.STATUS[rc] == "MGS_ERR_INVALID_ARG"
     finally:
         rast.release_frame(frame)
+
+
+def test_first_forward_on_a_stream_that_does_not_wait_for_the_null_stream(rast):
+    """A frame made and used on a non-blocking stream while the null stream is
+    busy: nothing of its set-up waits behind the null stream's work to write
+    into the frame later."""
+    from paper_2412_20522_amd import maskgs as M
+    s = scenegen.small_scene(2000, 90, 70, seed=507, sh_degree=1, log_scale_mean=-2.3, n_views=2)
+    cams = s["cameras"]
+    dev = U.to_device(s)
+    params = {k: dev[k] for k in U.PARAM_KEYS}
+    P = sum(c["width"] * c["height"] for c in cams)
+    dl = torch.from_numpy(np.random.default_rng(9).normal(size=3 * P).astype(np.float32)).cuda()
+    frame = rast.acquire_frame()
+    ref_img = rast.forward(frame, params, dev["masks"], cams)
+    ref = rast.backward(frame, params, dl)
+    rast.release_frame(frame)
+    side = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    torch.cuda._sleep(20_000_000)  # the null stream: some 10 ms
+    fresh = M.mgs_frame_create(rast.ctx)
+    with torch.cuda.stream(side):
+        for _ in range(3):
+            img = rast.forward(fresh, params, dev["masks"], cams)
+            g = rast.backward(fresh, params, dl)
+        side.synchronize()
+        rast.check(fresh)
+    torch.cuda.synchronize()
+    assert torch.equal(img, ref_img)
+    for k in (*U.PARAM_KEYS, "masks"):
+        assert U.rel_err(getattr(g, k).cpu().numpy(), getattr(ref, k).cpu().numpy()) <= 1e-5, k
+    M.mgs_frame_destroy(fresh)
