@@ -1915,7 +1915,12 @@ __device__ __forceinline__ int rows_add(int x) {
     const auto b = __builtin_amdgcn_permlane32_swap((uint32_t)y, (uint32_t)y, false, false);
     return (int)(b[0] + b[1]);
 }
-// maximum over the 16 lanes of each row, in every lane of the row
+// The bit of row r and this lane's column in a mask over the wave's lanes.
+__device__ __forceinline__ bool row_in_all_rows(uint64_t mask, int r) {
+    uint32_t m = (uint32_t)(mask >> (16 * r)) & 0xffffu;
+    m |= m << 16;
+    return __builtin_amdgcn_inverse_ballot_w64((uint64_t)m << 32 | m);
+}
 
 // LDS of one workgroup after the staging area of lds_bytes: per wave the
 // block's list (byte offsets of its entries in L.E, two rounds of padding)
@@ -2125,12 +2130,14 @@ __global__ void __launch_bounds__(FINE_NT, 6) hybrid_fwd_fine_kernel(
             const float wgt = hit ? B.z * e.alpha * Tb : 0.f;
             const Rows2 wr = row_pairs(wgt);
             const Rows2 wa = row_halves(wr.lo), wb = row_halves(wr.hi);
-            // (an entry that does not reach the pixel must not touch its
-            // colour: it may be infinite)
-            if (wa.lo != 0.f) C = fmaf(wa.lo, c0, C);
-            if (wb.lo != 0.f) C = fmaf(wb.lo, c1, C);
-            if (wa.hi != 0.f) C = fmaf(wa.hi, c2, C);
-            if (wb.hi != 0.f) C = fmaf(wb.hi, c3, C);
+            // an entry that does not reach the pixel must not touch its
+            // colour, which may be infinite; one that does always adds to it,
+            // also with weight 0, as in hybrid_fwd_kernel
+            const uint64_t hm = ballot(hit);
+            if (row_in_all_rows(hm, 0)) C = fmaf(wa.lo, c0, C);
+            if (row_in_all_rows(hm, 1)) C = fmaf(wb.lo, c1, C);
+            if (row_in_all_rows(hm, 2)) C = fmaf(wa.hi, c2, C);
+            if (row_in_all_rows(hm, 3)) C = fmaf(wb.hi, c3, C);
             if (hit) {
                 last = k;
                 if (STATS) {

@@ -380,3 +380,35 @@ def test_mask_loss_and_gradient_over_the_reduction_variants(n):
     o = out.cpu().numpy().astype(np.float64)
     # a few FP32 roundings of the sum and the product
     assert np.all(np.abs(o[:, 0] - g) <= 1e-6 * (np.abs(g) + np.abs(d) + 1.0)) and np.array_equal(o[:, 1], -o[:, 0])
+
+
+@pytest.mark.parametrize("away", [False, True], ids=["small-splat", "tile-wide"])
+def test_infinite_colours_reach_the_pixels_of_their_splats_only(away):
+    """A splat of infinite colour makes the pixels it is blended into infinite,
+    or NaN where its mask (its weight) is 0, and no others: in both kernels."""
+    from paper_2412_20522_amd.raster import Rasterizer
+    n, w, h = 400, 64, 48
+    s = scenegen.small_scene(n, w, h, seed=961, sh_degree=1, log_scale_mean=-3.0, opacity_mean=-2.0)
+    s["masks"][:] = 1.0
+    s["masks"][1::2] = 0.0
+    bad = np.array([10, 11, 200, 201])  # two of mask 1, two of mask 0
+    cams = [s["cameras"][0]] + ([_big()] if away else [])
+    dl = np.random.default_rng(8).normal(size=3 * w * h).astype(np.float32)
+    rast = Rasterizer(0)
+    ref, _ = _run(rast, s, cams, dl, **_settings((16, 16)))
+    reach = []
+    for k in bad:  # the pixels a splat is blended into, from the counters without it
+        one = dict(s, opacity_logits=s["opacity_logits"].copy())
+        one["opacity_logits"][k] = -20.0  # below the alpha filter
+        a, _ = _run(rast, one, cams, dl, **_settings((16, 16)))
+        reach.append(ref["stats"].reshape(-1, 4)[:, 1] > a["stats"].reshape(-1, 4)[:, 1])
+        assert reach[-1].any() and not reach[-1].all()
+    s["sh"][bad, 0] = np.inf
+    b, _ = _run(rast, s, cams, dl, **_settings((16, 16)))
+    img = b["image"].reshape(3, -1)
+    nan = reach[1] | reach[3]
+    inf = (reach[0] | reach[2]) & ~nan
+    assert np.isnan(img[:, nan]).all() and np.isposinf(img[:, inf]).all()
+    rest = ~(nan | inf)
+    assert np.array_equal(img[:, rest], ref["image"].reshape(3, -1)[:, rest])
+    assert np.array_equal(b["t_final"], ref["t_final"]) and np.array_equal(b["last"], ref["last"])
