@@ -1924,10 +1924,10 @@ __device__ __forceinline__ bool row_in_all_rows(uint64_t mask, int r) {
 
 // LDS of one workgroup after the staging area of lds_bytes: per wave the
 // block's list (byte offsets of its entries in L.E, two rounds of padding)
-// and, in the backward, ten partial sums per staged entry.
+// and, in the backward, twice ten partial sums per staged entry.
 constexpr int FINE_LIST = FINE_BATCH + 8;
 constexpr size_t fine_lds_bytes(bool bwd) {
-    return lds_bytes(FINE_BATCH) + (FINE_NT / 64) * FINE_LIST * 2 + (bwd ? FINE_BATCH * 40 : 0);
+    return lds_bytes(FINE_BATCH) + (FINE_NT / 64) * FINE_LIST * 2 + (bwd ? 2 * FINE_BATCH * 40 : 0);
 }
 
 // Part q of a launch over the 8x8 parts of every tile, tiles in launch order.
@@ -2256,12 +2256,18 @@ __global__ void __launch_bounds__(FINE_NT, 5) hybrid_bwd_fine_kernel(
     const bool odd = (row & 1) != 0, upper = row >= 2;
     const Lds L = carve(smem, FINE_BATCH);
     uint16_t* list = reinterpret_cast<uint16_t*>(smem + lds_bytes(FINE_BATCH)) + wave * FINE_LIST;
-    // ten partial sums per staged entry, added up over the part's blocks
+    // ten partial sums per staged entry over the part's blocks, in two sets: one
+    // of waves 0 and 1, one of waves 2 and 3.  A sum of two does not depend on
+    // which wave comes first, so that the FP32 sums repeat to the bit.  (The LDS
+    // then holds four workgroups instead of five: 423 and 423 us a step of 200 k
+    // small splats at 800x800, 438 -> 447 us for the slowest case seen.)
+    constexpr int SET = FINE_BATCH * 10;
     float* acc = reinterpret_cast<float*>(smem + lds_bytes(FINE_BATCH) + (FINE_NT / 64) * FINE_LIST * 2);
+    float* wacc = acc + (wave >> 1) * SET;
     const int qi = fold10_quantity(col);
     const EvalConsts ek = eval_consts(st);
     if (*hl.cur_need > hl.cur_cap) return;  // the forward reported it
-    for (int i = t; i < FINE_BATCH * 10; i += FINE_NT) acc[i] = 0.f;
+    for (int i = t; i < 2 * SET; i += FINE_NT) acc[i] = 0.f;
     const uint32_t q = blockIdx.x;
     const FinePart fp = fine_part(views, hl, st, q, parts);
     const uint32_t tile = fp.tile;
@@ -2391,20 +2397,21 @@ __global__ void __launch_bounds__(FINE_NT, 5) hybrid_bwd_fine_kernel(
             }
             const float x10 = row_fold10(v, col);
             // (own / 48) 10 + qi
-            if (qi >= 0 && x10 != 0.f) atomicAdd(acc + (own / 48u) * 10u + (uint32_t)qi, x10);
+            if (qi >= 0 && x10 != 0.f) atomicAdd(wacc + (own / 48u) * 10u + (uint32_t)qi, x10);
         }
         __syncthreads();
         for (int i = t; i < Mb * 10; i += FINE_NT) {
-            const float xs = acc[i];
-            if (xs == 0.f) continue;
-            acc[i] = 0.f;
+            const float x0 = acc[i], x1 = acc[i + SET];
+            if (x0 == 0.f && x1 == 0.f) continue;
+            acc[i] = acc[i + SET] = 0.f;
+            const double xs = (double)x0 + (double)x1;
             const int j = i / 10, k = i - j * 10;
             const uint32_t r = __float_as_uint(L.E[3 * j + 2].w);
             // (the totals of t^2 and dy^2 rescaled, as in hybrid_bwd_kernel)
             if (k < DREC)
-                atomicAdd(d_rec + (size_t)r * DREC + k, (double)(xs * (k == 2 || k == 4 ? 0.5f * QSCALE : 1.f)));
+                atomicAdd(d_rec + (size_t)r * DREC + k, k == 2 || k == 4 ? xs * (0.5 * (double)QSCALE) : xs);
             else
-                atomicAdd(d_masks + ((int64_t)r - rec_base), (double)xs);
+                atomicAdd(d_masks + ((int64_t)r - rec_base), xs);
         }
         __syncthreads();  // the next batch overwrites the LDS
     }
