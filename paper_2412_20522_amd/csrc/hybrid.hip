@@ -521,6 +521,8 @@ __device__ __forceinline__ uint64_t waves_scan(uint64_t x) {
     }
     return x;
 }
+// (only where the whole wave is active: in a branch, what the compiler moved
+// into it is missing in the lanes that are not)
 __device__ __forceinline__ uint64_t read_lane(uint64_t x, int l) {
     const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)x, l);
     return (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(x >> 32), l) << 32 | lo;
@@ -554,7 +556,8 @@ __global__ void __launch_bounds__(LO_GROUP) list_offsets_group_kernel(const uint
     }
     __syncthreads();
     const uint64_t ws = waves_scan(s_w[lane & 15][0]);
-    if (w < nw) lo.wave_rel[w] = (wid > 0 ? read_lane(ws, wid - 1) : 0u) + x - c;
+    const uint64_t before = wid > 0 ? read_lane(ws, wid - 1) : 0u;
+    if (w < nw) lo.wave_rel[w] = before + x - c;
     if (t < 5) {
         uint64_t tot = 0;
 #pragma unroll
@@ -611,7 +614,8 @@ __global__ void __launch_bounds__(LO_GROUP) list_offsets_total_kernel(int64_t ng
         if (lane == 63) s_w[wid][0] = x;
         __syncthreads();
         const uint64_t ws = waves_scan(s_w[lane & 15][0]);
-        if (g < ng) lo.group_off[g] = carry + (wid > 0 ? read_lane(ws, wid - 1) : 0u) + x - c;
+        const uint64_t before = wid > 0 ? read_lane(ws, wid - 1) : 0u;
+        if (g < ng) lo.group_off[g] = carry + before + x - c;
         carry += read_lane(ws, 15);
         __syncthreads();  // s_w is written again by the next round
     }

@@ -429,3 +429,28 @@ def test_small_splat_gradients_of_one_part_repeat_to_the_bit(n):
         first = got if first is None else first
         for k, v in got.items():
             assert np.array_equal(v, first[k]), k
+
+
+@pytest.mark.parametrize("waves", [4100, 4108, 4612, 4676, 4748, 4936, 4996, 5000, 5060, 5116, 5120, 5124, 9160])
+def test_list_offsets_of_a_group_that_ends_within_a_wave(waves):
+    """Numbers of positions whose last group of 1024 waves ends in each part of
+    a 64-lane row of it, with few lanes there: every slot of the lists is
+    filled, each record once per tile of its rectangle."""
+    from paper_2412_20522_amd import maskgs as M
+    from paper_2412_20522_amd.raster import Rasterizer
+    n = 64 * waves - 37
+    s = scenegen.small_scene(n, 70, 50, seed=970, sh_degree=0, log_scale_mean=-5.0)
+    dev = U.to_device(s)
+    rast = Rasterizer(0, **_settings((16, 16), sh_degree=0, tile_cull=0, wide_tiles=-1, stats=0))
+    frame = rast.acquire_frame()
+    rast.forward(frame, {k: dev[k] for k in U.PARAM_KEYS}, dev["masks"], s["cameras"])
+    ex = {k: M.mgs_frame_export(rast.ctx, frame, k) for k in ("order", "tiles", "values", "ranges")}
+    torch.cuda.synchronize()
+    K = rast.stats(frame)["n_instances"]
+    rast.release_frame(frame)
+    tiles = U.u32(ex["tiles"]).astype(np.int64)
+    vals, order = U.u32(ex["values"]).astype(np.int64)[:K], U.u32(ex["order"])
+    assert K == tiles.sum() and vals.max() < n
+    assert np.array_equal(np.bincount(order[vals], minlength=n), tiles)
+    r = U.u32(ex["ranges"]).reshape(-1, 2).astype(np.int64)
+    assert (r[:, 1] - r[:, 0]).sum() == K
