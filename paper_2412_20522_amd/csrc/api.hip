@@ -685,8 +685,8 @@ mgs_status forward_impl(mgs_frame* f, mgs_stream stream_, const mgs_gaussians* g
         // the entries staged for the backward: room for the previous forward's
         // count with a margin (a batch that does not fit is merged again)
         const uint64_t prev = f->h_pinned[24];
-        const uint64_t first = (uint64_t)T * staged_first((uint64_t)T);
-        const uint64_t want = std::min<uint64_t>(std::max<uint64_t>((uint64_t)P + first, prev + prev / 4), STG_NOWHERE);
+        const uint64_t want = std::min<uint64_t>(std::max<uint64_t>(staged_room((uint64_t)T, (uint64_t)P), prev + prev / 4),
+                                                 STG_NOWHERE);
         // (the count includes the unused tails of the workgroups' chunks; the
         // kernels for small splats keep no staged list)
         if (!f->fine && (s = grow(ctx, f->stg, (size_t)want * 8 + 8))) return s;

@@ -7,19 +7,31 @@
 namespace mgs {
 
 // A workgroup's first chunk is its own by its index, further ones come from a
-// global counter (with every workgroup of a launch at that counter at its
-// start, forward compositing waits).
+// global counter, where forward compositing waits: with every workgroup of a
+// launch there at its start, and later at 6.5 ns for each of them.
 constexpr uint32_t STG_FIRST = 256;
 constexpr uint32_t STG_CHUNK = 512;
-// First chunks take 2 KB per tile whether or not the tile has entries; beyond
-// this many entries for all of them (256 MB), every chunk comes from the
-// counter.
-constexpr uint64_t STG_FIRST_MAX = 1ull << 25;
+// First chunks take their room (8 bytes an entry) whether or not the tile has
+// entries: 2 KB per tile, and in launches of more than STG_MANY workgroups (1
+// GB) 512 bytes, which is an entry per pixel of the smallest tiles.  16 views
+// of 1920x1080 in 8x8 tiles (518,400), forward with first chunks of 256, 64 and
+// no entries: 256 splats 584, 582 and 1,705 us, 4096 splats 641, 637 and 3,381
+// us, 20,000 splats, whose lists are longer than 64, 1,065, 1,684 and 3,631 us.
+constexpr uint64_t STG_MANY = 524288;
+constexpr uint32_t STG_FIRST_MANY = 64;
 constexpr uint32_t STG_NOWHERE = 0xffffffffu;
 
 // Entries of each workgroup's first chunk in a launch of so many workgroups.
 constexpr uint32_t staged_first(uint64_t workgroups) {
-    return workgroups <= STG_FIRST_MAX / STG_FIRST ? STG_FIRST : 0u;
+    return workgroups <= STG_MANY ? STG_FIRST : STG_FIRST_MANY;
+}
+
+// Entries of the list for a first forward over so many tiles and pixels: the
+// first chunks, and an entry per pixel, beside them or, with many tiles, among
+// them.
+constexpr uint64_t staged_room(uint64_t tiles, uint64_t pixels) {
+    const uint64_t first = tiles * staged_first(tiles);
+    return tiles <= STG_MANY ? pixels + first : (pixels > first ? pixels : first);
 }
 
 // The 32-bit offset of m entries from `base` on in a list of `cap` entries, or

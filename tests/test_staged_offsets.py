@@ -19,13 +19,15 @@ using namespace mgs;
 // index, then one of the counter for every batch that does not fit.
 static int check(uint64_t groups, uint64_t cap, uint64_t counter) {
     const uint64_t first = staged_first(groups);
-    if (first != 0 && first * groups > STG_FIRST_MAX) return 1;
+    // at most 2 KB per tile below, an entry per pixel of 8x8 tiles above the line
+    if (first == 0 || first > (groups <= STG_MANY ? 256u : 64u) || staged_room(groups, 64 * groups) > 256 * groups + 64 * groups)
+        return 1;
+    if (groups > STG_MANY && staged_room(groups, 64 * groups) > 64 * groups) return 1;
     const uint64_t probes[] = {0, groups / 3, groups / 2, groups - 1};
     uint64_t end = 0;  // the highest entry in use by an earlier chunk
     for (const uint64_t g : probes) {
         const uint64_t base = g * first;
         const uint32_t off = staged_offset(base, (uint32_t)first, cap);
-        if (first == 0) continue;
         if (off != STG_NOWHERE && (off != base || off + first > cap)) return 2;
         if (off == STG_NOWHERE && base + first <= cap && base + first <= STG_NOWHERE) return 3;
         if (off != STG_NOWHERE && base + first > end) end = base + first;
@@ -41,7 +43,7 @@ static int check(uint64_t groups, uint64_t cap, uint64_t counter) {
 }
 
 int main() {
-    const uint64_t groups[] = {1, 2, 131071, 131072, 131073, (1u << 24) - 1, 1u << 24, (1u << 24) + 1, 20971520, 67108864};
+    const uint64_t groups[] = {1, 2, 131072, 524287, 524288, 524289, (1u << 24) - 1, 1u << 24, (1u << 24) + 1, 20971520, 67108864};
     const uint64_t caps[] = {0, 255, 256, 4096, 1u << 25, 0x7fffffffull, 0xfffffffeull, 0xffffffffull, 0x100000000ull,
                              0x200000000ull};
     const uint64_t counters[] = {0, 512, 0xfffff000ull, 0xfffffe00ull, 0x100000000ull, 0x300000200ull};
