@@ -715,6 +715,10 @@ __global__ void __launch_bounds__(LO_GROUP) list_offsets_one_kernel(const uint32
 // 300 k (1.6 M); walking runs 104, 23 and 14 us (20.2 M entries: 41 us of
 // traffic for them, 27 us for the cells).  Writes never leave the wave's counted slots; a slot
 // the emission does not fill gets KEY_NONE.  No step waits on another wave.
+// Words that a thread clears at most: few records over many tiles take further
+// workgroups, which only clear (left to the records', 256 of one view in 32,400
+// tiles: stage 56 -> 14 us, of 16 views in 518,400 tiles 58 -> 20 us).
+constexpr int DUP_CLEAR = 4;
 __global__ void __launch_bounds__(256) duplicate_kernel(
     const float4* __restrict__ srec, const uint32_t* __restrict__ cnt_sorted,
     const uint4* __restrict__ cells, ListOffsets lo, int64_t R, int64_t n, ViewSet views, DevSettings st,
@@ -2600,10 +2604,11 @@ void launch_duplicate_lists(hipStream_t stream, const float* srec, const uint32_
         launch_fill_spans(stream, fill, fill_count);
         return;
     }
-    hipLaunchKernelGGL(duplicate_kernel, dim3(blocks_of(R)), dim3(256), 0, stream,
-                       reinterpret_cast<const float4*>(srec), cnt_sorted, reinterpret_cast<const uint4*>(cells),
-                       list_offsets(part, R), R,
-                       n, views, st, keys, keys16, vals, capacity, flags, make_fill_set(fill, fill_count));
+    const FillSet fs = make_fill_set(fill, fill_count);
+    const unsigned grid = std::max(blocks_of(R), blocks_of((fs.total + DUP_CLEAR - 1) / DUP_CLEAR));
+    hipLaunchKernelGGL(duplicate_kernel, dim3(grid), dim3(256), 0, stream, reinterpret_cast<const float4*>(srec),
+                       cnt_sorted, reinterpret_cast<const uint4*>(cells), list_offsets(part, R), R, n, views, st, keys,
+                       keys16, vals, capacity, flags, fs);
 }
 
 void launch_tile_order(hipStream_t stream, const uint32_t* key, uint32_t tiles, uint32_t* hist_cursor,

@@ -454,3 +454,31 @@ def test_list_offsets_of_a_group_that_ends_within_a_wave(waves):
     assert np.array_equal(np.bincount(order[vals], minlength=n), tiles)
     r = U.u32(ex["ranges"]).reshape(-1, 2).astype(np.int64)
     assert (r[:, 1] - r[:, 0]).sum() == K
+
+
+@pytest.mark.parametrize("n", [1, 3, 300])
+def test_few_records_over_many_tiles_leave_no_range_of_the_forward_before(n):
+    """The duplication clears the cells' ranges, with workgroups beyond those
+    of the records where there are many cells."""
+    from paper_2412_20522_amd import maskgs as M
+    from paper_2412_20522_amd.raster import Rasterizer
+    w, h = 2000, 1100
+    s = scenegen.small_scene(40_000, w, h, seed=980, sh_degree=0, log_scale_mean=-4.0)
+    s["means"] *= 2.5  # over the whole view
+    dev = U.to_device(s)
+    few = {k: v[:n].contiguous() for k, v in dev.items() if torch.is_tensor(v)}
+    rast = Rasterizer(0, **_settings((8, 8), sh_degree=0, tile_cull=0, wide_tiles=-1, stats=0))
+    frame, fresh = rast.acquire_frame(), M.mgs_frame_create(rast.ctx)
+    rast.forward(frame, {k: dev[k] for k in U.PARAM_KEYS}, dev["masks"], s["cameras"])
+    r = U.u32(M.mgs_frame_export(rast.ctx, frame, "ranges")).reshape(-1, 2)
+    assert (r[:, 1] > r[:, 0]).mean() > 0.5
+    out = []
+    for f in (frame, fresh):
+        img = rast.forward(f, {k: few[k] for k in U.PARAM_KEYS}, few["masks"], s["cameras"])
+        r = U.u32(M.mgs_frame_export(rast.ctx, f, "ranges")).reshape(-1, 2).astype(np.int64)
+        assert (r[:, 1] - r[:, 0]).sum() == rast.stats(f)["n_instances"]
+        out.append((img.cpu().numpy(), r))
+    assert np.array_equal(out[0][0], out[1][0])
+    assert np.array_equal(out[0][1], out[1][1])
+    rast.release_frame(frame)
+    rast.release_frame(fresh)
