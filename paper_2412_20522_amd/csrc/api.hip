@@ -327,7 +327,7 @@ struct mgs_frame {
     // misc: flags (2 u32) at 0, list entry count (u64) at 8, wide record count
     // (u64) at 16, checkpoint count (u64) at 24, region entry count (u64) at
     // 32, footprint tiles of all and of large splats (u64) at 40 and 48,
-    // staged-entry counters (2 u64) at 192; the histogram and cursors (2 x 256
+    // staged-list counter (u32) at 192; the histogram and cursors (2 x 256
     // u32) of the forward's tile order from 256, of the backward's from 2304
     bool misc_cleared = false;     // by the first forward
     uint64_t* h_pinned = nullptr;  // read-back of misc
@@ -347,7 +347,7 @@ struct mgs_frame {
     uint64_t* wide_counts() { return (uint64_t*)((char*)misc.p + 16); }
     uint64_t* cur_need() { return (uint64_t*)((char*)misc.p + 24); }
     uint32_t* live() { return (uint32_t*)((char*)misc.p + 64); }  // per view: records with tiles
-    uint64_t* stg_count() { return (uint64_t*)((char*)misc.p + 192); }
+    uint32_t* stg_count() { return (uint32_t*)((char*)misc.p + 192); }
     uint32_t* order_hist() { return (uint32_t*)((char*)misc.p + 256); }
     uint32_t* order_hist_b() { return order_hist() + 512; }
     double* dm_acc() { return (double*)d_rec.p + (size_t)R * DREC; }
@@ -358,7 +358,7 @@ struct mgs_frame {
         // bytes of slack for an odd count)
         const uint64_t n2 = clear_drec ? ((uint64_t)R * DREC + (uint64_t)n + 1) / 2 : 0;
         return HybridBuffers{vals_sorted(), (const uint32_t*)ranges.p, (uint32_t*)cur.p, (const uint32_t*)cur_off.p, (uint32_t*)nbatch.p, cur_need(), cap,
-                             flags(), (uint32_t*)cur_stg.p, (uint32_t*)stg.p, stg_count(), scap, staged_first((uint64_t)total_tiles),
+                             flags(), (uint32_t*)cur_stg.p, (uint32_t*)stg.p, stg_count(), scap,
                              clear_drec ? (double*)d_rec.p : nullptr, n2, (const uint32_t*)order.p, fine};
     }
 };
@@ -507,10 +507,10 @@ mgs_status mgs_frame_reserve(mgs_frame* f, mgs_stream stream_, double slack) {
     if (!(slack >= 1.0)) return fail(ctx, MGS_ERR_INVALID_ARG, "slack %g must be >= 1 (or <= 0 to release)", slack);
     if (!f->have_forward || f->reserved)
         return fail(ctx, MGS_ERR_STATE, "mgs_frame_reserve needs a preceding plain mgs_forward");
-    MGS_HIP(ctx, hipMemcpyAsync(f->h_pinned, f->misc.p, 208, hipMemcpyDeviceToHost, stream));
+    MGS_HIP(ctx, hipMemcpyAsync(f->h_pinned, f->misc.p, 200, hipMemcpyDeviceToHost, stream));
     MGS_HIP(ctx, hipStreamSynchronize(stream));
     const double K = (double)f->h_pinned[1], C = (double)f->h_pinned[3];
-    const double S = (double)f->h_pinned[24] + (double)f->h_pinned[25];
+    const double S = (double)(f->h_pinned[24] & 0xffffffffu) * STG_CHUNK;
     const int64_t K_cap = (int64_t)std::ceil(K * slack) + 4096;
     const int64_t cur_cap = (int64_t)std::ceil(C * slack) + 4096;
     const int64_t stg_cap = std::min<int64_t>((int64_t)std::ceil(S * slack) + 4096, 0xffffffffll);
@@ -607,7 +607,7 @@ mgs_status forward_impl(mgs_frame* f, mgs_stream stream_, const mgs_gaussians* g
         return s;
     if (!f->misc_cleared) {
         // before the first use, on the stream of that use (one that does not
-        // wait for the null stream, possibly): the staged-entry counters and
+        // wait for the null stream, possibly): the staged-list counter and
         // the backward's histogram are read before a forward has written them
         launch_fill_u32(stream, (uint32_t*)f->misc.p, f->misc.bytes / 4, 0u);
         f->misc_cleared = f->flag_clear[0] = f->flag_clear[1] = true;
@@ -696,11 +696,12 @@ mgs_status forward_impl(mgs_frame* f, mgs_stream stream_, const mgs_gaussians* g
     if (imp && (s = grow(ctx, f->imp_acc, (size_t)f->n * 8 + 8))) return s;
     const bool keys16 = cell_keys16(f->K, T + NR);
     // the duplication's launch also clears the ranges, the forward's tile
-    // order's histogram and cursors, the staged-entry counter, the importance sums
-    // and, in the plain path, the next forward's flags
+    // order's histogram and cursors, the importance sums and, in the plain path,
+    // the next forward's flags, and sets the staged-list counter behind the
+    // workgroups' first chunks
     const FillSpan zero[] = {{(uint32_t*)f->ranges.p, 2 * (T + NR), 0u},
                              {f->order_hist(), 512, 0u},
-                             {(uint32_t*)f->stg_count(), 4, 0u},
+                             {f->stg_count(), 1, f->fine ? 0u : staged_first_units((uint64_t)T)},
                              {f->reserved ? nullptr : f->flag_words() + (f->flag_word ^ 1), 1, 0u},
                              {imp ? (uint32_t*)f->imp_acc.p : nullptr, 2 * f->n, 0u},
                              {imp ? (uint32_t*)imp_max : nullptr, f->n, 0u}};

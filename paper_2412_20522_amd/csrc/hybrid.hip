@@ -573,7 +573,7 @@ struct ListTotals {
     uint64_t* total;
     uint64_t* wide;
     const uint32_t* flags;   // two words
-    const uint64_t* staged;  // two
+    const uint32_t* staged;
     uint64_t* host;
 };
 // thread k of the workgroup holds total k (0: entries, 1 .. 4: as group_tot)
@@ -586,7 +586,7 @@ __device__ __forceinline__ void put_totals(const ListTotals& o, int k, uint64_t 
         if (k == 0) {
             o.host[1] = v;
             o.host[0] = (uint64_t)o.flags[0] | (uint64_t)o.flags[1] << 32;
-            o.host[24] = o.staged[0] + o.staged[1];
+            o.host[24] = (uint64_t)*o.staged * STG_CHUNK;
         } else {
             o.host[2 + w] = v;
         }
@@ -1383,10 +1383,9 @@ __device__ __forceinline__ void pixel_of(int t, int i, const TileGeom& tg, int& 
 }
 
 // Words of Lds::wsum behind the scan's, of the workgroup's staged-list chunk:
-// next free entry (two words), entries left, where the batch's entries go
-// (STG_NOWHERE: nowhere).  (The batch is a multiple of 32, so that the two
-// words are 8-byte aligned.)
-constexpr int STG_BASE = 8, STG_LEFT = 10, STG_OFF = 11;
+// next free entry, entries left, where the batch's entries go (both
+// STG_NOWHERE: nowhere).
+constexpr int STG_BASE = 8, STG_LEFT = 9, STG_OFF = 10;
 
 struct HybridLists {
     const uint32_t* vals;      // list entries (sorted positions) in (cell, position) order
@@ -1402,9 +1401,8 @@ struct HybridLists {
     // entry (sorted position, index within the merged batch)
     uint2* cur_stg;
     uint2* stg;                // null: the backward merges again
-    uint64_t* stg_count;       // two: entries taken from the counter, entries of the first chunks
-    uint64_t stg_cap;
-    uint32_t stg_first;        // entries of each workgroup's first chunk (staged_first)
+    uint32_t* stg_count;       // the next chunk, in units of STG_CHUNK entries (behind the first chunks)
+    uint32_t stg_cap;
     double* drec_clear;        // the backward's FP64 accumulators, cleared by the forward
     uint64_t drec_clear_n2;    // their size in pairs of doubles
     const uint32_t* order;     // optional: tile of each workgroup
@@ -1458,9 +1456,9 @@ __global__ void __launch_bounds__(TW * TH / PPT, PPT >= 4 ? 5 : STATS ? 7 : 8) h
     }
     // staged-list chunk of this workgroup (used by thread 0 only)
     if (hl.stg && t == 0) {
-        *reinterpret_cast<uint64_t*>(L.wsum + STG_BASE) = (uint64_t)blockIdx.x * hl.stg_first;
-        L.wsum[STG_LEFT] = hl.stg_first;
-        if (blockIdx.x == 0) hl.stg_count[1] = (uint64_t)gridDim.x * hl.stg_first;
+        const uint32_t first = staged_first(gridDim.x);
+        L.wsum[STG_BASE] = staged_first_base(blockIdx.x, first);
+        L.wsum[STG_LEFT] = first;
     }
     const uint32_t tile = uniform(hl.order ? hl.order[blockIdx.x] : blockIdx.x);
     const TileGeom tg = tile_geom(views, tile, TW, TH);
@@ -1515,17 +1513,14 @@ __global__ void __launch_bounds__(TW * TH / PPT, PPT >= 4 ? 5 : STATS ? 7 : 8) h
         // thread 0 sub-allocates from a chunk the workgroup took from the
         // global counter (one atomic per chunk, not per batch)
         if (hl.stg && t == 0) {
-            uint64_t* const base = reinterpret_cast<uint64_t*>(L.wsum + STG_BASE);
-            uint64_t cbase = *base;
-            uint32_t cleft = L.wsum[STG_LEFT];
+            uint32_t cbase = L.wsum[STG_BASE], cleft = L.wsum[STG_LEFT];
             if ((uint32_t)bt.M > cleft) {
-                cbase = (uint64_t)gridDim.x * hl.stg_first +
-                        atomicAdd(reinterpret_cast<unsigned long long*>(hl.stg_count), (unsigned long long)STG_CHUNK);
+                cbase = staged_base(atomicAdd(hl.stg_count, 1u));
                 cleft = STG_CHUNK;
             }
             const uint32_t off = staged_offset(cbase, (uint32_t)bt.M, hl.stg_cap);
             L.wsum[STG_OFF] = off;
-            *base = cbase + (uint32_t)bt.M;
+            L.wsum[STG_BASE] = staged_next(off, (uint32_t)bt.M);
             L.wsum[STG_LEFT] = cleft - (uint32_t)bt.M;
             hl.cur_stg[hl.cur_off[tile] + b] = make_uint2(off, (uint32_t)bt.M);
         }
@@ -2509,8 +2504,7 @@ HybridLists make_lists(const HybridBuffers& b) {
     hl.stg = reinterpret_cast<uint2*>(b.stg);
     hl.stg_count = b.stg_count;
     hl.order = b.order;
-    hl.stg_cap = b.stg_cap;
-    hl.stg_first = b.stg_first;
+    hl.stg_cap = (uint32_t)std::min<uint64_t>(b.stg_cap, STG_NOWHERE);
     hl.drec_clear = b.drec_clear;
     hl.drec_clear_n2 = b.drec_clear_n2;
     return hl;
@@ -2580,7 +2574,7 @@ ListOffsets list_offsets(uint32_t* part, int64_t R) {
 size_t classify_parts_bytes(int64_t R) { return counts_bytes(R) + (size_t)(waves_of(R) + 6 * groups_of(R)) * 8 + 8; }
 
 void launch_list_offsets(hipStream_t stream, uint32_t* part, int64_t R, uint64_t* total, uint64_t* wide_counts,
-                         bool sizes, const uint32_t* flags, const uint64_t* staged, uint64_t* host) {
+                         bool sizes, const uint32_t* flags, const uint32_t* staged, uint64_t* host) {
     const ListOffsets lo = list_offsets(part, R);
     const ListTotals out{total, wide_counts, flags, staged, host};
     const int64_t ng = R > 0 ? groups_of(R) : 0, nb = (int64_t)blocks_of(R);

@@ -133,9 +133,9 @@ void launch_permute_classify(hipStream_t stream, const uint32_t* order, const ui
 // the classification; else 0) [3] = tiles of all footprints, [4] = of those
 // of large splats; host (optional, pinned memory the device can write)
 // receives for the host [0] = the two flag words, [1] = the entry total, [2] ..
-// [6] = wide_counts, [24] = staged[0] + staged[1]
+// [6] = wide_counts, [24] = *staged in entries
 void launch_list_offsets(hipStream_t stream, uint32_t* part, int64_t R, uint64_t* total, uint64_t* wide_counts,
-                         bool sizes, const uint32_t* flags, const uint64_t* staged, uint64_t* host);
+                         bool sizes, const uint32_t* flags, const uint32_t* staged, uint64_t* host);
 // The rule that picks the compositing kernels (pixels over all views; the two
 // counts above, needed where fine_needs_sizes).
 bool fine_needs_sizes(int64_t pixels);
@@ -171,9 +171,9 @@ struct HybridBuffers {
     uint32_t* flags;             // device flags (capacity)
     uint32_t* cur_stg;           // [checkpoints, 2] staged-list offset (or ~0) and count
     uint32_t* stg;               // [stg_cap, 2] staged entries; null: the backward merges again
-    uint64_t* stg_count;         // [2], zeroed before the forward: entries of the staged list in use
+    uint32_t* stg_count;         // the staged list in use, in units of STG_CHUNK entries; before the
+                                 // forward staged_first_units
     uint64_t stg_cap;
-    uint32_t stg_first;          // entries of each workgroup's own first chunk (staged_first)
     double* drec_clear;          // optional: FP64 gradient accumulators (per record, then the masks') the forward clears
     uint64_t drec_clear_n2;      // their size in pairs of doubles
     const uint32_t* order;       // optional [tiles]: tile of each workgroup

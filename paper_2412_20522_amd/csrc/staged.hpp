@@ -26,20 +26,39 @@ constexpr uint32_t staged_first(uint64_t workgroups) {
     return workgroups <= STG_MANY ? STG_FIRST : STG_FIRST_MANY;
 }
 
+// The list in units of STG_CHUNK, in which the counter runs, that the first
+// chunks take.
+constexpr uint32_t staged_first_units(uint64_t workgroups) {
+    return (uint32_t)((workgroups * staged_first(workgroups) + STG_CHUNK - 1) / STG_CHUNK);
+}
+
 // Entries of the list for a first forward over so many tiles and pixels: the
 // first chunks, and an entry per pixel, beside them or, with many tiles, among
 // them.
 constexpr uint64_t staged_room(uint64_t tiles, uint64_t pixels) {
-    const uint64_t first = tiles * staged_first(tiles);
+    const uint64_t first = (uint64_t)staged_first_units(tiles) * STG_CHUNK;
     return tiles <= STG_MANY ? pixels + first : (pixels > first ? pixels : first);
 }
 
-// The 32-bit offset of m entries from `base` on in a list of `cap` entries, or
-// STG_NOWHERE if they do not fit (the backward then forms the batch again).
-// The base is 64-bit: neither a workgroup's index times its chunk nor the
-// counter may wrap into entries of another workgroup.
-constexpr uint32_t staged_offset(uint64_t base, uint32_t m, uint64_t cap) {
-    return base + m <= cap && base + m <= STG_NOWHERE ? (uint32_t)base : STG_NOWHERE;
+// The first entry of a workgroup's first chunk.  (At most 16 views of 2,048 x
+// 2,048 tiles: below 2^32.)
+constexpr uint32_t staged_first_base(uint32_t workgroup, uint32_t first) { return workgroup * first; }
+
+// The first entry of the counter's chunk `unit`, or STG_NOWHERE: a product of
+// 2^32 or more must not wrap into entries of another workgroup.
+constexpr uint32_t staged_base(uint32_t unit) {
+    return unit < STG_NOWHERE / STG_CHUNK ? unit * STG_CHUNK : STG_NOWHERE;
+}
+
+// The offset of the next m entries of a chunk with `base` next in a list of
+// `cap` entries, or STG_NOWHERE if they have no place (the backward then forms
+// the batch again).
+constexpr uint32_t staged_offset(uint32_t base, uint32_t m, uint32_t cap) {
+    return m <= cap && base <= cap - m ? base : STG_NOWHERE;
+}
+// ... and the entry after them.
+constexpr uint32_t staged_next(uint32_t offset, uint32_t m) {
+    return offset == STG_NOWHERE ? STG_NOWHERE : offset + m;
 }
 
 }  // namespace mgs
