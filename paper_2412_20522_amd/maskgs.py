@@ -185,8 +185,15 @@ _CAMERA_TAIL = struct.Struct("=4f2i")  # mgs_camera behind viewmat
 
 def camera_struct(cam: dict) -> mgs_camera:
     vm = np.asarray(cam["viewmat"], np.float32).reshape(16)
-    return mgs_camera.from_buffer_copy(vm.tobytes() + _CAMERA_TAIL.pack(
-        float(cam["fx"]), float(cam["fy"]), float(cam["cx"]), float(cam["cy"]), int(cam["width"]), int(cam["height"])))
+    f = float(cam["fx"]), float(cam["fy"]), float(cam["cx"]), float(cam["cy"])
+    size = int(cam["width"]), int(cam["height"])
+    try:
+        tail = _CAMERA_TAIL.pack(*f, *size)
+    except (OverflowError, struct.error):
+        # beyond float32 or int32, which struct refuses: as ctypes converts
+        # them (to infinity, modulo 2^32); the library checks the values
+        tail = bytes((C.c_float * 4)(*f)) + bytes((C.c_int32 * 2)(*size))
+    return mgs_camera.from_buffer_copy(vm.tobytes() + tail)
 
 
 def cameras_array(cams: Sequence[dict]):

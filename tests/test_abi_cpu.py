@@ -101,3 +101,22 @@ def test_library_queues_nothing_on_the_null_stream():
     for name in sorted(os.listdir(src)):
         txt = re.sub(r"//[^\n]*", "", open(os.path.join(src, name)).read())
         assert not re.search(r"\bhip(Memset|Memcpy)(D8|D16|D32|2D|3D|DtoD|DtoH|HtoD|ToSymbol|FromSymbol)?\s*\(", txt), name
+
+
+@pytest.mark.parametrize("change", [{}, {"fx": 1e39}, {"cy": -1e300}, {"cx": float("nan")}, {"fy": float("inf")},
+                                    {"width": 2 ** 33 + 5}, {"height": -2 ** 40}, {"width": -1, "cx": 4e38}])
+def test_camera_values_beyond_the_struct_convert_as_ctypes_does(change):
+    import numpy as np
+    M = _lib()
+    rng = np.random.default_rng(3)
+    cam = dict(viewmat=rng.normal(size=(4, 4)), fx=100.0, fy=101.5, cx=64.0, cy=32.25, width=128, height=64)
+    cam.update(change)
+    got, want = M.camera_struct(cam), M.mgs_camera()
+    for i, v in enumerate(np.asarray(cam["viewmat"], np.float32).reshape(16)):
+        want.viewmat[i] = float(v)
+    want.fx, want.fy, want.cx, want.cy = (float(cam[k]) for k in ("fx", "fy", "cx", "cy"))
+    want.width, want.height = cam["width"], cam["height"]
+    # (the bytes of two NaN may differ)
+    assert [np.float32(v).tobytes() if v == v else "nan" for v in [*got.viewmat, got.fx, got.fy, got.cx, got.cy]] == \
+           [np.float32(v).tobytes() if v == v else "nan" for v in [*want.viewmat, want.fx, want.fy, want.cx, want.cy]]
+    assert (got.width, got.height) == (want.width, want.height)
