@@ -170,14 +170,20 @@ def _ptr(t: Optional[torch.Tensor], dtype=torch.float32, name: str = "tensor"):
     raise ValueError(f"{name} must be contiguous")
 
 
+# (private to torch: without it the public way, which costs more)
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream(stream=None):
     # the raw handle: a Stream object of the current stream costs more than
     # the rest of a call's marshalling (with the addresses passed as integers
     # and the cameras packed at once, an eager step of 4096 Gaussians, bound by
     # the host: 282 -> 243 us; the six mask and loss calls 58 -> 46 us)
-    if stream is None:
-        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
-    return stream.cuda_stream
+    if stream is not None:
+        return stream.cuda_stream
+    if _raw_stream is None:
+        return torch.cuda.current_stream().cuda_stream
+    return _raw_stream(torch.cuda.current_device())
 
 
 _CAMERA_TAIL = struct.Struct("=4f2i")  # mgs_camera behind viewmat

@@ -183,3 +183,23 @@ def test_gumbel_bound_decides_pruning_draws_like_the_exact_rule():
         # the extreme partner (the smallest uniform) is the worst case
         u_min = 0.5 / 16777216.0
         assert not np.any(((s0 + g(u_grid)) > (s1 + g(u_min)))[u_grid < t0]), d
+
+
+def test_stream_handle_without_the_private_call(monkeypatch):
+    """A torch that lacks its private call for the raw stream handle: the
+    current stream's handle from the public one, and a given stream's own."""
+    import torch
+    from paper_2412_20522_amd import maskgs as M
+
+    class Stream:
+        cuda_stream = 0x1230
+
+    monkeypatch.setattr(M, "_raw_stream", None)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: Stream())
+    assert M._stream() == 0x1230
+    other = Stream()
+    other.cuda_stream = 0x4560
+    assert M._stream(other) == 0x4560
+    monkeypatch.setattr(M, "_raw_stream", lambda device: 0x7890 + device)
+    monkeypatch.setattr(torch.cuda, "current_device", lambda: 2)
+    assert M._stream() == 0x7892
