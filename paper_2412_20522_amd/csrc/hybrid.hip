@@ -2359,8 +2359,8 @@ __global__ void __launch_bounds__(FINE_NT, 5) hybrid_bwd_fine_kernel(
             const float4 B = *reinterpret_cast<const float4*>(smem + own + 16);
             const float4 Cc = *reinterpret_cast<const float4*>(smem + own + 32);
             Eval e;
-            const bool hit =
-                eval_entry(A, B, px, py, ek, e) & (e0 + row < ne) & (__float_as_int(B.w) <= lastk);
+            const bool reach = eval_entry(A, B, px, py, ek, e);
+            const bool hit = reach & (e0 + row < ne) & (__float_as_int(B.w) <= lastk);
             if (!ballot(hit)) continue;
             const float M = B.z;
             const float ma = hit ? M * e.alpha : 0.f;
