@@ -128,3 +128,26 @@ def test_pruning_masked_gaussians_changes_nothing(cull):
         assert U.rel_err(b, a) <= 1e-6, name
     rast.release_frame(f_full)
     rast.release_frame(f_pr)
+
+
+@pytest.mark.parametrize("base", [0.0, 37.5])
+def test_prune_draws_next_to_the_kernel_s_bounds_match_oracle(ctx, base):
+    """One draw each of 3.4 M Gaussians over score gaps on both sides of those
+    where a draw is decided from one uniform: some hundred uniforms of each gap
+    lie within 1e-5 of its bounds.  Every draw is the oracle's, which takes the
+    64-bit rule throughout; infinite and undefined scores as well."""
+    gaps = np.array([-90, -40, -25, -16, -12, -8, -5, -2.5, -1.5, -0.5, -1e-3, 0, 1e-3, 0.5, 1.5, 2.5, 5, 8, 12, 16, 25,
+                     40, 90], np.float32)
+    n = 150_000
+    s = np.repeat(np.stack([base + gaps / 2, base - gaps / 2], 1), n, axis=0).astype(np.float32)
+    odd = np.array([[np.inf, 0], [0, np.inf], [-np.inf, 0], [0, -np.inf], [np.inf, np.inf], [-np.inf, -np.inf],
+                    [np.nan, 0], [0, np.nan], [3e38, -3e38], [-3e38, 3e38]], np.float32)
+    s = np.concatenate([s, np.tile(odd, (50, 1))])
+    keep = torch.full((s.shape[0],), 7, dtype=torch.int32, device="cuda")
+    U.M().mgs_prune_sample(ctx, torch.from_numpy(s).cuda(), 2412, 11, 1, keep)
+    torch.cuda.synchronize()
+    want = oracle.prune_keep(s, 2412, 11, 1)
+    got = keep.cpu().numpy()
+    assert np.array_equal(got, want.astype(np.int32))
+    rate = got[:gaps.size * n].reshape(gaps.size, n).mean(1)
+    assert rate[0] == 0 and rate[-1] == 1 and abs(rate[11] - 0.5) < 0.01
