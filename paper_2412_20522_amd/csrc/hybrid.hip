@@ -1662,15 +1662,23 @@ __global__ void __launch_bounds__(TW * TH / PPT, PPT >= 4 ? 5 : STATS ? 7 : 8) h
 
 // SUM (several waves to a tile): the waves' totals of BWD_ROUND entries meet in
 // LDS and are added to the accumulators once per tile and entry, a lane to a
-// quantity.  Where all tiles run at once they reach the same splats, the last
-// of their lists, at the same time, and the atomics wait for each other; with
-// more tiles they drift apart, and the barriers cost more.  Two pixels per
-// thread, batches of 256, splats of an unbounded scene, every wave for itself /
-// summed: 1,000 tiles 91 / 90 us, 4,346 tiles 238 / 170, 4,108 tiles 232 / 200,
-// 6,004 tiles 247 / 252, 7,110 tiles 315 / 284, 8,664 tiles 328 / 349, 24,937
-// tiles 800 / 906 us.
+// quantity: fewer atomics, which wait for each other where tiles reach the same
+// splats at the same time, for two barriers a round.  Splats of an unbounded
+// scene, 1,392 to 24,937 tiles of 256 pixels, summed against every wave for
+// itself:
+//   one pixel per thread (two or four waves): 0.45 to 0.94 of the time at any
+//   number of tiles and batch depth (4,346 tiles 349 -> 188 us, 24,937 tiles
+//   1,450 -> 1,060 us)
+//   two pixels per thread (two waves), batches of 32 to 128: 0.74 to 1.02 (4,346
+//   tiles 220 -> 167, 8,664 tiles 305 -> 294, 24,937 tiles 785 -> 747 us)
+//   two pixels per thread, batches of 256 (whose LDS leaves room for fewer
+//   workgroups with the sums): 1,392 tiles 104 / 107 us, 4,346 tiles 237 /
+//   174, 6,000 tiles 256 / 253, 7,110 tiles 320 / 279, 7,740 tiles 302 / 309,
+//   8,664 tiles 320 / 334, 24,937 tiles 778 / 838
+// So the waves sum, but with two pixels per thread and batches of 256 only up
+// to SUM_TILES tiles.
 constexpr int BWD_ROUND = 32;
-constexpr uint32_t SUM_TILES = 5632;
+constexpr uint32_t SUM_TILES = 7424;
 template <int TW, int TH, int PPT, bool SUM>
 __global__ void __launch_bounds__(TW * TH / PPT, 5) hybrid_bwd_kernel(
     const float4* __restrict__ srec, HybridLists hl, ViewSet views, DevSettings st, const float* __restrict__ t_final,
@@ -2473,10 +2481,14 @@ void hybrid_bwd_t(hipStream_t s, const float* srec, const HybridLists& hl, const
                            dim3(TW * TH / PPT), lds_bytes(st.batch), s, reinterpret_cast<const float4*>(srec), hl, views,
                            st, t_final, last, dl, n, d_rec, d_masks);
     };
-    if constexpr (TW * TH / PPT > 64) {
-        if (views.total_tiles <= SUM_TILES) return launch(std::true_type{});
+    if constexpr (TW * TH / PPT == 64) {
+        launch(std::false_type{});
+    } else if constexpr (PPT == 1) {
+        launch(std::true_type{});
+    } else {
+        if (st.batch < MAXB || views.total_tiles <= SUM_TILES) launch(std::true_type{});
+        else launch(std::false_type{});
     }
-    launch(std::false_type{});
 }
 
 #define MGS_HYBRID_SHAPES(X) \

@@ -148,3 +148,31 @@ def test_checkpoints_beyond_a_fixed_workspace_are_reported(large):
             assert U.rel_err(getattr(g, k).cpu().numpy(), getattr(g_ref, k).cpu().numpy()) <= 1e-5, k
     rast.reserve(frame, 0)
     rast.release_frame(frame)
+
+
+@pytest.mark.parametrize("width", [1352, 1400], ids=["7,392 tiles", "7,656 tiles"])
+@pytest.mark.parametrize("tile,fwd_ppt", [((16, 16), 2), ((32, 8), 2)])
+def test_backward_on_both_sides_of_the_line_for_sums_over_a_tile_s_waves(width, tile, fwd_ppt):
+    """Two pixels per thread and batches of 256: the waves' totals meet in LDS up
+    to 7,424 tiles and go to the accumulators one by one beyond; with batches of
+    128 they always meet."""
+    from paper_2412_20522_amd.raster import Rasterizer
+    s = scenegen.small_scene(6000, width, 1392, seed=995, sh_degree=0, log_scale_mean=-2.8)
+    cams = s["cameras"]
+    dev = U.to_device(s)
+    params = {k: dev[k] for k in U.PARAM_KEYS}
+    dl = torch.from_numpy(np.random.default_rng(5).normal(size=3 * width * 1392).astype(np.float32)).cuda()
+    out = []
+    for batch, ppt in ((256, 2), (128, 2), (256, 1)):
+        rast = Rasterizer(0, sh_degree=0, stats=0, tile_w=tile[0], tile_h=tile[1], batch_depth=batch, fwd_ppt=fwd_ppt,
+                          bwd_ppt=ppt)
+        frame = rast.acquire_frame()
+        img = rast.forward(frame, params, dev["masks"], cams)
+        g = rast.backward(frame, params, dl)
+        torch.cuda.synchronize()
+        out.append((img.cpu().numpy(), {k: getattr(g, k).cpu().numpy() for k in (*U.PARAM_KEYS, "masks")}))
+        rast.release_frame(frame)
+    for img, g in out[1:]:
+        assert np.array_equal(img, out[0][0])
+        for k, v in g.items():
+            assert U.rel_err(v, out[0][1][k]) <= 1e-5, k
