@@ -2270,15 +2270,15 @@ __global__ void __launch_bounds__(FINE_NT, 5) hybrid_bwd_fine_kernel(
     // ten partial sums per staged entry over the part's blocks, in two sets: one
     // of waves 0 and 1, one of waves 2 and 3.  A sum of two does not depend on
     // which wave comes first, so that the FP32 sums repeat to the bit.  (The LDS
-    // then holds four workgroups instead of five: 423 and 423 us a step of 200 k
-    // small splats at 800x800, 438 -> 447 us for the slowest case seen.)
+    // then holds four workgroups instead of five: 200 k small splats at 800x800
+    // 139 -> 140 us, 4096 splats at 128x128 44.5 -> 45.5 us.)
     constexpr int SET = FINE_BATCH * 10;
     float* acc = reinterpret_cast<float*>(smem + lds_bytes(FINE_BATCH) + (FINE_NT / 64) * FINE_LIST * 2);
     float* wacc = acc + (wave >> 1) * SET;
     const int qi = fold10_quantity(col);
     const EvalConsts ek = eval_consts(st);
     if (*hl.cur_need > hl.cur_cap) return;  // the forward reported it
-    for (int i = t; i < 2 * SET; i += FINE_NT) acc[i] = 0.f;
+    for (int i = t; i < SET / 2; i += FINE_NT) reinterpret_cast<float4*>(acc)[i] = make_float4(0.f, 0.f, 0.f, 0.f);
     const uint32_t q = blockIdx.x;
     const FinePart fp = fine_part(views, hl, st, q, parts);
     const uint32_t tile = fp.tile;
@@ -2415,14 +2415,14 @@ __global__ void __launch_bounds__(FINE_NT, 5) hybrid_bwd_fine_kernel(
             const float x0 = acc[i], x1 = acc[i + SET];
             if (x0 == 0.f && x1 == 0.f) continue;
             acc[i] = acc[i + SET] = 0.f;
-            const double xs = (double)x0 + (double)x1;
+            const float xs = x0 + x1;
             const int j = i / 10, k = i - j * 10;
             const uint32_t r = __float_as_uint(L.E[3 * j + 2].w);
             // (the totals of t^2 and dy^2 rescaled, as in hybrid_bwd_kernel)
             if (k < DREC)
-                atomicAdd(d_rec + (size_t)r * DREC + k, k == 2 || k == 4 ? xs * (0.5 * (double)QSCALE) : xs);
+                atomicAdd(d_rec + (size_t)r * DREC + k, (double)(xs * (k == 2 || k == 4 ? 0.5f * QSCALE : 1.f)));
             else
-                atomicAdd(d_masks + ((int64_t)r - rec_base), xs);
+                atomicAdd(d_masks + ((int64_t)r - rec_base), (double)xs);
         }
         __syncthreads();  // the next batch overwrites the LDS
     }
