@@ -283,10 +283,11 @@ __device__ __forceinline__ uint64_t digit_peers(uint32_t d) {
 // Above DROP_MIN keys that pass also drops the dead ones (all ones: records
 // without tiles): it counts and scatters the others only, writes their number
 // per segment into live[seg], and places the dead keys' values behind them in
-// the final value buffer, in order; the later passes end at live[seg].  8 x 1 M
-// keys, 30 % dead (a view inside its scene), four passes 176 -> 157 us; at 0.3
-// to 1.5 M keys, where a pass takes as long for fewer keys, the first one 3 us
-// more.
+// the final value buffer, in order; the later passes end at live[seg].  A third
+// of the keys dead (views inside their scene), the four passes with / without:
+// 0.3 to 3.6 M keys 1.05 to 1.02 of the time (77 / 73 us, 216 / 212), where a
+// pass takes as long for fewer keys and the first one longer; 4 M in four views
+// 229 / 224, in eight 227 / 237; 5 M 270 / 269, 6.4 M 320 / 332, 8 M 372 / 387.
 constexpr int64_t DROP_MIN = 4000000;
 enum FirstPass { LATER = 0, INDEX = 1, INDEX_DROP = 2 };
 struct SortSeg {
