@@ -263,6 +263,10 @@ MGS_API mgs_status mgs_backward(mgs_frame* frame, mgs_stream stream, const float
  * growing buffers.  Records (N * views), tiles and pixels may not exceed the
  * forward the reservation was taken from (MGS_ERR_CAPACITY on the host).
  * slack <= 0 releases the fixed workspace.  Synchronises `stream` once.
+ * The compositing kernels stay those of the forward that sized the workspace
+ * (a plain forward picks those for small or those for large splats by its own
+ * splats' sizes; they differ in time only): where splats grow or shrink much,
+ * release, run a plain forward and reserve again.
  * Outputs of a forward whose counts overflowed are undefined; mgs_frame_check
  * reports it. */
 MGS_API mgs_status mgs_frame_reserve(mgs_frame* frame, mgs_stream stream, double slack);

@@ -294,8 +294,8 @@ struct mgs_frame {
     // fixed workspace (mgs_frame_reserve): no allocation, no synchronisation
     bool reserved = false;
     int64_t res_R = 0, res_P = 0, res_T = 0, K_cap = 0, cur_cap = 0, stg_cap = 0;
-    // device buffers: per record, then per list entry (32-bit cell keys), per
-    // tile and region, per pixel
+    // device buffers: per record, then per list entry (16- or 32-bit cell
+    // keys), per tile and region, per pixel
     DevBuf rec, srec, depth, tiles, rkeys, rvals, rkeys_alt, rvals_alt, cnt_sorted, cells,
         cls_part;
     // order, order_b: the tile orders of the forward and the backward

@@ -833,8 +833,7 @@ __global__ void __launch_bounds__(256) duplicate_kernel(
     if (lim < total && lane == 0) atomicOr(flags, FLAG_CAPACITY);
 }
 
-// Upper bound on the batches a tile can take: a batch either emits `batch`
-// merged entries or exhausts a whole window of one of the two streams.
+// Cell of the region that holds tile (tx, ty).
 __device__ __forceinline__ uint32_t region_of_tile(int tx, int ty, const DevView& cam, const ViewSet& views) {
     return views.total_tiles + cam.reg_off + (uint32_t)(ty / REGION) * (uint32_t)cam.reg_w + (uint32_t)(tx / REGION);
 }
@@ -1413,7 +1412,7 @@ struct HybridLists {
 // the loop, the launch's arguments stay live in registers across it, and
 // resident workgroups that pop one counter wait for each other.  What the tile
 // and the batch determine is read into scalar registers (`uniform`), so that a
-// thread holds its pixels and the entry only: 55 registers for the forward at
+// thread holds its pixels and the entry only: 56 registers for the forward at
 // two pixels per thread (72 and spills before), 90 for the backward at four.
 // Measured on splats of an unbounded scene, batches of 128, two pixels per
 // thread forward and four backward, queue loop -> now: 4,346 tiles forward 143
@@ -1438,7 +1437,7 @@ __global__ void __launch_bounds__(TW * TH / PPT, PPT >= 4 ? 5 : STATS ? 7 : 8) h
     uint32_t* __restrict__ imp_max) {
     constexpr int NT = TW * TH / PPT;
     // entries per round: with IMP four, whose reductions over the wave share
-    // their steps (2 views of 400 k Gaussians: 154 -> IMPT us against one)
+    // their steps (2 views of 400 k Gaussians: 154 -> 138 us against one)
     constexpr int ROUND = IMP ? 4 : 1;
     // IMP: the batch's sums and maxima over the tile, added to the Gaussians'
     // once per tile, a lane to an entry (138 -> 102 us against atomics of
@@ -1890,12 +1889,17 @@ __global__ void __launch_bounds__(TW * TH / PPT, 5) hybrid_bwd_kernel(
 // along the rows through the gfx950 lane swaps.  Per pixel and entry this
 // issues about three times the instructions of the kernels above, so it pays
 // where splats reach a fraction of the tile or the tiles leave the device idle
-// (rule: use_fine).  Measured against the kernels above at two pixels per
-// thread: 200 k small splats at 800x800, forward 304 -> 80 us, backward 449 ->
-// 112 us; 4096 splats at 128x128, 216 -> 33 and 336 -> 44 us.  Bound by VALU
-// issue where a few parts hold long lists.  Launches are plain (one workgroup
-// per part, the tiles in launch order): a loop over a device queue keeps the
-// kernel arguments live and spills (forward 97 -> 80 us without it).
+// (rule: use_fine).  Measured against the kernels above, which then popped a
+// device queue: 200 k small splats at 800x800, 16x16 tiles with the work
+// counters, forward 304 -> 77 us, backward 449 -> 109 us; 8x8 tiles without
+// them 291 -> 66 and 321 -> 105 us; 4096 splats at 128x128, 216 -> 33 and 336
+// -> 42 us.  At 200 k splats the forward issues VALU instructions at 0.65 of the
+// chip's rate and the backward at 0.58, and their waves wait half of the time: a
+// few parts hold long lists, whose entries depend on each other.  Launches are
+// plain (one workgroup per part, the tiles in launch order): a loop over a
+// device queue keeps the kernel arguments live and spills more (forward 97 ->
+// 80 us without it).  At six waves per SIMD the forward spills 36 bytes a lane,
+// with the counters or the scores 56.
 constexpr int FINE_NT = 256;
 constexpr int FINE_BATCH = 256;  // entries per batch: one per thread
 

@@ -126,7 +126,9 @@ class Rasterizer:
     # -- fixed workspace, capture, tuning ------------------------------------
     def reserve(self, frame, slack: float = 1.25) -> None:
         """Fix the frame's workspace after a plain forward, so that forward and
-        backward on it neither allocate nor synchronise (capturable)."""
+        backward on it neither allocate nor synchronise (capturable).  The
+        compositing kernels stay those that forward picked by its splats'
+        sizes: reserve(frame, 0) and a new plain forward pick again."""
         M.mgs_frame_reserve(self.ctx, frame, slack)
 
     def check(self, frame) -> None:
