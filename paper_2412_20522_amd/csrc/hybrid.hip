@@ -1893,13 +1893,13 @@ __global__ void __launch_bounds__(TW * TH / PPT, 5) hybrid_bwd_kernel(
 // device queue: 200 k small splats at 800x800, 16x16 tiles with the work
 // counters, forward 304 -> 77 us, backward 449 -> 109 us; 8x8 tiles without
 // them 291 -> 66 and 321 -> 105 us; 4096 splats at 128x128, 216 -> 33 and 336
-// -> 42 us.  At 200 k splats the forward issues VALU instructions at 0.65 of the
-// chip's rate and the backward at 0.58, and their waves wait half of the time: a
-// few parts hold long lists, whose entries depend on each other.  Launches are
-// plain (one workgroup per part, the tiles in launch order): a loop over a
-// device queue keeps the kernel arguments live and spills more (forward 97 ->
-// 80 us without it).  At six waves per SIMD the forward spills 36 bytes a lane,
-// with the counters or the scores 56.
+// -> 42 us.  The forward issues VALU instructions at 0.41 to 0.65 of the chip's
+// rate and the backward at 0.5 to 0.58 (200 k splats), and their waves wait half
+// of the time: a few parts hold long lists, whose entries depend on each other.
+// Launches are plain (one workgroup per part, the tiles in launch order): a loop
+// over a device queue keeps the kernel arguments live and spills more (forward
+// 97 -> 80 us without it).  At six waves per SIMD the forward spills 36 bytes a
+// lane, with the counters or the scores 56.
 constexpr int FINE_NT = 256;
 constexpr int FINE_BATCH = 256;  // entries per batch: one per thread
 
